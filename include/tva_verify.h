@@ -37,6 +37,11 @@ extern "C" {
 int tva_accept_greedy(const int32_t *parent, const int32_t *cu_T, const int32_t *draft_token,
                       const int32_t *target_token, int32_t B, int32_t max_path, int32_t *path,
                       int32_t *path_len, int32_t *next_token, void *stream);
+/* The same, and the entries of `path` past path_len[b] are set to -1 (a caller that hands whole rows of it on need not
+ * clear it with a launch of its own). */
+int tva_accept_greedy_filled(const int32_t *parent, const int32_t *cu_T, const int32_t *draft_token,
+                             const int32_t *target_token, int32_t B, int32_t max_path, int32_t *path,
+                             int32_t *path_len, int32_t *next_token, void *stream);
 
 /*
  * Acceptance by speculative sampling on draft trees (paper, Preliminary, "Speculative Decoding": a drafted
@@ -105,6 +110,8 @@ typedef struct tva_sample_args {
 } tva_sample_args;
 
 int tva_accept_sampling(const tva_sample_args *a, void *stream);
+/* The same, and the entries of `path` past path_len[b] are set to -1 (a flagged sequence's too). */
+int tva_accept_sampling_filled(const tva_sample_args *a, void *stream);
 size_t tva_sample_workspace_bytes(int32_t B);
 size_t tva_sample_workspace_bytes_rows(int32_t B, int32_t sum_T, int32_t V);  /* the same plus room for the row sums */
 /* For tests of the bounded wait: the same call (workspace given, workgroups_per_sequence >= 2), but every wait expects

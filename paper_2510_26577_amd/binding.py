@@ -20,6 +20,8 @@ SRC_PATH = os.path.join(_HERE, "csrc", "tva.hip")
 CAST_SRC_PATH = os.path.join(_HERE, "csrc", "cast.cpp")  # host part: tree-size selection
 VERIFY_SRC_PATH = os.path.join(_HERE, "csrc", "verify.hip")  # acceptance + commit kernels
 DRAFT_SRC_PATH = os.path.join(_HERE, "csrc", "draft.hip")    # draft-tree expansion + subtree kernels
+PYCALL_SRC_PATH = os.path.join(_HERE, "csrc", "pycall.cpp")  # calls on tensors in native code (module _pycall)
+PYCALL_LIB_PATH = os.path.join(_HERE, "_pycall.so")
 INCLUDE_DIR = os.path.join(_ROOT, "include")
 
 TVA_OK = 0
@@ -49,6 +51,25 @@ def build_library(verbose: bool = False, timeline: bool = False) -> str:
     if res.returncode:
         raise RuntimeError(f"hipcc failed building {os.path.basename(out)}")
     return out
+
+
+def build_pycall(verbose: bool = False) -> str:
+    """Compile csrc/pycall.cpp (the Python entry points' native part, host code on torch's C++ objects) in-tree."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = [INCLUDE_DIR, os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall", "-Wno-unused-function",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-isystem{i}" for i in inc], "-o", PYCALL_LIB_PATH, PYCALL_SRC_PATH, f"-L{os.path.join(root, 'lib')}",
+           "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.stdout and (verbose or res.returncode):
+        print(res.stdout)
+    if res.returncode:
+        raise RuntimeError("the compiler failed building _pycall.so")
+    return PYCALL_LIB_PATH
 
 
 class TvaArgs(ctypes.Structure):
@@ -82,7 +103,7 @@ EXPORTS = ("tva_build_ancestor_mask", "tva_build_ancestor_mask_host", "tva_works
 DRAFT_EXPORTS = ("tva_expand_workspace_bytes", "tva_expand_layer", "tva_sizeof_expand_args", "tva_tree_select_subtree",
                  "tva_tree_rerank_count", "tva_rerank_workspace_bytes",
                  "tva_layer_breadth_count")
-VERIFY_EXPORTS = ("tva_accept_greedy", "tva_accept_sampling", "tva_accept_sampling_wait_bound_test", "tva_sample_workspace_bytes", "tva_sample_workspace_bytes_rows", "tva_sizeof_sample_args", "tva_commit_path",
+VERIFY_EXPORTS = ("tva_accept_greedy", "tva_accept_greedy_filled", "tva_accept_sampling", "tva_accept_sampling_filled", "tva_accept_sampling_wait_bound_test", "tva_sample_workspace_bytes", "tva_sample_workspace_bytes_rows", "tva_sizeof_sample_args", "tva_commit_path",
                   "tva_sizeof_commit_args")
 # host entry points of include/tva_cast.h (bound in cast.py)
 CAST_EXPORTS = ("tva_cast_select_context", "tva_cast_select_max_valid_index", "tva_cast_layer_utility",
@@ -146,8 +167,55 @@ def load_library():
     lib.tva_timeline_read.argtypes = [ctypes.c_void_p, ctypes.c_int32]
     if lib.tva_version() != EXPECTED_VERSION or lib.tva_sizeof_args() != ctypes.sizeof(TvaArgs):
         raise RuntimeError("libtva.so is stale: rebuild it")
+    _bind_native(lib)
     _lib = lib
     return lib
+
+
+# The native part of the entry points below (csrc/pycall.cpp) and the library's functions it calls, in its order.
+_native = None
+_NATIVE_CALLS = ("tva_tree_verify_attn", "tva_workspace_bytes", "tva_build_ancestor_mask", "tva_accept_greedy", "tva_accept_greedy_filled",
+                 "tva_accept_sampling_filled", "tva_sample_workspace_bytes_rows", "tva_commit_path", "tva_tree_rerank_count",
+                 "tva_rerank_workspace_bytes", "tva_tree_select_subtree")
+_address = {}  # of the functions called on argument blocks their callers keep
+
+
+def _bind_native(lib) -> None:
+    global _native
+    if not os.path.exists(PYCALL_LIB_PATH):
+        raise RuntimeError(f"{PYCALL_LIB_PATH} not built: run `python -c 'import __graft_entry__ as g; g.build()'`")
+    from . import _pycall
+    at = lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+    for name in ("tva_sizeof_sample_args", "tva_sizeof_commit_args"):
+        getattr(lib, name).restype = ctypes.c_size_t
+    sizes = lib.tva_sizeof_args() + 1024 * (lib.tva_sizeof_sample_args() + 1024 * lib.tva_sizeof_commit_args())
+    if _pycall.sizes != sizes or _pycall.functions != len(_NATIVE_CALLS):
+        raise RuntimeError("_pycall.so is stale: rebuild it")
+    _pycall.bind(*map(at, _NATIVE_CALLS))
+    for name in ("tva_tree_verify_attn", "tva_tree_verify_attn_static", "tva_tree_verify_attn_splits", "tva_expand_layer", "tva_commit_path"):
+        _address[name] = at(name)
+    _native = _pycall
+
+
+def native():
+    """The native module, the library loaded and bound."""
+    if _native is None:
+        load_library()
+    return _native
+
+
+def _result(r):
+    """What a native call returned: its results, or a negative status."""
+    if r.__class__ is int:
+        raise TvaError(r)
+    return r
+
+
+def call_raw(name: str, args, stream=None) -> None:
+    """Queue a library call on an argument block its caller keeps."""
+    code = native().call(_address[name], args, stream)
+    if code != TVA_OK:
+        raise TvaError(code)
 
 
 class TvaError(RuntimeError):
@@ -162,9 +230,7 @@ def _check(code: int) -> None:
 
 
 def _stream_ptr(stream) -> Optional[int]:
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return ctypes.c_void_p(native().stream(stream))
 
 
 def _p(t) -> Optional[int]:
@@ -192,17 +258,7 @@ def build_ancestor_mask(parent, cu_T, max_T: int, mask=None, err_flag=None, stre
     """parent int32 [sum_T], cu_T int32 [B+1] (device) -> mask int64 [sum_T, W]
     holding the uint64 bit patterns.  `err_flag` (int32[1], zeroed by the
     caller) receives 1 + index of the first malformed node, asynchronously."""
-    import torch
-    lib = load_library()
-    B = cu_T.numel() - 1
-    W = max(1, (int(max_T) + 63) // 64)
-    if mask is None:
-        mask = torch.empty((parent.numel(), W), dtype=torch.int64, device=parent.device)
-    else:
-        W = mask.shape[1]
-    _check(lib.tva_build_ancestor_mask(_p(parent), _p(cu_T), B, int(max_T), W, _p(mask), _p(err_flag),
-                                       _stream_ptr(stream)))
-    return mask
+    return _result(native().ancestor_mask(parent, cu_T, max_T, mask, err_flag, stream))
 
 
 def make_args(*, q, k_tree, v_tree, k_cache, v_cache, anc_mask, cu_T, L, max_T: int, max_L: int,
@@ -288,18 +344,18 @@ def plan_workgroup_rows(args: TvaArgs) -> int:
 
 def tree_verify_attn_raw(args: TvaArgs, stream=None) -> None:
     """Queue the attention on `stream` with a prepared argument struct."""
-    _check(load_library().tva_tree_verify_attn(ctypes.byref(args), _stream_ptr(stream)))
+    call_raw("tva_tree_verify_attn", args, stream)
 
 
 def tree_verify_attn_static_raw(args: TvaArgs, stream=None) -> None:
     """Queue the attention with the KV splits' partial results in the library's own device array
     (tva_tree_verify_attn_static: nothing is allocated, args.workspace is ignored)."""
-    _check(load_library().tva_tree_verify_attn_static(ctypes.byref(args), _stream_ptr(stream)))
+    call_raw("tva_tree_verify_attn_static", args, stream)
 
 
 def tree_verify_attn_splits_raw(args: TvaArgs, stream=None) -> None:
     """Queue only the split-KV attention kernel (no merge) with a prepared argument struct."""
-    _check(load_library().tva_tree_verify_attn_splits(ctypes.byref(args), _stream_ptr(stream)))
+    call_raw("tva_tree_verify_attn_splits", args, stream)
 
 
 def tree_verify_attn(q, k_tree, v_tree, k_cache, v_cache, anc_mask, cu_T, L, *, max_T: int, max_L: int,
@@ -311,24 +367,12 @@ def tree_verify_attn(q, k_tree, v_tree, k_cache, v_cache, anc_mask, cu_T, L, *, 
     bf16 tensors may be torch.bfloat16 or int16/uint16 bit patterns; with kv_fp8 the K/V tensors are uint8
     (E4M3 bytes) and K = k_scale * value, V = v_scale * value.  anc_mask may be None when the
     trees' parent array (int32 [sum_T]) is passed instead: the kernel then derives the masks itself."""
-    import torch
-    if out is None:
-        out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    if lse is None:
-        lse = torch.empty(q.shape[:2], dtype=torch.float32, device=q.device)
-    args = make_args(q=q, k_tree=k_tree, v_tree=v_tree, k_cache=k_cache, v_cache=v_cache, anc_mask=anc_mask,
-                     cu_T=cu_T, L=L, max_T=max_T, max_L=max_L, scale=scale, cu_L=cu_L, page_table=page_table,
-                     page_size=page_size, strides=strides, num_splits=num_splits, out=out, lse=lse, parent=parent,
-                     cu_Q=cu_Q, max_Q=max_Q, sum_T=sum_T, kv_fp8=kv_fp8, k_scale=k_scale, v_scale=v_scale, sum_L=sum_L,
-                     plan_shape=plan_shape, L_host=L_host)
-    need = workspace_bytes(args)
-    if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty((need + 3) // 4, dtype=torch.float32, device=q.device)
-    if workspace is not None:
-        args.workspace = workspace.data_ptr()
-        args.workspace_bytes = workspace.numel() * workspace.element_size()
-    tree_verify_attn_raw(args, stream)
-    return out, lse
+    if L_host is not None:
+        import numpy as np
+        L_host = np.ascontiguousarray(L_host, dtype=np.int32)
+    return _result(native().attn(q, k_tree, v_tree, k_cache, v_cache, anc_mask, cu_T, L, max_T, max_L, scale, cu_L, page_table, page_size,
+                                 strides, num_splits, out, lse, workspace, stream, parent, cu_Q, max_Q, sum_T, kv_fp8, k_scale,
+                                 v_scale, sum_L, plan_shape, L_host))
 
 
 def merge_splits(part_out, part_lse, out=None, lse=None, stream=None):

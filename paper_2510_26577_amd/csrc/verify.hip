@@ -31,8 +31,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(64) accept_kernel(const int32_t *__restrict__ parent, const int32_t *__restrict__ cu_T,
                                                     const int32_t *__restrict__ draft, const int32_t *__restrict__ target,
                                                     int max_path, int32_t *__restrict__ path,
-                                                    int32_t *__restrict__ path_len, int32_t *__restrict__ next_token) {
+                                                    int32_t *__restrict__ path_len, int32_t *__restrict__ next_token, int fill) {
   const int b = blockIdx.x, lane = threadIdx.x;
+  auto fill_from = [&](int len) {
+    if (fill)
+      for (int i = len + lane; i < max_path; i += 64) path[(size_t)b * max_path + i] = -1;
+  };
   const int t0 = cu_T[b];
   const int T = cu_T[b + 1] - t0;
   if (T <= 0) {
@@ -40,6 +44,7 @@ __global__ void __launch_bounds__(64) accept_kernel(const int32_t *__restrict__ 
       path_len[b] = 0;
       next_token[b] = -1;
     }
+    fill_from(0);
     return;
   }
   int cur = 0, len = 1;
@@ -63,6 +68,7 @@ __global__ void __launch_bounds__(64) accept_kernel(const int32_t *__restrict__ 
     path_len[b] = len;
     next_token[b] = target[t0 + cur];
   }
+  fill_from(len);
 }
 
 // ---- acceptance by speculative sampling ----
@@ -80,6 +86,7 @@ struct SampleParams {
   // dependent access to a row of its own)
   const float *first;
   int pieces, sum_T;
+  int fill_path;  // the path's entries past its length are set to -1
   int unit_rows;  // every target row is taken to sum to one: a freshly reached node's normaliser is 1, not summed
 };
 
@@ -340,6 +347,8 @@ __global__ void __launch_bounds__(kSampleThreads) sample_kernel(const SamplePara
   __shared__ int32_t s_parent[kSampleTreeLds], s_token[kSampleTreeLds];
   __shared__ float s_u[kSampleTreeLds];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  if (p.fill_path)  // (the walk's entries are stored behind a barrier)
+    for (int i = tid; i < p.max_path; i += kSampleThreads) p.path[(size_t)b * p.max_path + i] = -1;
   const int t0 = p.cu_T[b];
   const int T = p.cu_T[b + 1] - t0;
   if (T <= 0) {
@@ -353,8 +362,8 @@ __global__ void __launch_bounds__(kSampleThreads) sample_kernel(const SamplePara
   if (T <= kSampleTreeLds) {
     for (int i = tid; i < T; i += kSampleThreads) s_parent[i] = parent[i], s_token[i] = token[i], s_u[i] = u[i];
     parent = s_parent, token = s_token, u = s_u;
-    __syncthreads();
   }
+  __syncthreads();
   const int V = p.V;
   const int seg = ((V + kSampleWaves - 1) / kSampleWaves + VEC - 1) / VEC * VEC;
   float *const r = p.residual + (size_t)b * V;
@@ -480,6 +489,8 @@ __global__ void __launch_bounds__(kSampleThreads) sample_coop_kernel(const CoopP
   __shared__ float s_u[kSampleTreeLds];
   const int W = cp.W;
   const int b = blockIdx.x / W, w = blockIdx.x % W, tid = threadIdx.x, lane = tid & 63;
+  if (p.fill_path && w == 0)  // (the walk's entries are stored behind a barrier)
+    for (int i = tid; i < p.max_path; i += kSampleThreads) p.path[(size_t)b * p.max_path + i] = -1;
   const int t0 = p.cu_T[b];
   const int T = p.cu_T[b + 1] - t0;
   if (T <= 0) {
@@ -804,28 +815,41 @@ __global__ void __launch_bounds__(256) compact_kernel(const CommitParams p) {
 
 extern "C" {
 
-int tva_accept_greedy(const int32_t *parent, const int32_t *cu_T, const int32_t *draft_token,
-                      const int32_t *target_token, int32_t B, int32_t max_path, int32_t *path, int32_t *path_len,
-                      int32_t *next_token, void *stream) {
+static int accept_greedy_impl(const int32_t *parent, const int32_t *cu_T, const int32_t *draft_token,
+                              const int32_t *target_token, int32_t B, int32_t max_path, int32_t *path, int32_t *path_len,
+                              int32_t *next_token, void *stream, int fill) {
   if (B < 0 || max_path < 1) return TVA_INVALID_ARG;
   if (B == 0) return TVA_OK;
   if (!parent || !cu_T || !draft_token || !target_token || !path || !path_len || !next_token) return TVA_INVALID_ARG;
   (void)hipGetLastError();  // the status below is this launch's
   hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(64), 0, (hipStream_t)stream, parent, cu_T, draft_token, target_token,
-                     max_path, path, path_len, next_token);
+                     max_path, path, path_len, next_token, fill);
   return hipPeekAtLastError() == hipSuccess ? TVA_OK : TVA_HIP_ERROR;
 }
 
-static int accept_sampling_impl(const tva_sample_args *a, void *stream, int missing_arrivals, int spins);
+int tva_accept_greedy(const int32_t *parent, const int32_t *cu_T, const int32_t *draft_token,
+                      const int32_t *target_token, int32_t B, int32_t max_path, int32_t *path, int32_t *path_len,
+                      int32_t *next_token, void *stream) {
+  return accept_greedy_impl(parent, cu_T, draft_token, target_token, B, max_path, path, path_len, next_token, stream, 0);
+}
 
-int tva_accept_sampling(const tva_sample_args *a, void *stream) { return accept_sampling_impl(a, stream, 0, kCoopSpins); }
+int tva_accept_greedy_filled(const int32_t *parent, const int32_t *cu_T, const int32_t *draft_token,
+                             const int32_t *target_token, int32_t B, int32_t max_path, int32_t *path, int32_t *path_len,
+                             int32_t *next_token, void *stream) {
+  return accept_greedy_impl(parent, cu_T, draft_token, target_token, B, max_path, path, path_len, next_token, stream, 1);
+}
+
+static int accept_sampling_impl(const tva_sample_args *a, void *stream, int missing_arrivals, int spins, bool fill);
+
+int tva_accept_sampling(const tva_sample_args *a, void *stream) { return accept_sampling_impl(a, stream, 0, kCoopSpins, false); }
+int tva_accept_sampling_filled(const tva_sample_args *a, void *stream) { return accept_sampling_impl(a, stream, 0, kCoopSpins, true); }
 
 int tva_accept_sampling_wait_bound_test(const tva_sample_args *a, int32_t spins, void *stream) {
   if (!a || spins < 1 || spins > kCoopSpins || !a->workspace || a->workgroups_per_sequence < 2) return TVA_INVALID_ARG;
-  return accept_sampling_impl(a, stream, 1, spins);
+  return accept_sampling_impl(a, stream, 1, spins, false);
 }
 
-static int accept_sampling_impl(const tva_sample_args *a, void *stream, int missing_arrivals, int spins) {
+static int accept_sampling_impl(const tva_sample_args *a, void *stream, int missing_arrivals, int spins, bool fill) {
   if (!a || a->B < 0 || a->V < 1 || a->max_path < 1) return TVA_INVALID_ARG;
   if (a->B == 0) return TVA_OK;
   if (!a->parent || !a->cu_T || !a->draft_token || !a->p_target || !a->q_draft || !a->u || !a->u_final || !a->residual ||
@@ -839,6 +863,7 @@ static int accept_sampling_impl(const tva_sample_args *a, void *stream, int miss
   p.V = a->V, p.max_path = a->max_path;
   p.rowpart = nullptr, p.first = nullptr, p.pieces = row_pieces(a->V), p.sum_T = 0;
   p.unit_rows = a->unit_rows != 0;
+  p.fill_path = fill;
   // groups of four need every row to start on 16 bytes
   const bool vec = a->V % 4 == 0 && (((uintptr_t)a->p_target | (uintptr_t)a->q_draft | (uintptr_t)a->residual) & 15) == 0;
   if (a->sum_T < 0) return TVA_INVALID_ARG;

@@ -67,7 +67,7 @@ def make_expand_args(*, cu_N, score, logp, K: int, sum_N: int, max_N: int, cand_
 
 
 def expand_layer_raw(args: ExpandArgs, stream=None) -> None:
-    _check(_lib().tva_expand_layer(ctypes.byref(args), _stream_ptr(stream)))
+    binding.call_raw("tva_expand_layer", args, stream)
 
 
 def expand_layer(cu_N, score, logp, K: int, max_N: int, stream=None):
@@ -91,36 +91,15 @@ def select_subtree(score, parent, cu_M, cu_T, max_M: int, old_index=None, new_pa
                    total_kept: int = None):
     """Device tensors in; returns (old_index, new_parent), each int32 [cu_T[B]] (total_kept, a host copy of cu_T[B],
     sizes them when they are not passed)."""
-    import torch
-    B = cu_M.numel() - 1
-    if old_index is None:
-        old_index = torch.empty(max(1, total_kept), dtype=torch.int32, device=score.device)
-    if new_parent is None:
-        new_parent = torch.empty(max(1, total_kept), dtype=torch.int32, device=score.device)
-    _check(_lib().tva_tree_select_subtree(_p(score), _p(parent), _p(cu_M), _p(cu_T), B, int(max_M), _p(old_index),
-                                          _p(new_parent), _p(err_flag), _stream_ptr(stream)))
-    return old_index, new_parent
+    return binding._result(binding.native().select_subtree(score, parent, cu_M, cu_T, max_M, old_index, new_parent, err_flag, stream,
+                                                           total_kept))
 
 
 def rerank_count(tree_scores, cost_row, m: int, C3: float, count=None, cu_T=None, err_flag=None, stream=None, workspace=None):
     """Device tensors in (tree_scores float32 [B, N_tot], cost_row float64 [>= min(N_tot, m)]); returns the device
     tensors (count int32 [1], cu_T int32 [B + 1] = b * count).  workspace: a device tensor of
     tva_rerank_workspace_bytes(B, N_tot, m) bytes (allocated when not passed)."""
-    import torch
-    B, N_tot = int(tree_scores.shape[0]), int(tree_scores.shape[1])
-    if count is None:
-        count = torch.empty(1, dtype=torch.int32, device=tree_scores.device)
-    if cu_T is None:
-        cu_T = torch.empty(B + 1, dtype=torch.int32, device=tree_scores.device)
-    if workspace is None:
-        need = _lib().tva_rerank_workspace_bytes(B, N_tot, int(m))
-        if need == ctypes.c_size_t(-1).value:
-            raise binding.TvaError(-1)
-        workspace = torch.empty(max(1, need // 4), dtype=torch.float32, device=tree_scores.device)
-    _check(_lib().tva_tree_rerank_count(_p(tree_scores), B, N_tot, _p(cost_row), int(m), float(C3), _p(count), _p(cu_T),
-                                        _p(err_flag), _p(workspace), workspace.numel() * workspace.element_size(),
-                                        _stream_ptr(stream)))
-    return count, cu_T
+    return binding._result(binding.native().rerank_count(tree_scores, cost_row, m, C3, count, cu_T, err_flag, stream, workspace))
 
 
 def breadth_count(cand_score, draft_cost_row, target_cost_one: float, C1: float, count=None, u_c_at=None, err_flag=None,

@@ -64,18 +64,8 @@ def _lib():
 def accept_greedy(parent, cu_T, draft_token, target_token, max_path: int, path=None, path_len=None, next_token=None,
                   stream=None):
     """Device int32 tensors in; returns (path [B, max_path], path_len [B], next_token [B])."""
-    import torch
-    B = cu_T.numel() - 1
-    dev = cu_T.device
-    if path is None:
-        path = torch.full((B, max_path), -1, dtype=torch.int32, device=dev)
-    if path_len is None:
-        path_len = torch.empty(B, dtype=torch.int32, device=dev)
-    if next_token is None:
-        next_token = torch.empty(B, dtype=torch.int32, device=dev)
-    _check(_lib().tva_accept_greedy(_p(parent), _p(cu_T), _p(draft_token), _p(target_token), B, int(max_path),
-                                    _p(path), _p(path_len), _p(next_token), _stream_ptr(stream)))
-    return path, path_len, next_token
+    return binding._result(binding.native().accept_greedy(parent, cu_T, draft_token, target_token, max_path, path, path_len, next_token,
+                                                          stream))
 
 
 def accept_sampling(parent, cu_T, draft_token, p_target, q_draft, u, u_final, max_path: int, residual=None,
@@ -86,6 +76,12 @@ def accept_sampling(parent, cu_T, draft_token, p_target, q_draft, u, u_final, ma
     workgroups share a sequence (and, with sum_T, holds the row sums made ahead of the walk), None runs one
     workgroup per sequence, or a device tensor of tva_sample_workspace_bytes[_rows] bytes.  sum_T: the host's
     count of the batch's nodes (cu_T[B]), or 0."""
+    if not wait_bound_test_spins:
+        make = isinstance(workspace, str)
+        return binding._result(binding.native().accept_sampling(
+            parent, cu_T, draft_token, p_target, q_draft, u, u_final, max_path, residual, err_flag, stream, None if make else workspace,
+            make, workgroups_per_sequence, sum_T, unit_rows))
+    # (tests of the bounded wait: every wait misses one arrival and gives up)
     import torch
     B, V = cu_T.numel() - 1, int(p_target.shape[1])
     dev = cu_T.device
@@ -107,10 +103,7 @@ def accept_sampling(parent, cu_T, draft_token, p_target, q_draft, u, u_final, ma
     a.workgroups_per_sequence = int(workgroups_per_sequence)
     a.sum_T = int(sum_T)
     a.unit_rows = int(bool(unit_rows))
-    if wait_bound_test_spins:                 # (tests of the bounded wait: every wait misses one arrival and gives up)
-        _check(_lib().tva_accept_sampling_wait_bound_test(ctypes.byref(a), int(wait_bound_test_spins), _stream_ptr(stream)))
-    else:
-        _check(_lib().tva_accept_sampling(ctypes.byref(a), _stream_ptr(stream)))
+    _check(_lib().tva_accept_sampling_wait_bound_test(ctypes.byref(a), int(wait_bound_test_spins), _stream_ptr(stream)))
     return path, path_len, next_token
 
 
@@ -144,13 +137,16 @@ def make_commit_args(*, cu_T, L, path, path_len, k_tree, v_tree, k_cache, v_cach
 
 
 def commit_path_raw(args: CommitArgs, stream=None) -> None:
-    _check(_lib().tva_commit_path(ctypes.byref(args), _stream_ptr(stream)))
+    binding.call_raw("tva_commit_path", args, stream)
 
 
-def commit_path(**kw):
+def commit_path(*, cu_T, L, path, path_len, k_tree, v_tree, k_cache, v_cache, cu_L=None, page_table=None, page_size: int = 0,
+                strides=(0, 0, 0), L_out=None, err_flag=None, n_layers: int = 0, layer_stride_cache: int = 0,
+                layer_stride_tree: int = 0, stream=None):
     """Keyword arguments of make_commit_args plus stream; writes the caches in place."""
-    stream = kw.pop("stream", None)
-    commit_path_raw(make_commit_args(**kw), stream)
+    code = binding.native().commit_path(cu_T, L, path, path_len, k_tree, v_tree, k_cache, v_cache, cu_L, page_table, page_size, strides,
+                                        L_out, err_flag, n_layers, layer_stride_cache, layer_stride_tree, stream)
+    _check(code)
 
 
 def _bench(argv=None) -> int:
