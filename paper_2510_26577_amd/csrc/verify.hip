@@ -725,14 +725,17 @@ struct CommitParams {
   int32_t *L_out, *err_flag;
   int Hkv, D, max_path, page_size, max_pages;
   int64_t stride_page, stride_tok, stride_head;  // elements
-  int64_t layer_cache, layer_tree;                // bytes between the tensors of consecutive layers (blockIdx.z)
+  int64_t layer_cache, layer_tree;                // bytes between the tensors of consecutive layers
+  int n_layers, layers_per_wg;
 };
 
+// layers whose pieces a thread has in flight at once
+constexpr int kCommitLayers = 4;
 __global__ void __launch_bounds__(256) commit_kernel(const CommitParams p) {
-  const int j = blockIdx.x, b = blockIdx.y, layer = blockIdx.z;
+  const int j = blockIdx.x, b = blockIdx.y, layer0 = blockIdx.z * p.layers_per_wg;
   const int n = p.path_len[b];
   const int Lb = p.L[b];
-  if (j == 0 && layer == 0 && threadIdx.x == 0 && p.L_out) p.L_out[b] = Lb + (n < p.max_path ? n : p.max_path);
+  if (j == 0 && layer0 == 0 && threadIdx.x == 0 && p.L_out) p.L_out[b] = Lb + (n < p.max_path ? n : p.max_path);
   if (j >= n || Lb < 0) return;
   const int node = p.path[(size_t)b * p.max_path + j];
   if (node < 0 || node >= p.cu_T[b + 1] - p.cu_T[b]) {  // not a node of this tree: nothing is copied
@@ -763,9 +766,18 @@ __global__ void __launch_bounds__(256) commit_kernel(const CommitParams p) {
     const bool is_v = q >= pieces;
     const int r = is_v ? q - pieces : q;
     const int g = r / per_head, e = (r - g * per_head) * 8;
-    const char *src = (is_v ? p.v_tree : p.k_tree) + layer * p.layer_tree + ((src_row * p.Hkv + g) * p.D + e) * 2;
-    char *out = (is_v ? p.v_cache : p.k_cache) + layer * p.layer_cache + (dst + (int64_t)g * p.stride_head + e) * 2;
-    *reinterpret_cast<u32x4 *>(out) = *reinterpret_cast<const u32x4 *>(src);
+    const char *src = (is_v ? p.v_tree : p.k_tree) + ((src_row * p.Hkv + g) * p.D + e) * 2;
+    char *out = (is_v ? p.v_cache : p.k_cache) + (dst + (int64_t)g * p.stride_head + e) * 2;
+    const int end = layer0 + p.layers_per_wg < p.n_layers ? layer0 + p.layers_per_wg : p.n_layers;
+    for (int l = layer0; l < end; l += kCommitLayers) {
+      u32x4 x[kCommitLayers];
+#pragma unroll
+      for (int i = 0; i < kCommitLayers; ++i)
+        if (l + i < end) x[i] = *reinterpret_cast<const u32x4 *>(src + (l + i) * p.layer_tree);
+#pragma unroll
+      for (int i = 0; i < kCommitLayers; ++i)
+        if (l + i < end) *reinterpret_cast<u32x4 *>(out + (l + i) * p.layer_cache) = x[i];
+    }
   }
 }
 
@@ -939,10 +951,19 @@ int tva_commit_path(const tva_commit_args *a, void *stream) {
   p.stride_head = a->stride_head ? a->stride_head : a->D;
   p.stride_tok = a->stride_tok ? a->stride_tok : (int64_t)a->Hkv * a->D;
   p.stride_page = a->stride_page ? a->stride_page : (int64_t)p.page_size * p.stride_tok;
+  p.n_layers = layers;
   p.layer_cache = a->layer_stride_cache * 2, p.layer_tree = a->layer_stride_tree * 2;
   (void)hipGetLastError();
   if (in_cache) hipLaunchKernelGGL(compact_kernel, dim3(a->B, layers), dim3(256), 0, (hipStream_t)stream, p);
-  else hipLaunchKernelGGL(commit_kernel, dim3(a->max_path, a->B, layers), dim3(256), 0, (hipStream_t)stream, p);
+  else {
+    // A workgroup finds its row through a chain of three reads (length, node, position) before it moves a byte: where
+    // there are workgroups enough without one per layer, each moves the row in several layers (64 sequences, 32
+    // layers: 17.8 us one layer each -> 14.9, 3.6 TB/s read and written).
+    p.layers_per_wg = 1;
+    while (p.layers_per_wg < 8 && (int64_t)a->max_path * a->B * layers / (2 * p.layers_per_wg) >= 2048) p.layers_per_wg *= 2;
+    hipLaunchKernelGGL(commit_kernel, dim3(a->max_path, a->B, (layers + p.layers_per_wg - 1) / p.layers_per_wg), dim3(256), 0,
+                       (hipStream_t)stream, p);
+  }
   return hipPeekAtLastError() == hipSuccess ? TVA_OK : TVA_HIP_ERROR;
 }
 
