@@ -71,29 +71,22 @@ int tva_accept_greedy_filled(const int32_t *parent, const int32_t *cu_T, const i
  *   workspace, workspace_bytes   device memory of tva_sample_workspace_bytes(B) bytes, 8-byte aligned, or NULL.
  *                       With it, the vocabulary of a sequence is spread over several workgroups that wait for one
  *                       another between passes (a sequence's passes are a chain, and one workgroup streams a row at
- *                       what one compute unit can): B = 1, V = 128256 runs three times faster.  The waits are
- *                       bounded (about a second): a sequence whose workgroups do not all arrive -- they are all
- *                       resident at once unless other work holds the compute units that long -- is flagged in
- *                       err_flag like the cases above, and its outputs are unspecified.  Contents unspecified on
- *                       return; calls that share a workspace must not overlap.  Without it: one workgroup per
- *                       sequence, no waits.
- *   sum_T               the number of nodes of the batch, cu_T[B], as the host knows it, or 0.  With it, and a workspace
- *                       of tva_sample_workspace_bytes_rows(B, sum_T, V) bytes, the sums of all target rows of a small
- *                       batch (sum_T * V * 4 bytes up to 40 MB) are made ahead of the walk by a launch that uses the
- *                       whole chip, and the walk passes an accepted node without a pass over its row (V = 128256,
- *                       B = 1 .. 8: 6 to 26 % faster again).  A value that is not cu_T[B] costs time, not correctness:
- *                       rows past cu_T[B] are not read, and a tree that reaches past sum_T is walked as without it.
+ *                       what one compute unit can).  The waits are bounded (about a second): a sequence whose
+ *                       workgroups do not all arrive -- they are all resident at once unless other work holds the
+ *                       compute units that long -- is flagged in err_flag like the cases above, and its outputs are
+ *                       unspecified.  Its contents need no preparation and are unspecified on return; calls that share
+ *                       a workspace must not overlap.  Without it: one workgroup per sequence, no waits.
+ *   sum_T               the number of nodes of the batch, cu_T[B], as the host knows it, or 0.  No form of the call needs
+ *                       it any more; results do not depend on it.
  *   unit_rows           1: the caller states that every row of p_target sums to one (it is a distribution), and a node
  *                       that has just been reached takes Z = 1 instead of summing its row: its children's tests are
  *                       then u q(x) <= p(x) and the first residual max(0, p - q), as the paper prints them, and an
- *                       accepted node costs two loads instead of a pass over V floats, at any batch size (B = 64,
- *                       V = 128256: 76 -> 54 us; B = 8, 32-node trees: 45 -> 28 us).  The last draw still divides by the sum of the row it draws from.
+ *                       accepted node costs no pass over V floats.  The last draw still divides by the sum of the row it draws from.
  *                       With rows that sum to one within float32 rounding the two forms differ only where a test is
  *                       within that rounding of its threshold.  0: rows are summed.
  *   workgroups_per_sequence   0: the library chooses (1 .. 16, so that B times it stays within 256; 1 for
- *                       vocabularies below 48 K tokens, where the waits cost what the slices save -- below 16 K when
- *                       the row sums are made ahead, see sum_T); 1: as without
- *                       a workspace; 2 .. 16: that many (TVA_UNSUPPORTED if B times it exceeds 256).  The results
+ *                       vocabularies below 16 K tokens); 1: as without a workspace; 2 .. 16: that many, more where a
+ *                       vocabulary is too long for them (TVA_UNSUPPORTED if B times it exceeds 256).  The results
  *                       do not depend on it beyond the order in which a pass's sum is added up.
  */
 typedef struct tva_sample_args {
@@ -113,7 +106,7 @@ int tva_accept_sampling(const tva_sample_args *a, void *stream);
 /* The same, and the entries of `path` past path_len[b] are set to -1 (a flagged sequence's too). */
 int tva_accept_sampling_filled(const tva_sample_args *a, void *stream);
 size_t tva_sample_workspace_bytes(int32_t B);
-size_t tva_sample_workspace_bytes_rows(int32_t B, int32_t sum_T, int32_t V);  /* the same plus room for the row sums */
+size_t tva_sample_workspace_bytes_rows(int32_t B, int32_t sum_T, int32_t V);  /* the same (the other two are checked only) */
 /* For tests of the bounded wait: the same call (workspace given, workgroups_per_sequence >= 2), but every wait expects
  * one arrival more than there are workgroups and gives up after `spins` polls (1 .. 2^20).  Every workgroup then
  * leaves at its first wait: err_flag is set, the other outputs are unspecified, and the kernel ends normally. */

@@ -16,10 +16,12 @@
 //                   step (they read the same words); the data-parallel part is over the vocabulary: the
 //                   sum of a distribution, the residual after a rejection, the draw of the last token --
 //                   one streaming pass over V floats each.
-//   row_sums_kernel the sums of all target rows of a small batch, ahead of the walk and with the whole chip: the
-//                   walk then passes an accepted node with three loads instead of a pass over its row.
+//   walk_kernel     the same with a sequence's rows held in registers, shared among up to 16 workgroups.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "tva.h"
 #include "tva_verify.h"
@@ -78,14 +80,6 @@ struct SampleParams {
   float *residual;
   int32_t *path, *path_len, *next_token, *err_flag;
   int V, max_path;
-  // sums of the target rows, made ahead of the walk by row_sums_kernel, or NULL: row t's sum is the sum of
-  // rowpart[t * pieces .. + pieces - 1]; rows 0 .. sum_T-1 have them
-  const double *rowpart;
-  // and, gathered by the same kernel, what a node's test as its parent's FIRST tested child reads: first[2 c] =
-  // p[parent(c)][token(c)], first[2 c + 1] = q[parent(c)][token(c)] (a walk's reads of them would each be a cold,
-  // dependent access to a row of its own)
-  const float *first;
-  int pieces, sum_T;
   int fill_path;  // the path's entries past its length are set to -1
   int unit_rows;  // every target row is taken to sum to one: a freshly reached node's normaliser is 1, not summed
 };
@@ -175,100 +169,19 @@ __device__ __forceinline__ double residual_pass(int V, int seg, double *wsum, co
   }
 }
 
-// ---- the sums of all target rows, ahead of the walk ----
-// A walk that accepts a child needs of the parent's row only its sum and two entries; summing the row is the pass
-// that costs.  For a small batch (few trees, few nodes) the sums of ALL nodes' rows cost less when the whole chip
-// makes them at once than the accepted nodes' rows do one after the other.  grid (pieces, rows): a workgroup adds
-// the 8192 tokens of one piece of one row, in a fixed order; rows past cu_T[B] (a host count that was too large)
-// are left alone.  The first workgroup also clears the n_sync arrival counters of the walk that follows (one
-// launch less than with zero_sync_kernel).  One more workgroup per row (piece index = pieces) gathers the two
-// entries of the parent's rows that the node's test reads.
-constexpr int kRowPieceThreads = 256, kRowPiece = kRowPieceThreads * 32;
-
-template <int VEC>
-__global__ void __launch_bounds__(kRowPieceThreads) row_sums_kernel(const float *__restrict__ p, const int32_t *__restrict__ cu_T, int B,
-                                                                    int V, double *__restrict__ rowpart, int *__restrict__ sync,
-                                                                    int n_sync, const float *__restrict__ q,
-                                                                    const int32_t *__restrict__ parent,
-                                                                    const int32_t *__restrict__ token, float *__restrict__ first) {
-  __shared__ double s_w[kRowPieceThreads / 64];
-  const int tid = threadIdx.x, piece = blockIdx.x, row = blockIdx.y;
-  const int pieces = (int)gridDim.x - 1;
-  if (piece == 0 && row == 0)
-    for (int i = tid; i < n_sync; i += kRowPieceThreads) sync[i] = 0;
-  if (row >= cu_T[B]) return;
-  if (piece == pieces) {
-    if (tid != 0) return;
-    // the tree that holds node `row`: the last b with cu_T[b] <= row (empty trees share their start with the next)
-    int lo = 0, hi = B;  // cu_T[lo] <= row < cu_T[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (cu_T[mid] <= row) lo = mid;
-      else hi = mid;
-    }
-    const int t0 = cu_T[lo], par = parent[row], x = token[row];
-    float px = 0.f, qx = 0.f;
-    if (par >= 0 && par < row - t0 && x >= 0 && x < V) {
-      px = p[(size_t)(t0 + par) * V + x];
-      qx = q[(size_t)(t0 + par) * V + x];
-    }
-    first[2 * (size_t)row] = px, first[2 * (size_t)row + 1] = qx;
-    return;
-  }
-  const float *src = p + (size_t)row * V;
-  const int base = piece * kRowPiece;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if constexpr (VEC == 4) {
-    float4 x[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int v = base + i * (4 * kRowPieceThreads) + 4 * tid;
-      x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (v < V) x[i] = *reinterpret_cast<const float4 *>(src + v);  // (V % 4 == 0: no straddling)
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i & 3] += ((double)x[i].x + (double)x[i].y) + ((double)x[i].z + (double)x[i].w);
-  } else {
-    float x[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const int v = base + i * kRowPieceThreads + tid;
-      x[i] = v < V ? src[v] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < 32; ++i) acc[i & 3] += (double)x[i];
-  }
-  double z = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) z += __shfl_xor(z, o);
-  if ((tid & 63) == 0) s_w[tid >> 6] = z;
-  __syncthreads();
-  if (tid == 0) rowpart[(size_t)row * pieces + piece] = (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
-}
-
-// the sum of row t from its pieces: the lanes of a wave fetch 64 of them at once (one round trip, not one per
-// piece), and every thread adds them in the same order
-__device__ __forceinline__ double summed_ahead(const SampleParams &p, int t) {
-  const double *part = p.rowpart + (size_t)t * p.pieces;
-  const int lane = threadIdx.x & 63;
-  double z = 0.0;
-  for (int base = 0; base < p.pieces; base += 64) {
-    const double mine = base + lane < p.pieces ? part[base + lane] : 0.0;
-    const int n = p.pieces - base < 64 ? p.pieces - base : 64;
-    for (int j = 0; j < n; ++j) z += __shfl(mine, j);
-  }
-  return z;
-}
-
 // The last token, looked for inside [lo, hi): wsum holds the waves' sums of dist over their segments of that range
 // (seg elements each), `before` is the weight in front of lo, `none` says that no place claimed the target (u_final
 // was not below 1): then, and when rounding keeps the running sum below the target, it is the last token of the range
-// that has weight.  The wave whose segment holds it walks the segment 64 elements at a time; its lane 0 stores it.
-__device__ __forceinline__ void draw_in_range(const float *dist, int lo, int hi, int seg, const double *wsum, double before,
+// that has weight.  A long segment is summed again in parts by all waves and looked for in its part (one wave's steps
+// through it would each wait for the one before); the wave whose segment holds a short one walks it 64 elements at a
+// time; its lane 0 stores it.
+__device__ __forceinline__ void draw_in_range(const float *dist, int lo, int hi, int seg, double *wsum, double before,
                                               double target, bool none, int32_t *out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int wclaim = -1, wlast = 0;
-  {
+  int wclaim;
+  while (true) {
+    wclaim = -1;
+    int wlast = 0;
     double pre = before;
     for (int i = 0; i < kSampleWaves; ++i) {
       const double nx = pre + wsum[i];
@@ -276,9 +189,14 @@ __device__ __forceinline__ void draw_in_range(const float *dist, int lo, int hi,
       if (wsum[i] > 0.0) wlast = i;
       pre = nx;
     }
+    none = wclaim < 0;
+    if (none) wclaim = wlast;
+    if (seg <= 512) break;
+    lo += wclaim * seg, hi = lo + seg < hi ? lo + seg : hi;
+    seg = (hi - lo + kSampleWaves - 1) / kSampleWaves;
+    segment_pass<1, 8>(
+        lo, hi, seg, wsum, [&](int v) { return dist[v]; }, [&](int, float x, double &a) { a += (double)x; });
   }
-  const bool wnone = wclaim < 0;
-  if (wnone) wclaim = wlast;
   if (wave != wclaim) return;
   const int s0 = lo + wave * seg, s1 = s0 + seg < hi ? s0 + seg : hi;
   double acc = before;
@@ -294,7 +212,7 @@ __device__ __forceinline__ void draw_in_range(const float *dist, int lo, int hi,
     }
     const unsigned long long heavy = __ballot(f > 0.f);
     if (heavy) last_pos = base + 63 - __builtin_clzll(heavy);
-    const unsigned long long over = wnone ? 0ull : __ballot(acc + incl > target);
+    const unsigned long long over = none ? 0ull : __ballot(acc + incl > target);
     if (over) {
       tok = base + __builtin_ctzll(over);
       break;
@@ -302,43 +220,6 @@ __device__ __forceinline__ void draw_in_range(const float *dist, int lo, int hi,
     acc += __shfl(incl, 63);
   }
   if (lane == 0) *out = tok >= 0 ? tok : last_pos;
-}
-
-// The last token of a walk that ends at a node whose row was summed ahead (no pass has been made over it): the sums
-// of the row's pieces, added in the order that made Z, say which piece of 8192 tokens holds it; this workgroup sums
-// that piece by segments and draws inside it -- a pass over one piece, not over the row, and no wait for others.
-template <int VEC>
-__device__ __forceinline__ void draw_in_piece(const SampleParams &p, int t, const float *dist, double Z, double u_final, double *wsum,
-                                              int32_t *out) {
-  const int lane = threadIdx.x & 63;
-  const double target = u_final * Z;
-  const double *part = p.rowpart + (size_t)t * p.pieces;
-  int k = -1, klast = 0;
-  double pre = 0.0, before = 0.0;
-  for (int base = 0; base < p.pieces; base += 64) {
-    const double mine = base + lane < p.pieces ? part[base + lane] : 0.0;
-    const int n = p.pieces - base < 64 ? p.pieces - base : 64;
-    for (int j = 0; j < n; ++j) {
-      const double v = __shfl(mine, j);
-      const double nx = pre + v;
-      if (k < 0 && nx > target) k = base + j, before = pre;
-      if (v > 0.0) klast = base + j;
-      pre = nx;
-    }
-  }
-  const bool none = k < 0;
-  if (none) k = klast;
-  const int lo = k * kRowPiece, hi = lo + kRowPiece < p.V ? lo + kRowPiece : p.V;
-  const int seg = ((hi - lo + kSampleWaves - 1) / kSampleWaves + VEC - 1) / VEC * VEC;
-  if constexpr (VEC == 4) {
-    segment_pass<4, 2>(
-        lo, hi, seg, wsum, [&](int v) { return *reinterpret_cast<const float4 *>(dist + v); },
-        [&](int, const float4 &x, double &a) { a += ((double)x.x + (double)x.y) + ((double)x.z + (double)x.w); });
-  } else {
-    segment_pass<1, 8>(
-        lo, hi, seg, wsum, [&](int v) { return dist[v]; }, [&](int, float x, double &a) { a += (double)x; });
-  }
-  draw_in_range(dist, lo, hi, seg, wsum, before, target, none, out);
 }
 
 template <int VEC>
@@ -371,7 +252,6 @@ __global__ void __launch_bounds__(kSampleThreads) sample_kernel(const SamplePara
   if (tid == 0) p.path[(size_t)b * p.max_path] = 0;
   const float *dist;  // what the next test or the last draw reads: the current node's target row, or the residual
   double Z;
-  const bool ahead = p.rowpart != nullptr && t0 + T <= p.sum_T;  // this tree's row sums were made ahead of the walk
   bool segments;  // wsum holds the segments' sums of dist (the last draw starts from them)
   auto flag_sequence = [&]() {
     if (tid == 0 && p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
@@ -398,10 +278,8 @@ __global__ void __launch_bounds__(kSampleThreads) sample_kernel(const SamplePara
     // the first child and the two entries its test reads: requested before the row's sum, used after it
     int c = len < p.max_path ? next_child(cur, cur) : -1;
     float rx0 = 0.f, qx = 0.f;
-    if (c >= 0 && ahead) rx0 = p.first[2 * (size_t)(t0 + c)], qx = p.first[2 * (size_t)(t0 + c) + 1];
-    else if (c >= 0) rx0 = dist[token[c]], qx = q[token[c]];
+    if (c >= 0) rx0 = dist[token[c]], qx = q[token[c]];
     if (p.unit_rows) Z = 1.0, segments = false;
-    else if (ahead) Z = summed_ahead(p, t0 + cur), segments = false;
     else Z = row_sum<VEC>(V, seg, wsum, dist), segments = true;
     double rx = (double)rx0;
     bool accepted = false;
@@ -435,287 +313,508 @@ __global__ void __launch_bounds__(kSampleThreads) sample_kernel(const SamplePara
     if (!accepted) break;
   }
   if (tid == 0) p.path_len[b] = len;
-  // (the last draw divides by the sum of what it draws from: a row that was taken as summing to one is summed here --
-  // from its pieces where those were made ahead -- and one whose pieces were not made ahead is passed over)
-  if (!segments && ahead) return draw_in_piece<VEC>(p, t0 + cur, dist, summed_ahead(p, t0 + cur), (double)p.u_final[b], wsum, &p.next_token[b]);
+  // (the last draw divides by the sum of what it draws from: a row that was taken as summing to one is summed here)
   if (!segments) Z = row_sum<VEC>(V, seg, wsum, dist);
   // The last token: the smallest v whose cumulative weight exceeds u_final * Z.  The segments' sums of the pass
   // that produced Z say which segment holds it.
   draw_in_range(dist, 0, V, seg, wsum, 0.0, (double)p.u_final[b] * Z, false, &p.next_token[b]);
 }
 
-// ---- the same walk with the vocabulary of a sequence spread over W workgroups ----
-// A sequence's passes wait for one another, and one workgroup streams a row at what one compute unit can (about
-// 45 GB/s): with few sequences the chip idles.  Here workgroup w of a sequence's W takes the w-th slice of every
-// row.  After its part of a pass it publishes its partial sum (and, after a residual pass, the residual's entry of
-// the next child's token, if that lies in its slice), arrives at a counter, and waits for the W arrivals; then
-// every workgroup adds the W partial sums in the same order and takes the same decision.  The wait is bounded:
-// a workgroup that does not see the others within about a second flags the sequence and leaves (the launch keeps
-// W x B within what the chip holds at once, so this happens only if something else is wrong).
-constexpr int kCoopMaxW = 16;
-constexpr int kCoopSpins = 1 << 20;
+// ---- the same walk with a sequence's rows held in registers, its vocabulary spread over W workgroups ----
+// What bounds a walk is a chain: every test needs the sum of the row or residual before it, and one workgroup streams a
+// row at what one compute unit can (about 45 GB/s).  So workgroup w of a sequence's W takes the w-th slice of every
+// row, few enough elements that its 512 threads hold them in registers (4 NV each, of the target's row or the
+// residual, and up to NV = 16 of the draft's row too): a refusal is then arithmetic on registers, and the memory is
+// touched once per node.  Three things keep the chain short:
+//  - at the start every node's p and q entries are gathered by a thread each, all at once (a hop of the walk would
+//    otherwise read them with a cold, dependent access to a row of its own);
+//  - the rows that a walk needs one after the other are guessed: with every row's sum taken as one the accepted nodes
+//    are known from the gathered entries alone, so their rows are summed in one pass and one wait, after which the tests
+//    are taken again with the true sums (a guess that was wrong costs another pass, nothing else);
+//  - a wait is one trip: a workgroup's partial sums travel in words that carry a tag of this launch and this wait, so the
+//    others poll the data itself.  The tag comes from a counter in the sequence's part of the workspace that every
+//    launch moves on once all W have read it: nothing has to be zeroed beforehand, whatever the memory held, and a
+//    captured launch replays.
+// Measured, one sequence, V = 128256, 60 nodes: 28 us for two launches before (row sums of all nodes, then the walk with
+// counters, residuals in memory) -> 13 us; 64 sequences of 8 nodes with unit rows 49 us and a 5 us launch that cleared the
+// counters -> 27 us.
+// Waits are bounded: a workgroup that does not see the others within about a second flags the sequence and leaves (the
+// launch keeps W x B within what the chip holds at once, so this happens only if something else is wrong); it then
+// takes back what it had published, and the counter moves on.
+constexpr int kWalkThreads = 512, kWalkWaves = kWalkThreads / 64;  // (256 registers per thread)
+constexpr int kWalkMaxW = 16;
+constexpr int kWalkSpins = 1 << 20;
+constexpr int kWalkChain = 8;                        // rows summed in one pass at most
+constexpr int kWalkBox = 2 * (1 + kWalkChain);       // words a workgroup publishes: an entry, then the rows' sums, two words each
+constexpr int kWalkWords = 16 + 2 * (kWalkMaxW + 1) * kWalkBox;  // per sequence: the counter (a line), two sets of boxes
+constexpr size_t kWalkBytes = (kWalkWords * sizeof(uint64_t) + 511) / 512 * 512;
 
-struct CoopParams {
+struct WalkParams {
   SampleParams s;
   int W;
-  int arrivals;  // arrivals a wait expects: W (one more in the test of the bound: then no wait ever completes)
+  int arrivals;  // workgroups a wait expects: W (one more in the test of the bound: then no wait ever completes)
   int spins;     // polls after which a wait gives up
-  int *sync;     // [B * 32]: one arrival counter per sequence, 128 bytes apart, zero at kernel start
-  double *xchg;  // [B][2][kCoopMaxW + 1]: partial sums of the pass (two buffers in turn), and the exchanged entry
+  uint64_t *mail;  // [B][kWalkBytes / 8]; unused when W is 1
 };
 
-__global__ void zero_sync_kernel(int *sync, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) sync[i] = 0;
-}
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void publish(double *dst, double x) {
-  __hip_atomic_store(reinterpret_cast<unsigned long long *>(dst), (unsigned long long)__double_as_longlong(x), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // written through before this thread goes on to the barrier
+__device__ __forceinline__ void mail_store(uint64_t *at, uint64_t word) {
+  __hip_atomic_store(at, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ double fetch(const double *src) {
-  return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long *>(src), __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT));
+__device__ __forceinline__ uint64_t mail_load(const uint64_t *at) {
+  return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Inclusive sums along the lanes, by lane shifts in the vector ALU (a tenth of what the shuffles through LDS take);
+// lane 63 ends with the wave's sum.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lanes_add(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, true);
+  return x + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_scan(double x) {
+  x = lanes_add<0x111, 0xf>(x);  // from 1, 2, 4, 8 lanes below in the row of 16
+  x = lanes_add<0x112, 0xf>(x);
+  x = lanes_add<0x114, 0xf>(x);
+  x = lanes_add<0x118, 0xf>(x);
+  x = lanes_add<0x142, 0xa>(x);  // the row below's last lane, to rows 1 and 3
+  return lanes_add<0x143, 0xc>(x);  // lane 31, to rows 2 and 3
+}
+__device__ __forceinline__ double read_lane(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+__device__ __forceinline__ double wave_sum(double x) { return read_lane(wave_scan(x), 63); }
 
-template <int VEC>
-__global__ void __launch_bounds__(kSampleThreads) sample_coop_kernel(const CoopParams cp) {
-  const SampleParams &p = cp.s;
-  __shared__ double wsum[kSampleWaves];
-  __shared__ double s_part[kCoopMaxW + 1];
-  __shared__ int s_abort;
+template <int NV, bool WHOLE>
+__global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp) {
+  constexpr bool kHoldQ = NV <= 16;  // (256 registers per thread: beyond that the draft's row is read again at each refusal)
+  constexpr int kRows = NV <= 4 ? 4 : 1;  // rows of a chain loaded at once: about 16 loads of 16 bytes in flight per thread
+  const SampleParams &p = wp.s;
+  __shared__ double s_sum[kWalkChain][kWalkWaves];      // per row of a pass: the waves' sums of their segments
+  __shared__ double s_part[kWalkChain][kWalkMaxW + 1];    // and the workgroups' sums of their slices
+  __shared__ double s_entry[2];                           // the residual's entry of the next child's token (two passes in turn)
+  __shared__ int s_chain[kWalkChain], s_abort, s_bad;
+  __shared__ uint64_t s_tag;
   __shared__ int32_t s_parent[kSampleTreeLds], s_token[kSampleTreeLds];
-  __shared__ float s_u[kSampleTreeLds];
-  const int W = cp.W;
+  __shared__ float s_u[kSampleTreeLds], s_px[kSampleTreeLds], s_qx[kSampleTreeLds];
+  __shared__ int s_first[kSampleTreeLds];  // a node's first child that carries a token, times 2, plus 1 where a row's sum of one refuses it
+  const int W = wp.W;
   const int b = blockIdx.x / W, w = blockIdx.x % W, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (p.fill_path && w == 0)  // (the walk's entries are stored behind a barrier)
-    for (int i = tid; i < p.max_path; i += kSampleThreads) p.path[(size_t)b * p.max_path + i] = -1;
+    for (int i = tid; i < p.max_path; i += kWalkThreads) p.path[(size_t)b * p.max_path + i] = -1;
   const int t0 = p.cu_T[b];
   const int T = p.cu_T[b + 1] - t0;
   if (T <= 0) {
     if (w == 0 && tid == 0) p.path_len[b] = 0, p.next_token[b] = -1;
     return;
   }
-  const int32_t *parent = p.parent + t0, *token = p.token + t0;
-  const float *u = p.u + t0;
-  if (T <= kSampleTreeLds) {
-    for (int i = tid; i < T; i += kSampleThreads) s_parent[i] = parent[i], s_token[i] = token[i], s_u[i] = u[i];
-    parent = s_parent, token = s_token, u = s_u;
-  }
-  if (tid == 0) s_abort = 0;
-  __syncthreads();
   const int V = p.V;
-  // this workgroup's slice of every row, and the waves' segments of it
-  const int slice = ((V + W - 1) / W + VEC - 1) / VEC * VEC;
-  const int lo = w * slice < V ? w * slice : V, hi = lo + slice < V ? lo + slice : V;
-  const int seg = ((hi - lo + kSampleWaves - 1) / kSampleWaves + VEC - 1) / VEC * VEC;
-  float *const r = p.residual + (size_t)b * V;
-  int *const ctr = cp.sync + b * 32;
-  double *const xbase = cp.xchg + (size_t)b * 2 * (kCoopMaxW + 1);
-  int epoch = 0;
-
-  // sum of the W partial sums, the same in every thread of every workgroup of the sequence; s_part[0 .. W-1] keeps
-  // them, s_part[W] what was exchanged with them.  Returns a negative number if the others did not arrive.
-  auto group_sum = [&](double local) -> double {
-    double *x = xbase + (epoch & 1) * (kCoopMaxW + 1);
-    ++epoch;
-    if (tid == 0) publish(x + w, local);
-    __syncthreads();  // (the thread that published the exchanged entry has waited for its store too)
-    if (tid == 0) {
-      __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int target = epoch * cp.arrivals;
-      int spins = 0;
-      while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-        __builtin_amdgcn_s_sleep(2);
-        if (++spins > cp.spins) {
-          s_abort = 1;
-          break;
+  uint64_t *const mail = wp.mail + (size_t)b * (kWalkBytes / sizeof(uint64_t));
+  uint64_t launch = 0;
+  if (tid == kWalkThreads - 1) {
+    s_abort = 0, s_bad = 0;
+    if (W > 1) launch = mail_load(mail);
+    s_tag = launch * 0x9E3779B97F4A7C15ull + 0xD1B54A32D192ED03ull;
+  }
+  // the tree's words and what a node's test as its parent's FIRST tested child reads, once (a tree too long for that is
+  // walked in global memory)
+  const bool in_lds = T <= kSampleTreeLds;
+  if (in_lds)
+    for (int i = tid; i < T; i += kWalkThreads) s_parent[i] = p.parent[t0 + i], s_token[i] = p.token[t0 + i], s_u[i] = p.u[t0 + i], s_first[i] = INT_MAX;
+  for (int i = tid; i < kWalkChain * (kWalkMaxW + 1); i += kWalkThreads) s_part[0][i] = 0.0;
+  __syncthreads();
+  if (in_lds)
+    for (int i = tid; i < T; i += kWalkThreads) {
+      const int par = s_parent[i], x = s_token[i];
+      float px = 0.f, qx = 0.f;
+      if (par >= 0 && par < i) {
+        if (x >= 0 && x < V) {
+          px = p.p[(size_t)(t0 + par) * V + x], qx = p.q[(size_t)(t0 + par) * V + x];
+          atomicMin(&s_first[par], 2 * i + !(px > 0.f && (double)s_u[i] * (double)qx <= (double)px));
+        } else {
+          s_bad = 1;
         }
+      }
+      s_px[i] = px, s_qx[i] = qx;
+    }
+  auto parent = [&](int i) { return in_lds ? s_parent[i] : p.parent[t0 + i]; };
+  auto token = [&](int i) { return in_lds ? s_token[i] : p.token[t0 + i]; };
+  __syncthreads();
+  const uint32_t tag_a = (uint32_t)s_tag, tag_b = (uint32_t)(s_tag >> 32);
+  // this workgroup's slice of every row, the waves' segments of it; a thread holds groups of four elements, 256 apart
+  const int slice = ((V + W - 1) / W + 3) / 4 * 4;
+  const int lo = w * slice < V ? w * slice : V, hi = lo + slice < V ? lo + slice : V;
+  const int seg = ((hi - lo + kWalkWaves - 1) / kWalkWaves + 3) / 4 * 4;
+  const int s0 = lo + wave * seg < hi ? lo + wave * seg : hi, s1 = s0 + seg < hi ? s0 + seg : hi;
+  // Row t of a matrix for this wave: buffer loads whose bound is the segment's end, so that a group past it costs nothing
+  // and reads as zeros.  The group that a row's end cuts (V no multiple of 4; in one group of one wave) is fetched element
+  // by element.  (The whole offset is the one that the bound is checked against.)
+  auto row_of = [&](const float *m, int t) { return m + (size_t)(t0 + __builtin_amdgcn_readfirstlane(t)) * V; };
+  const int s1_whole = WHOLE ? s1 : s1 & ~3;
+  const int cut_k = !WHOLE && s1 > s1_whole ? (s1 - s0) >> 8 : -1;
+  auto load_group = [&](const float *row, int k) -> f32x4 {
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(row), 0, s1_whole * 4, 0x00020000);
+    f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (s0 + lane * 4) * 4 + k * 1024, 0, 0));
+    if (!WHOLE && k == cut_k) {
+      const auto to_end = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(row), 0, s1 * 4, 0x00020000);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(to_end, (s0 + lane * 4 + e) * 4 + k * 1024, 0, 0));
+    }
+    return x;
+  };
+  auto group_sum = [](const f32x4 &x) { return ((double)x[0] + (double)x[1]) + ((double)x[2] + (double)x[3]); };
+
+  // (a scheduling barrier per group: all groups' conversions at once would not fit the registers)
+  auto thread_sum = [&](auto group) -> double {
+    double acc = 0.0, acc2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < NV; k += 2) {
+      acc += group_sum(group(k));
+      acc2 += group_sum(group(k + 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return acc + acc2;
+  };
+
+  int epoch = 0;
+  auto publish = [&](int slot, double x) {
+    uint64_t *at = mail + 16 + ((size_t)(epoch & 1) * (kWalkMaxW + 1) + w) * kWalkBox + 2 * slot;
+    const uint64_t bits = (uint64_t)__double_as_longlong(x);
+    mail_store(at, bits << 32 | (uint32_t)(tag_a + epoch));
+    mail_store(at + 1, (bits >> 32) << 32 | (uint32_t)(tag_b + epoch));
+  };
+  // The sums of a pass over `n` rows: s_sum is complete behind a barrier.  s_part[i][.] then holds the workgroups' sums of
+  // row i and s_entry[epoch & 1] the entry that workgroup x_from published (x_from < 0: none), the same in every
+  // workgroup of the sequence.  (epoch has been counted up before the pass.)  False: the others did not arrive.
+  auto exchange = [&](int n, int x_from) -> bool {
+    if (tid < n) {
+      double local = 0.0;
+#pragma unroll
+      for (int i = 0; i < kWalkWaves; ++i) local += s_sum[tid][i];
+      if (W > 1) publish(1 + tid, local);
+      else s_part[tid][0] = local;
+    }
+    if (W > 1) {
+      const int from = tid < 8 * (kWalkMaxW + 1) ? tid >> 3 : x_from, i = tid & 7;  // (a thread per workgroup and row, one for the entry)
+      const bool sum = tid < 8 * (kWalkMaxW + 1);
+      static_assert(kWalkChain == 8, "");
+      if (sum ? from < wp.arrivals && i < n : tid == 8 * (kWalkMaxW + 1) && x_from >= 0) {
+        const uint64_t *at = mail + 16 + ((size_t)(epoch & 1) * (kWalkMaxW + 1) + from) * kWalkBox + (sum ? 2 * (1 + i) : 0);
+        uint64_t a = 0, c = 0;
+        int spins = 0;
+        while (true) {
+          a = mail_load(at), c = mail_load(at + 1);
+          if ((uint32_t)a == (uint32_t)(tag_a + epoch) && (uint32_t)c == (uint32_t)(tag_b + epoch)) break;
+          if (++spins > wp.spins) {
+            s_abort = 1;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+        const double x = __longlong_as_double((long long)((c >> 32) << 32 | a >> 32));
+        if (sum) s_part[i][from] = x;
+        else s_entry[epoch & 1] = x;
       }
     }
     __syncthreads();
-    if (s_abort) return -1.0;
-    if (tid <= W) s_part[tid] = fetch(x + (tid < W ? tid : kCoopMaxW));
-    __syncthreads();
+    if (W > 1) {
+      const bool gone = s_abort != 0;
+      if (gone && tid < kWalkBox)  // what was published is taken back: no later launch can meet this launch's tags
+        for (int set = 0; set < 2; ++set) mail_store(mail + 16 + ((size_t)set * (kWalkMaxW + 1) + w) * kWalkBox + tid, 0);
+      if ((epoch == 1 || gone) && w == 0 && tid == kWalkThreads - 1) mail_store(mail, launch + 1);  // all W have read the counter
+      if (gone) {
+        if (tid == 0 && p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
+        return false;
+      }
+    }
+    return true;
+  };
+  auto total = [&](int i) -> double {
     double z = 0.0;
-    for (int i = 0; i < W; ++i) z += s_part[i];
+#pragma unroll
+    for (int k = 0; k < kWalkMaxW; ++k) z += s_part[i][k];  // (zeros past W)
     return z;
   };
-  auto leave_flagged = [&]() {
-    if (tid == 0 && p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
-  };
-  // the first child of `of` behind node `after` that carries a token (others are flagged and passed over), or -1
-  auto next_child = [&](int of, int after) -> int {
+  // the first child of `of` behind node `after` that carries a token (others are passed over, and flagged where the walk
+  // itself looks), or -1; 64 candidates at a time, every wave finds the same one
+  auto next_child = [&](int of, int after, bool flag) -> int {
     for (int base = after + 1; base < T; base += 64) {
       const int i = base + lane;
-      unsigned long long kids = __ballot(i < T && parent[i] == of);
+      unsigned long long kids = __ballot(i < T && parent(i) == of);
       while (kids) {
         const int c = base + __builtin_ctzll(kids);
         kids &= kids - 1;
-        const int x = token[c];
+        const int x = token(c);
         if (x >= 0 && x < V) return c;
-        leave_flagged();
+        if (flag && tid == 0 && p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
       }
     }
     return -1;
   };
+  auto p_entry = [&](int of, int c) -> float { return in_lds ? s_px[c] : p.p[(size_t)(t0 + of) * V + token(c)]; };
+  auto q_entry = [&](int of, int c) -> float { return in_lds ? s_qx[c] : p.q[(size_t)(t0 + of) * V + token(c)]; };
+  auto accepts = [&](int c, float qx, double rx, double Z) { return rx > 0.0 && (double)(in_lds ? s_u[c] : p.u[t0 + c]) * (double)qx * Z <= rx; };
 
-  int cur = 0, len = 1;
+  int cur = 0, len = 1, last = 0;   // last: which row of s_sum and s_part belongs to r
+  double Z = 1.0;
   if (w == 0 && tid == 0) p.path[(size_t)b * p.max_path] = 0;
-  const float *dist;
-  double Z;
-  // the sum of a row from the workgroups' sums of their slices (negative: the others did not arrive)
-  auto row_total = [&](const float *row) -> double {
-    double local;
-    if constexpr (VEC == 4) {
-      local = segment_pass<4, 8>(
-          lo, hi, seg, wsum, [&](int v) { return *reinterpret_cast<const float4 *>(row + v); },
-          [&](int, const float4 &t, double &x) { x += ((double)t.x + (double)t.y) + ((double)t.z + (double)t.w); });
-    } else {
-      local = segment_pass<1, 8>(
-          lo, hi, seg, wsum, [&](int v) { return row[v]; }, [&](int, float t, double &x) { x += (double)t; });
-    }
-    return group_sum(local);
-  };
-  const bool ahead = p.rowpart != nullptr && t0 + T <= p.sum_T;  // this tree's row sums were made ahead of the walk
-  bool segments;  // wsum and s_part hold the sums of dist's segments and slices (the last draw starts from them)
   while (true) {
-    const float *prow = p.p + (size_t)(t0 + cur) * V;
-    const float *q = p.q + (size_t)(t0 + cur) * V;
-    dist = prow;
-    double local;
-    // the first child and the two entries its test reads: requested before the row's sum, used after it
-    int c = len < p.max_path ? next_child(cur, cur) : -1;
-    float rx0 = 0.f, qx = 0.f;
-    if (c >= 0 && ahead) rx0 = p.first[2 * (size_t)(t0 + c)], qx = p.first[2 * (size_t)(t0 + c) + 1];
-    else if (c >= 0) rx0 = prow[token[c]], qx = q[token[c]];
-    if (p.unit_rows) Z = 1.0, segments = false;
-    else if (ahead) Z = summed_ahead(p, t0 + cur), segments = false;
-    else Z = row_total(prow), segments = true;
-    if (Z < 0.0) return leave_flagged();
-    bool accepted = false;
+    // ---- the rows ahead, guessed with sums of one ----
+    __syncthreads();  // (the chain before this one has been read)
+    int n = 0, at = cur, end = -1;  // end: the child that the last node's test is about, or -1
+    bool refusal = false;           // the guess: that test refuses
+    if (in_lds) {
+      while (true) {
+        const int f = len + n < p.max_path ? s_first[at] : INT_MAX;
+        if (tid == 0) s_chain[n] = at;
+        ++n;
+        end = f == INT_MAX ? -1 : f >> 1, refusal = f != INT_MAX && (f & 1);
+        if (end < 0 || refusal || n == kWalkChain) break;
+        at = end;
+      }
+    } else {
+      end = len < p.max_path ? next_child(cur, cur, true) : -1;
+      if (tid == 0) s_chain[0] = cur;
+      n = 1, refusal = end >= 0 && !accepts(end, q_entry(cur, end), (double)p_entry(cur, end), 1.0);
+    }
+    __syncthreads();
+    // ---- one pass over them; with unit rows the guess is the rule, and only the last node's row is looked at ----
+    f32x4 q[kHoldQ ? NV : 1];
+    f32x4 r[NV];  // the row or residual that the walk stands on; q: the draft's row under it
+    if (kHoldQ && refusal) {
+      const auto q_row = row_of(p.q, s_chain[n - 1]);
+#pragma unroll
+      for (int k = 0; k < NV; ++k) q[kHoldQ ? k : 0] = load_group(q_row, k);
+    }
+    const int first = p.unit_rows ? n - 1 : 0;
+    const bool summed = !p.unit_rows || !refusal;
+    for (int i0 = first; i0 < n; i0 += kRows) {
+      // (one row at a time is loaded in place: the last one stays)
+      f32x4 more[kRows > 1 ? kRows : 1][kRows > 1 ? NV : 1];
+      auto part = [&](int j, int k) -> f32x4 & { return kRows > 1 ? more[kRows > 1 ? j : 0][kRows > 1 ? k : 0] : r[k]; };
+#pragma unroll
+      for (int j = 0; j < kRows; ++j)
+        if (i0 + j < n) {
+          const auto row = row_of(p.p, s_chain[i0 + j]);
+#pragma unroll
+          for (int k = 0; k < NV; ++k) part(j, k) = load_group(row, k);
+        }
+#pragma unroll
+      for (int j = 0; j < kRows; ++j)
+        if (i0 + j < n) {
+          if (summed) {
+            const double acc = wave_sum(thread_sum([&](int k) -> const f32x4 & { return part(j, k); }));
+            if (lane == 0) s_sum[i0 + j - first][wave] = acc;
+          }
+          if (kRows > 1 && i0 + j == n - 1) {
+#pragma unroll
+            for (int k = 0; k < NV; ++k) r[k] = part(j, k);
+          }
+        }
+    }
+    last = n - 1 - first;
+    if (summed) {
+      __syncthreads();
+      ++epoch;
+      if (!exchange(n - first, -1)) return;
+    }
+    // ---- the tests, with the true sums: a lane takes one node of the chain ----
+    int i, c;  // nodes whose child is accepted; the child that is refused, or -1
     {
-      double rx = (double)rx0;
-      while (c >= 0) {
-        if (rx > 0.0 && (double)u[c] * (double)qx * Z <= rx) {
-          cur = c;
-          if (w == 0 && tid == 0) p.path[(size_t)b * p.max_path + len] = c;
-          ++len;
-          accepted = true;
-          break;
+      const int k = lane < n ? lane : 0, node = s_chain[k], child = k < n - 1 ? s_chain[k + 1 < kWalkChain ? k + 1 : k] : end;
+      const double z = p.unit_rows ? 1.0 : total(k);
+      const bool ok = lane < n && child >= 0 && accepts(child, q_entry(node, child), (double)p_entry(node, child), z);
+      const unsigned long long taken = __ballot(ok);
+      i = __builtin_ctzll(~taken);
+      if (w == 0 && tid < i) p.path[(size_t)b * p.max_path + len + tid] = child;
+      if (in_lds && s_bad && p.err_flag) {  // (children without a token, passed over at the nodes that were reached)
+        for (int bad = tid; bad < T; bad += kWalkThreads) {
+          const int par = s_parent[bad], x = s_token[bad];
+          if (par < 0 || par >= bad || (x >= 0 && x < V) || bad > s_first[par] >> 1) continue;
+          for (int j = 0; j <= i && j < n; ++j)
+            if (s_chain[j] == par && len + j < p.max_path) atomicCAS(p.err_flag, 0, 1 + b);
         }
-        // rejected: the residual max(0, r - Z q) over this workgroup's slice; the entry of the next child's token
-        // goes to the others with the partial sum
-        const int cn = next_child(cur, c);
-        const int xn = cn >= 0 ? token[cn] : -1;
-        if (cn >= 0) qx = q[xn];  // (the draft's row stays as it is: requested before the pass)
-        double *xslot = xbase + (epoch & 1) * (kCoopMaxW + 1) + kCoopMaxW;
-        const float *from = dist;
-        const double Zq = Z;
-        auto one = [&](float pv, float qv) {
-          const double d = (double)pv - Zq * (double)qv;
-          return d > 0.0 ? (float)d : 0.f;
-        };
-        __syncthreads();  // every thread has read what it needs of the row before the slice is overwritten in place
-        if constexpr (VEC == 4) {
-          local = segment_pass<4, 4>(
-              lo, hi, seg, wsum,
-              [&](int v) {
-                return Float4Pair{*reinterpret_cast<const float4 *>(from + v), *reinterpret_cast<const float4 *>(q + v)};
-              },
-              [&](int v, const Float4Pair &t, double &acc) {
-                float4 o;
-                o.x = one(t.a.x, t.c.x), o.y = one(t.a.y, t.c.y), o.z = one(t.a.z, t.c.z), o.w = one(t.a.w, t.c.w);
-                *reinterpret_cast<float4 *>(r + v) = o;
-                if (xn >= v && xn < v + 4) publish(xslot, (double)(xn == v ? o.x : xn == v + 1 ? o.y : xn == v + 2 ? o.z : o.w));
-                acc += ((double)o.x + (double)o.y) + ((double)o.z + (double)o.w);
-              });
-        } else {
-          local = segment_pass<1, 4>(
-              lo, hi, seg, wsum, [&](int v) { return FloatPair{from[v], q[v]}; },
-              [&](int v, const FloatPair &t, double &acc) {
-                const float o = one(t.a, t.c);
-                r[v] = o;
-                if (v == xn) publish(xslot, (double)o);
-                acc += (double)o;
-              });
-        }
-        const double Zn = group_sum(local);
-        if (Zn < 0.0) return leave_flagged();
-        if (!(Zn > 0.0)) {
-          // q was not a distribution the child could have been drawn from: flagged; the walk ends here
-          leave_flagged();
-          if (w == 0 && tid == 0) p.path_len[b] = len, p.next_token[b] = -1;
-          return;
-        }
-        Z = Zn;
-        dist = r;
-        segments = true;
-        rx = s_part[W];
-        c = cn;
+      }
+      len += i;
+      cur = i < n ? s_chain[i] : end;
+      c = i < n ? __builtin_amdgcn_readlane(child, i) : -1;
+      Z = read_lane(z, i < n ? i : 0);
+    }
+    if (i == n) continue;  // (the chain was cut at its longest, or its last guess was a refusal that is none)
+    // ---- refused at `cur`: its rows are held already, unless the guess went past it ----
+    if (c >= 0 && (i != n - 1 || !refusal)) {
+      const auto p_at = row_of(p.p, cur), q_at = row_of(p.q, cur);
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        r[k] = load_group(p_at, k);
+        if (kHoldQ) q[kHoldQ ? k : 0] = load_group(q_at, k);
       }
     }
-    if (!accepted) break;
-  }
-  if (w == 0 && tid == 0) p.path_len[b] = len;
-  if (!segments && ahead) {  // (the walk ends at a node whose row was summed ahead: one workgroup draws, from one piece of the row)
-    if (w == 0) draw_in_piece<VEC>(p, t0 + cur, dist, summed_ahead(p, t0 + cur), (double)p.u_final[b], wsum, &p.next_token[b]);
+    bool accepted = false;
+    if (c >= 0) last = 0;
+    else if (p.unit_rows) Z = total(last);  // (nothing to test, which only the chain's last node can be: the draw divides by its row's sum)
+    while (c >= 0) {
+      // the residual max(0, r - Z q), unnormalised; the entry of the next child's token goes to the others with its sum
+      const int cn = next_child(cur, c, true);
+      const int xn = cn >= 0 ? token(cn) : -1;
+      const int off = xn - s0;
+      const int own = xn >= s0 && xn < s1 && (off >> 2 & 63) == lane ? off >> 8 : -1;  // this thread's group that holds it
+      const auto q_at = row_of(p.q, cur);
+      double acc = 0.0, acc2 = 0.0;
+      const auto pass = [&](auto unit_tag) __attribute__((always_inline)) {
+      constexpr bool unit = decltype(unit_tag)::value;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        f32x4 qk = kHoldQ ? q[kHoldQ ? k : 0] : load_group(q_at, k);
+        // (opaque, or the conversions to double would be kept from pass to pass, in twice the registers)
+        asm volatile("" : "+v"(qk), "+v"(r[k]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          // (a sum of one: the subtraction in float32 is the one in double rounded to float32)
+          const float d = unit ? r[k][e] - qk[e] : (float)((double)r[k][e] - Z * (double)qk[e]);
+          r[k][e] = fmaxf(d, 0.f);
+        }
+        if (k & 1) acc2 += group_sum(r[k]);
+        else acc += group_sum(r[k]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      };
+      if (Z == 1.0) pass(std::true_type{});
+      else pass(std::false_type{});
+      ++epoch;
+      if (xn >= s0 && xn < s1) {  // (one wave of one workgroup)
+        f32x4 g = r[0];
+#pragma unroll
+        for (int k = 1; k < NV; ++k)
+          if (k == own) g = r[k];
+        const double entry = (double)((off & 2) ? (off & 1) ? g[3] : g[2] : (off & 1) ? g[1] : g[0]);
+        if (own >= 0) {
+          if (W > 1) publish(0, entry);
+          else s_entry[epoch & 1] = entry;
+        }
+      }
+      acc = wave_sum(acc + acc2);
+      if (lane == 0) s_sum[0][wave] = acc;
+      __syncthreads();
+      if (!exchange(1, xn >= 0 ? xn / slice : -1)) return;
+      Z = total(0);
+      if (!(Z > 0.0)) {
+        // q was not a distribution the child could have been drawn from: flagged; the walk ends here
+        if (w == 0 && tid == 0) {
+          if (p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
+          p.path_len[b] = len, p.next_token[b] = -1;
+        }
+        return;
+      }
+      c = cn;
+      if (c >= 0 && accepts(c, q_entry(cur, c), s_entry[epoch & 1], Z)) {
+        if (w == 0 && tid == 0) p.path[(size_t)b * p.max_path + len] = c;
+        ++len;
+        cur = c;
+        accepted = true;
+        break;
+      }
+    }
+    if (accepted) continue;
+    if (w == 0 && tid == 0) p.path_len[b] = len;
+    // ---- the last token: the smallest v whose cumulative weight exceeds u_final Z ----
+    // The slices' sums say which workgroup holds it, the segments' which wave; where no place claims it (u_final was not
+    // below 1, or rounding kept the running sum below) it is the last token that has weight.
+    const double target = (double)p.u_final[b] * Z;
+    double before = 0.0;
+    bool none;
+    {
+      int claim = -1, heavy = 0;
+      double pre = 0.0;
+#pragma unroll
+      for (int k = 0; k < kWalkMaxW; ++k) {
+        const double x = s_part[last][k], nx = pre + x;
+        if (claim < 0 && nx > target) claim = k, before = pre;
+        if (x > 0.0) heavy = k;
+        pre = nx;
+      }
+      none = claim < 0;
+      if (none) claim = heavy;
+      if (w != claim) return;
+      claim = -1, heavy = 0, pre = before;
+      for (int k = 0; k < kWalkWaves; ++k) {
+        const double x = s_sum[last][k], nx = pre + x;
+        if (claim < 0 && !none && nx > target) claim = k, before = pre;
+        if (x > 0.0) heavy = k;
+        pre = nx;
+      }
+      none = claim < 0;
+      if (none) claim = heavy;
+      if (wave != claim) return;
+    }
+    // this wave's segment: which group of 256 elements, then where in it
+    int claim = -1, heavy = 0;
+    double pre = before;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const double x = wave_sum(group_sum(r[k])), nx = pre + x;
+      if (claim < 0 && !none && nx > target) claim = k, before = pre;
+      if (x > 0.0) heavy = k;
+      pre = nx;
+      if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    none = claim < 0;
+    if (none) claim = heavy;
+    f32x4 x = r[0];
+#pragma unroll
+    for (int k = 1; k < NV; ++k)
+      if (k == claim) x = r[k];
+    const double mine = group_sum(x);
+    double run = before + (wave_scan(mine) - mine);
+    int tok = -1, weight = -1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int v = s0 + (claim * 64 + lane) * 4 + e;
+      run += (double)x[e];
+      if (x[e] > 0.f) weight = v;
+      if (!none && tok < 0 && x[e] > 0.f && run > target) tok = v;
+    }
+    const unsigned long long over = __ballot(tok >= 0), some = __ballot(weight >= 0);
+    const int drawn = over ? __shfl(tok, __builtin_ctzll(over)) : some ? __shfl(weight, 63 - __builtin_clzll(some)) : -1;
+    if (lane == 0) p.next_token[b] = drawn;
     return;
   }
-  if (!segments) {  // (a row taken as summing to one, its pieces not made ahead: the last draw sums it)
-    Z = row_total(dist);
-    if (Z < 0.0) return leave_flagged();
-  }
-  // The last token: the workgroup whose slice holds the smallest v with cumulative weight above u_final * Z, then
-  // the wave of it whose segment does.
-  const double target = (double)p.u_final[b] * Z;
-  int claim = -1, last_heavy = 0;
-  double before = 0.0;
-  {
-    double pre = 0.0;
-    for (int i = 0; i < W; ++i) {
-      const double nx = pre + s_part[i];
-      if (claim < 0 && nx > target) claim = i, before = pre;
-      if (s_part[i] > 0.0) last_heavy = i;
-      pre = nx;
+}
+
+// How a call runs: workgroups per sequence, and groups of four elements a thread of walk_kernel holds (0: sample_kernel).
+// With a workspace the library takes as many workgroups as keep the launch within one per compute unit (all of them
+// resident at once, which the waits rely on), at most 16, a power of two, slices of 4096 tokens or more, and one below
+// 16 K tokens.  sample_kernel, one workgroup that keeps its residual in memory, is left for what 512 threads
+// cannot hold: more than 64 K tokens and no workspace, or more than 128 sequences.
+struct WalkPlan {
+  int W, NV;
+};
+int walk_plan(const tva_sample_args *a, WalkPlan *plan) {
+  if (a->workgroups_per_sequence < 0 || a->workgroups_per_sequence > kWalkMaxW) return TVA_INVALID_ARG;
+  int W = 1;
+  if (a->workspace && a->workgroups_per_sequence != 1) {
+    if (((uintptr_t)a->workspace & 7) || a->workspace_bytes < (size_t)a->B * kWalkBytes) return TVA_WORKSPACE_TOO_SMALL;
+    while (a->V >= 16384 && 2 * W <= kWalkMaxW && (int64_t)a->B * 2 * W <= 256 && a->V / (2 * W) >= 4096) W *= 2;
+    if (a->workgroups_per_sequence > 1) {
+      W = a->workgroups_per_sequence;
+      if ((int64_t)a->B * W > 256) return TVA_UNSUPPORTED;  // more than the chip holds at once
     }
   }
-  const bool none = claim < 0;  // (u_final was not below 1: the last token that has weight)
-  if (none) claim = last_heavy;
-  if (w == claim) draw_in_range(dist, lo, hi, seg, wsum, before, target, none, &p.next_token[b]);
-}
-
-// Workgroups per sequence: as many as keep the launch within one workgroup per compute unit (all of them resident at
-// once, which the waits between passes rely on), at most 16, a power of two, slices of 4096 tokens or more, and
-// one only for vocabularies below 48 K: a wait between passes costs about 4.5 us, what one workgroup needs for
-// a pass over 32 K tokens (measured: V = 32000 30.6 us with one workgroup, 35.3 with eight).  With the row sums made
-// ahead of the walk only refusals still cost a pass and its wait, and sharing pays from 16 K tokens on (V = 32000,
-// B = 1: 28.4 us with four workgroups against 31.2 with one; B = 4: 24.8 against 34.0).  Negative: a status.
-int sample_workgroups(const tva_sample_args *a, bool ahead) {
-  if (a->workgroups_per_sequence < 0 || a->workgroups_per_sequence > kCoopMaxW) return TVA_INVALID_ARG;
-  if (!a->workspace || a->workgroups_per_sequence == 1) return 1;
-  if (((uintptr_t)a->workspace & 7) || a->workspace_bytes < (size_t)a->B * 512) return TVA_WORKSPACE_TOO_SMALL;
-  int W = 1;
-  const int shared_from = ahead ? 16384 : 49152;
-  while (a->V >= shared_from && 2 * W <= kCoopMaxW && (int64_t)a->B * 2 * W <= 256 && a->V / (2 * W) >= 4096) W *= 2;
-  if (a->workgroups_per_sequence > 1) {
-    W = a->workgroups_per_sequence;
-    if ((int64_t)a->B * W > 256) return TVA_UNSUPPORTED;  // more than the chip holds at once
-  }
-  return W;
-}
-
-// Row sums ahead of the walk: where the host gave the number of nodes, the workspace has room behind the waits'
-// words, and all rows together are few enough bytes (40 MB: 5 .. 8 us with the whole chip, what the passes over two
-// accepted nodes' rows cost one after the other).
-constexpr int64_t kRowSumsMaxBytes = 40 << 20;
-inline int row_pieces(int V) { return (V + kRowPiece - 1) / kRowPiece; }
-inline size_t row_sums_offset(int B) { return (size_t)B * 512; }
-bool sums_ahead(const tva_sample_args *a) {
-  if (a->sum_T <= 0 || !a->workspace || ((uintptr_t)a->workspace & 7)) return false;
-  if ((int64_t)a->sum_T * a->V * (int64_t)sizeof(float) > kRowSumsMaxBytes || a->sum_T > 65535) return false;
-  return a->workspace_bytes >= row_sums_offset(a->B) + (size_t)a->sum_T * (row_pieces(a->V) * sizeof(double) + 2 * sizeof(float));
+  auto groups = [&](int n) {  // the groups of four that a thread holds when n workgroups share a row
+    const int64_t slice = ((int64_t)a->V + n - 1) / n + 3, seg = (slice + kWalkWaves - 1) / kWalkWaves + 3;
+    return (seg + 255) / 256;
+  };
+  int64_t g = groups(W);
+  const int most = a->V % 4 == 0 ? 32 : 16;
+  while (g > most && W > 1 && W < kWalkMaxW && (int64_t)a->B * 2 * W <= 256) W *= 2, g = groups(W);  // (a named number too small for the vocabulary)
+  if (g > most) W = 1, g = groups(1);
+  plan->W = W;
+  // (no form for 32 groups of a vocabulary that is no multiple of 4: its registers do not suffice)
+  plan->NV = a->V < 4 ? 0 : g <= 4 ? 4 : g <= 8 ? 8 : g <= 16 ? 16 : g <= 32 && a->V % 4 == 0 ? 32 : 0;
+  return TVA_OK;
 }
 
 struct CommitParams {
@@ -853,11 +952,11 @@ int tva_accept_greedy_filled(const int32_t *parent, const int32_t *cu_T, const i
 
 static int accept_sampling_impl(const tva_sample_args *a, void *stream, int missing_arrivals, int spins, bool fill);
 
-int tva_accept_sampling(const tva_sample_args *a, void *stream) { return accept_sampling_impl(a, stream, 0, kCoopSpins, false); }
-int tva_accept_sampling_filled(const tva_sample_args *a, void *stream) { return accept_sampling_impl(a, stream, 0, kCoopSpins, true); }
+int tva_accept_sampling(const tva_sample_args *a, void *stream) { return accept_sampling_impl(a, stream, 0, kWalkSpins, false); }
+int tva_accept_sampling_filled(const tva_sample_args *a, void *stream) { return accept_sampling_impl(a, stream, 0, kWalkSpins, true); }
 
 int tva_accept_sampling_wait_bound_test(const tva_sample_args *a, int32_t spins, void *stream) {
-  if (!a || spins < 1 || spins > kCoopSpins || !a->workspace || a->workgroups_per_sequence < 2) return TVA_INVALID_ARG;
+  if (!a || spins < 1 || spins > kWalkSpins || !a->workspace || a->workgroups_per_sequence < 2) return TVA_INVALID_ARG;
   return accept_sampling_impl(a, stream, 1, spins, false);
 }
 
@@ -873,52 +972,44 @@ static int accept_sampling_impl(const tva_sample_args *a, void *stream, int miss
   p.residual = a->residual;
   p.path = a->path, p.path_len = a->path_len, p.next_token = a->next_token, p.err_flag = a->err_flag;
   p.V = a->V, p.max_path = a->max_path;
-  p.rowpart = nullptr, p.first = nullptr, p.pieces = row_pieces(a->V), p.sum_T = 0;
   p.unit_rows = a->unit_rows != 0;
   p.fill_path = fill;
   // groups of four need every row to start on 16 bytes
   const bool vec = a->V % 4 == 0 && (((uintptr_t)a->p_target | (uintptr_t)a->q_draft | (uintptr_t)a->residual) & 15) == 0;
   if (a->sum_T < 0) return TVA_INVALID_ARG;
-  const bool ahead = sums_ahead(a);
-  const int W = sample_workgroups(a, ahead);
-  if (W < 0) return W;
-  (void)hipGetLastError();  // the status below is these launches'
+  WalkPlan plan;
+  if (const int rc = walk_plan(a, &plan)) return rc;
+  (void)hipGetLastError();  // the status below is this launch's
   hipStream_t st = (hipStream_t)stream;
-  if (ahead) {
-    double *rowpart = reinterpret_cast<double *>(static_cast<char *>(a->workspace) + row_sums_offset(a->B));
-    int *sync = static_cast<int *>(a->workspace);
-    const int n_sync = W > 1 ? a->B * 32 : 0;  // (the arrival counters of the walk start at zero)
-    float *first = reinterpret_cast<float *>(rowpart + (size_t)a->sum_T * p.pieces);
-    const dim3 grid(p.pieces + 1, a->sum_T);
-    if (vec)
-      hipLaunchKernelGGL(row_sums_kernel<4>, grid, dim3(kRowPieceThreads), 0, st, a->p_target, a->cu_T, a->B, a->V, rowpart, sync, n_sync,
-                         a->q_draft, a->parent, a->draft_token, first);
-    else
-      hipLaunchKernelGGL(row_sums_kernel<1>, grid, dim3(kRowPieceThreads), 0, st, a->p_target, a->cu_T, a->B, a->V, rowpart, sync, n_sync,
-                         a->q_draft, a->parent, a->draft_token, first);
-    p.rowpart = rowpart, p.first = first, p.sum_T = a->sum_T;
-  }
-  if (W == 1) {
+  if (plan.NV == 0) {
     if (vec) hipLaunchKernelGGL(sample_kernel<4>, dim3(a->B), dim3(kSampleThreads), 0, st, p);
     else hipLaunchKernelGGL(sample_kernel<1>, dim3(a->B), dim3(kSampleThreads), 0, st, p);
   } else {
-    CoopParams cp;
-    cp.s = p, cp.W = W, cp.arrivals = W + missing_arrivals, cp.spins = spins;
-    cp.sync = static_cast<int *>(a->workspace);
-    cp.xchg = reinterpret_cast<double *>(static_cast<char *>(a->workspace) + (size_t)a->B * 128);
-    // the arrival counters start at zero (a kernel, not a memset node: the call may be captured into a graph)
-    if (!ahead) hipLaunchKernelGGL(zero_sync_kernel, dim3((a->B * 32 + 255) / 256), dim3(256), 0, st, cp.sync, a->B * 32);
-    if (vec) hipLaunchKernelGGL(sample_coop_kernel<4>, dim3(a->B * W), dim3(kSampleThreads), 0, st, cp);
-    else hipLaunchKernelGGL(sample_coop_kernel<1>, dim3(a->B * W), dim3(kSampleThreads), 0, st, cp);
+    WalkParams wp;
+    wp.s = p, wp.W = plan.W, wp.arrivals = plan.W + missing_arrivals, wp.spins = spins;
+    wp.mail = static_cast<uint64_t *>(a->workspace);
+    const dim3 grid(a->B * plan.W), block(kWalkThreads);
+    auto launch = [&](auto whole) {
+      constexpr bool WHOLE = decltype(whole)::value;
+      switch (plan.NV) {
+        case 4: hipLaunchKernelGGL((walk_kernel<4, WHOLE>), grid, block, 0, st, wp); break;
+        case 8: hipLaunchKernelGGL((walk_kernel<8, WHOLE>), grid, block, 0, st, wp); break;
+        case 16: hipLaunchKernelGGL((walk_kernel<16, WHOLE>), grid, block, 0, st, wp); break;
+        default:
+          if constexpr (WHOLE) hipLaunchKernelGGL((walk_kernel<32, true>), grid, block, 0, st, wp);
+          break;
+      }
+    };
+    if (a->V % 4 == 0) launch(std::true_type{});
+    else launch(std::false_type{});
   }
   return hipPeekAtLastError() == hipSuccess ? TVA_OK : TVA_HIP_ERROR;
 }
 
-size_t tva_sample_workspace_bytes(int32_t B) { return B < 0 ? (size_t)-1 : (size_t)B * 512; }
+size_t tva_sample_workspace_bytes(int32_t B) { return B < 0 ? (size_t)-1 : (size_t)B * kWalkBytes; }
 
 size_t tva_sample_workspace_bytes_rows(int32_t B, int32_t sum_T, int32_t V) {
-  if (B < 0 || sum_T < 0 || V < 1) return (size_t)-1;
-  return row_sums_offset(B) + (size_t)sum_T * (row_pieces(V) * sizeof(double) + 2 * sizeof(float));  // sums, then entries
+  return B < 0 || sum_T < 0 || V < 1 ? (size_t)-1 : tva_sample_workspace_bytes(B);
 }
 
 size_t tva_sizeof_sample_args(void) { return sizeof(tva_sample_args); }

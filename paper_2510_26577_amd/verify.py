@@ -73,9 +73,9 @@ def accept_sampling(parent, cu_T, draft_token, p_target, q_draft, u, u_final, ma
                     sum_T: int = 0, unit_rows: bool = False):
     """Device tensors in (int32 trees and tokens, float32 distributions [sum_T, V] and uniform numbers); returns
     (path [B, max_path], path_len [B], next_token [B]).  workspace: "auto" allocates the one that lets several
-    workgroups share a sequence (and, with sum_T, holds the row sums made ahead of the walk), None runs one
-    workgroup per sequence, or a device tensor of tva_sample_workspace_bytes[_rows] bytes.  sum_T: the host's
-    count of the batch's nodes (cu_T[B]), or 0."""
+    workgroups share a sequence, None runs one workgroup per sequence, or a device tensor of
+    tva_sample_workspace_bytes bytes.  sum_T: the host's count of the batch's nodes (cu_T[B]), or 0; results do not
+    depend on it."""
     if not wait_bound_test_spins:
         make = isinstance(workspace, str)
         return binding._result(binding.native().accept_sampling(

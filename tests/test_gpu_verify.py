@@ -705,6 +705,35 @@ def test_accept_sampling_flags_bad_input_and_leaves_other_sequences_alone(torch_
     assert [int(nxt[0]), int(nxt[1])] == ref_next[:2]
 
 
+@pytest.mark.parametrize("V,workgroups", [(3, 1), (4, 1), (5, 3), (255, 2), (8192, 1), (8193, 1), (8200, 1), (16388, 1), (32768, 4),
+                                          (32771, 1), (65533, 2), (65536, 1), (65540, 1), (66001, 1), (131077, 2), (40001, 16)])
+def test_accept_sampling_at_the_edges_of_slices_and_held_groups(torch_dev, V, workgroups):
+    """Vocabularies at the edges of what a thread holds (and past it), slices that end inside a group of four, more
+    workgroups than the elements need; a chain longer than the rows summed in one pass, a star whose children are mostly
+    refused, and a forest of one node."""
+    torch = torch_dev
+    rng = np.random.Generator(np.random.PCG64(4000 + V + workgroups))
+    trees = [np.arange(-1, 19), np.array([-1] + [0] * 7 + [3, 3, 5]), np.array([-1])]
+    parent = np.concatenate(trees).astype(np.int32)
+    cu_T = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
+    p, q, tok, u, uf = wl.sampling_inputs(rng, parent, cu_T, V, drift=0.7)
+    q[:17] = p[:17]                              # the chain's first 17 nodes are accepted whatever u says (q = p)
+    for i in range(1, 18):
+        tok[i] = int(rng.choice(V, p=p[i - 1].astype(np.float64) / p[i - 1].astype(np.float64).sum()))
+    uf[2] = np.float32(0.99999994)               # the last draw close to the end of the row
+    for unit in (False, True):
+        ref_paths, ref_next = vo.accept_sampling(parent, cu_T, tok, p, q, u, uf, unit_rows=unit)
+        assert len(ref_paths[0]) >= 18
+        assert sampling_margin(parent, cu_T, tok, p, q, u, uf, ref_paths, ref_next, unit_rows=unit) > 1e-9
+        say(f"[case] accept_sampling V={V} workgroups={workgroups} unit={unit}")
+        for misalign in (False, True) if V > 4 else (False,):
+            path, n, nxt, flag = run_sampling(torch, parent, cu_T, tok, p, q, u, uf, 20, workgroups=workgroups, unit_rows=unit,
+                                              misalign=misalign)
+            assert flag == 0 and list(n) == [len(x) for x in ref_paths] and list(nxt) == ref_next
+            for b, x in enumerate(ref_paths):
+                assert list(path[b, :len(x)]) == x
+
+
 def test_accept_sampling_waits_are_bounded(torch_dev):
     """The waits between the workgroups that share a sequence give up after a bounded number of polls: forced from the
     host (every wait expects one arrival more than there are workgroups, 64 polls), every workgroup leaves at its first
