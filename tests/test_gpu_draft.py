@@ -170,6 +170,32 @@ def test_expand_layer_when_few_threads_hold_the_large_values(torch_dev):
     check_expand(torch, cu_N, score, logp, K)
 
 
+@pytest.mark.parametrize("V,K,kind", [(8191, 16, "normal"), (8192, 16, "normal"), (8193, 12, "normal"), (8192 + 61, 16, "normal"),
+                                       (17 * 8192 + 1, 15, "normal"), (33 * 8192 + 2, 1, "normal"), (20001, 16, "rising"),
+                                       (20001, 16, "falling"), (16384, 16, "masked"), (16390, 7, "level"), (9000, 8, "groups")])
+def test_expand_layer_at_the_edges_of_pieces_and_lists(torch_dev, V, K, kind):
+    """Last pieces of one token, of fewer and of slightly more than K, more pieces than a load of the merge takes; rows in
+    which more tokens reach the selection bound than the lists hold: sorted ones, ones that are -inf but for a few tokens,
+    ones of a single value, and ones in which just over 32 groups of four do."""
+    torch = torch_dev
+    rng = np.random.Generator(np.random.PCG64(640 + V + K))
+    cu_N, score, logp = wl.expansion_inputs(rng, [3, 2], V)
+    if kind in ("rising", "falling"):
+        logp = np.sort(logp, axis=1)[:, ::1 if kind == "rising" else -1]
+    elif kind == "masked":
+        keep = rng.integers(0, V, (5, 5))
+        for r in range(5):
+            logp[r, np.setdiff1d(np.arange(V), keep[r])] = -np.inf
+    elif kind == "level":
+        logp[:] = np.float32(-3.25)
+    elif kind == "groups":
+        logp = np.minimum(logp, np.float32(-9.0))
+        for r in range(5):                        # 31 .. 35 groups of the first piece hold a token at the bound
+            logp[r, rng.choice(2048, 31 + r, replace=False) * 4 + rng.integers(0, 4)] = np.float32(-0.5)
+    say(f"[case] expand edges V={V} K={K} {kind}")
+    check_expand(torch, cu_N, score, np.ascontiguousarray(logp), K)
+
+
 def random_scored_tree(rng, M, ties=0.2):
     parent = np.array([-1] + [int(rng.integers(max(0, i - 9), i)) for i in range(1, M)], np.int32)
     score = np.zeros(M, np.float32)
