@@ -73,6 +73,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
+// Full tiles from which a split runs the steady loop.  (A shorter one would run little of it, from a cold instruction
+// cache, and its blocks still move the reference: 4 full tiles 13.4 us -> 14.2 with it.)
+constexpr int kSteadyTiles = 8;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 // A tile takes the low-order P pass when, for some row, (largest probability of the tile) >
@@ -82,7 +85,7 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kLoThreshold = 0.125f;
 // The reference maximum of a row is only moved (and O, l rescaled) when a tile maximum exceeds it by
 // more than 2^kLazy: probabilities then stay below 2^kLazy, harmless in fp32 sums and bf16 operands.
-constexpr float kLazy = 8.f;
+constexpr float kLazy = 8.f, kLazyCap = 256.f;  // (the cap: 2^kLazy)
 
 // ---------------------------------------------------------------------------------------
 // ancestor masks
@@ -150,6 +153,8 @@ struct AttnParams {
   int chunk_keys, n_chunks, n_row_blocks, max_L;
   int pair_slots;          // > 0: sequences are matched to workgroup slots by length: slot j takes the sequence in
   uint32_t slot_seq[16];   // byte j of this array
+  int real_splits;         // > 0: the splits that the given lengths fill come first, this many of them: half-word b of
+                           // slot_seq is the number of those of sequences 0 .. b
   int page_size, page_shift, max_pages;
   int64_t stride_page, stride_tok, stride_head;
   float scale_log2;  // scale * log2(e) (times the K scale of an fp8 cache)
@@ -210,6 +215,8 @@ struct AttnCfg {
   static constexpr int NL = KV8_REG ? 0 : KV8 ? NST : 0;
   static constexpr int LAND_SLOT = KV8 ? 2 * TK * D : 0;
   static constexpr int NSTAGE = KV8_REG ? 4 : KV8 ? 2 : NST;
+  // the 256-row shape's loop has a steady part of its own (the others ran no faster with one: they wait for data)
+  static constexpr bool STEADY = WK == 1 && !KV8;
   static constexpr int PD = KV8_REG ? NSTAGE - 1 : KV8 ? NL : NSTAGE - 1;  // tiles in flight ahead of the one being computed (widened)
   static constexpr int WG_PER_CU = KV8 ? (KV8_REG ? 2 : 1) : (NSTAGE == 2 && TK == 64) ? 2 : 1;
   // after the key loop the ring is reused: exchange area of the key-group merge, then (behind it,
@@ -223,12 +230,15 @@ struct AttnCfg {
   static constexpr int PATCH_BYTES = (PAIR ? NW : WM) * 32 * TP * 4;
   static constexpr int LAND_OFF = NSTAGE * STAGE_BYTES;
   static constexpr int RING_BYTES = NSTAGE * STAGE_BYTES + NL * LAND_SLOT;
-  // paged cache: table entries of the next two tiles, fetched by the same LDS-writing loads as the
-  // tiles themselves: [2 slots][wave][load instruction of a tile][lane], behind the ring
+  // paged cache: table entries of the next LOOK tiles, fetched by the same LDS-writing loads as the
+  // tiles themselves: [slot][wave][load instruction of a tile][lane], behind the ring.  Entries are needed when their
+  // tile is queued, PD tiles ahead; requested LOOK >= PD tiles ahead they are older than every tile still in flight, so
+  // that waiting for them drains none.
+  static constexpr int LOOK = PD >= 3 ? 3 : 2, PG_SLOTS = LOOK >= 3 ? 4 : 2;
   static constexpr int NPG = PAGED ? NLDK : 0;   // table-entry loads per wave and tile
   static constexpr int TILE_OPS = NLD + NPG;     // this wave's memory operations per tile
   static constexpr int PG_SLOT = NW * NLDK * 256;
-  static constexpr int PG_BYTES = PAGED ? 2 * PG_SLOT : 0;
+  static constexpr int PG_BYTES = PAGED ? PG_SLOTS * PG_SLOT : 0;
   // parent indices of the sequence's tree (used when no ancestor masks are passed), behind those
   static constexpr int PARENT_OFF = RING_BYTES + PG_BYTES;
   static constexpr int PARENT_BYTES = TVA_MAX_TREE * 4;
@@ -237,7 +247,7 @@ struct AttnCfg {
   // load instruction n of a tile (n = wave * NLDK + j): the first tile row it covers
   static constexpr int load_row0(int n) { return KV8 ? n * RPI8 : n / IPB + NBLK * ((n % IPB) * RPI); }
   static_assert(SMEM * WG_PER_CU <= 160 * 1024, "LDS of the workgroups that share a CU");
-  static_assert(PD <= 3 && TILE_OPS * (PD > 1 ? PD - 1 : 1) < 64, "the wait counter holds 6 bits");
+  static_assert(PD <= 3 && TILE_OPS * (PD > 1 ? PD - 1 : 1) < 64 && NPG * LOOK + TILE_OPS < 64, "the wait counter holds 6 bits");
   static_assert(TK % ((KV8 ? RPI8 : RPI) * NW) == 0, "tile must divide evenly over the waves");
   static_assert(!KV8 || (D == 128 && NLDK >= 1), "8-bit K/V: head dimension 128");
   static_assert(BLKB % 1024 == 0, "a block is a whole number of wave-wide loads");
@@ -352,7 +362,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   const int kvh = blockIdx.x;
   const int rblk = blockIdx.y;
   int b = (int)blockIdx.z / p.n_chunks;
-  const int chunk = (int)blockIdx.z - b * p.n_chunks;
+  const int chunk_of_slot = (int)blockIdx.z - b * p.n_chunks;
   if (p.pair_slots > 0) {
     // (a permutation of the sequences, made on the host: see fill_slots; picked with scalar selects, so that the
     // argument block is never indexed by a register)
@@ -361,6 +371,32 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     for (int i = 0; i < 16; ++i) word = (b >> 2) == i ? p.slot_seq[i] : word;
     b = (int)((word >> (8 * (b & 3))) & 0xFFu);
   }
+  int split = chunk_of_slot;
+  if (C::WG_PER_CU == 1 && p.real_splits > 0) {
+    // (a permutation of (sequence, split), made on the host: see fill_slots)
+    const int z = (int)blockIdx.z, over = z - p.real_splits;
+    int before = 0;  // filled (or, past them, unfilled) splits of the sequences before this one
+    b = 0;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      const int filled = (int)((p.slot_seq[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
+      const int upto = over < 0 ? filled : (i + 1) * p.n_chunks - filled;
+      if (i < p.B && upto <= (over < 0 ? z : over)) b = i + 1, before = upto;
+    }
+    split = (over < 0 ? z : over) - before;
+    if (over >= 0) {
+      // the unfilled splits of b are its last ones
+      int filled_b = 0, filled_a = 0;
+#pragma unroll
+      for (int i = 0; i < 32; ++i) {
+        const int filled = (int)((p.slot_seq[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
+        if (i == b) filled_b = filled;
+        if (i == b - 1) filled_a = filled;
+      }
+      split += filled_b - filled_a;
+    }
+  }
+  const int chunk = split;
 
   // every per-sequence scalar is requested before the first one is needed
   // (read through the constant address space: none of these arrays changes while the kernel
@@ -442,11 +478,13 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
 
   // ---- running softmax state (log2 domain; m_run is the reference the exponentials use) ----
-  float m_run[RB], l_run[RB];
+  // (m_use: m_run, or 0 while there is none; cap: the largest sum of one lane's probabilities of a block that needs no
+  // look at the maximum, -1 while there is no reference)
+  float m_run[RB], l_run[RB], m_use[RB], cap[RB];
   f32x16 oacc[RB][ND];
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
-    m_run[r] = -INFINITY;
+    m_run[r] = -INFINITY, m_use[r] = 0.f, cap[r] = -1.f;
     l_run[r] = 0.f;
 #pragma unroll
     for (int d = 0; d < ND; ++d)
@@ -470,6 +508,11 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   // slot): wave-uniform.  (Plain expressions: with calls in their place the host pass of the compiler
   // silently drops the kernel's launch stub.)
   auto row0_of = [&](int j) __attribute__((always_inline)) { return C::load_row0(wave * NLDK + j); };
+  // A full cache tile's keys may sit in any of its rows (nothing in it is masked, K and V agree): there, the rows one
+  // instruction fills take consecutive keys -- one page of a paged cache, neighbouring lines of a dense one, instead of
+  // rows 16 keys apart (paged, 4 x 24576 keys: 179 -> 176 us).
+  constexpr int LPI = KV8 ? C::RPI8 : RPI;
+  auto full_key = [&](int j) __attribute__((always_inline)) { return (wave * NLDK + j) * LPI + lsub; };
 #define kdst_of(j) (KV8 ? (wave * 2 * NLDK + (j)) * 1024 : ((wave * NLDK + (j)) / IPB) * PK + ((wave * NLDK + (j)) % IPB) * 1024)
 #define vdst_of(j) (KV8 ? (wave * 2 * NLDK + NLDK + (j)) * 1024 : KTILE + ((wave * NLDK + (j)) / IPB) * PV + ((wave * NLDK + (j)) % IPB) * 1024)
   const char *const kc_bytes = reinterpret_cast<const char *>(p.k_cache);
@@ -478,8 +521,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   const char *const vt_bytes = reinterpret_cast<const char *>(p.v_tree);
   const int64_t cache_base = PAGED ? 0 : (int64_t)cuL * p.stride_tok + (int64_t)kvh * p.stride_head;
   // paged cache: each lane needs the page of the row it loads, one table entry per load
-  // instruction of a cache tile.  The entries of tile t + 2 are requested right after the loads of
-  // tile t have been queued, by LDS-writing loads like the tiles' own, into one of two slots; the
+  // instruction of a cache tile.  The entries of tile t + LOOK are requested right after the loads of
+  // tile t have been queued, by LDS-writing loads like the tiles' own, into a ring of slots; the
   // wave's memory operations then come in a fixed order and number per tile (every tile, also a
   // tree tile or the last ones, is followed by a request: past the end it re-reads the entry of the
   // last key), which is what the counted waits below rely on.
@@ -492,13 +535,13 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     const int last = tree_in_cache ? Lb0 + Tb - 1 : k1 - 1;
 #pragma unroll
     for (int j = 0; j < NLDK; ++j) {
-      int key = base + row0_of(j) + lrow;
+      int key = base + (t < n_full ? full_key(j) : row0_of(j) + lrow);
       key = key < last ? key : last;
       key = key < 0 ? 0 : key;
       int pidx = p.page_shift >= 0 ? (key >> p.page_shift) : (key / p.page_size);
       pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;  // never past the sequence's row of the table
       const int32_t *src = p.page_table + (int64_t)b * p.max_pages + pidx;
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), pg_lds + (t & 1) * C::PG_SLOT + j * 256, 4, 0, 0);
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256, 4, 0, 0);
     }
   };
   // full tiles of a dense cache: a wave-uniform row pointer plus one tile-independent lane offset
@@ -506,8 +549,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   // slot (row, c) fetches chunk c ^ row ^ (j & 1) of that row, j the piece's index: the 8-byte operand
   // reads and the byte transpose reads then spread over the LDS banks)
   auto chunk_of = [&](int j) __attribute__((always_inline)) { return C::KV8_REG ? (lpos ^ lsub ^ (j & 1)) : lpos; };
-  const uint32_t lane_off2[2] = {(uint32_t)lrow * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(0) * 16u,
-                                 (uint32_t)lrow * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(1) * 16u};
+  const uint32_t lane_off2[2] = {(uint32_t)lsub * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(0) * 16u,
+                                 (uint32_t)lsub * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(1) * 16u};
   auto issue_impl = [&](int t, auto tree_tag) __attribute__((always_inline)) {
     constexpr bool tree = decltype(tree_tag)::value;
     const int base = tree ? (t - n_ct) * TK : k0 + t * TK;
@@ -517,7 +560,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     if (!PAGED && t < n_full) {
 #pragma unroll
       for (int j = 0; j < NLDK; ++j) {
-        const int64_t urow = cache_base + (int64_t)(base + row0_of(j)) * p.stride_tok;
+        const int64_t urow = cache_base + (int64_t)(base + (wave * NLDK + j) * LPI) * p.stride_tok;
         const char *ksrc = kc_bytes + urow * EB + lane_off2[j & 1];
         const char *vsrc = vc_bytes + urow * EB + lane_off2[j & 1];
         __builtin_amdgcn_global_load_lds(GLOBAL_PTR(ksrc), stage + kdst_of(j), 16, 0, kLoadOnce);
@@ -527,7 +570,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 #pragma unroll
     for (int j = 0; j < NLDK; ++j) {
       const char *ksrc, *vsrc;
-      int key = base + row0_of(j) + lrow;
+      int key = base + (!tree && t < n_full ? full_key(j) : row0_of(j) + lrow);
       key = key < limit ? key : limit - 1;
       const int eoff = chunk_of(j) * (16 / EB);  // first element of the lane's 16-byte chunk
       if (tree && p.k_tree != nullptr) {
@@ -540,7 +583,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         int64_t off;
         if (PAGED) {
           const int pidx = p.page_shift >= 0 ? (pos >> p.page_shift) : (pos / p.page_size);
-          const int page = *reinterpret_cast<const __attribute__((address_space(3))) int *>(pg_lds + (t & 1) * C::PG_SLOT + j * 256 + lane * 4);
+          const int page = *reinterpret_cast<const __attribute__((address_space(3))) int *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
           off = (int64_t)page * p.stride_page + (int64_t)(pos - pidx * p.page_size) * p.stride_tok +
                 (int64_t)kvh * p.stride_head + eoff;
         } else {
@@ -550,7 +593,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         vsrc = vc_bytes + off * EB;
       } else if (PAGED) {
         const int pidx = p.page_shift >= 0 ? (key >> p.page_shift) : (key / p.page_size);
-        const int page = *reinterpret_cast<const __attribute__((address_space(3))) int *>(pg_lds + (t & 1) * C::PG_SLOT + j * 256 + lane * 4);
+        const int page = *reinterpret_cast<const __attribute__((address_space(3))) int *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
         const int64_t off = (int64_t)page * p.stride_page + (int64_t)(key - pidx * p.page_size) * p.stride_tok +
                             (int64_t)kvh * p.stride_head + eoff;
         ksrc = kc_bytes + off * EB;
@@ -569,7 +612,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   auto issue_tile = [&](int t) __attribute__((always_inline)) {
     if (t >= n_ct) issue_impl(t, std::true_type{});
     else issue_impl(t, std::false_type{});
-    request_pages(t + 2);
+    request_pages(t + C::LOOK);
   };
 
   // per-lane LDS read bases (row r of a tile: block r % NBLK, sub-row r / NBLK)
@@ -601,8 +644,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   constexpr int V8_SECOND = (NLDK >= 4 ? 2 : 2 * NLDK) * 1024;  // keys 16 .. 31 of the wave: two pieces further on
 
   // ---- one 32-key block of one tile: S^T = K Q^T, online softmax, O^T += V^T P^T ----
-  auto compute_block = [&](const lds_byte *stage, auto kb_tag, int base, int limit, bool tree, auto masked_tag) __attribute__((always_inline)) {
-    constexpr bool MASKED = decltype(masked_tag)::value;
+  auto compute_block = [&](const lds_byte *stage, auto kb_tag, int base, int limit, bool tree, auto masked_tag, auto settled_tag) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked_tag)::value, SETTLED = decltype(settled_tag)::value;
     constexpr int kb = decltype(kb_tag)::value;
     constexpr int KBOFF = kb * (32 / NBLK) * ROWB;     // this 32-key block inside the wave's part of the tile
     constexpr int V8 = (NBLK == 16) ? 8 * PV : ROWB;   // V rows 8 keys further on
@@ -680,43 +723,69 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         }
       }
     }
+    // Probabilities against the reference as it stands.  What the maximum of the block would be needed for -- moving the
+    // reference, the low-order pass -- is ruled out by the lane's sum of the block's 16 probabilities, which bounds each
+    // of them: a sum up to 2^kLazy keeps the reference, a sum up to kLoThreshold of the lane's own running sum
+    // (a part of the row's) excludes a weight that large.  After the first few blocks of a split that holds for every
+    // lane, and the maximum, its exchange between the lane halves and its exponential are not computed at all (256-row
+    // shape, 32 sequences of 2048 keys: 89 -> 85.5 us).  SETTLED: the steady part of a long split; elsewhere the
+    // question would be answered with yes most of the time and is not asked.
     bf16x8 pb[2][RB];
-    float m_use[RB];
-    bool need_lo = false;
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      float sv[16];
-      float mx = -INFINITY;
+    float ls[RB];
+    auto exponentials = [&](int r) __attribute__((always_inline)) {
+      ls[r] = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        sv[i] = sacc[r][i];
-        if (MASKED) sv[i] = ((ok[r] >> i) & 1u) ? sv[i] : -INFINITY;
-        mx = fmaxf(mx, sv[i]);
-      }
-      mx = half_max(mx) * p.scale_log2;
-      // lazy reference update: only when some row's tile maximum exceeds its reference by > 2^kLazy
-      if (__builtin_amdgcn_ballot_w64(mx > m_run[r] + kLazy) != 0) {
-        const float m_new = fmaxf(m_run[r], mx);
-        const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[r] - m_new);
-        m_run[r] = m_new;
-        l_run[r] *= alpha;
-#pragma unroll
-        for (int d = 0; d < ND; ++d)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) oacc[r][d][i] *= alpha;
-      }
-      m_use[r] = (m_run[r] == -INFINITY) ? 0.f : m_run[r];
-      const float pmax = fast_exp2(mx - m_use[r]);
-      float ls = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float pv = fast_exp2(fmaf(sv[i], p.scale_log2, -m_use[r]));
-        ls += pv;
+        float sv = sacc[r][i];
+        if (MASKED) sv = ((ok[r] >> i) & 1u) ? sv : -INFINITY;
+        const float pv = fast_exp2(fmaf(sv, p.scale_log2, -m_use[r]));
+        ls[r] += pv;
         pb[i / 8][r][i % 8] = (__bf16)pv;
       }
-      l_run[r] += ls;
-      need_lo = need_lo || (pmax > kLoThreshold * half_sum(l_run[r]));
+    };
+    bool look = !SETTLED;
+    if (SETTLED) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        exponentials(r);
+        look = look || !(ls[r] <= fminf(kLoThreshold * (l_run[r] + ls[r]), cap[r]));
+      }
+      look = __builtin_amdgcn_ballot_w64(look) != 0;
     }
+    uint64_t lo_votes = 0;
+    if (look) {
+      bool need_lo = false;
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          float sv = sacc[r][i];
+          if (MASKED) sv = ((ok[r] >> i) & 1u) ? sv : -INFINITY;
+          mx = fmaxf(mx, sv);
+        }
+        mx = half_max(mx) * p.scale_log2;
+        // lazy reference update: only when some row's tile maximum exceeds its reference by > 2^kLazy
+        const bool move = __builtin_amdgcn_ballot_w64(mx > m_run[r] + kLazy) != 0;
+        if (move) {
+          const float m_new = fmaxf(m_run[r], mx);
+          const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[r] - m_new);
+          m_run[r] = m_new;
+          m_use[r] = (m_new == -INFINITY) ? 0.f : m_new;
+          cap[r] = (m_new == -INFINITY) ? -1.f : kLazyCap;
+          l_run[r] *= alpha;
+#pragma unroll
+          for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[r][d][i] *= alpha;
+        }
+        if (!SETTLED || move) exponentials(r);
+        need_lo = need_lo || (fast_exp2(mx - m_use[r]) > kLoThreshold * half_sum(l_run[r] + ls[r]));
+      }
+      lo_votes = __builtin_amdgcn_ballot_w64(need_lo);
+    }
+#pragma unroll
+    for (int r = 0; r < RB; ++r) l_run[r] += ls[r];
     // O^T += V^T P^T: first 16 keys while the operands of the second 16 arrive
     constexpr int S2OFF = (16 / NBLK) * ROWB;
     static_assert(ND == 4 || ND == 2, "head dimension 128 or 64");
@@ -750,7 +819,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         oacc[r][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop, pb[1][r], oacc[r][d], 0, 0, 0);
     }
     // low-order pass (rare): the bf16 rounding remainder of P, recomputed from the scores
-    if (__builtin_amdgcn_ballot_w64(need_lo) != 0) {
+    if (lo_votes != 0) {
       bf16x8 plo[2][RB];
 #pragma unroll
       for (int r = 0; r < RB; ++r)
@@ -779,9 +848,10 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     constexpr int OPS = C::TILE_OPS;
     const int later = n_tiles - 1 - it;  // tiles after `it` whose loads are already queued: min(later, PD - 1)
     if constexpr (PAGED) {
-      // queued after the loads of tile `it`: entries(it+2), then per later tile its loads and the
-      // entries two tiles on.  entries(it+PD) are needed next, so at most one later tile may stay.
-      if (PD >= 2 && later >= 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(OPS));
+      // queued after the loads of tile `it`: entries(it+LOOK), then per later tile its loads and the entries LOOK
+      // tiles on.  entries(it+PD) are needed next: they came no later than the first of those.
+      if (PD >= 3 && later >= 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(OPS * 2));
+      else if (PD >= 2 && later >= 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(OPS));
       else if (PD == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::NPG));
       else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     } else {
@@ -845,13 +915,13 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     // wave-uniform: a block is skipped when none of its keys exists, and all of them by a wave
     // none of whose query rows exists (it still loads its share of every tile)
     if (!wave_has_rows) return;
-    if (base + wk * KBW * 32 < limit) compute_block(stage, std::integral_constant<int, 0>{}, base, limit, tree, masked_tag);
+    if (base + wk * KBW * 32 < limit) compute_block(stage, std::integral_constant<int, 0>{}, base, limit, tree, masked_tag, std::false_type{});
     if constexpr (KBW > 1)
-      if (base + (wk * KBW + 1) * 32 < limit) compute_block(stage, std::integral_constant<int, 1>{}, base, limit, tree, masked_tag);
+      if (base + (wk * KBW + 1) * 32 < limit) compute_block(stage, std::integral_constant<int, 1>{}, base, limit, tree, masked_tag, std::false_type{});
     if constexpr (KBW > 2)
-      if (base + (wk * KBW + 2) * 32 < limit) compute_block(stage, std::integral_constant<int, 2>{}, base, limit, tree, masked_tag);
+      if (base + (wk * KBW + 2) * 32 < limit) compute_block(stage, std::integral_constant<int, 2>{}, base, limit, tree, masked_tag, std::false_type{});
     if constexpr (KBW > 3)
-      if (base + (wk * KBW + 3) * 32 < limit) compute_block(stage, std::integral_constant<int, 3>{}, base, limit, tree, masked_tag);
+      if (base + (wk * KBW + 3) * 32 < limit) compute_block(stage, std::integral_constant<int, 3>{}, base, limit, tree, masked_tag, std::false_type{});
     }
   };
 
@@ -863,8 +933,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     idx = idx < Tb ? idx : Tb - 1;
     __builtin_amdgcn_global_load_lds(GLOBAL_PTR(p.parent + t0 + idx), lds + C::PARENT_OFF + wave * 256, 4, 0, 0);
   }
-  request_pages(0);
-  request_pages(1);
+#pragma unroll
+  for (int t = 0; t < C::LOOK; ++t) request_pages(t);
   // The first PD tiles (fewer if the chunk has fewer).  Q and the mask rows were requested before
   // them and have arrived once no more than the tiles' own operations are outstanding; that wait
   // sits in the same branch as the loads it counts, so that the number is plainly a constant.
@@ -874,13 +944,14 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     for (int t = 0; t < n; ++t) {
       if constexpr (PAGED) {
         // entries(t) have landed once only what was queued after them is outstanding
-        if (t == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::NPG));
-        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS));
+        if (t == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::NPG * (C::LOOK - 1)));
+        else if (t == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::NPG * (C::LOOK - 2) + C::TILE_OPS));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * 2));
         asm volatile("" ::: "memory");  // the entries are read from LDS below this line, not above
       }
       issue_tile(t);
     }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(vm_cap(2 * C::NPG + C::TILE_OPS * n)));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(vm_cap(C::LOOK * C::NPG + C::TILE_OPS * n)));
   };
   if (PD >= 3 && n_tiles >= 3) issue_first(std::integral_constant<int, PD >= 3 ? 3 : 1>{});
   else if (PD >= 2 && n_tiles >= 2) issue_first(std::integral_constant<int, PD >= 2 ? 2 : 1>{});
@@ -921,6 +992,65 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
   TL_STAMP(3);  // first full tile done (a split without one: the same moment as the stamp before)
 #endif
+  if constexpr (C::STEADY) if (n_full >= kSteadyTiles) {
+    // ---- the steady part of the loop: full cache tiles that queue full cache tiles.  One address per tile and operand, carried
+    // along in scalar registers (dense), or one multiply-add per load on its page's number (paged); every wait is a constant ----
+    int64_t row_off[NLDK];  // bytes from a tile's first row to the row of (load instruction j, lane 0)
+#pragma unroll
+    for (int j = 0; j < NLDK; ++j) row_off[j] = (int64_t)((wave * NLDK + j) * LPI) * p.stride_tok * EB;
+    const char *k_next = kc_bytes + (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
+    const char *v_next = vc_bytes + (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
+    const int64_t tile_bytes = (int64_t)TK * p.stride_tok * EB;
+    // (paged: pages whose slots and strides fit 32 bits; others take the general path)
+    const bool small_pages = PAGED && p.page_shift >= 0 && p.stride_page * EB < (1ll << 31) &&
+                             ((int64_t)p.page_size * p.stride_tok + (int64_t)p.Hkv * p.stride_head) * EB < (1ll << 31);
+    const uint32_t page_bytes = (uint32_t)(p.stride_page * EB), tok_bytes = (uint32_t)(p.stride_tok * EB);
+    const uint32_t head_bytes = (uint32_t)(kvh * p.stride_head * EB), slot_mask = (uint32_t)p.page_size - 1u;
+    auto issue_steady = [&](int t) __attribute__((always_inline)) {
+      lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
+      if constexpr (PAGED) {
+#pragma unroll
+        for (int j = 0; j < NLDK; ++j) {
+          const uint32_t page = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
+          const uint32_t slot = (uint32_t)(k0 + t * TK + full_key(j)) & slot_mask;
+          const uint64_t off = (uint64_t)page * page_bytes + (slot * tok_bytes + head_bytes + (uint32_t)chunk_of(j) * 16u);
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + off), stage + kdst_of(j), 16, 0, kLoadOnce);
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vc_bytes + off), stage + vdst_of(j), 16, 0, kLoadOnce);
+        }
+        // (the entries of tile t + LOOK; past the last key they re-read its entry)
+#pragma unroll
+        for (int j = 0; j < NLDK; ++j) {
+          const int ahead = t + C::LOOK, row = ahead < n_full ? full_key(j) : row0_of(j) + lrow;
+          int key = k0 + ahead * TK + row;
+          key = key < k1 ? key : k1 - 1;
+          if (ahead >= n_ct && p.k_tree == nullptr) key = Lb0 + (ahead - n_ct) * TK + row, key = key < Lb0 + Tb ? key : Lb0 + Tb - 1;
+          int pidx = key >> p.page_shift;
+          pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(p.page_table + (int64_t)b * p.max_pages + pidx), pg_lds + ((t + C::LOOK) & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256, 4, 0, 0);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < NLDK; ++j) {
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(k_next + row_off[j] + lane_off2[j & 1]), stage + kdst_of(j), 16, 0, kLoadOnce);
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(v_next + row_off[j] + lane_off2[j & 1]), stage + vdst_of(j), 16, 0, kLoadOnce);
+        }
+        k_next += tile_bytes;
+        v_next += tile_bytes;
+      }
+    };
+    auto step_steady = [&](int t) __attribute__((always_inline)) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(PAGED && PD == 1 ? C::NPG : C::TILE_OPS * (PD - 1)));
+      __builtin_amdgcn_s_barrier();
+      issue_steady(t + PD);
+      if (!wave_has_rows) return;
+      const lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
+      compute_block(stage, std::integral_constant<int, 0>{}, 0, 0, false, std::false_type{}, std::true_type{});
+      if constexpr (KBW > 1) compute_block(stage, std::integral_constant<int, 1>{}, 0, 0, false, std::false_type{}, std::true_type{});
+    };
+    static_assert(KBW <= 2, "");
+    if (!PAGED || small_pages)
+      for (; it + PD < n_full; ++it) step_steady(it);
+  }
   for (; it < n_full; ++it) step(it, std::false_type{}, std::false_type{});
   for (; it < n_ct; ++it) step(it, std::true_type{}, std::false_type{});   // the partial cache tile
   for (; it < n_tiles; ++it) step(it, std::true_type{}, std::true_type{});  // the tree's own keys
@@ -1163,8 +1293,26 @@ inline int64_t query_rows(const tva_args *a) { return a->cu_Q ? a->sum_Q : a->su
 void fill_slots(const tva_args *a, const Plan &pl, AttnParams *p) {
   p->pair_slots = 0;
   for (uint32_t &w : p->slot_seq) w = 0;
+  p->real_splits = 0;
   const bool two_per_cu = pl.variant == V_K2 || pl.variant == V_M2K2;
   const int n = a->B;
+  // A split launch of unequal sequences: a shorter one's last splits are empty.  Workgroups go to the shader engines in
+  // turn whatever they do; with the empty ones among them one engine can be given more work than it has CUs while
+  // another idles, and the launch then lasts two rounds (four sequences of 16384 .. 32768 keys, 31 of 40 splits filled: 176 us,
+  // 146 with 25 of 32; 129 with the filled ones first).  So: the filled splits, by the lengths given, come first.  As above
+  // this is a permutation whatever L_host holds.
+  if (a->L_host && !two_per_cu && pl.n_chunks > 1 && n > 1 && n <= 32 && (int64_t)n * pl.n_chunks <= 65535 &&
+      (int64_t)n * pl.n_chunks * a->Hkv * pl.n_row_blocks > 256) {
+    int filled = 0;
+    for (int i = 0; i < n; ++i) {
+      const int64_t L = a->L_host[i] < a->max_L ? a->L_host[i] : a->max_L;
+      const int64_t nc = L > 0 ? (L + pl.chunk_keys - 1) / pl.chunk_keys : 1;
+      filled += (int)nc;
+      p->slot_seq[i >> 1] |= (uint32_t)filled << (16 * (i & 1));
+    }
+    if (filled < n * pl.n_chunks) p->real_splits = filled;
+    return;
+  }
   if (!a->L_host || !two_per_cu || pl.n_chunks != 1 || pl.n_row_blocks != 1 || a->Hkv != 8 || n <= 32 || n > 64) return;
   int order[64];  // sequences, longest first (equal lengths: lower index first)
   for (int i = 0; i < n; ++i) order[i] = i;

@@ -445,6 +445,64 @@ def test_host_lengths_hint_in_split_launches_matches_oracle(gpu, L, T):
     assert binding.plan_chunk_keys(a) <= plain
 
 
+@pytest.mark.parametrize("shape,page_size,D", [(5, 0, 128), (5, 16, 128), (5, 5, 128), (5, 256, 128), (5, 0, 64), (5, 32, 64), (4, 16, 128),
+                                               (4, 0, 128), (3, 16, 128)])
+def test_long_splits_whose_scores_grow_match_oracle(gpu, shape, page_size, D):
+    """Splits long enough for the steady part of the loop, with ends inside a tile: the keys grow along the cache, so that
+    the softmax reference has to move and single weights dominate far into the split; page sizes below, at and above a
+    load's rows and a tile, and one that is no power of two."""
+    import torch
+    w = wl.random_workload(800 + shape + page_size + D, 2, 8, 2, D, [1500, 1089], [37, 11], page_size=page_size)
+    grow = lambda n: np.where(np.arange(n) % 400 > 380, 5.0, 1.0 + np.arange(n) / 700.0).astype(np.float32)
+    def scaled(bits, factor):
+        x = (bits.astype(np.uint32) << 16).view(np.float32) * factor
+        u = np.ascontiguousarray(x.astype(np.float32)).view(np.uint32)
+        return ((u + 0x8000) >> 16).astype(np.uint16)
+    if page_size == 0:
+        for b in range(2):
+            rows = slice(int(w.cu_L[b]), int(w.cu_L[b]) + int(w.L[b]))
+            w.k_cache[rows] = scaled(w.k_cache[rows], grow(int(w.L[b]))[:, None, None])
+    else:
+        for b in range(2):
+            for pos0 in range(0, int(w.L[b]), page_size):
+                n = min(page_size, int(w.L[b]) - pos0)
+                page = w.page_table[b, pos0 // page_size]
+                w.k_cache[page, :n] = scaled(w.k_cache[page, :n], grow(int(w.L[b]))[pos0:pos0 + n, None, None])
+    ro, rl = orc.tree_verify_attn(w)
+    dw = gpu.to_device(w)
+    mask = gpu.build_mask(dw)
+    for splits in (1, 2):
+        say(f"[case] growing scores shape={shape} page_size={page_size} D={D} splits={splits}")
+        o, l = gpu.attention(dw, mask, num_splits=splits, plan_shape=shape)
+        torch.cuda.synchronize()
+        assert np.abs(o.cpu().numpy().astype(np.float64) - ro).max() <= TOL_O
+        assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
+
+
+@pytest.mark.parametrize("shape", [3, 4, 5])
+def test_filled_splits_first_is_a_permutation(gpu, shape):
+    """Split launches of more workgroups than the chip holds put the splits that the host's lengths fill first: true
+    lengths, reversed ones, zeros and nonsense give bit for bit what no hint gives, and that agrees with the oracle."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(560 + shape))
+    B = 11
+    L = rng.integers(0, 900, size=B)
+    L[:4] = [900, 0, 1, 300]
+    w = wl.random_workload(950, B, 32, 8, 128, L, 9, max_depth=6)
+    dw = gpu.to_device(w)
+    mask = gpu.build_mask(dw)
+    say(f"[case] filled splits first shape={shape}")
+    base, lbase = gpu.attention(dw, mask, num_splits=5, plan_shape=shape)
+    torch.cuda.synchronize()
+    ro, rl = orc.tree_verify_attn(w)
+    assert np.abs(base.cpu().numpy().astype(np.float64) - ro).max() <= TOL_O
+    assert np.abs(lbase.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
+    for hint in (w.L, w.L[::-1], np.zeros(B), np.full(B, 10 ** 9), rng.integers(-5, 2000, size=B)):
+        o, l = gpu.attention(dw, mask, num_splits=5, plan_shape=shape, L_host=np.ascontiguousarray(hint, dtype=np.int32))
+        torch.cuda.synchronize()
+        assert torch.equal(o, base) and torch.equal(l, lbase)
+
+
 @pytest.mark.parametrize("splits", [2, 3, 7])
 def test_splits_entry_point_partials_match_oracle_key_ranges(gpu, splits):
     """tva_tree_verify_attn_splits leaves per-split partials that equal the oracle restricted to
