@@ -38,6 +38,7 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include <atomic>
 #include <type_traits>
@@ -372,7 +373,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     b = (int)((word >> (8 * (b & 3))) & 0xFFu);
   }
   int split = chunk_of_slot;
-  if (C::WG_PER_CU == 1 && p.real_splits > 0) {
+  if (C::NW == 8 && p.real_splits > 0) {
     // (a permutation of (sequence, split), made on the host: see fill_slots)
     const int z = (int)blockIdx.z, over = z - p.real_splits;
     int before = 0;  // filled (or, past them, unfilled) splits of the sequences before this one
@@ -510,7 +511,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   auto row0_of = [&](int j) __attribute__((always_inline)) { return C::load_row0(wave * NLDK + j); };
   // A full cache tile's keys may sit in any of its rows (nothing in it is masked, K and V agree): there, the rows one
   // instruction fills take consecutive keys -- one page of a paged cache, neighbouring lines of a dense one, instead of
-  // rows 16 keys apart (paged, 4 x 24576 keys: 179 -> 176 us).
+  // rows 16 keys apart (paged, 4 x 24576 keys, 256-row shape: 179 -> 176 us; the others ran no faster).
   constexpr int LPI = KV8 ? C::RPI8 : RPI;
   auto full_key = [&](int j) __attribute__((always_inline)) { return (wave * NLDK + j) * LPI + lsub; };
 #define kdst_of(j) (KV8 ? (wave * 2 * NLDK + (j)) * 1024 : ((wave * NLDK + (j)) / IPB) * PK + ((wave * NLDK + (j)) % IPB) * 1024)
@@ -535,7 +536,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     const int last = tree_in_cache ? Lb0 + Tb - 1 : k1 - 1;
 #pragma unroll
     for (int j = 0; j < NLDK; ++j) {
-      int key = base + (t < n_full ? full_key(j) : row0_of(j) + lrow);
+      int key = base + (C::STEADY && t < n_full ? full_key(j) : row0_of(j) + lrow);
       key = key < last ? key : last;
       key = key < 0 ? 0 : key;
       int pidx = p.page_shift >= 0 ? (key >> p.page_shift) : (key / p.page_size);
@@ -549,8 +550,9 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   // slot (row, c) fetches chunk c ^ row ^ (j & 1) of that row, j the piece's index: the 8-byte operand
   // reads and the byte transpose reads then spread over the LDS banks)
   auto chunk_of = [&](int j) __attribute__((always_inline)) { return C::KV8_REG ? (lpos ^ lsub ^ (j & 1)) : lpos; };
-  const uint32_t lane_off2[2] = {(uint32_t)lsub * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(0) * 16u,
-                                 (uint32_t)lsub * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(1) * 16u};
+  const int full_row = C::STEADY ? lsub : lrow;
+  const uint32_t lane_off2[2] = {(uint32_t)full_row * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(0) * 16u,
+                                 (uint32_t)full_row * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(1) * 16u};
   auto issue_impl = [&](int t, auto tree_tag) __attribute__((always_inline)) {
     constexpr bool tree = decltype(tree_tag)::value;
     const int base = tree ? (t - n_ct) * TK : k0 + t * TK;
@@ -560,7 +562,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     if (!PAGED && t < n_full) {
 #pragma unroll
       for (int j = 0; j < NLDK; ++j) {
-        const int64_t urow = cache_base + (int64_t)(base + (wave * NLDK + j) * LPI) * p.stride_tok;
+        const int64_t urow = cache_base + (int64_t)(base + (C::STEADY ? (wave * NLDK + j) * LPI : row0_of(j))) * p.stride_tok;
         const char *ksrc = kc_bytes + urow * EB + lane_off2[j & 1];
         const char *vsrc = vc_bytes + urow * EB + lane_off2[j & 1];
         __builtin_amdgcn_global_load_lds(GLOBAL_PTR(ksrc), stage + kdst_of(j), 16, 0, kLoadOnce);
@@ -570,7 +572,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 #pragma unroll
     for (int j = 0; j < NLDK; ++j) {
       const char *ksrc, *vsrc;
-      int key = base + (!tree && t < n_full ? full_key(j) : row0_of(j) + lrow);
+      int key = base + (C::STEADY && !tree && t < n_full ? full_key(j) : row0_of(j) + lrow);
       key = key < limit ? key : limit - 1;
       const int eoff = chunk_of(j) * (16 / EB);  // first element of the lane's 16-byte chunk
       if (tree && p.k_tree != nullptr) {
@@ -1301,7 +1303,7 @@ void fill_slots(const tva_args *a, const Plan &pl, AttnParams *p) {
   // another idles, and the launch then lasts two rounds (four sequences of 16384 .. 32768 keys, 31 of 40 splits filled: 176 us,
   // 146 with 25 of 32; 129 with the filled ones first).  So: the filled splits, by the lengths given, come first.  As above
   // this is a permutation whatever L_host holds.
-  if (a->L_host && !two_per_cu && pl.n_chunks > 1 && n > 1 && n <= 32 && (int64_t)n * pl.n_chunks <= 65535 &&
+  if (a->L_host && (pl.variant == V_W8 || pl.variant == V_M4K2) && pl.n_chunks > 1 && n > 1 && n <= 32 && (int64_t)n * pl.n_chunks <= 65535 &&
       (int64_t)n * pl.n_chunks * a->Hkv * pl.n_row_blocks > 256) {
     int filled = 0;
     for (int i = 0; i < n; ++i) {
@@ -1325,42 +1327,11 @@ void fill_slots(const tva_args *a, const Plan &pl, AttnParams *p) {
   p->pair_slots = n;
 }
 
-bool make_plan(const tva_args *a, Plan *pl) {
-  if (!a || a->B <= 0 || a->Hq <= 0 || a->Hkv <= 0 || a->Hq % a->Hkv) return false;
-  if (a->sum_T < 0 || a->max_T < 0 || a->max_L < 0 || a->num_splits < 0) return false;
-  if (a->plan_shape < TVA_SHAPE_AUTO || a->plan_shape > V_LAST + 1) return false;
+// The splits of one workgroup shape.  named: the shape is to be this one (else the 2 x 2 shape may take its deeper ring).
+void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
   const int G = a->Hq / a->Hkv;
   const int rows = (a->cu_Q ? a->max_Q : a->max_T) * G;
-  // Workgroup shape, from sweeps over the benchmark shapes and batch / length variations of them.
-  // Up to 32 rows per KV head: 32-row workgroups of two waves that split the keys of 64-key tiles.
-  // More rows: 64-row workgroups of 2 x 2 waves (two row groups x two key groups).  Both keep a
-  // two-stage ring, small enough that two workgroups share a CU and hide each other's start-up
-  // and drain.  From 128 rows on, larger workgroups that read each key fewer times take over
-  // where the launch can feed them:
-  //  - 128-row workgroups of 4 x 2 waves when 96 .. 256 of them exist (one per CU; with two KV
-  //    splits at most, and those 16 tiles or longer);
-  //  - 256-row workgroups of eight waves (32 rows each, two waves per SIMD) when there would be more
-  //    than 256 of the former, or when there are fewer than 96 but the keys are many: half a million
-  //    over the (sequence, KV head) pairs, or half of that with long caches, which splits then
-  //    spread over the chip.
   const int pairs = a->B * a->Hkv;
-  const int64_t keys = (int64_t)pairs * a->max_L;
-  const int n128 = pairs * ((rows + 127) / 128);
-  const int s128 = n128 * 3 >= 512 ? 1 : 256 / (n128 > 0 ? n128 : 1);
-  int variant = V_M2K2;
-  if (rows <= 32) variant = V_K2;
-  // (the draft stage's attention of one or two sequences -- queries are the newest nodes, at most 48 rows per KV head:
-  // two 32-row workgroups, the second three quarters empty, beat one of 64 rows by 0.4 .. 1.1 us of 12; from eight
-  // sequences on the 64-row shape wins)
-  else if (a->cu_Q && rows <= 48 && pairs <= 16) variant = V_K2;
-  else if (rows >= 128) {
-    if (n128 >= 96 && n128 <= 256 && (s128 == 1 || a->max_L / s128 >= 16 * 64)) variant = V_M4K2;
-    else if (n128 > 256 || keys >= (512 << 10) || (keys >= (256 << 10) && a->max_L >= 4096)) variant = V_W8;
-  }
-  // tuning and test aid: the caller names the workgroup shape
-  const bool forced = a->plan_shape != TVA_SHAPE_AUTO;
-  if (forced) variant = a->plan_shape - 1;
-  if (a->kv_fp8 && variant == V_M2K2_3) variant = V_M2K2;  // (8-bit K/V: no deep variant of the 2 x 2 shape)
   pl->variant = variant;
   pl->BM = variant == V_W8 ? 256 : variant == V_M4K2 ? 128 : variant == V_K2 ? 32 : 64;
   pl->TK = 64;
@@ -1444,8 +1415,111 @@ bool make_plan(const tva_args *a, Plan *pl) {
   pl->n_chunks = a->max_L > 0 ? (a->max_L + ck - 1) / ck : 1;
   // one 2 x 2 workgroup per CU at most and long splits: a third ring stage (two tiles in flight)
   // pays; with more workgroups the second one on the CU hides more than the deeper ring would
-  if (pl->variant == V_M2K2 && !forced && !a->kv_fp8 && (int64_t)pairs * pl->n_row_blocks * pl->n_chunks <= 256 && ck >= 12 * pl->TK)
+  if (pl->variant == V_M2K2 && !named && !a->kv_fp8 && (int64_t)pairs * pl->n_row_blocks * pl->n_chunks <= 256 && ck >= 12 * pl->TK)
     pl->variant = V_M2K2_3;
+}
+
+
+// A launch's duration as a model of it says, in us, up to what all plans share: fitted to 3540 timed launches (every
+// shape, B = 1 .. 64, 150 .. 16000 keys, 4 .. 480 rows per KV head, D = 64 and 128, both storage types; 8 % off in the
+// geometric mean).  A round of workgroups takes (tiles of the longest split) x (time per tile), more where two share a CU;
+// further rounds start and drain once each; the launch takes no less than its bytes at the rate the shape streams;
+// with splits there is a merge pass.
+double plan_cost(const tva_args *a, const Plan &pl) {
+  struct Shape {
+    double tile, fixed, round, d64, f8, tb_s, tb_s8;
+  };
+  static const Shape shapes[V_LAST + 1] = {{1.00, 5.4, 2.5, 0.59, 1.02, 6.6, 4.5},   // V_K2
+                                           {1.09, 5.3, 3.3, 0.58, 0.97, 6.6, 4.9},   // V_M2K2
+                                           {1.03, 7.2, 4.7, 0.55, 1.00, 7.8, 4.9},   // V_M2K2_3
+                                           {1.14, 7.7, 5.6, 0.60, 1.11, 6.9, 4.9},   // V_M4K2
+                                           {2.00, 7.5, 5.5, 0.64, 1.19, 5.7, 4.9}};  // V_W8
+  const Shape &s = shapes[pl.variant];
+  const int G = a->Hq / a->Hkv, rows = (a->cu_Q ? a->max_Q : a->max_T) * G;
+  const int64_t keys = (int64_t)a->B * a->max_L, splits = (int64_t)a->B * pl.n_chunks;
+  const double wgs = (double)splits * a->Hkv * pl.n_row_blocks;
+  const bool two = pl.variant == V_K2 || pl.variant == V_M2K2;
+  const double holds = two ? 512.0 : 256.0;
+  double tile = pl.variant == V_W8 && rows <= 128 ? 1.1 : s.tile;  // (half of the eight waves have no rows)
+  if (a->D == 64) tile *= s.d64;
+  if (a->kv_fp8) tile *= s.f8;
+  const int longest = pl.n_chunks > 1 ? pl.chunk_keys / pl.TK : (a->max_L + pl.TK - 1) / pl.TK, own = (a->max_T + pl.TK - 1) / pl.TK;
+  const double tiles = longest + own * (pl.n_chunks > 1 ? 0.4 : 1.0);
+  double rounds = wgs > holds ? wgs / holds : 1.0;
+  if (!two && rounds > 1.0 && rounds < 1.6) rounds = 1.6;
+  const double compute = (tile * tiles + (rounds > 1.0 ? s.round : 0.0)) * rounds * (two && wgs > 256 ? 1.38 : 1.0);
+  const double mb = ((double)(keys + a->sum_T) * a->Hkv * 2 * (a->kv_fp8 ? 1 : 2) + 6.0 * (double)query_rows(a) * a->Hq) * a->D * 1e-6;
+  const double stream = mb / (a->kv_fp8 ? s.tb_s8 : s.tb_s);
+  const double c2 = compute * compute, m2 = stream * stream;
+  double us = s.fixed + std::sqrt(std::sqrt(c2 * c2 + m2 * m2));
+  if (pl.n_chunks > 1) us += 2.7 + 0.137 * 2.0 * pl.n_chunks * (double)query_rows(a) * a->Hq * (a->D + 1) * sizeof(float) * 1e-6;
+  return us;
+}
+
+bool make_plan(const tva_args *a, Plan *pl) {
+  if (!a || a->B <= 0 || a->Hq <= 0 || a->Hkv <= 0 || a->Hq % a->Hkv) return false;
+  if (a->sum_T < 0 || a->max_T < 0 || a->max_L < 0 || a->num_splits < 0) return false;
+  if (a->plan_shape < TVA_SHAPE_AUTO || a->plan_shape > V_LAST + 1) return false;
+  const int G = a->Hq / a->Hkv;
+  const int rows = (a->cu_Q ? a->max_Q : a->max_T) * G;
+  // Workgroup shape, from sweeps over the benchmark shapes and batch / length variations of them.
+  // Up to 32 rows per KV head: 32-row workgroups of two waves that split the keys of 64-key tiles.
+  // More rows: 64-row workgroups of 2 x 2 waves (two row groups x two key groups).  Both keep a
+  // two-stage ring, small enough that two workgroups share a CU and hide each other's start-up
+  // and drain.  From 128 rows on, larger workgroups that read each key fewer times take over
+  // where the launch can feed them:
+  //  - 128-row workgroups of 4 x 2 waves when 96 .. 256 of them exist (one per CU; with two KV
+  //    splits at most, and those 16 tiles or longer);
+  //  - 256-row workgroups of eight waves (32 rows each, two waves per SIMD) when there would be more
+  //    than 256 of the former, or when there are fewer than 96 but the keys are many: half a million
+  //    over the (sequence, KV head) pairs, or half of that with long caches, which splits then
+  //    spread over the chip.
+  const int pairs = a->B * a->Hkv;
+  const int64_t keys = (int64_t)pairs * a->max_L;
+  const int n128 = pairs * ((rows + 127) / 128);
+  const int s128 = n128 * 3 >= 512 ? 1 : 256 / (n128 > 0 ? n128 : 1);
+  int variant = V_M2K2;
+  // (8-bit K/V from 128 K keys on, lengths known: four waves queue a tile's loads faster than two; 4 sequences of 16000
+  // keys 36 -> 31.5 us; not where long and short sequences share a CU, see fill_slots: 41.4 -> 42.0)
+  if (rows <= 32) variant = a->kv_fp8 && a->L_host && a->B <= 32 && keys >= (128 << 10) ? V_M2K2 : V_K2;
+  // (the draft stage's attention of one or two sequences -- queries are the newest nodes, at most 48 rows per KV head:
+  // two 32-row workgroups, the second three quarters empty, beat one of 64 rows by 0.4 .. 1.1 us of 12; from eight
+  // sequences on the 64-row shape wins)
+  else if (a->cu_Q && rows <= 48 && pairs <= 16) variant = V_K2;
+  else if (rows >= 128) {
+    if (n128 >= 96 && n128 <= 256 && (s128 == 1 || a->max_L / s128 >= 16 * 64)) variant = V_M4K2;
+    else if (n128 > 256 || keys >= (512 << 10) || (keys >= (256 << 10) && a->max_L >= 4096)) variant = V_W8;
+  }
+  // tuning and test aid: the caller names the workgroup shape
+  const bool forced = a->plan_shape != TVA_SHAPE_AUTO;
+  if (forced) variant = a->plan_shape - 1;
+  if (a->kv_fp8 && variant == V_M2K2_3) variant = V_M2K2;  // (8-bit K/V: no deep variant of the 2 x 2 shape)
+  plan_splits_of(a, variant, forced, pl);
+  // The rules above against the model: another shape is taken where it promises 6 % or more.  Asked where the rules have
+  // most to lose: with the lengths of the caches known, and without them where more than 80 rows per KV head meet more than 64
+  // pairs or 4096 keys (against the best shape of 553 timed launches: rules 2.7 % slower in the geometric mean, 37 % at
+  // worst; with the model 0.7 %).  Unsplit launches of 33 .. 64 sequences of few rows keep their shape: there the lengths only
+  // place the workgroups (fill_slots).
+  const bool placed_only = a->Hkv == 8 && a->B > 32 && a->B <= 64 && rows <= 64;
+  // (Nor does the draft stage's attention ask: few of a tree's nodes are queries there, which the fit has not seen.)
+  const bool ask = a->cu_Q ? false : a->L_host ? !placed_only : rows > 80 && (pairs > 64 || a->max_L > 4096);
+  if (!forced && ask && a->max_L > 0 && a->num_splits == 0) {
+    tva_args shapes = *a;  // (the lengths shorten the splits of a shape, they do not choose it)
+    shapes.sum_L = 0, shapes.L_host = nullptr;
+    Plan plan;
+    plan_splits_of(&shapes, variant, false, &plan);
+    double best = 0.94 * plan_cost(&shapes, plan);
+    int chosen = -1;
+    const int first = rows <= 64 ? V_K2 : V_M2K2, last = rows <= 32 ? V_M2K2 : V_LAST;
+    for (int v = first; v <= last; ++v) {
+      // (8-bit K/V: no deep variant; its four-wave shape widens every key once per row group, which short caches show)
+      if (v == variant || (a->kv_fp8 && (v == V_M2K2_3 || (v == V_M2K2 && rows > 64)))) continue;
+      plan_splits_of(&shapes, v, true, &plan);
+      const double us = plan_cost(&shapes, plan);
+      if (us < best) best = us, chosen = v;
+    }
+    if (chosen >= 0) plan_splits_of(a, chosen, true, pl);
+  }
   return true;
 }
 
