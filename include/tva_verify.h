@@ -74,8 +74,11 @@ int tva_accept_greedy_filled(const int32_t *parent, const int32_t *cu_T, const i
  *                       what one compute unit can).  The waits are bounded (about a second): a sequence whose
  *                       workgroups do not all arrive -- they are all resident at once unless other work holds the
  *                       compute units that long -- is flagged in err_flag like the cases above, and its outputs are
- *                       unspecified.  Its contents need no preparation and are unspecified on return; calls that share
- *                       a workspace must not overlap.  Without it: one workgroup per sequence, no waits.
+ *                       unspecified.  Its contents need no preparation: what other programs' data, an earlier call or
+ *                       any mixture of the two left there is not taken for a sum (the words that carry sums are told
+ *                       by 62 bits of tag, and every call clears its own before it ends).  They are unspecified on
+ *                       return; calls that share a workspace must not overlap.  Without it: one workgroup per
+ *                       sequence, no waits.
  *   sum_T               the number of nodes of the batch, cu_T[B], as the host knows it, or 0.  No form of the call needs
  *                       it any more; results do not depend on it.
  *   unit_rows           1: the caller states that every row of p_target sums to one (it is a distribution), and a node

@@ -332,15 +332,19 @@ __global__ void __launch_bounds__(kSampleThreads) sample_kernel(const SamplePara
 //    are known from the gathered entries alone, so their rows are summed in one pass and one wait, after which the tests
 //    are taken again with the true sums (a guess that was wrong costs another pass, nothing else);
 //  - a wait is one trip: a workgroup's partial sums travel in words that carry a tag of this launch and this wait, so the
-//    others poll the data itself.  The tag comes from a counter in the sequence's part of the workspace that every
-//    launch moves on once all W have read it: nothing has to be zeroed beforehand, whatever the memory held, and a
-//    captured launch replays.
+//    others poll the data itself, and nothing has to be zeroed beforehand: no launch leaves a word with a tag behind.  A
+//    sequence's part of the workspace starts with a counter, which all W read before the first wait and count up by one
+//    each behind the last; the one that completes the W has seen all others leave, and clears what was published (a
+//    cleared word matches no tag).  So the memory may be taken away, overwritten in whole or in part, put back and
+//    handed to the next launch or replay with any counter: what that launch meets is what others wrote there, which
+//    passes for a sum only if it holds the launch's 62 bits of tag by chance.
+// (Clearing behind the last wait: the call of one sequence, with a commit of 32 layers, 16.35 -> 16.98 us.)
 // Measured, one sequence, V = 128256, 60 nodes: 28 us for two launches before (row sums of all nodes, then the walk with
 // counters, residuals in memory) -> 13 us; 64 sequences of 8 nodes with unit rows 49 us and a 5 us launch that cleared the
 // counters -> 27 us.
 // Waits are bounded: a workgroup that does not see the others within about a second flags the sequence and leaves (the
 // launch keeps W x B within what the chip holds at once, so this happens only if something else is wrong); it then
-// takes back what it had published, and the counter moves on.
+// takes back what it had published and counts itself as having left.
 constexpr int kWalkThreads = 512, kWalkWaves = kWalkThreads / 64;  // (256 registers per thread)
 constexpr int kWalkMaxW = 16;
 constexpr int kWalkSpins = 1 << 20;
@@ -395,7 +399,7 @@ __global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp)
   __shared__ double s_part[kWalkChain][kWalkMaxW + 1];    // and the workgroups' sums of their slices
   __shared__ double s_entry[2];                           // the residual's entry of the next child's token (two passes in turn)
   __shared__ int s_chain[kWalkChain], s_abort, s_bad;
-  __shared__ uint64_t s_tag;
+  __shared__ uint64_t s_launch;  // the counter as this launch found it
   __shared__ int32_t s_parent[kSampleTreeLds], s_token[kSampleTreeLds];
   __shared__ float s_u[kSampleTreeLds], s_px[kSampleTreeLds], s_qx[kSampleTreeLds];
   __shared__ int s_first[kSampleTreeLds];  // a node's first child that carries a token, times 2, plus 1 where a row's sum of one refuses it
@@ -412,11 +416,9 @@ __global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp)
   }
   const int V = p.V;
   uint64_t *const mail = wp.mail + (size_t)b * (kWalkBytes / sizeof(uint64_t));
-  uint64_t launch = 0;
   if (tid == kWalkThreads - 1) {
     s_abort = 0, s_bad = 0;
-    if (W > 1) launch = mail_load(mail);
-    s_tag = launch * 0x9E3779B97F4A7C15ull + 0xD1B54A32D192ED03ull;
+    s_launch = W > 1 ? mail_load(mail) : 0;
   }
   // the tree's words and what a node's test as its parent's FIRST tested child reads, once (a tree too long for that is
   // walked in global memory)
@@ -442,7 +444,9 @@ __global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp)
   auto parent = [&](int i) { return in_lds ? s_parent[i] : p.parent[t0 + i]; };
   auto token = [&](int i) { return in_lds ? s_token[i] : p.token[t0 + i]; };
   __syncthreads();
-  const uint32_t tag_a = (uint32_t)s_tag, tag_b = (uint32_t)(s_tag >> 32);
+  const uint64_t tag = s_launch * 0x9E3779B97F4A7C15ull + 0xD1B54A32D192ED03ull;
+  const uint32_t tag_a = __builtin_amdgcn_readfirstlane(((uint32_t)tag & 0x3fffffffu) | 0x80000000u);  // (tag_a + epoch is never zero)
+  const uint32_t tag_b = __builtin_amdgcn_readfirstlane((uint32_t)(tag >> 32));
   // this workgroup's slice of every row, the waves' segments of it; a thread holds groups of four elements, 256 apart
   const int slice = ((V + W - 1) / W + 3) / 4 * 4;
   const int lo = w * slice < V ? w * slice : V, hi = lo + slice < V ? lo + slice : V;
@@ -486,6 +490,18 @@ __global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp)
     mail_store(at, bits << 32 | (uint32_t)(tag_a + epoch));
     mail_store(at + 1, (bits >> 32) << 32 | (uint32_t)(tag_b + epoch));
   };
+  // Called once by every workgroup, behind its last wait (a barrier after the last word it polled): counts it as having
+  // left.  The last of the W to do so clears all that they published.  Every word of an earlier wait has been read by all
+  // when a later one is complete, and those of the last wait have by then been read by all W, each before it counted
+  // itself.  One wave; the others go on with the draw.
+  auto leave = [&]() {
+    if (W == 1 || wave != kWalkWaves - 1) return;
+    bool last_one = false;
+    if (lane == 0) last_one = __hip_atomic_fetch_add(mail, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - s_launch == (uint64_t)(W - 1);
+    if (__ballot(last_one) == 0) return;
+    for (int set = 0; set < 2; ++set)
+      for (int i = lane; i < W * kWalkBox; i += 64) mail_store(mail + 16 + (size_t)set * (kWalkMaxW + 1) * kWalkBox + i, 0);
+  };
   // The sums of a pass over `n` rows: s_sum is complete behind a barrier.  s_part[i][.] then holds the workgroups' sums of
   // row i and s_entry[epoch & 1] the entry that workgroup x_from published (x_from < 0: none), the same in every
   // workgroup of the sequence.  (epoch has been counted up before the pass.)  False: the others did not arrive.
@@ -521,11 +537,12 @@ __global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp)
     }
     __syncthreads();
     if (W > 1) {
-      const bool gone = s_abort != 0;
-      if (gone && tid < kWalkBox)  // what was published is taken back: no later launch can meet this launch's tags
-        for (int set = 0; set < 2; ++set) mail_store(mail + 16 + ((size_t)set * (kWalkMaxW + 1) + w) * kWalkBox + tid, 0);
-      if ((epoch == 1 || gone) && w == 0 && tid == kWalkThreads - 1) mail_store(mail, launch + 1);  // all W have read the counter
-      if (gone) {
+      if (s_abort != 0) {
+        // Taken back by itself: a workgroup that starts after this one has counted itself reads another counter, and
+        // then no count need come to W.  (It never comes to W too early: a later start only lowers it.)
+        if (tid < kWalkBox)
+          for (int set = 0; set < 2; ++set) mail_store(mail + 16 + ((size_t)set * (kWalkMaxW + 1) + w) * kWalkBox + tid, 0);
+        leave();
         if (tid == 0 && p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
         return false;
       }
@@ -702,6 +719,7 @@ __global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp)
       if (!exchange(1, xn >= 0 ? xn / slice : -1)) return;
       Z = total(0);
       if (!(Z > 0.0)) {
+        leave();
         // q was not a distribution the child could have been drawn from: flagged; the walk ends here
         if (w == 0 && tid == 0) {
           if (p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
@@ -719,6 +737,7 @@ __global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp)
       }
     }
     if (accepted) continue;
+    leave();
     if (w == 0 && tid == 0) p.path_len[b] = len;
     // ---- the last token: the smallest v whose cumulative weight exceeds u_final Z ----
     // The slices' sums say which workgroup holds it, the segments' which wave; where no place claims it (u_final was not

@@ -760,3 +760,93 @@ def test_accept_sampling_waits_are_bounded(torch_dev):
     ref_paths, ref_next = vo.accept_sampling(parent, cu_T, tok, p, q, u, uf, max_path=6)
     assert int(flag.item()) == 0 and list(nxt.cpu().numpy()) == ref_next
     assert list(n.cpu().numpy()) == [len(x) for x in ref_paths]
+
+
+def _sampling_steps(seed, T, V, n):
+    """n steps' inputs for the same trees (distributions, tokens, uniform numbers of their own) and the oracle's answers."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    cu_T = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
+    parent = np.concatenate([wl.tree_expand_prune(rng, int(t)) for t in T]).astype(np.int32)
+    steps = []
+    while len(steps) < n:
+        p, q, tok, u, uf = wl.sampling_inputs(rng, parent, cu_T, V, drift=0.8)
+        ref = vo.accept_sampling(parent, cu_T, tok, p, q, u, uf, max_path=8)
+        assert sampling_margin(parent, cu_T, tok, p, q, u, uf, *ref) > 1e-9
+        if not steps or ref[1] != steps[-1][1][1]:   # (an answer that the step before would not have given)
+            steps.append(((p, q, tok, u, uf), ref))
+    return parent, cu_T, steps
+
+
+def _check_step(got, ref):
+    path, n, nxt = (t.cpu().numpy() for t in got)
+    assert list(n) == [len(x) for x in ref[0]] and list(nxt) == ref[1]
+    for b, x in enumerate(ref[0]):
+        assert list(path[b, :len(x)]) == x
+
+
+@pytest.mark.parametrize("V,workgroups", [(20000, 4), (40001, 16), (128256, 0)])
+def test_accept_sampling_leaves_no_sums_behind_in_the_workspace(torch_dev, V, workgroups):
+    """Two steps with different inputs on one workspace whose counters are set back in between to what the first step
+    met (a small tensor that was placed there in the meantime does that): the second takes nothing for a sum that the
+    first left.  Behind every step, also one whose waits were given up, only the counters differ from zero."""
+    torch = torch_dev
+    from paper_2510_26577_amd import verify
+    T = np.array([9, 14, 5])
+    parent, cu_T, steps = _sampling_steps(4100 + V, T, V, 2)
+    d = lambda a, t: torch.from_numpy(np.ascontiguousarray(a, dtype=t)).cuda()
+    tree = (d(parent, np.int32), d(cu_T, np.int32))
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(verify._lib().tva_sample_workspace_bytes(len(T)) // 8, dtype=torch.int64, device="cuda")
+    parts = ws.view(len(T), -1)
+    for counter in (0, 0, 1 << 40, -1, 0):
+        for i, ((p, q, tok, u, uf), ref) in enumerate(steps):
+            say(f"[case] accept_sampling V={V} workgroups={workgroups}, counters set back to {counter}, step {i}")
+            parts[:, :16] = counter
+            got = verify.accept_sampling(*tree, d(tok, np.int32), d(p, np.float32), d(q, np.float32), d(u, np.float32),
+                                         d(uf, np.float32), 8, err_flag=flag, workspace=ws, workgroups_per_sequence=workgroups)
+            torch.cuda.synchronize()
+            assert int(flag.item()) == 0
+            _check_step(got, ref)
+            assert not bool(parts[:, 16:].any()) and bool((parts[:, 0] != counter).all())
+    (p, q, tok, u, uf), _ = steps[0]
+    say(f"[case] accept_sampling V={V}, waits given up after 64 polls")
+    verify.accept_sampling(*tree, d(tok, np.int32), d(p, np.float32), d(q, np.float32), d(u, np.float32), d(uf, np.float32), 8,
+                           err_flag=flag, workspace=ws, workgroups_per_sequence=workgroups or 8, wait_bound_test_spins=64)
+    torch.cuda.synchronize()
+    assert int(flag.item()) != 0 and not bool(parts[:, 16:].any())
+
+
+def test_captured_sampling_shares_its_counters_with_a_small_tensor(torch_dev):
+    """A captured call whose workspace's first 512 bytes (the counter, not the words that carry sums) are rewritten with the
+    same values before it on every replay, as a small tensor of a graph's memory pool would be; new inputs per replay."""
+    torch = torch_dev
+    from paper_2510_26577_amd import verify
+    T, V = np.array([12, 7]), 50000
+    parent, cu_T, steps = _sampling_steps(4200, T, V, 4)
+    d = lambda a, t: torch.from_numpy(np.ascontiguousarray(a, dtype=t)).cuda()
+    tree = (d(parent, np.int32), d(cu_T, np.int32))
+    types = (np.float32, np.float32, np.int32, np.float32, np.float32)
+    p, q, tok, u, uf = ins = [d(x, t) for x, t in zip(steps[0][0], types)]
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(verify._lib().tva_sample_workspace_bytes(len(T)) // 8, dtype=torch.int64, device="cuda")
+    small = ws.view(len(T), -1)[:, :64]
+
+    def one_pass(stream=None):
+        small.fill_(3)
+        return verify.accept_sampling(*tree, tok, p, q, u, uf, 8, err_flag=flag, stream=stream, workspace=ws, workgroups_per_sequence=8)
+
+    one_pass()
+    torch.cuda.synchronize()
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        outs = one_pass(side)
+    for replay in range(2):
+        for i, (step, ref) in enumerate(steps):
+            say(f"[case] captured sampling with rewritten counters, replay {replay}, step {i}")
+            for t, x, ty in zip(ins, step, types):
+                t.copy_(d(x, ty))
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert int(flag.item()) == 0
+            _check_step(outs, ref)
