@@ -177,7 +177,7 @@ _native = None
 _NATIVE_CALLS = ("tva_tree_verify_attn", "tva_workspace_bytes", "tva_build_ancestor_mask", "tva_accept_greedy", "tva_accept_greedy_filled",
                  "tva_accept_sampling_filled", "tva_sample_workspace_bytes_rows", "tva_commit_path", "tva_tree_rerank_count",
                  "tva_rerank_workspace_bytes", "tva_tree_select_subtree")
-_address = {}  # of the functions called on argument blocks their callers keep
+_address = {}  # of the functions called on argument blocks their callers keep, and the size of the block each reads
 
 
 def _bind_native(lib) -> None:
@@ -186,14 +186,16 @@ def _bind_native(lib) -> None:
         raise RuntimeError(f"{PYCALL_LIB_PATH} not built: run `python -c 'import __graft_entry__ as g; g.build()'`")
     from . import _pycall
     at = lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
-    for name in ("tva_sizeof_sample_args", "tva_sizeof_commit_args"):
+    for name in ("tva_sizeof_sample_args", "tva_sizeof_commit_args", "tva_sizeof_expand_args"):
         getattr(lib, name).restype = ctypes.c_size_t
     sizes = lib.tva_sizeof_args() + 1024 * (lib.tva_sizeof_sample_args() + 1024 * lib.tva_sizeof_commit_args())
     if _pycall.sizes != sizes or _pycall.functions != len(_NATIVE_CALLS):
         raise RuntimeError("_pycall.so is stale: rebuild it")
     _pycall.bind(*map(at, _NATIVE_CALLS))
-    for name in ("tva_tree_verify_attn", "tva_tree_verify_attn_static", "tva_tree_verify_attn_splits", "tva_expand_layer", "tva_commit_path"):
-        _address[name] = at(name)
+    for size, names in ((lib.tva_sizeof_args(), ("tva_tree_verify_attn", "tva_tree_verify_attn_static", "tva_tree_verify_attn_splits")),
+                        (lib.tva_sizeof_expand_args(), ("tva_expand_layer",)), (lib.tva_sizeof_commit_args(), ("tva_commit_path",))):
+        for name in names:
+            _address[name] = (at(name), size)
     _native = _pycall
 
 
@@ -211,9 +213,11 @@ def _result(r):
     return r
 
 
-def call_raw(name: str, args, stream=None) -> None:
-    """Queue a library call on an argument block its caller keeps."""
-    code = native().call(_address[name], args, stream)
+def call_raw(name: str, block, args, stream=None) -> None:
+    """Queue a library call on an argument block its caller keeps: an instance of `block`, anything else is refused."""
+    call = native().call
+    address, size = _address[name]
+    code = call(address, size, block, args, stream)
     if code != TVA_OK:
         raise TvaError(code)
 
@@ -344,18 +348,18 @@ def plan_workgroup_rows(args: TvaArgs) -> int:
 
 def tree_verify_attn_raw(args: TvaArgs, stream=None) -> None:
     """Queue the attention on `stream` with a prepared argument struct."""
-    call_raw("tva_tree_verify_attn", args, stream)
+    call_raw("tva_tree_verify_attn", TvaArgs, args, stream)
 
 
 def tree_verify_attn_static_raw(args: TvaArgs, stream=None) -> None:
     """Queue the attention with the KV splits' partial results in the library's own device array
     (tva_tree_verify_attn_static: nothing is allocated, args.workspace is ignored)."""
-    call_raw("tva_tree_verify_attn_static", args, stream)
+    call_raw("tva_tree_verify_attn_static", TvaArgs, args, stream)
 
 
 def tree_verify_attn_splits_raw(args: TvaArgs, stream=None) -> None:
     """Queue only the split-KV attention kernel (no merge) with a prepared argument struct."""
-    call_raw("tva_tree_verify_attn_splits", args, stream)
+    call_raw("tva_tree_verify_attn_splits", TvaArgs, args, stream)
 
 
 def tree_verify_attn(q, k_tree, v_tree, k_cache, v_cache, anc_mask, cu_T, L, *, max_T: int, max_L: int,

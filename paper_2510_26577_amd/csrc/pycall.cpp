@@ -357,19 +357,31 @@ PyObject *select_subtree(PyObject *, PyObject *const *a, Py_ssize_t n) {
   END_HANDLE_TH_ERRORS
 }
 
-// A call on an argument block the caller keeps: (address of int f(const void *args, void *stream), the ctypes
-// structure, stream) -> status
+// A call on an argument block the caller keeps: (address of int f(const void *args, void *stream), how many bytes f reads
+// of the block, the block's class, the block, stream) -> status.  Another structure is refused: f would take its fields
+// for its own, and read past a shorter one's end.
 PyObject *call(PyObject *, PyObject *const *a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
-  expect(n, 3);
+  expect(n, 5);
   auto f = reinterpret_cast<int (*)(const void *, void *)>(PyLong_AsVoidPtr(a[0]));
   if (!f) fail(PyExc_ValueError, "the function has no address");
-  void *st = stream_of(a[2]);
-  Py_buffer view;
-  if (PyObject_GetBuffer(a[1], &view, PyBUF_SIMPLE) != 0) throw python_error();
-  const int rc = unlocked([&] { return f(view.buf, st); });
-  PyBuffer_Release(&view);
-  return PyLong_FromLong(rc);
+  const int64_t size = integer(a[1]);
+  const int right = PyObject_IsInstance(a[3], a[2]);
+  if (right < 0) throw python_error();
+  if (!right) {
+    PyErr_Format(PyExc_TypeError, "expected %S, not %S", a[2], reinterpret_cast<PyObject *>(Py_TYPE(a[3])));
+    throw python_error();
+  }
+  struct Block {
+    Py_buffer view{};
+    explicit Block(PyObject *o) {
+      if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw python_error();
+    }
+    ~Block() { PyBuffer_Release(&view); }
+  } block(a[3]);
+  if (block.view.len < size) fail(PyExc_TypeError, "the argument block is shorter than the library's");
+  void *st = stream_of(a[4]);
+  return PyLong_FromLong(unlocked([&] { return f(block.view.buf, st); }));
   END_HANDLE_TH_ERRORS
 }
 

@@ -67,7 +67,7 @@ def make_expand_args(*, cu_N, score, logp, K: int, sum_N: int, max_N: int, cand_
 
 
 def expand_layer_raw(args: ExpandArgs, stream=None) -> None:
-    binding.call_raw("tva_expand_layer", args, stream)
+    binding.call_raw("tva_expand_layer", ExpandArgs, args, stream)
 
 
 def expand_layer(cu_N, score, logp, K: int, max_N: int, stream=None):

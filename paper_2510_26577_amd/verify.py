@@ -137,7 +137,7 @@ def make_commit_args(*, cu_T, L, path, path_len, k_tree, v_tree, k_cache, v_cach
 
 
 def commit_path_raw(args: CommitArgs, stream=None) -> None:
-    binding.call_raw("tva_commit_path", args, stream)
+    binding.call_raw("tva_commit_path", CommitArgs, args, stream)
 
 
 def commit_path(*, cu_T, L, path, path_len, k_tree, v_tree, k_cache, v_cache, cu_L=None, page_table=None, page_size: int = 0,

@@ -418,3 +418,21 @@ def test_host_mask_builder_matches_oracle_and_validates(lib):
     assert lib.tva_strerror(-5).startswith(b"malformed tree")
     with pytest.raises(binding.TvaError):
         binding.build_ancestor_mask_host(parent, cu_T, 64)      # max_T below the largest tree
+
+
+def test_calls_on_argument_blocks_take_their_own_structure_only(lib):
+    """Another structure than the call's is refused before the library (or a device) is reached, a shorter one too."""
+    from paper_2510_26577_amd import draft, verify
+    blocks = (binding.TvaArgs, draft.ExpandArgs, verify.CommitArgs, verify.SampleArgs)
+    calls = ((binding.tree_verify_attn_raw, binding.TvaArgs), (binding.tree_verify_attn_static_raw, binding.TvaArgs),
+             (binding.tree_verify_attn_splits_raw, binding.TvaArgs), (draft.expand_layer_raw, draft.ExpandArgs),
+             (verify.commit_path_raw, verify.CommitArgs))
+    for call, own in calls:
+        for other in [b() for b in blocks if b is not own] + [bytes(1024), np.zeros(256), None, ctypes.pointer(own())]:
+            with pytest.raises(TypeError):
+                call(other)
+
+    class Short(ctypes.Structure):
+        _fields_ = verify.CommitArgs._fields_[:8]
+    with pytest.raises(TypeError):
+        binding.call_raw("tva_commit_path", Short, Short())
