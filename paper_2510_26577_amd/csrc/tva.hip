@@ -374,28 +374,21 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
   int split = chunk_of_slot;
   if (C::NW == 8 && p.real_splits > 0) {
-    // (a permutation of (sequence, split), made on the host: see fill_slots)
-    const int z = (int)blockIdx.z, over = z - p.real_splits;
-    int before = 0;  // filled (or, past them, unfilled) splits of the sequences before this one
-    b = 0;
+    // (a permutation of (sequence, split), made on the host: see fill_slots.  Lane i looks at sequence i: the argument block is
+    // never indexed by a register, and none of its words is held past this.  Picked with scalars instead, up to 54 of the
+    // kernel's were parked in lanes of vector registers over the whole loop, in every launch of these shapes: 43 paged
+    // sequences of 223 keys, 8-bit, 256-row shape 42.3 us instead of 39.9; 63 of 648 keys, D = 64, 128-row shape, which then needed
+    // more than 128 registers, 36.5 instead of 27.2.)
+    const int z = (int)blockIdx.z, over = z - p.real_splits, i = (int)threadIdx.x & 63;
+    uint32_t word = 0;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const int filled = (int)((p.slot_seq[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
-      const int upto = over < 0 ? filled : (i + 1) * p.n_chunks - filled;
-      if (i < p.B && upto <= (over < 0 ? z : over)) b = i + 1, before = upto;
-    }
-    split = (over < 0 ? z : over) - before;
-    if (over >= 0) {
-      // the unfilled splits of b are its last ones
-      int filled_b = 0, filled_a = 0;
-#pragma unroll
-      for (int i = 0; i < 32; ++i) {
-        const int filled = (int)((p.slot_seq[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
-        if (i == b) filled_b = filled;
-        if (i == b - 1) filled_a = filled;
-      }
-      split += filled_b - filled_a;
-    }
+    for (int k = 0; k < 16; ++k) word = (i >> 1) == k ? p.slot_seq[k] : word;
+    const int filled = (int)((word >> (16 * (i & 1))) & 0xFFFFu);  // of sequences 0 .. i; past them, the unfilled ones
+    const int upto = over < 0 ? filled : (i + 1) * p.n_chunks - filled, place = over < 0 ? z : over;
+    b = __builtin_popcountll(__builtin_amdgcn_ballot_w64(i < p.B && upto <= place));
+    split = place - (b > 0 ? __builtin_amdgcn_readlane(upto, b - 1) : 0);
+    // (the unfilled splits of b are its last ones)
+    if (over >= 0) split += __builtin_amdgcn_readlane(filled, b) - (b > 0 ? __builtin_amdgcn_readlane(filled, b - 1) : 0);
   }
   const int chunk = split;
 

@@ -1,0 +1,55 @@
+"""What the compiler gave the kernels of the built library: nothing they keep is spilled (the kernel descriptors' metadata in
+the library's own gfx950 code objects)."""
+import os
+import struct
+
+import pytest
+
+from paper_2510_26577_amd import binding
+
+
+def kernels():
+    """{demangled-enough name: metadata} of every kernel in libtva.so."""
+    import msgpack
+    if not os.path.exists(binding.LIB_PATH):
+        binding.build_library()
+    data = open(binding.LIB_PATH, "rb").read()
+    found, at = {}, 0
+    while (at := data.find(b"\x7fELF\x02\x01\x01\x40", at)) >= 0:  # 64-bit little-endian, OS/ABI AMDGPU_HSA
+        shoff, = struct.unpack_from("<Q", data, at + 40)
+        shentsize, shnum = struct.unpack_from("<HH", data, at + 58)
+        for i in range(shnum):
+            kind, _, _, offset, size = struct.unpack_from("<IQQQQ", data, at + shoff + i * shentsize + 4)
+            if kind != 7:  # SHT_NOTE
+                continue
+            p, end = at + offset, at + offset + size
+            while p < end:
+                nlen, dlen, what = struct.unpack_from("<III", data, p)
+                body = p + 12 + (nlen + 3) // 4 * 4
+                if what == 32:  # NT_AMDGPU_METADATA
+                    for k in msgpack.unpackb(data[body:body + dlen])["amdhsa.kernels"]:
+                        found[k[".name"]] = k
+                p = body + (dlen + 3) // 4 * 4
+        at += 64
+    return found
+
+
+@pytest.fixture(scope="module")
+def table():
+    t = kernels()
+    assert sum("attn_kernel" in n for n in t) >= 28 and sum("walk_kernel" in n for n in t) == 7, sorted(t)
+    return t
+
+
+def test_eight_wave_attention_shapes_keep_no_scalars_in_vector_registers(table):
+    """Scalars that do not fit are written to lanes of vector registers and read back in the loop.  (A handful at most: the
+    paged 256-row shape with D = 128 parks one.)"""
+    for name, k in table.items():
+        if "attn_kernel" in name and ("ELi8ELi1ELi1E" in name or "ELi4ELi2ELi1E" in name):
+            assert k[".sgpr_spill_count"] <= 4, (name, k[".sgpr_spill_count"])
+
+
+def test_attention_kernels_spill_no_vector_registers(table):
+    for name, k in table.items():
+        if "attn_kernel" in name or "merge_kernel" in name:
+            assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, name
