@@ -472,13 +472,12 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
 
   // ---- running softmax state (log2 domain; m_run is the reference the exponentials use) ----
-  // (m_use: m_run, or 0 while there is none; cap: the largest sum of one lane's probabilities of a block that needs no
-  // look at the maximum, -1 while there is no reference)
+  // (m_use, cap: see use_reference; outside the steady part of the loop m_use belongs to the block at hand)
   float m_run[RB], l_run[RB], m_use[RB], cap[RB];
   f32x16 oacc[RB][ND];
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
-    m_run[r] = -INFINITY, m_use[r] = 0.f, cap[r] = -1.f;
+    m_run[r] = -INFINITY;
     l_run[r] = 0.f;
 #pragma unroll
     for (int d = 0; d < ND; ++d)
@@ -638,6 +637,12 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
   constexpr int V8_SECOND = (NLDK >= 4 ? 2 : 2 * NLDK) * 1024;  // keys 16 .. 31 of the wave: two pieces further on
 
+  // what the steady part of the loop keeps of row r's reference: m_use, the reference or 0 while there is none; cap, the
+  // largest sum of one lane's probabilities of a block that needs no look at the maximum, -1 while there is no reference
+  auto use_reference = [&](int r) __attribute__((always_inline)) {
+    m_use[r] = (m_run[r] == -INFINITY) ? 0.f : m_run[r];
+    cap[r] = (m_run[r] == -INFINITY) ? -1.f : kLazyCap;
+  };
   // ---- one 32-key block of one tile: S^T = K Q^T, online softmax, O^T += V^T P^T ----
   auto compute_block = [&](const lds_byte *stage, auto kb_tag, int base, int limit, bool tree, auto masked_tag, auto settled_tag) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_tag)::value, SETTLED = decltype(settled_tag)::value;
@@ -718,69 +723,90 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         }
       }
     }
-    // Probabilities against the reference as it stands.  What the maximum of the block would be needed for -- moving the
-    // reference, the low-order pass -- is ruled out by the lane's sum of the block's 16 probabilities, which bounds each
-    // of them: a sum up to 2^kLazy keeps the reference, a sum up to kLoThreshold of the lane's own running sum
-    // (a part of the row's) excludes a weight that large.  After the first few blocks of a split that holds for every
-    // lane, and the maximum, its exchange between the lane halves and its exponential are not computed at all (256-row
-    // shape, 32 sequences of 2048 keys: 89 -> 85.5 us).  SETTLED: the steady part of a long split; elsewhere the
-    // question would be answered with yes most of the time and is not asked.
     bf16x8 pb[2][RB];
-    float ls[RB];
-    auto exponentials = [&](int r) __attribute__((always_inline)) {
-      ls[r] = 0.f;
+    uint64_t lo_votes = 0;
+    // moves row r's reference up to a block's maximum and rescales what was summed against the old one
+    auto move_reference = [&](int r, float mx) __attribute__((always_inline)) {
+      const float m_new = fmaxf(m_run[r], mx);
+      const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[r] - m_new);
+      m_run[r] = m_new;
+      l_run[r] *= alpha;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        float sv = sacc[r][i];
-        if (MASKED) sv = ((ok[r] >> i) & 1u) ? sv : -INFINITY;
-        const float pv = fast_exp2(fmaf(sv, p.scale_log2, -m_use[r]));
-        ls[r] += pv;
-        pb[i / 8][r][i % 8] = (__bf16)pv;
-      }
+      for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[r][d][i] *= alpha;
     };
-    bool look = !SETTLED;
-    if (SETTLED) {
+    if constexpr (!SETTLED) {
+      bool need_lo = false;
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        float sv[16];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          sv[i] = sacc[r][i];
+          if (MASKED) sv[i] = ((ok[r] >> i) & 1u) ? sv[i] : -INFINITY;
+          mx = fmaxf(mx, sv[i]);
+        }
+        mx = half_max(mx) * p.scale_log2;
+        // lazy reference update: only when some row's tile maximum exceeds its reference by > 2^kLazy
+        if (__builtin_amdgcn_ballot_w64(mx > m_run[r] + kLazy) != 0) move_reference(r, mx);
+        m_use[r] = (m_run[r] == -INFINITY) ? 0.f : m_run[r];
+        float ls = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float pv = fast_exp2(fmaf(sv[i], p.scale_log2, -m_use[r]));
+          ls += pv;
+          pb[i / 8][r][i % 8] = (__bf16)pv;
+        }
+        l_run[r] += ls;
+        need_lo = need_lo || (fast_exp2(mx - m_use[r]) > kLoThreshold * half_sum(l_run[r]));
+      }
+      lo_votes = __builtin_amdgcn_ballot_w64(need_lo);
+    } else {
+      // The steady part of a long split: probabilities against the reference as it stands.  What the maximum of the block
+      // would be needed for -- moving the reference, the low-order pass -- is ruled out by the lane's sum of the block's 16
+      // probabilities, which bounds each of them: a sum up to 2^kLazy keeps the reference, a sum up to kLoThreshold of the
+      // lane's own running sum (a part of the row's) excludes a weight that large.  After the first few blocks of a split
+      // that holds for every lane, and the maximum, its exchange between the lane halves and its exponential are not
+      // computed at all (256-row shape, 32 sequences of 2048 keys: 89 -> 85.5 us).
+      static_assert(!MASKED, "full tiles");
+      float ls[RB];
+      auto exponentials = [&](int r) __attribute__((always_inline)) {
+        ls[r] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float pv = fast_exp2(fmaf(sacc[r][i], p.scale_log2, -m_use[r]));
+          ls[r] += pv;
+          pb[i / 8][r][i % 8] = (__bf16)pv;
+        }
+      };
+      bool look = false;
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
         exponentials(r);
         look = look || !(ls[r] <= fminf(kLoThreshold * (l_run[r] + ls[r]), cap[r]));
       }
-      look = __builtin_amdgcn_ballot_w64(look) != 0;
-    }
-    uint64_t lo_votes = 0;
-    if (look) {
-      bool need_lo = false;
+      if (__builtin_amdgcn_ballot_w64(look) != 0) {
+        bool need_lo = false;
 #pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        float mx = -INFINITY;
+        for (int r = 0; r < RB; ++r) {
+          float mx = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          float sv = sacc[r][i];
-          if (MASKED) sv = ((ok[r] >> i) & 1u) ? sv : -INFINITY;
-          mx = fmaxf(mx, sv);
+          for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[r][i]);
+          mx = half_max(mx) * p.scale_log2;
+          if (__builtin_amdgcn_ballot_w64(mx > m_run[r] + kLazy) != 0) {
+            move_reference(r, mx);
+            use_reference(r);
+            exponentials(r);
+          }
+          need_lo = need_lo || (fast_exp2(mx - m_use[r]) > kLoThreshold * half_sum(l_run[r] + ls[r]));
         }
-        mx = half_max(mx) * p.scale_log2;
-        // lazy reference update: only when some row's tile maximum exceeds its reference by > 2^kLazy
-        const bool move = __builtin_amdgcn_ballot_w64(mx > m_run[r] + kLazy) != 0;
-        if (move) {
-          const float m_new = fmaxf(m_run[r], mx);
-          const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[r] - m_new);
-          m_run[r] = m_new;
-          m_use[r] = (m_new == -INFINITY) ? 0.f : m_new;
-          cap[r] = (m_new == -INFINITY) ? -1.f : kLazyCap;
-          l_run[r] *= alpha;
-#pragma unroll
-          for (int d = 0; d < ND; ++d)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[r][d][i] *= alpha;
-        }
-        if (!SETTLED || move) exponentials(r);
-        need_lo = need_lo || (fast_exp2(mx - m_use[r]) > kLoThreshold * half_sum(l_run[r] + ls[r]));
+        lo_votes = __builtin_amdgcn_ballot_w64(need_lo);
       }
-      lo_votes = __builtin_amdgcn_ballot_w64(need_lo);
-    }
 #pragma unroll
-    for (int r = 0; r < RB; ++r) l_run[r] += ls[r];
+      for (int r = 0; r < RB; ++r) l_run[r] += ls[r];
+    }
     // O^T += V^T P^T: first 16 keys while the operands of the second 16 arrive
     constexpr int S2OFF = (16 / NBLK) * ROWB;
     static_assert(ND == 4 || ND == 2, "head dimension 128 or 64");
@@ -1043,6 +1069,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       if constexpr (KBW > 1) compute_block(stage, std::integral_constant<int, 1>{}, 0, 0, false, std::false_type{}, std::true_type{});
     };
     static_assert(KBW <= 2, "");
+#pragma unroll
+    for (int r = 0; r < RB; ++r) use_reference(r);
     if (!PAGED || small_pages)
       for (; it + PD < n_full; ++it) step_steady(it);
   }
