@@ -220,6 +220,10 @@ struct AttnCfg {
   static constexpr bool STEADY = WK == 1 && !KV8;
   static constexpr int PD = KV8_REG ? NSTAGE - 1 : KV8 ? NL : NSTAGE - 1;  // tiles in flight ahead of the one being computed (widened)
   static constexpr int WG_PER_CU = KV8 ? (KV8_REG ? 2 : 1) : (NSTAGE == 2 && TK == 64) ? 2 : 1;
+  // wavefronts per SIMD that the registers have to leave room for.  (The rings of the eight-wave shapes with D = 64 let two
+  // workgroups share a CU, and so do up to 128 registers per lane: with 131, 50 sequences of 200 keys took 21 us instead
+  // of 14.5, paged, 256-row shape.  The dense 256-row shape needs four more than that and has one workgroup per CU.)
+  static constexpr int WAVES_PER_SIMD = D == 64 && NW == 8 && (PAGED || WK == 2) ? 4 : WG_PER_CU;
   // after the key loop the ring is reused: exchange area of the key-group merge, then (behind it,
   // when the groups are paired; else on top of it, after a barrier) the output transpose patches
   static constexpr bool PAIR = (WK == 2);
@@ -339,7 +343,7 @@ __device__ __forceinline__ void widen_e4m3(const u32x4 raw, bf16x8 &lo, bf16x8 &
 }
 
 template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8>
-__global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>::WG_PER_CU))
+__global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>::WAVES_PER_SIMD))
     attn_kernel(const AttnParams p_in) {
   using C = AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>;
   // The arguments the prologue needs, tied together by an empty statement so that they are fetched
@@ -495,7 +499,9 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   constexpr int EB = KV8 ? 1 : 2;                 // bytes per K/V element
   constexpr int LDC = KV8 ? C::DC8 : DC;          // lanes (16-byte chunks) per row of a wave-wide load
   const int lsub = lane / LDC, lpos = lane % LDC;
-  const int lrow = KV8 ? lsub : NBLK * lsub;      // the lane's row within its load instruction's rows
+  // the lane's row within its load instruction's rows (an expression and not a variable: the register it would be kept in
+  // is the one too many for two workgroups of the paged 256-row shape with D = 64 to share a CU, 128 per lane)
+#define lrow (KV8 ? lsub : NBLK * lsub)
   // tile row of (load instruction j of this wave, lane 0), and the LDS byte offsets of that
   // instruction's K and V destinations inside a stage (8-bit: inside the wave's zone of a landing
   // slot): wave-uniform.  (Plain expressions: with calls in their place the host pass of the compiler
@@ -1201,6 +1207,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   TL_STAMP(5);  // key groups merged, result stores issued
   TL_STORE(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), 0, 6);
 }
+#undef lrow
 #undef kdst_of
 #undef vdst_of
 

@@ -53,3 +53,17 @@ def test_attention_kernels_spill_no_vector_registers(table):
     for name, k in table.items():
         if "attn_kernel" in name or "merge_kernel" in name:
             assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, name
+
+
+def test_attention_kernels_of_which_two_share_a_compute_unit_leave_the_registers_for_it(table):
+    """Wavefronts per SIMD that the registers allow (512 per lane), against what the shape's rings leave room for: two
+    workgroups of four waves, with D = 64 two of eight (the dense 256-row shape runs one)."""
+    seen = 0
+    for name, k in table.items():
+        for shape, most in (("ILi128ELi1ELi2ELi1ELb0ELi2E", 256), ("ILi128ELi2ELi2ELi1ELb0ELi2E", 256), ("ILi128ELi1ELi2ELi1ELb1ELi2E", 256),
+                            ("ILi128ELi2ELi2ELi1ELb1ELi2E", 256), ("ILi64ELi4ELi2ELi1ELb0E", 128), ("ILi64ELi4ELi2ELi1ELb1E", 128),
+                            ("ILi64ELi8ELi1ELi1ELb1E", 128)):
+            if "attn_kernel" + shape in name:
+                assert k[".vgpr_count"] <= most, (name, k[".vgpr_count"])
+                seen += 1
+    assert seen == 7
