@@ -74,9 +74,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
-// Full tiles from which a split runs the steady loop.  (A shorter one would run little of it, from a cold instruction
-// cache, and its blocks still move the reference: 4 full tiles 13.4 us -> 14.2 with it.)
-constexpr int kSteadyTiles = 8;
+// Full tiles from which a split runs the steady loop.  A shorter one would run little of it, from a cold instruction
+// cache, and its blocks still move the reference.  Timed with and without it, six head shapes, unsplit and in four
+// splits, geometric mean with / without at 8, 12, 16, 20 and 32 full tiles: D = 128, dense 1.04, 1.02, 1.00, 0.98, 0.95, paged
+// 1.02, 1.01, 0.99, 0.98, 0.97; D = 64, dense 1.02, 0.98, 0.98, 0.92, 0.88, paged 1.00, 0.98, 0.95, 0.92, 0.87.
+template <int D>
+constexpr int kSteadyTiles = D == 64 ? 11 : 16;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 // A tile takes the low-order P pass when, for some row, (largest probability of the tile) >
@@ -1019,7 +1022,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
   TL_STAMP(3);  // first full tile done (a split without one: the same moment as the stamp before)
 #endif
-  if constexpr (C::STEADY) if (n_full >= kSteadyTiles) {
+  if constexpr (C::STEADY) if (n_full >= kSteadyTiles<D>) {
     // ---- the steady part of the loop: full cache tiles that queue full cache tiles.  One address per tile and operand, carried
     // along in scalar registers (dense), or one multiply-add per load on its page's number (paged); every wait is a constant ----
     int64_t row_off[NLDK];  // bytes from a tile's first row to the row of (load instruction j, lane 0)

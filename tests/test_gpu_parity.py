@@ -479,6 +479,24 @@ def test_long_splits_whose_scores_grow_match_oracle(gpu, shape, page_size, D):
         assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
 
 
+@pytest.mark.parametrize("D,tiles", [(128, 15), (128, 16), (64, 10), (64, 11)])
+@pytest.mark.parametrize("page_size", [0, 16])
+def test_splits_at_the_start_of_the_steady_loop_match_oracle(gpu, D, tiles, page_size):
+    """Second splits (their keys do not start at 0) of the last number of full tiles that runs without the steady loop and
+    the first that runs with it, whole and with a tile begun; a sequence whose last split is short."""
+    import torch
+    for more in (0, 1, 63):
+        w = wl.random_workload(970 + tiles + more + page_size, 2, 8, 2, D, [2 * 64 * tiles + more, 64 * tiles + 5], [33, 9], page_size=page_size)
+        ro, rl = orc.tree_verify_attn(w)
+        dw = gpu.to_device(w)
+        say(f"[case] steady loop's edge D={D} tiles={tiles} more={more} page_size={page_size}")
+        for splits in (1, 2):
+            o, l = gpu.attention(dw, gpu.build_mask(dw), num_splits=splits, plan_shape=5)
+            torch.cuda.synchronize()
+            assert np.abs(o.cpu().numpy().astype(np.float64) - ro).max() <= TOL_O
+            assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
+
+
 @pytest.mark.parametrize("shape", [3, 4, 5])
 def test_filled_splits_first_is_a_permutation(gpu, shape):
     """Split launches of more workgroups than the chip holds put the splits that the host's lengths fill first: true
