@@ -221,6 +221,10 @@ struct AttnCfg {
   static constexpr int NSTAGE = KV8_REG ? 4 : KV8 ? 2 : NST;
   // the 256-row shape's loop has a steady part of its own (the others ran no faster with one: they wait for data)
   static constexpr bool STEADY = WK == 1 && !KV8;
+  // m_use (in the kernel) is kept from block to block, or derived in each from the reference: kept, launches are 0.5 %
+  // faster, but 1 % slower where 8-bit tiles are widened through LDS, and the paged 256-row shape with D = 64 has no
+  // register for it
+  static constexpr bool KEEP_USE = (!KV8 || KV8_REG) && !(D == 64 && PAGED && WK == 1);
   static constexpr int PD = KV8_REG ? NSTAGE - 1 : KV8 ? NL : NSTAGE - 1;  // tiles in flight ahead of the one being computed (widened)
   static constexpr int WG_PER_CU = KV8 ? (KV8_REG ? 2 : 1) : (NSTAGE == 2 && TK == 64) ? 2 : 1;
   // wavefronts per SIMD that the registers have to leave room for.  (The rings of the eight-wave shapes with D = 64 let two
@@ -479,12 +483,13 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
 
   // ---- running softmax state (log2 domain; m_run is the reference the exponentials use) ----
-  // (m_use, cap: see use_reference; outside the steady part of the loop m_use belongs to the block at hand)
+  // (m_use: the reference, or 0 while there is none; cap, steady part of the loop only: the largest sum of one lane's
+  // probabilities of a block that needs no look at the maximum, -1 while there is no reference)
   float m_run[RB], l_run[RB], m_use[RB], cap[RB];
   f32x16 oacc[RB][ND];
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
-    m_run[r] = -INFINITY;
+    m_run[r] = -INFINITY, m_use[r] = 0.f;
     l_run[r] = 0.f;
 #pragma unroll
     for (int d = 0; d < ND; ++d)
@@ -646,12 +651,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
   constexpr int V8_SECOND = (NLDK >= 4 ? 2 : 2 * NLDK) * 1024;  // keys 16 .. 31 of the wave: two pieces further on
 
-  // what the steady part of the loop keeps of row r's reference: m_use, the reference or 0 while there is none; cap, the
-  // largest sum of one lane's probabilities of a block that needs no look at the maximum, -1 while there is no reference
-  auto use_reference = [&](int r) __attribute__((always_inline)) {
-    m_use[r] = (m_run[r] == -INFINITY) ? 0.f : m_run[r];
-    cap[r] = (m_run[r] == -INFINITY) ? -1.f : kLazyCap;
-  };
+  auto use_reference = [&](int r) __attribute__((always_inline)) { m_use[r] = (m_run[r] == -INFINITY) ? 0.f : m_run[r]; };
+  auto set_cap = [&](int r) __attribute__((always_inline)) { cap[r] = (m_run[r] == -INFINITY) ? -1.f : kLazyCap; };
   // ---- one 32-key block of one tile: S^T = K Q^T, online softmax, O^T += V^T P^T ----
   auto compute_block = [&](const lds_byte *stage, auto kb_tag, int base, int limit, bool tree, auto masked_tag, auto settled_tag) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_tag)::value, SETTLED = decltype(settled_tag)::value;
@@ -759,8 +760,11 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         }
         mx = half_max(mx) * p.scale_log2;
         // lazy reference update: only when some row's tile maximum exceeds its reference by > 2^kLazy
-        if (__builtin_amdgcn_ballot_w64(mx > m_run[r] + kLazy) != 0) move_reference(r, mx);
-        m_use[r] = (m_run[r] == -INFINITY) ? 0.f : m_run[r];
+        if (__builtin_amdgcn_ballot_w64(mx > m_run[r] + kLazy) != 0) {
+          move_reference(r, mx);
+          if (C::KEEP_USE) use_reference(r);
+        }
+        if (!C::KEEP_USE) use_reference(r);
         float ls = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -807,6 +811,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           if (__builtin_amdgcn_ballot_w64(mx > m_run[r] + kLazy) != 0) {
             move_reference(r, mx);
             use_reference(r);
+            set_cap(r);
             exponentials(r);
           }
           need_lo = need_lo || (fast_exp2(mx - m_use[r]) > kLoThreshold * half_sum(l_run[r] + ls[r]));
@@ -1079,7 +1084,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     };
     static_assert(KBW <= 2, "");
 #pragma unroll
-    for (int r = 0; r < RB; ++r) use_reference(r);
+    for (int r = 0; r < RB; ++r) set_cap(r);
     if (!PAGED || small_pages)
       for (; it + PD < n_full; ++it) step_steady(it);
   }
