@@ -436,3 +436,22 @@ def test_calls_on_argument_blocks_take_their_own_structure_only(lib):
         _fields_ = verify.CommitArgs._fields_[:8]
     with pytest.raises(TypeError):
         binding.call_raw("tva_commit_path", Short, Short())
+
+
+@pytest.mark.parametrize("B,heads,D,T,L,paged,hint,rows", [
+    # a workgroup more than the chip holds at once costs most of a round: 64-row workgroups would be 600 and 576 here
+    (15, 32, 128, 71, 2029, True, False, 256), (12, 64, 128, 45, 5124, True, False, 256), (8, 64, 128, 71, 1063, False, True, 256),
+    # pages cost the 64-row shape more than the 256-row shape
+    (24, 64, 128, 18, 974, True, True, 256),
+    # few workgroups of long splits; rounds of a half-empty shape; D = 64 dense, one 256-row workgroup per compute unit
+    (6, 32, 128, 18, 5579, False, True, 128), (24, 32, 128, 25, 1641, False, True, 128), (6, 32, 128, 39, 4387, True, True, 256),
+    (18, 32, 128, 46, 584, False, True, 64), (48, 32, 64, 71, 794, False, True, 64)])
+def test_shapes_that_the_duration_model_decides(lib, B, heads, D, T, L, paged, hint, rows):
+    """Calls timed in every shape where the rules, or the model without pages and part rounds, took one 15 .. 45 % slower."""
+    host = np.full(B, L, np.int32)
+    kw = dict(B=B, Hq=heads, Hkv=8, D=D, max_T=T, sum_T=B * T, mask_words=(T + 63) // 64, max_L=L)
+    if hint:
+        kw.update(sum_L=B * L, L_host=host.ctypes.data)
+    if paged:
+        kw.update(page_table=1 << 12, page_size=16, max_pages=-(-L // 16))   # (a plan reads no device memory)
+    assert binding.plan_workgroup_rows(shape_args(**kw)) == rows
