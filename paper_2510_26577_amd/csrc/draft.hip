@@ -269,8 +269,12 @@ __device__ __forceinline__ void count_tail(const double *s_u, const double *s_c,
 // piece has fewer than K tokens).  A thread holds 32 tokens.  The bound -- the K-th largest of the 256 threads' largest
 // values -- comes from a sort per wave and a merge of the four; the tokens that reach it, at least K and few more, go
 // to a list per wave in the groups of four they were loaded in (places by ballots, no atomics), which one wave sorts.  On
-// values alone ties all pass: where more than 32 groups do (and where a value is no number) the selection is made again on keys, and where even
-// then too many pass (a few threads hold most of the piece's large values) by K searches for the maximum.
+// values alone ties all pass, and rows masked by a grammar or cut to their best tokens are mostly of one value.  Where a
+// wave would list more than 32 groups it takes only the first K of those whose largest token just equals the bound: it
+// meets them in the order of their tokens, and any later one has K equal and earlier before it (rows cut to the best 50
+// of 128256 tokens: 640 rows 253 -> 60 us, 12 rows 21.6 -> 11.5; before, the selection was made again on keys from memory).
+// Where that still leaves more than 32 groups (a few threads hold most of the piece's large values), and where a value is
+// no number, it is made again on keys, and where even then too many pass by K searches for the maximum.
 // Bound by HBM for many rows (640 rows of 128256 tokens: 63.5 -> 52 us, 6.3 TB/s, with eight
 // maxima of groups in place of 32 keys per thread to compare); for one sequence's dozen rows by the chain load -
 // select (12 rows: 7.3 -> 4.6 us).
@@ -329,19 +333,31 @@ __global__ void __launch_bounds__(kPieceThreads) topk_parts_kernel(const float *
     const float merged = merge_rows(s_value[lane]);
     const float bound = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(merged), K - 1));
     int count = 0;  // groups of four with a token that reaches the bound (the others of a group read as none)
+    const uint64_t below = (1ull << lane) - 1ull;
+    auto list_group = [&](int i, bool in) {
+      const uint64_t votes = __ballot(in);
+      if (votes == 0) return;
+      const int pos = count + __popcll(votes & below);
+      count += __popcll(votes);
+      if (in && pos < 32) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int v = token_of(i, e);
+          s_list[wave][4 * pos + e] = x[i][e] >= bound && v < V ? make_key(x[i][e], (uint32_t)v) : 0ull;
+        }
+      }
+    };
     if (!keys_wanted) {
 #pragma unroll
-      for (int i = 0; i < kGroups; ++i) {
-        const uint64_t votes = __ballot(most[i] >= bound);
-        if (votes == 0) continue;
-        const int pos = count + __popcll(votes & ((1ull << lane) - 1ull));
-        count += __popcll(votes);
-        if (most[i] >= bound && pos < 32) {
+      for (int i = 0; i < kGroups; ++i) list_group(i, most[i] >= bound);
+      if (count > 32) {  // (the wave's list again, with K of the groups that only equal the bound)
+        count = 0;
+        int equal = 0;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int v = token_of(i, e);
-            s_list[wave][4 * pos + e] = x[i][e] >= bound && v < V ? make_key(x[i][e], (uint32_t)v) : 0ull;
-          }
+        for (int i = 0; i < kGroups; ++i) {
+          const uint64_t level = __ballot(most[i] == bound);
+          list_group(i, most[i] > bound || (most[i] == bound && equal + __popcll(level & below) < K));
+          equal += __popcll(level);
         }
       }
     }
@@ -359,10 +375,10 @@ __global__ void __launch_bounds__(kPieceThreads) topk_parts_kernel(const float *
   // the lists' keys in order, by one wave; zeros past the last token of a piece of fewer than K
   {
     const int c0 = 4 * s_count[0], c1 = 4 * s_count[1], c2 = 4 * s_count[2], c3 = 4 * s_count[3];
-    if (!keys_wanted && c0 + c1 + c2 + c3 <= 128) {
+    if (!keys_wanted && max(max(c0, c1), max(c2, c3)) <= 128) {
       if (wave != 0) return;
       uint64_t key = sort_row(entry(lane, c0, c1, c2, c3));
-      if (c0 + c1 + c2 + c3 > 64) key = merge_sorted(key, sort_row(entry(lane + 64, c0, c1, c2, c3)));
+      for (int e = 64; e < c0 + c1 + c2 + c3; e += 64) key = merge_sorted(key, sort_row(entry(lane + e, c0, c1, c2, c3)));
       key = merge_rows(key);
       if (lane < K) dst[lane] = key;
       return;

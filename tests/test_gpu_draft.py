@@ -196,6 +196,28 @@ def test_expand_layer_at_the_edges_of_pieces_and_lists(torch_dev, V, K, kind):
     check_expand(torch, cu_N, score, np.ascontiguousarray(logp), K)
 
 
+@pytest.mark.parametrize("V,K", [(8192, 16), (16390, 7), (8192 * 3 + 5, 12)])
+@pytest.mark.parametrize("floor", [-np.inf, np.finfo(np.float32).min, -7.5])
+@pytest.mark.parametrize("kept", [0, 3, 50, 700])
+def test_expand_layer_of_rows_that_are_mostly_one_value(torch_dev, V, K, floor, kept):
+    """Rows masked to a few tokens, with -inf, the type's lowest value or one that many tokens share: a piece then has fewer
+    tokens above the selection bound than K, and of those at it the first ones count.  One row's tokens sit in one piece,
+    one's at the end, one's in six threads (48 groups above the bound, more than a wave lists)."""
+    torch = torch_dev
+    rng = np.random.Generator(np.random.PCG64(660 + V + K + kept))
+    cu_N, score, logp = wl.expansion_inputs(rng, [3, 2], V)
+    spots = [rng.choice(V, kept, replace=False), 1000 + np.arange(kept), V - 1 - np.arange(kept), rng.choice(V, kept, replace=False),
+             np.add.outer(1024 * np.arange(8), np.arange(24)).reshape(-1)[:kept]]
+    for r, keep in enumerate(spots):
+        row = np.full(V, floor, np.float32)
+        row[keep] = -rng.random(len(keep)).astype(np.float32) * 6
+        if r == 3:
+            row[keep[::2]] = row[keep[0]] if kept else 0   # (ties above the floor too)
+        logp[r] = row
+    say(f"[case] expand floor={floor} kept={kept} V={V} K={K}")
+    check_expand(torch, cu_N, score, np.ascontiguousarray(logp), K)
+
+
 def random_scored_tree(rng, M, ties=0.2):
     parent = np.array([-1] + [int(rng.integers(max(0, i - 9), i)) for i in range(1, M)], np.int32)
     score = np.zeros(M, np.float32)
