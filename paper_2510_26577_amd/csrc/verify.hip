@@ -392,7 +392,9 @@ __device__ __forceinline__ double wave_sum(double x) { return read_lane(wave_sca
 
 template <int NV, bool WHOLE>
 __global__ void __launch_bounds__(kWalkThreads) walk_kernel(const WalkParams wp) {
-  constexpr bool kHoldQ = NV <= 16;  // (256 registers per thread: beyond that the draft's row is read again at each refusal)
+  // 256 registers per thread: beyond 16 groups the draft's row is read again at each refusal.  (16 groups of an odd vocabulary
+  // are 12 registers too many, and the compiler spills those: 100 sequences, V = 50257, 35 us; with the row read again 42.)
+  constexpr bool kHoldQ = NV <= 16;
   constexpr int kRows = NV <= 4 ? 4 : 1;  // rows of a chain loaded at once: about 16 loads of 16 bytes in flight per thread
   const SampleParams &p = wp.s;
   __shared__ double s_sum[kWalkChain][kWalkWaves];      // per row of a pass: the waves' sums of their segments

@@ -67,3 +67,11 @@ def test_attention_kernels_of_which_two_share_a_compute_unit_leave_the_registers
                 assert k[".vgpr_count"] <= most, (name, k[".vgpr_count"])
                 seen += 1
     assert seen == 7
+
+
+def test_sampling_kernels_spill_vector_registers_in_one_form_only(table):
+    """walk_kernel<16, false> (16 groups of a vocabulary that is no multiple of 4) keeps both rows and spills a dozen."""
+    for name, k in table.items():
+        if "walk_kernel" in name or "sample_kernel" in name or "topk_parts_kernel" in name:
+            most = 12 if "walk_kernelILi16ELb0E" in name else 0
+            assert k[".vgpr_spill_count"] <= most, (name, k[".vgpr_spill_count"])
