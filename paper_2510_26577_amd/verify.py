@@ -350,24 +350,22 @@ def _bench_sampling(steps: int) -> None:
             cases.append(case)
         sums, rejs = sums / copies, rejs / copies
 
-        # the three forms: row sums ahead of the walk where the library sees fit (the host's node count given), several
-        # workgroups per sequence without them, one workgroup per sequence
+        # the three forms: several workgroups per sequence, the same with rows taken as distributions, one workgroup per sequence
         def run(form):
             for k in cases:
                 accept_sampling(k["parent"], k["cu_T"], k["tok"], k["p"], k["q"], k["u"], k["uf"], depth + 1,
                                 residual=k["residual"], err_flag=k["flag"], stream=stream,
-                                workspace=None if form == "one" else k["ws"], sum_T=B * T if form in ("ahead", "unit") else 0,
-                                unit_rows=form == "unit")
+                                workspace=None if form == "one" else k["ws"], unit_rows=form == "unit")
 
         times = {}
-        for shared in ("unit", "ahead", "shared", "one"):
+        for form in ("unit", "shared", "one"):
             with torch.cuda.stream(stream):
-                run(shared)
+                run(form)
                 stream.synchronize()
                 g = torch.cuda.CUDAGraph()
                 with torch.cuda.graph(g, stream=stream):
                     for _ in range(max(1, steps // copies)):
-                        run(shared)
+                        run(form)
                 g.replay()
                 stream.synchronize()
                 best = 1e30
@@ -378,12 +376,11 @@ def _bench_sampling(steps: int) -> None:
                     e1.record(stream)
                     e1.synchronize()
                     best = min(best, e0.elapsed_time(e1) * 1e3 / (max(1, steps // copies) * copies))
-            times[shared] = best
+            times[form] = best
             assert all(int(k["flag"].item()) == 0 for k in cases)
         moved = 4.0 * V * (sums + 3 * rejs + B / 16.0)   # a sum reads a row; a residual reads two and writes one; the draw a segment
         print(json.dumps({"shape": name, "accepted_nodes_per_step": sums, "refused_children_per_step": rejs,
-                          "sampling_us": times["ahead"], "sampling_us_rows_taken_as_distributions": times["unit"],
-                          "sampling_us_without_the_node_count": times["shared"],
+                          "sampling_us": times["shared"], "sampling_us_rows_taken_as_distributions": times["unit"],
                           "sampling_us_one_workgroup_per_sequence": times["one"],
                           "vocabulary_bytes": moved, "GBps": moved / (times["shared"] * 1e-6) / 1e9}), flush=True)
         del cases

@@ -433,10 +433,11 @@ def test_a_tree_grown_and_cut_on_the_gpu_is_the_oracles_and_feeds_the_attention(
 
 @pytest.mark.parametrize("node_count", [False, True])
 def test_draft_and_sampling_kernels_replayed_from_a_graph(torch_dev, node_count):
-    """tva_expand_layer, tva_tree_select_subtree and tva_accept_sampling (several workgroups per sequence: a
-    counter-zeroing kernel -- with the host's node count the kernel that sums the rows ahead of the walk -- then the
+    """tva_expand_layer, tva_tree_select_subtree and tva_accept_sampling (several workgroups per sequence, one launch: the
     walk with its waits) captured in one HIP graph: every replay, with the outputs and the scratch memory overwritten
-    by eager work in between, reproduces the eager results bit for bit."""
+    by eager work in between -- counters and the words that carry sums alike, so that no tag of an earlier replay is
+    met again; a rewritten counter under standing sums is test_captured_sampling_shares_its_counters_with_a_small_tensor
+    -- reproduces the eager results bit for bit."""
     torch = torch_dev
     from paper_2510_26577_amd import draft, verify
     from oracle import verify_oracle as vo

@@ -548,8 +548,8 @@ def test_commit_of_an_8bit_cache(torch_dev, page_size):
 def run_sampling(torch, parent, cu_T, tok, p, q, u, uf, max_path, with_flag=True, misalign=False, workgroups=0, sum_T=0,
                  unit_rows=False):
     """workgroups: 0 = the library spreads a sequence over as many workgroups as it sees fit, 1 = one per sequence
-    (no workspace passed, unless sum_T asks for the row sums ahead of the walk), 2 .. 16 = that many.
-    sum_T: the host's count of nodes (0 = not given: no row sums ahead of the walk)."""
+    (no workspace passed, unless sum_T is given too), 2 .. 16 = that many.  sum_T: the host's count of nodes, on which
+    nothing depends (0 = not given)."""
     from paper_2510_26577_amd import verify
     d = lambda a, t: torch.from_numpy(np.ascontiguousarray(a, dtype=t)).cuda()
     flag = torch.zeros(1, dtype=torch.int32, device="cuda") if with_flag else None
@@ -620,8 +620,7 @@ def test_accept_sampling_matches_oracle(torch_dev, B, T_hi, V, temp, drift):
         for workgroups in (0, 1, 2, 16) if max_path not in (2, 3) else (0, 1):
             if B * workgroups > 256:
                 continue
-            # the row sums made ahead of the walk (the host's node count given): the right count, one that is too
-            # small (the trees past it are walked without) and one that is too large (no row is read past the last)
+            # the host's node count: not given, right, too small and too large (nothing may depend on it)
             for sum_T in (0, int(cu_T[-1])) + ((int(cu_T[-1]) // 2 + 1, int(cu_T[-1]) + 37) if workgroups in (0, 2) else ()):
                 path, n, nxt, flag = run_sampling(torch, parent, cu_T, tok, p, q, u, uf, max_path, workgroups=workgroups,
                                                   sum_T=sum_T, unit_rows=unit)
