@@ -12,6 +12,7 @@
 #include <ATen/core/LegacyTypeDispatch.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -104,6 +105,14 @@ void strides_of(PyObject *o, int64_t *page, int64_t *tok, int64_t *head) {
 at::Tensor make(at::IntArrayRef sizes, at::ScalarType type, const at::Tensor &like) {
   at::AutoDispatchBelowADInplaceOrView below;
   return at::empty(sizes, at::TensorOptions().dtype(type).device(like.device()));
+}
+// Scratch memory made here comes from the current stream's pool and goes back to it when the call returns.  Work queued
+// on another stream still uses it then: the allocator is told, and hands it out again only behind that work.
+void hold_for(const at::Tensor &scratch, void *st, PyObject *stream_given) {
+  if (!scratch.defined() || stream_given == Py_None) return;
+  const auto device = scratch.device().index();
+  if (c10::hip::getCurrentHIPStream(device).stream() == st) return;
+  c10::hip::HIPCachingAllocator::recordStream(scratch.storage().data_ptr(), c10::hip::getStreamFromExternal(static_cast<hipStream_t>(st), device));
 }
 int64_t bytes_of(const at::Tensor &t) { return t.numel() * static_cast<int64_t>(t.element_size()); }
 
@@ -200,6 +209,7 @@ PyObject *attn(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (ws) t.workspace = ws->data_ptr(), t.workspace_bytes = (size_t)bytes_of(*ws);
   void *st = stream_of(a[19]);
   const int rc = unlocked([&] { return lib.attn(&t, st); });
+  hold_for(new_ws, st, a[19]);
   if (rc != TVA_OK) return PyLong_FromLong(rc);
   return pair(*out, *lse);
   END_HANDLE_TH_ERRORS
@@ -274,6 +284,8 @@ PyObject *accept_sampling(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (ws) t.workspace = ws->data_ptr(), t.workspace_bytes = (size_t)bytes_of(*ws);
   void *st = stream_of(a[10]);
   const int rc = unlocked([&] { return lib.sampling_filled(&t, st); });
+  hold_for(made, st, a[10]);
+  hold_for(made_ws, st, a[10]);
   if (rc != TVA_OK) return PyLong_FromLong(rc);
   return triple(path, len, next);
   END_HANDLE_TH_ERRORS
@@ -329,6 +341,7 @@ PyObject *rerank_count(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return lib.rerank(ptr<const float>(&scores), B, N, ptr<const double>(&cost), m, C3, ptr<int32_t>(count), ptr<int32_t>(cu_T),
                       ptr<int32_t>(flag), ws->data_ptr(), (size_t)bytes_of(*ws), st);
   });
+  hold_for(new_ws, st, a[7]);
   if (rc != TVA_OK) return PyLong_FromLong(rc);
   return pair(*count, *cu_T);
   END_HANDLE_TH_ERRORS

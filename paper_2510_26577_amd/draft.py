@@ -84,6 +84,8 @@ def expand_layer(cu_N, score, logp, K: int, max_N: int, stream=None):
     a = make_expand_args(cu_N=cu_N, score=score, logp=logp, K=K, sum_N=sum_N, max_N=max_N, cand_score=cs, cand_parent=cp,
                          cand_token=ct, workspace=ws, workspace_bytes=need)
     expand_layer_raw(a, stream)
+    if stream is not None:
+        ws.record_stream(stream)  # (it goes back to the current stream's pool when this returns)
     return cs, cp, ct
 
 

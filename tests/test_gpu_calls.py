@@ -53,3 +53,42 @@ def test_results_and_scratch_passed_in_are_used_and_refusals_raise():
         call(L_host=[1, 2, 3])
     with pytest.raises(TypeError):
         call(max_L=None)
+
+
+def test_scratch_of_calls_on_another_stream_is_not_handed_out_while_they_wait():
+    """Calls queued on a stream that is busy, from a program whose current stream is another: memory allocated and
+    overwritten right behind them on the current stream must not be the scratch memory they are going to use."""
+    import torch
+    from oracle import verify_oracle as vo
+    from paper_2510_26577_amd import binding, draft, verify, workloads as wl
+    from paper_2510_26577_amd.device import to_device
+    d = lambda x, t: torch.from_numpy(np.ascontiguousarray(x, dtype=t)).cuda()
+    w = wl.random_workload(4, 1, 8, 2, 128, [3000], [9])
+    dw = to_device(w, "cuda:0")
+    rng = np.random.Generator(np.random.PCG64(31))
+    cu_T, parent = np.array([0, 12], np.int32), wl.tree_expand_prune(rng, 12).astype(np.int32)
+    p, q, tok, u, uf = wl.sampling_inputs(rng, parent, cu_T, 50000, drift=0.6)
+    ref = vo.accept_sampling(parent, cu_T, tok, p, q, u, uf, max_path=8)
+    scores = torch.rand((16, 145), device="cuda")
+    cost = torch.cumsum(torch.full((72,), 0.03, dtype=torch.float64, device="cuda"), 0) + 4.0
+    cu_N, score, logp = wl.expansion_inputs(rng, [5], 20000)
+    sample = (d(parent, np.int32), d(cu_T, np.int32), d(tok, np.int32), d(p, np.float32), d(q, np.float32), d(u, np.float32), d(uf, np.float32), 8)
+    grow = (d(cu_N, np.int32), d(score, np.float32), d(logp, np.float32), 8, 5)
+    attn = dict(max_T=w.max_T, max_L=w.max_L, scale=w.scale, cu_L=dw.cu_L, parent=dw.parent, num_splits=8)
+    calls = (lambda s: binding.tree_verify_attn(dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, None, dw.cu_T, dw.L, stream=s, **attn),
+             lambda s: verify.accept_sampling(*sample, stream=s),
+             lambda s: draft.rerank_count(scores, cost, 72, 1.0, stream=s), lambda s: draft.expand_layer(*grow, stream=s))
+    want = [[t.clone() for t in c(None)] for c in calls]
+    torch.cuda.synchronize()
+    assert list(want[1][2].cpu().numpy()) == ref[1]
+    side = torch.cuda.Stream()
+    for c, expected in zip(calls, want):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(20_000_000)          # (some milliseconds)
+        got = c(side)
+        held = [torch.full((n,), float("nan"), device="cuda") for n in [64, 256, 1 << 10, 1 << 11, 1 << 12, 1 << 14, 1 << 16, 50000] for _ in range(8)]
+        torch.cuda.synchronize()
+        for g, e in zip(got, expected):
+            assert torch.equal(g, e)
+        del held
