@@ -1496,6 +1496,11 @@ double plan_cost(const tva_args *a, const Plan &pl) {
   return us;
 }
 
+// the partial rows and their LSEs
+inline size_t scratch_bytes(const tva_args *a, const Plan &pl) {
+  return pl.n_chunks > 1 ? (size_t)pl.n_chunks * query_rows(a) * a->Hq * (a->D + 1) * sizeof(float) : 0;
+}
+
 bool make_plan(const tva_args *a, Plan *pl) {
   if (!a || a->B <= 0 || a->Hq <= 0 || a->Hkv <= 0 || a->Hq % a->Hkv) return false;
   if (a->sum_T < 0 || a->max_T < 0 || a->max_L < 0 || a->num_splits < 0) return false;
@@ -1560,6 +1565,9 @@ bool make_plan(const tva_args *a, Plan *pl) {
       if (variant == V_W8 && (a->D == 64 ? !a->page_table : v == V_M2K2)) return 0.98;
       return 0.92;
     };
+    // No shape whose partial rows need more than the library's own scratch array where the rules' plan does not: a call
+    // without a workspace (tva_tree_verify_attn_static) is refused for its size only where it always was.
+    const size_t own = TVA_STATIC_SCRATCH_BYTES, most = std::max(scratch_bytes(a, plan), own);
     double best = 0.0;
     int chosen = -1;
     const int first = rows <= 64 ? V_K2 : V_M2K2, last = rows <= 32 ? V_M2K2 : V_LAST;
@@ -1568,9 +1576,14 @@ bool make_plan(const tva_args *a, Plan *pl) {
       if (v == variant || (a->kv_fp8 && (v == V_M2K2_3 || (v == V_M2K2 && rows > 64)))) continue;
       plan_splits_of(&shapes, v, true, &plan);
       const double us = plan_cost(&shapes, plan);
-      if (us < enough(v) * rules && (chosen < 0 || us < best)) best = us, chosen = v;
+      if (us < enough(v) * rules && (chosen < 0 || us < best) && scratch_bytes(a, plan) <= most) best = us, chosen = v;
     }
-    if (chosen >= 0) plan_splits_of(a, chosen, true, pl);
+    if (chosen >= 0) {
+      // (splits that the lengths shorten are more splits: where those pass the limit they keep their length)
+      const size_t limit = std::max(scratch_bytes(a, *pl), own);
+      plan_splits_of(a, chosen, true, pl);
+      if (scratch_bytes(a, *pl) > limit) plan_splits_of(&shapes, chosen, true, pl);
+    }
   }
   return true;
 }
@@ -1777,8 +1790,7 @@ size_t tva_workspace_bytes(const tva_args *a) {
   if (check_args(a, true) != TVA_OK) return (size_t)-1;
   Plan pl;
   if (!make_plan(a, &pl)) return (size_t)-1;
-  if (pl.n_chunks <= 1) return 0;
-  return (size_t)pl.n_chunks * query_rows(a) * a->Hq * (a->D + 1) * sizeof(float);
+  return scratch_bytes(a, pl);
 }
 
 static int run_attention(const tva_args *a, void *workspace, size_t workspace_bytes, void *stream, bool merge);
@@ -1817,7 +1829,7 @@ static int run_attention(const tva_args *a, void *workspace, size_t workspace_by
   if (a->sum_T == 0 || a->max_T == 0 || query_rows(a) == 0) return TVA_OK;
   Plan pl;
   if (!make_plan(a, &pl)) return TVA_INVALID_ARG;
-  const size_t need = pl.n_chunks > 1 ? (size_t)pl.n_chunks * query_rows(a) * a->Hq * (a->D + 1) * sizeof(float) : 0;
+  const size_t need = scratch_bytes(a, pl);
   if (need > 0 && (!workspace || workspace_bytes < need)) return TVA_WORKSPACE_TOO_SMALL;
 
   AttnParams p;

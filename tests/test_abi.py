@@ -455,3 +455,18 @@ def test_shapes_that_the_duration_model_decides(lib, B, heads, D, T, L, paged, h
     if paged:
         kw.update(page_table=1 << 12, page_size=16, max_pages=-(-L // 16))   # (a plan reads no device memory)
     assert binding.plan_workgroup_rows(shape_args(**kw)) == rows
+
+
+@pytest.mark.parametrize("B,heads,T,L,paged,hint,fp8", [(8, 64, 64, 8192, False, False, 0), (3, 32, 99, 14340, True, True, 0),
+                                                        (7, 64, 44, 107099, True, True, 0), (6, 32, 114, 109139, False, True, 1),
+                                                        (9, 32, 51, 41139, False, True, 0), (4, 64, 64, 9186, True, True, 0)])
+def test_the_model_takes_no_plan_past_the_static_scratch_that_the_rules_keep_within(lib, B, heads, T, L, paged, hint, fp8):
+    """Calls whose plan by the rules fits the library's own scratch array (or needs none) and that a shape of more splits,
+    promised to be faster, would take past it: tva_tree_verify_attn_static accepts them as ever."""
+    host = np.full(B, L, np.int32)
+    kw = dict(B=B, Hq=heads, Hkv=8, max_T=T, sum_T=B * T, mask_words=(T + 63) // 64, max_L=L, kv_fp8=fp8)
+    if hint:
+        kw.update(sum_L=B * L, L_host=host.ctypes.data)
+    if paged:
+        kw.update(page_table=1 << 12, page_size=16, max_pages=-(-L // 16))
+    assert binding.workspace_bytes(shape_args(**kw)) <= binding.STATIC_SCRATCH_BYTES
