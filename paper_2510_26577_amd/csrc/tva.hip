@@ -71,13 +71,15 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
 // Full tiles from which a split runs the steady loop.  A shorter one would run little of it, from a cold instruction
-// cache, and its blocks still move the reference.  Timed with and without it, six head shapes, unsplit and in four
-// splits, geometric mean with / without at 8, 12, 16, 20 and 32 full tiles: D = 128, dense 1.04, 1.02, 1.00, 0.98, 0.95, paged
-// 1.02, 1.01, 0.99, 0.98, 0.97; D = 64, dense 1.02, 0.98, 0.98, 0.92, 0.88, paged 1.00, 0.98, 0.95, 0.92, 0.87.
+// cache, and its blocks still move the reference.  Timed with and without it: D = 64 (six head shapes, unsplit and in four
+// splits, geometric mean with / without at 8, 12, 16, 20 and 32 full tiles) dense 1.02, 0.98, 0.98, 0.92, 0.88, paged 1.00, 0.98,
+// 0.95, 0.92, 0.87; D = 128 (32 sequences of 60 nodes, us without / with at 8, 12, 16 and 24) dense 33.2 / 35.0, 42.6 / 43.6,
+// 52.6 / 52.0, 71.0 / 67.6, paged 37.3 / 38.2, 46.0 / 46.2, 56.3 / 55.0, 76.6 / 74.2.
 template <int D>
 constexpr int kSteadyTiles = D == 64 ? 11 : 16;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -289,6 +291,21 @@ __device__ __forceinline__ s16x4 lds_read_tr(uint32_t addr) {
 // Waits for every outstanding LDS read of this wave; the operands tie the wait to the values.
 __device__ __forceinline__ void lds_wait(s16x4 &a, s16x4 &b, s16x4 &c, s16x4 &d) {
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
+
+// The same into a given register, a 16-byte read of a K operand, and the wait until at most N LDS operations are
+// outstanding (they return in order): the pipelined loop's reads are in flight over several matrix instructions.
+template <int OFF>
+__device__ __forceinline__ void lds_read_v(s16x4 &v, uint32_t addr) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+}
+template <int OFF>
+__device__ __forceinline__ void lds_read_k(bf16x8 &v, uint32_t addr) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+}
+template <int N>
+__device__ __forceinline__ void lds_wait_n(bf16x8 &a, s16x4 &b, s16x4 &c) {
+  asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(a), "+v"(b), "+v"(c) : "n"(N));
 }
 
 // 16-byte LDS read from a landing zone of the 8-bit K/V path (inline assembly for the same reason),
@@ -783,7 +800,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       // probabilities, which bounds each of them: a sum up to 2^kLazy keeps the reference, a sum up to kLoThreshold of the
       // lane's own running sum (a part of the row's) excludes a weight that large.  After the first few blocks of a split
       // that holds for every lane, and the maximum, its exchange between the lane halves and its exponential are not
-      // computed at all (256-row shape, 32 sequences of 2048 keys: 89 -> 85.5 us).
+      // computed at all.
       static_assert(!MASKED, "full tiles");
       float ls[RB];
       auto exponentials = [&](int r) __attribute__((always_inline)) {
@@ -1042,52 +1059,266 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
                              ((int64_t)p.page_size * p.stride_tok + (int64_t)p.Hkv * p.stride_head) * EB < (1ll << 31);
     const uint32_t page_bytes = (uint32_t)(p.stride_page * EB), tok_bytes = (uint32_t)(p.stride_tok * EB);
     const uint32_t head_bytes = (uint32_t)(kvh * p.stride_head * EB), slot_mask = (uint32_t)p.page_size - 1u;
-    auto issue_steady = [&](int t) __attribute__((always_inline)) {
-      lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
-      if constexpr (PAGED) {
+    if constexpr (D == 128) {
+      // ---- as a software pipeline over 32-key blocks.  A step computes the scores of the next block, the probabilities of
+      // this one and the output of the one before, a matrix instruction of each product and two probabilities per lane at a time,
+      // with their operands read from LDS four such groups ahead: the matrix unit has work while the vector ALUs exponentiate,
+      // whatever the SIMD's other wave is at.  K is fetched a tile further ahead than V, whose place it would else wait for.
+      // (32 sequences of 2048 keys, 60 nodes: 150 -> 128 thousand cycles a workgroup, but the chip, at its power limit, lowers
+      // its clock from 2.1 to 1.75 GHz: 84.5 -> 80.5 us.  Paged, 4 x 16 .. 32 K keys: 126 -> 118 us.  Without the loads from
+      // memory the former takes 70 us, without the LDS reads as well 64, with neither nor the exponentials 57.) ----
+      static_assert(!C::STEADY || (D == 64 || (RB == 1 && NS == 8 && ND == 4 && KBW == 2 && NSTAGE == 4)), "");
+      const int end = n_full - PD;
+      if ((!PAGED || small_pages) && it < end) {
+        uint64_t row_at[NLDK];  // (paged) the offsets the last K loads used: V's follow one tile later
+        auto issue_k = [&](int t) __attribute__((always_inline)) {
+          lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
+          if constexpr (PAGED) {
 #pragma unroll
-        for (int j = 0; j < NLDK; ++j) {
-          const uint32_t page = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
-          const uint32_t slot = (uint32_t)(k0 + t * TK + full_key(j)) & slot_mask;
-          const uint64_t off = (uint64_t)page * page_bytes + (slot * tok_bytes + head_bytes + (uint32_t)chunk_of(j) * 16u);
-          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + off), stage + kdst_of(j), 16, 0, kLoadOnce);
-          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vc_bytes + off), stage + vdst_of(j), 16, 0, kLoadOnce);
-        }
-        // (the entries of tile t + LOOK; past the last key they re-read its entry)
+            for (int j = 0; j < NLDK; ++j) {
+              const uint32_t page = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
+              const uint32_t slot = (uint32_t)(k0 + t * TK + full_key(j)) & slot_mask;
+              row_at[j] = (uint64_t)page * page_bytes + (slot * tok_bytes + head_bytes + (uint32_t)chunk_of(j) * 16u);
+              __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + row_at[j]), stage + kdst_of(j), 16, 0, kLoadOnce);
+            }
+            // (the entries of tile t + LOOK; past the last key they re-read its entry)
 #pragma unroll
-        for (int j = 0; j < NLDK; ++j) {
-          const int ahead = t + C::LOOK, row = ahead < n_full ? full_key(j) : row0_of(j) + lrow;
-          int key = k0 + ahead * TK + row;
-          key = key < k1 ? key : k1 - 1;
-          if (ahead >= n_ct && p.k_tree == nullptr) key = Lb0 + (ahead - n_ct) * TK + row, key = key < Lb0 + Tb ? key : Lb0 + Tb - 1;
-          int pidx = key >> p.page_shift;
-          pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;
-          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(p.page_table + (int64_t)b * p.max_pages + pidx), pg_lds + ((t + C::LOOK) & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256, 4, 0, 0);
-        }
-      } else {
+            for (int j = 0; j < NLDK; ++j) {
+              const int ahead = t + C::LOOK, row = ahead < n_full ? full_key(j) : row0_of(j) + lrow;
+              int key = k0 + ahead * TK + row;
+              key = key < k1 ? key : k1 - 1;
+              if (ahead >= n_ct && p.k_tree == nullptr) key = Lb0 + (ahead - n_ct) * TK + row, key = key < Lb0 + Tb ? key : Lb0 + Tb - 1;
+              int pidx = key >> p.page_shift;
+              pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;
+              __builtin_amdgcn_global_load_lds(GLOBAL_PTR(p.page_table + (int64_t)b * p.max_pages + pidx), pg_lds + ((t + C::LOOK) & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256, 4, 0, 0);
+            }
+          } else {
 #pragma unroll
-        for (int j = 0; j < NLDK; ++j) {
-          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(k_next + row_off[j] + lane_off2[j & 1]), stage + kdst_of(j), 16, 0, kLoadOnce);
-          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(v_next + row_off[j] + lane_off2[j & 1]), stage + vdst_of(j), 16, 0, kLoadOnce);
+            for (int j = 0; j < NLDK; ++j)
+              __builtin_amdgcn_global_load_lds(GLOBAL_PTR(k_next + row_off[j] + lane_off2[j & 1]), stage + kdst_of(j), 16, 0, kLoadOnce);
+            k_next += tile_bytes;
+          }
+        };
+        auto issue_v = [&](int t) __attribute__((always_inline)) {
+          lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
+#pragma unroll
+          for (int j = 0; j < NLDK; ++j) {
+            const char *src = PAGED ? vc_bytes + row_at[j] : v_next + row_off[j] + lane_off2[j & 1];
+            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), stage + vdst_of(j), 16, 0, kLoadOnce);
+          }
+          if constexpr (!PAGED) v_next += tile_bytes;
+        };
+        // K of tile t + 1 has landed everywhere, V of tile t long before; K of tile t and V of tile t - 1 have been read
+        // everywhere: their places take K of tile t + 4 (not past the last tile queued here: the loop behind this one
+        // expects both halves of PD tiles) and V of tile t + 3.  Queued behind K(t+1) and the entries that came with it are
+        // V(t+1), K(t+2), V(t+2), K(t+3), each K with entries; before the third call, where the tiles' halves were queued
+        // together, half a tile less.
+        const int first = it;
+        auto enter = [&](int t) __attribute__((always_inline)) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          if (t < first + 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * (PD - 1) - NLDK));
+          else __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * (PD - 1)));
+          __builtin_amdgcn_s_barrier();
+          issue_v(t + PD);
+          if (t + 1 < end) issue_k(t + PD + 1);
+        };
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * (PD - 1)));
+        __builtin_amdgcn_s_barrier();
+        issue_k(it + PD);
+        if (!wave_has_rows) {
+          for (; it < end; ++it) enter(it);
+        } else {
+          constexpr int V8 = 8 * PV, S2OFF = ROWB, BLK = 2 * ROWB;
+          bf16x8 kr[4];           // K operands: four of the next block's eight
+          s16x4 vl[4], vh[4];     // V^T operands: four of the eight of the block before
+          f32x16 sA, sB;          // scores of the blocks, in turn
+          bf16x8 pA[2], pB[2];    // their probabilities
+#pragma unroll
+          for (int i = 0; i < 4; ++i) vl[i] = vh[i] = s16x4{0, 0, 0, 0};
+          const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+          auto stage_at = [&](int t) __attribute__((always_inline)) { return lds0 + (uint32_t)(t % NSTAGE) * STAGE_BYTES; };
+          const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          auto half = [&](auto &&f, auto second_tag) __attribute__((always_inline)) {
+            constexpr int g0 = decltype(second_tag)::value ? 4 : 0;
+            f(std::integral_constant<int, g0>{}), f(std::integral_constant<int, g0 + 1>{});
+            f(std::integral_constant<int, g0 + 2>{}), f(std::integral_constant<int, g0 + 3>{});
+          };
+          auto pv = [&](int d, const bf16x8 &pr) __attribute__((always_inline)) {
+            oacc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(bf16x8, __builtin_shufflevector(vl[d], vh[d], 0, 1, 2, 3, 4, 5, 6, 7)), pr, oacc[0][d], 0, 0, 0);
+          };
+          {  // the first block's scores
+            const uint32_t ka = stage_at(it) + kbase_off;
+            lds_read_k<0>(kr[0], ka), lds_read_k<32>(kr[1], ka), lds_read_k<64>(kr[2], ka), lds_read_k<96>(kr[3], ka);
+            auto group = [&](auto g_tag) __attribute__((always_inline)) {
+              constexpr int g = decltype(g_tag)::value;
+              lds_wait_n<3>(kr[g % 4], vl[0], vh[0]);
+              sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[g % 4], qreg[0][g], g == 0 ? zero16 : sA, 0, 0, 0);
+              lds_read_k<(g < 4 ? (g + 4) * 32 : BLK + (g - 4) * 32)>(kr[g % 4], ka);
+              __builtin_amdgcn_sched_barrier(0);
+            };
+            half(group, std::false_type{}), half(group, std::true_type{});
+          }
+          // A step.  Block kb of a tile; ka1, ka2: where K of the next block and of the one after it are, va1, va2: V of the block
+          // before and of this one.
+          auto block = [&](f32x16 &cur, f32x16 &nxt, bf16x8 (&pc)[2], bf16x8 (&pp)[2], uint32_t ka1, uint32_t ka2, uint32_t va1, uint32_t va2,
+                           auto kb_tag, auto pv_tag, auto middle) __attribute__((always_inline)) {
+            constexpr int kb = decltype(kb_tag)::value, HERE = kb * BLK, THERE = (1 - kb) * BLK;
+            constexpr bool HASPV = decltype(pv_tag)::value;
+            float ls = 0.f;
+            uint32_t pw[8];
+            auto group = [&](auto g_tag) __attribute__((always_inline)) {
+              constexpr int g = decltype(g_tag)::value, d = g % 4;
+              lds_wait_n<HASPV || g >= 4 ? 9 : 3>(kr[d], vl[d], vh[d]);  // (three reads a group; of K alone before the first)
+              nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[d], qreg[0][g], g == 0 ? zero16 : nxt, 0, 0, 0);
+              const float e0 = fast_exp2(fmaf(cur[2 * g], p.scale_log2, -m_use[0]));
+              const float e1 = fast_exp2(fmaf(cur[2 * g + 1], p.scale_log2, -m_use[0]));
+              if constexpr (g < 4) lds_read_k<THERE + (g + 4) * 32>(kr[d], ka1);
+              else lds_read_k<HERE + (g - 4) * 32>(kr[d], ka2);
+              __builtin_amdgcn_sched_barrier(0);
+              if constexpr (HASPV) pv(d, pp[g / 4]);
+              ls += e0;
+              ls += e1;
+              const bf16x2 pair = {(__bf16)e0, (__bf16)e1};
+              uint32_t w = __builtin_bit_cast(uint32_t, pair);
+              asm volatile("" : "+v"(w), "+v"(ls));  // (computed here, not where it is used)
+              pw[g] = w;
+              if constexpr (g >= 4) {
+                lds_read_v<HERE + d * 64>(vl[d], va2);
+                lds_read_v<HERE + V8 + d * 64>(vh[d], va2);
+              } else if constexpr (HASPV) {
+                lds_read_v<THERE + S2OFF + d * 64>(vl[d], va1);
+                lds_read_v<THERE + S2OFF + V8 + d * 64>(vh[d], va1);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            };
+            half(group, std::false_type{});
+            middle();
+            half(group, std::true_type{});
+#pragma unroll
+            for (int s = 0; s < 2; ++s) pc[s] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * s], pw[4 * s + 1], pw[4 * s + 2], pw[4 * s + 3]});
+            // (the bound of compute_block's settled form)
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(ls <= fminf(kLoThreshold * (l_run[0] + ls), cap[0]))) != 0, 0)) {
+              float mx = -INFINITY;
+#pragma unroll
+              for (int i = 0; i < 16; ++i) mx = fmaxf(mx, cur[i]);
+              mx = half_max(mx) * p.scale_log2;
+              if (__builtin_amdgcn_ballot_w64(mx > m_run[0] + kLazy) != 0) {
+                const float m_new = fmaxf(m_run[0], mx);
+                const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[0] - m_new);
+                m_run[0] = m_new;
+                l_run[0] *= alpha;
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+#pragma unroll
+                  for (int i = 0; i < 16; ++i) oacc[0][d][i] *= alpha;
+                use_reference(0);
+                set_cap(0);
+                ls = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                  const float e = fast_exp2(fmaf(cur[i], p.scale_log2, -m_use[0]));
+                  ls += e;
+                  pc[i / 8][i % 8] = (__bf16)e;
+                }
+              }
+              if (__builtin_amdgcn_ballot_w64(fast_exp2(mx - m_use[0]) > kLoThreshold * half_sum(l_run[0] + ls)) != 0) {
+                // the low-order pass of this block, at once: its V^T operands are read for it alone
+#pragma unroll
+                for (int s2 = 0; s2 < 2; ++s2) {
+                  bf16x8 plo;
+#pragma unroll
+                  for (int i = 0; i < 8; ++i)
+                    plo[i] = (__bf16)(fast_exp2(fmaf(cur[8 * s2 + i], p.scale_log2, -m_use[0])) - (float)pc[s2][i]);
+#pragma unroll
+                  for (int d = 0; d < ND; ++d) {
+                    s16x4 a, c;
+                    const uint32_t va = va2 + s2 * S2OFF + d * 64;
+                    lds_read_v<HERE>(a, va);
+                    lds_read_v<HERE + V8>(c, va);
+                    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(c));
+                    oacc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7)), plo, oacc[0][d], 0, 0, 0);
+                  }
+                }
+              }
+            }
+            l_run[0] += ls;
+          };
+          set_cap(0);
+          // (the barrier of a tile stands in the middle of its first block: K of the next tile is wanted from there on, V of the
+          // tile before up to there)
+          auto tile = [&](auto pv_tag) __attribute__((always_inline)) {
+            const uint32_t s0 = stage_at(it - 1 + NSTAGE), s1 = stage_at(it), s2 = stage_at(it + 1);
+            block(sA, sB, pA, pB, s1 + kbase_off, s2 + kbase_off, s0 + vbase_off, s1 + vbase_off, std::integral_constant<int, 0>{}, pv_tag,
+                  [&]() __attribute__((always_inline)) { enter(it); });
+            block(sB, sA, pB, pA, s2 + kbase_off, s2 + kbase_off, s1 + vbase_off, s1 + vbase_off, std::integral_constant<int, 1>{}, std::true_type{},
+                  [&]() __attribute__((always_inline)) {});
+          };
+          tile(std::false_type{});
+          for (++it; it < end; ++it) tile(std::true_type{});
+          // the last block's output
+          const uint32_t va = stage_at(it - 1) + vbase_off;
+          auto last = [&](auto g_tag) __attribute__((always_inline)) {
+            constexpr int g = decltype(g_tag)::value, d = g % 4;
+            lds_wait_n<0>(kr[d], vl[d], vh[d]);
+            pv(d, pB[g / 4]);
+            if constexpr (g < 4) {
+              lds_read_v<BLK + S2OFF + d * 64>(vl[d], va);
+              lds_read_v<BLK + S2OFF + V8 + d * 64>(vh[d], va);
+            }
+          };
+          half(last, std::false_type{}), half(last, std::true_type{});
         }
-        k_next += tile_bytes;
-        v_next += tile_bytes;
       }
-    };
-    auto step_steady = [&](int t) __attribute__((always_inline)) {
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(PAGED && PD == 1 ? C::NPG : C::TILE_OPS * (PD - 1)));
-      __builtin_amdgcn_s_barrier();
-      issue_steady(t + PD);
-      if (!wave_has_rows) return;
-      const lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
-      compute_block(stage, std::integral_constant<int, 0>{}, 0, 0, false, std::false_type{}, std::true_type{});
-      if constexpr (KBW > 1) compute_block(stage, std::integral_constant<int, 1>{}, 0, 0, false, std::false_type{}, std::true_type{});
-    };
-    static_assert(KBW <= 2, "");
+    } else {
+      auto issue_steady = [&](int t) __attribute__((always_inline)) {
+        lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
+        if constexpr (PAGED) {
 #pragma unroll
-    for (int r = 0; r < RB; ++r) set_cap(r);
-    if (!PAGED || small_pages)
-      for (; it + PD < n_full; ++it) step_steady(it);
+          for (int j = 0; j < NLDK; ++j) {
+            const uint32_t page = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
+            const uint32_t slot = (uint32_t)(k0 + t * TK + full_key(j)) & slot_mask;
+            const uint64_t off = (uint64_t)page * page_bytes + (slot * tok_bytes + head_bytes + (uint32_t)chunk_of(j) * 16u);
+            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + off), stage + kdst_of(j), 16, 0, kLoadOnce);
+            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vc_bytes + off), stage + vdst_of(j), 16, 0, kLoadOnce);
+          }
+          // (the entries of tile t + LOOK; past the last key they re-read its entry)
+#pragma unroll
+          for (int j = 0; j < NLDK; ++j) {
+            const int ahead = t + C::LOOK, row = ahead < n_full ? full_key(j) : row0_of(j) + lrow;
+            int key = k0 + ahead * TK + row;
+            key = key < k1 ? key : k1 - 1;
+            if (ahead >= n_ct && p.k_tree == nullptr) key = Lb0 + (ahead - n_ct) * TK + row, key = key < Lb0 + Tb ? key : Lb0 + Tb - 1;
+            int pidx = key >> p.page_shift;
+            pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;
+            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(p.page_table + (int64_t)b * p.max_pages + pidx), pg_lds + ((t + C::LOOK) & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256, 4, 0, 0);
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < NLDK; ++j) {
+            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(k_next + row_off[j] + lane_off2[j & 1]), stage + kdst_of(j), 16, 0, kLoadOnce);
+            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(v_next + row_off[j] + lane_off2[j & 1]), stage + vdst_of(j), 16, 0, kLoadOnce);
+          }
+          k_next += tile_bytes;
+          v_next += tile_bytes;
+        }
+      };
+      auto step_steady = [&](int t) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(PAGED && PD == 1 ? C::NPG : C::TILE_OPS * (PD - 1)));
+        __builtin_amdgcn_s_barrier();
+        issue_steady(t + PD);
+        if (!wave_has_rows) return;
+        const lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
+        compute_block(stage, std::integral_constant<int, 0>{}, 0, 0, false, std::false_type{}, std::true_type{});
+        if constexpr (KBW > 1) compute_block(stage, std::integral_constant<int, 1>{}, 0, 0, false, std::false_type{}, std::true_type{});
+      };
+      static_assert(KBW <= 2, "");
+#pragma unroll
+      for (int r = 0; r < RB; ++r) set_cap(r);
+      if (!PAGED || small_pages)
+        for (; it + PD < n_full; ++it) step_steady(it);
+    }
   }
   for (; it < n_full; ++it) step(it, std::false_type{}, std::false_type{});
   for (; it < n_ct; ++it) step(it, std::true_type{}, std::false_type{});   // the partial cache tile

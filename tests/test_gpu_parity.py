@@ -497,6 +497,34 @@ def test_splits_at_the_start_of_the_steady_loop_match_oracle(gpu, D, tiles, page
             assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
 
 
+@pytest.mark.parametrize("tiles", [16, 17, 19])
+@pytest.mark.parametrize("page_size", [0, 16])
+def test_spikes_in_every_part_of_the_pipelined_loop_match_oracle(gpu, tiles, page_size):
+    """256-row shape, D = 128, the smallest numbers of tiles that the pipelined loop takes (13, 14 and 16 of them in the loop):
+    one key at a time is scaled so that its block moves the reference or needs the low-order pass, in the first and second block
+    of the first tile, of one in the middle and of the last ones, and right behind the loop; waves with and without rows."""
+    import torch
+    L = 64 * tiles + 7
+    base = wl.random_workload(990 + tiles + page_size, 1, 8, 1, 128, [L], [25], page_size=page_size)
+    mask = None
+    for block in (0, 1, 2, 3, tiles, 2 * (tiles - 3) - 2, 2 * (tiles - 3) - 1, 2 * (tiles - 3), 2 * tiles - 1):
+        for factor in (4.0, 12.0):
+            key = 32 * block + (5 * block + 3) % 32
+            at = (int(base.cu_L[0]) + key,) if page_size == 0 else (int(base.page_table[0, key // page_size]), key % page_size)
+            kept = base.k_cache[at].copy()
+            x = (kept.astype(np.uint32) << 16).view(np.float32) * np.float32(factor)  # (a power of two, or rounded to bf16 below)
+            base.k_cache[at] = ((x.view(np.uint32) + 0x8000) >> 16).astype(np.uint16)
+            ro, rl = orc.tree_verify_attn(base)
+            dw = gpu.to_device(base)
+            mask = gpu.build_mask(dw)
+            say(f"[case] spike tiles={tiles} page_size={page_size} block={block} factor={factor}")
+            o, l = gpu.attention(dw, mask, num_splits=1, plan_shape=5)
+            torch.cuda.synchronize()
+            assert np.abs(o.cpu().numpy().astype(np.float64) - ro).max() <= TOL_O
+            assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
+            base.k_cache[at] = kept
+
+
 @pytest.mark.parametrize("shape", [3, 4, 5])
 def test_filled_splits_first_is_a_permutation(gpu, shape):
     """Split launches of more workgroups than the chip holds put the splits that the host's lengths fill first: true
