@@ -155,7 +155,8 @@ struct AttnParams {
   const int32_t *parent;  // used when mask is null: ancestor masks are derived in the kernel
   float *out, *lse;            // final results
   float *part_out, *part_lse;  // [S, sum_Q, Hq, D], [S, sum_Q, Hq] when S > 1
-  int B, Hq, Hkv, G, g_shift, sum_Q, W;  // sum_Q: query rows of the whole batch (= sum_T without cu_Q)
+  int B, Hq, Hkv, G, sum_Q, W;  // sum_Q: query rows of the whole batch (= sum_T without cu_Q)
+  uint32_t g_magic, g_bits;     // row / G, rows below 2^30: node_of
   int chunk_keys, n_chunks, n_row_blocks, max_L;
   int pair_slots;          // > 0: sequences are matched to workgroup slots by length: slot j takes the sequence in
   uint32_t slot_seq[16];   // byte j of this array
@@ -166,6 +167,10 @@ struct AttnParams {
   float scale_log2;  // scale * log2(e) (times the K scale of an fp8 cache)
   float v_scale;     // 1, or the V scale of an fp8 cache
 };
+
+// The node of a query row (row = node * G + head in the group): row / G, exact for rows below 2^30 (g_magic is
+// 2^(31 + g_bits) / G rounded up, 2^g_bits >= G).
+__device__ __forceinline__ int node_of(const AttnParams &p, int row) { return (int)(__umulhi((uint32_t)row * 2u, p.g_magic) >> p.g_bits); }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -374,7 +379,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   // in one batch at the top rather than one by one, each with its own wait, at their first uses.
   AttnParams p = p_in;
   asm("" : "+s"(p.cu_T), "+s"(p.L), "+s"(p.cu_L), "+s"(p.q), "+s"(p.k_cache), "+s"(p.v_cache), "+s"(p.mask),
-      "+s"(p.stride_tok), "+s"(p.stride_head), "+s"(p.G), "+s"(p.g_shift), "+s"(p.Hq), "+s"(p.chunk_keys),
+      "+s"(p.stride_tok), "+s"(p.stride_head), "+s"(p.G), "+s"(p.g_magic), "+s"(p.g_bits), "+s"(p.Hq), "+s"(p.chunk_keys),
       "+s"(p.n_chunks), "+s"(p.max_L));
   constexpr int TK = C::TK, BM = C::BM, DC = C::DC, ROWB = C::ROWB, RPI = C::RPI, NLDK = C::NLDK, NLD = C::NLD;
   constexpr int KBW = C::KBW, NSTAGE = C::NSTAGE, PD = C::PD, STAGE_BYTES = C::STAGE_BYTES;
@@ -451,7 +456,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   if (chunk >= nc) {
     // this sequence has fewer chunks than the launch provides: mark the slot empty for the merge
     for (int row = rblk * BM + (int)threadIdx.x; row < R && row < (rblk + 1) * BM; row += blockDim.x) {
-      const int t = p.g_shift >= 0 ? (row >> p.g_shift) : row / p.G, g = row - t * p.G;
+      const int t = node_of(p, row), g = row - t * p.G;
       p.part_lse[(size_t)chunk * p.sum_Q * p.Hq + (size_t)(tq0 + t) * p.Hq + kvh * p.G + g] = -INFINITY;
     }
     return;
@@ -468,6 +473,9 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WM, wk = wave / WM;
   const int l32 = lane & 31, hh = lane >> 5;
+  // Two key groups: at the end each wave keeps one half of the head dimension and hands the other to its partner.  The kept
+  // half's 32-wide blocks come first in the accumulators, whichever it is, so that both run the same instructions.
+  const int kept0 = C::PAIR ? wk * (D / 2) : 0, other0 = C::PAIR ? (1 - wk) * (D / 2) : 0;  // first element of each
 
   const bool wave_has_rows = rblk * BM + wm * RB * 32 < R;  // wave-uniform
   // ---- Q operands (B operand of S^T = K Q^T: lane = query row, 8 consecutive d per k-step) ----
@@ -481,7 +489,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     rvalid[r] = row < R;
     // rows past the end compute on a copy of the last row (finite data) and are never stored
     const int rowc = rvalid[r] ? row : R - 1;
-    const int t = p.g_shift >= 0 ? (rowc >> p.g_shift) : rowc / p.G;
+    const int t = node_of(p, rowc);
     const int g = rowc - t * p.G;
     orow[r] = (int64_t)(tq0 + t) * p.Hq + kvh * p.G + g;
     const __bf16 *qp = p.q + orow[r] * D + 8 * hh;
@@ -665,7 +673,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     const int row = L16 >> 1, vn = wk * 4 + (row >> 2), vr = 4 * hh + (row & 3);
 #pragma unroll
     for (int d = 0; d < ND; ++d)
-      voff8[d] = piece_off(vn) + NLDK * 1024 + ((vr * 8 + ((2 * d + grp1) ^ vr ^ (vn & 1))) << 4) + 8 * (L16 & 1);
+      voff8[d] = piece_off(vn) + NLDK * 1024 + ((vr * 8 + ((2 * (d ^ (wk * (ND / 2))) + grp1) ^ vr ^ (vn & 1))) << 4) + 8 * (L16 & 1);
   }
   constexpr int V8_SECOND = (NLDK >= 4 ? 2 : 2 * NLDK) * 1024;  // keys 16 .. 31 of the wave: two pieces further on
 
@@ -679,7 +687,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     constexpr int V8 = (NBLK == 16) ? 8 * PV : ROWB;   // V rows 8 keys further on
     const int kofs = (wk * KBW + kb) * 32;
     const lds_byte *kp = stage + kbase_off + KBOFF;
-    const uint32_t va = (uint32_t)(uintptr_t)(stage + vbase_off);
+    const uint32_t va = (uint32_t)(uintptr_t)(stage + vbase_off), va_kept = va + (uint32_t)kept0 * 2u, va_other = va + (uint32_t)other0 * 2u;
     f32x16 sacc[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r)
@@ -710,6 +718,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     }
     }
     // V^T operands of the first 16 keys: in flight during the softmax arithmetic
+    auto v_at = [&](int d) __attribute__((always_inline)) { return !C::PAIR ? va + d * 64 : d < ND / 2 ? va_kept + d * 64 : va_other + (d - ND / 2) * 64; };
     s16x4 vlo[2][ND], vhi[2][ND];
     u32x2 vraw[2][ND];  // (8-bit K/V read in place: one byte transpose read per operand)
 #pragma unroll
@@ -717,8 +726,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       if constexpr (C::KV8_REG) {
         vraw[0][d] = lds_read_tr8(sb8 + voff8[d]);
       } else {
-        vlo[0][d] = lds_read_tr<KBOFF + 0>(va + d * 64);
-        vhi[0][d] = lds_read_tr<KBOFF + V8>(va + d * 64);
+        vlo[0][d] = lds_read_tr<KBOFF + 0>(v_at(d));
+        vhi[0][d] = lds_read_tr<KBOFF + V8>(v_at(d));
       }
     }
     // the V^T operand of the PV product over keys 16 s2 .. 16 s2 + 15, d block d
@@ -850,8 +859,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       if constexpr (C::KV8_REG) {
         vraw[1][d] = lds_read_tr8(sb8 + voff8[d] + V8_SECOND);
       } else {
-        vlo[1][d] = lds_read_tr<KBOFF + S2OFF>(va + d * 64);
-        vhi[1][d] = lds_read_tr<KBOFF + S2OFF + V8>(va + d * 64);
+        vlo[1][d] = lds_read_tr<KBOFF + S2OFF>(v_at(d));
+        vhi[1][d] = lds_read_tr<KBOFF + S2OFF + V8>(v_at(d));
       }
     }
 #pragma unroll
@@ -1020,7 +1029,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     for (int r = 0; r < RB; ++r) {
       const int row = rblk * BM + (wm * RB + r) * 32 + l32;
       const int rowc = row < R ? row : R - 1;
-      int node = node_off + (p.g_shift >= 0 ? (rowc >> p.g_shift) : rowc / p.G);
+      int node = node_off + node_of(p, rowc);
       uint64_t b0 = 0, b1 = 0;
       for (int step = 0; step < Tb && node >= 0; ++step) {
         if (node < 64) b0 |= 1ull << node;
@@ -1327,67 +1336,64 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   __builtin_amdgcn_s_barrier();  // all waves are done reading the ring before it is reused below
   TL_STAMP(4);  // all tiles done
 
-  // ---- combine the two lane halves' partial sums ----
-  float l_tot[RB];
+  // ---- combine the two lane halves' partial sums, and the two key groups' references and sums ----
+  // (factor: what a row's O is multiplied by -- to the groups' common reference, and 1 / sum)
+  constexpr bool PAIR = C::PAIR;
+  float l_tot[RB], factor[RB];
+  float *const sm = reinterpret_cast<float *>(smem);  // [WK][WM][RB][32] references, then as many sums
+  float *const sl = sm + WK * WM * RB * 32;
 #pragma unroll
-  for (int r = 0; r < RB; ++r) l_tot[r] = half_sum(l_run[r]);
+  for (int r = 0; r < RB; ++r) {
+    l_tot[r] = half_sum(l_run[r]);
+    factor[r] = 1.f;
+    if (PAIR && hh == 0) sm[((wk * WM + wm) * RB + r) * 32 + l32] = m_run[r], sl[((wk * WM + wm) * RB + r) * 32 + l32] = l_tot[r];
+  }
+  if constexpr (PAIR) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const int other = (((1 - wk) * WM + wm) * RB + r) * 32 + l32;
+      const float mo = sm[other], lo = sl[other];
+      const float mf = fmaxf(m_run[r], mo), ref = (mf == -INFINITY) ? 0.f : mf;
+      factor[r] = fast_exp2(m_run[r] - ref);
+      l_tot[r] = l_tot[r] * factor[r] + lo * fast_exp2(mo - ref);
+      m_run[r] = mf;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < RB; ++r) factor[r] *= l_tot[r] > 0.f ? p.v_scale / l_tot[r] : 0.f;
 
   // ---- merge the WK key groups through LDS ----
   // Two key groups: each wave keeps one half of the head dimension and hands the other half to
   // its partner, so both take part in the reduction and in writing the result.
-  constexpr bool PAIR = C::PAIR;
   if constexpr (PAIR) {
     constexpr int H = ND / 2;
-    float *sm = reinterpret_cast<float *>(smem);            // m then l: [2][WK][WM][RB][32]
-    float *sl = sm + WK * WM * RB * 32;
     float *xo = sl + WK * WM * RB * 32;                      // [WM][WK][RB][H][4][64] x 16 bytes
-    if (hh == 0) {
+    f32x4 *const dst = reinterpret_cast<f32x4 *>(xo) + (size_t)((wm * WK + (1 - wk)) * RB * H * 4) * 64 + lane;
 #pragma unroll
-      for (int r = 0; r < RB; ++r) sm[((wk * WM + wm) * RB + r) * 32 + l32] = m_run[r];
-    }
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int d = 0; d < H; ++d)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = oacc[r][H + d][i4 * 4 + e] * factor[r];
+          dst[((r * H + d) * 4 + i4) * 64] = v;
+        }
     __syncthreads();
-    float a[RB];
+    const f32x4 *const src = reinterpret_cast<const f32x4 *>(xo) + (size_t)((wm * WK + wk) * RB * H * 4) * 64 + lane;
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-      const float mo = sm[(((1 - wk) * WM + wm) * RB + r) * 32 + l32];
-      const float mf = fmaxf(m_run[r], mo);
-      a[r] = fast_exp2(m_run[r] - ((mf == -INFINITY) ? 0.f : mf));
-      m_run[r] = mf;
-      l_tot[r] *= a[r];
-      if (hh == 0) sl[((wk * WM + wm) * RB + r) * 32 + l32] = l_tot[r];
+#pragma unroll
+      for (int d = 0; d < H; ++d)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 v = src[((r * H + d) * 4 + i4) * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) oacc[r][d][i4 * 4 + e] = fmaf(oacc[r][d][i4 * 4 + e], factor[r], v[e]);
+        }
     }
-    auto swap_halves = [&](auto me_tag) __attribute__((always_inline)) {
-      constexpr int me = decltype(me_tag)::value;  // keeps d blocks [me*H, me*H + H), hands over the others
-      f32x4 *dst = reinterpret_cast<f32x4 *>(xo) + (size_t)((wm * WK + (1 - me)) * RB * H * 4) * 64;
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int d = 0; d < H; ++d)
-#pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = oacc[r][(1 - me) * H + d][i4 * 4 + e] * a[r];
-            dst[((r * H + d) * 4 + i4) * 64 + lane] = v;
-          }
-      __syncthreads();
-      const f32x4 *src = reinterpret_cast<const f32x4 *>(xo) + (size_t)((wm * WK + me) * RB * H * 4) * 64;
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-#pragma unroll
-        for (int d = 0; d < H; ++d)
-#pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
-            const f32x4 v = src[((r * H + d) * 4 + i4) * 64 + lane];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              oacc[r][me * H + d][i4 * 4 + e] = fmaf(oacc[r][me * H + d][i4 * 4 + e], a[r], v[e]);
-          }
-        l_tot[r] += sl[(((1 - me) * WM + wm) * RB + r) * 32 + l32];
-      }
-    };
-    if (wk == 0) swap_halves(std::integral_constant<int, 0>{});
-    else swap_halves(std::integral_constant<int, 1>{});
   }
 
   // ---- write (normalised) result: final when there is one split, else the partial ----
@@ -1402,48 +1408,54 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   constexpr int LPR = NDW * 8;      // lanes that cover one row piece with 16 bytes each
   constexpr int RPP = 64 / LPR;     // rows per wave-wide store
   float *tbuf = reinterpret_cast<float *>(smem + C::PATCH_OFF) + (PAIR ? wave : wm) * (32 * TP);
-  auto write_out = [&](auto d0_tag, auto once_tag) __attribute__((always_inline)) {
-    constexpr int d0 = decltype(d0_tag)::value;  // first d block of this wave's share
+  // One basic block per 32 rows: rows past the last are stored as copies of the last one (to its own address, the same values),
+  // so that no store sits behind a branch of its own and the reads of all pieces are in flight together.  What remains is the
+  // LDS traffic of the two exchanges.  (One sequence of 2048 keys in 7 splits, from the last tile to the last store: 1.76 us
+  // with a branch, a division of the row's index and a read waited for per store, two copies of the code by key group, and
+  // the sums exchanged behind the outputs; 1.30 now.  Both groups' whole rows exchanged at once instead: 1.28 there, but 0.1
+  // more where two waves make a workgroup.)
+  auto write_out = [&](auto once_tag) __attribute__((always_inline)) {
     // partial rows (read next by the merge kernel, then dead) are stored with the non-temporal hint; final rows,
     // which the caller's next kernel reads, are left to the caches.  Two copies of the loop: one store whose hint
     // is chosen at run time would lose it.
     constexpr bool ONCE = decltype(once_tag)::value;
+    float *const first = obase + ((int64_t)tq0 * p.Hq + kvh * p.G) * D + kept0 + (lane % LPR) * 4;
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-      const float inv = l_tot[r] > 0.f ? p.v_scale / l_tot[r] : 0.f;
 #pragma unroll
       for (int d = 0; d < NDW; ++d)
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
           f32x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = oacc[r][d0 + d][i4 * 4 + e] * inv;
+          for (int e = 0; e < 4; ++e) v[e] = PAIR ? oacc[r][d][i4 * 4 + e] : oacc[r][d][i4 * 4 + e] * factor[r];
           *reinterpret_cast<f32x4 *>(tbuf + l32 * TP + 32 * d + 8 * i4 + 4 * hh) = v;
         }
       const int row0 = rblk * BM + (wm * RB + r) * 32;
+      if (row0 >= R) break;  // (wave-uniform)
+      const int last = R - 1 - row0;
+      f32x4 v[32 / RPP];
 #pragma unroll
       for (int i = 0; i < 32 / RPP; ++i) {
-        const int rl = i * RPP + lane / LPR;
-        const int row = row0 + rl;
-        const int t = p.g_shift >= 0 ? (row >> p.g_shift) : row / p.G;
-        const int64_t og = (int64_t)(tq0 + t) * p.Hq + kvh * p.G + (row - t * p.G);
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(tbuf + rl * TP + (lane % LPR) * 4);
-        f32x4 *dst = reinterpret_cast<f32x4 *>(obase + og * D + 32 * d0 + (lane % LPR) * 4);
-        if (row < R) {
-          if constexpr (ONCE) __builtin_nontemporal_store(v, dst);
-          else *dst = v;
-        }
+        int rl = i * RPP + lane / LPR;
+        rl = rl < last ? rl : last;
+        v[i] = *reinterpret_cast<const f32x4 *>(tbuf + rl * TP + (lane % LPR) * 4);
+      }
+#pragma unroll
+      for (int i = 0; i < 32 / RPP; ++i) {
+        int rl = i * RPP + lane / LPR;
+        rl = rl < last ? rl : last;
+        const int row = row0 + rl, t = node_of(p, row);
+        f32x4 *const dst = reinterpret_cast<f32x4 *>(first + (int64_t)(t * p.Hq + (row - t * p.G)) * D);
+        if constexpr (ONCE) __builtin_nontemporal_store(v[i], dst);
+        else *dst = v[i];
       }
       if (rvalid[r] && hh == 0 && wk == 0)
         lbase[orow[r]] = l_tot[r] > 0.f ? (m_run[r] + __builtin_amdgcn_logf(l_tot[r])) * kLn2 : -INFINITY;
     }
   };
-  auto write_rows = [&](auto d0_tag) __attribute__((always_inline)) {
-    if (final_out) write_out(d0_tag, std::false_type{});
-    else write_out(d0_tag, std::true_type{});
-  };
-  if (PAIR && wk == 1) write_rows(std::integral_constant<int, PAIR ? ND / 2 : 0>{});
-  else write_rows(std::integral_constant<int, 0>{});
+  if (final_out) write_out(std::false_type{});
+  else write_out(std::true_type{});
   TL_STAMP(5);  // key groups merged, result stores issued
   TL_STORE(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), 0, 6);
 }
@@ -2083,9 +2095,9 @@ static int run_attention(const tva_args *a, void *workspace, size_t workspace_by
   p.Hq = a->Hq;
   p.Hkv = a->Hkv;
   p.G = a->Hq / a->Hkv;
-  p.g_shift = -1;
-  for (int sft = 0; sft < 31; ++sft)
-    if ((1 << sft) == p.G) p.g_shift = sft;
+  p.g_bits = 0;
+  while (p.g_bits < 31 && (1ll << p.g_bits) < p.G) ++p.g_bits;
+  p.g_magic = (uint32_t)(((1ull << (31 + p.g_bits)) + (uint32_t)p.G - 1) / (uint32_t)p.G);
   p.sum_Q = (int)query_rows(a);
   p.cu_Q = a->cu_Q;
   p.W = a->mask_words;

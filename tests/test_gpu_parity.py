@@ -497,6 +497,29 @@ def test_splits_at_the_start_of_the_steady_loop_match_oracle(gpu, D, tiles, page
             assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(3, 3, 64), (6, 2, 128), (5, 1, 128), (48, 1, 64), (100, 2, 128)])
+def test_rows_are_stored_in_place_and_nowhere_else(gpu, Hq, Hkv, D):
+    """Group sizes that divide nothing, trees whose rows end inside a store's rows and inside a block of 32: every shape, with and
+    without splits, into the middle of a larger buffer whose other rows keep what they hold."""
+    import torch
+    from paper_2510_26577_amd import binding
+    w = wl.random_workload(1300 + Hq, 3, Hq, Hkv, D, [150, 70, 333], [11, 1, 7])
+    ro, rl = orc.tree_verify_attn(w)
+    dw = gpu.to_device(w)
+    for shape in (1, 2, 3, 4, 5):
+        for splits in (1, 3):
+            say(f"[case] stores Hq={Hq} Hkv={Hkv} D={D} shape={shape} splits={splits}")
+            big, big_lse = torch.full((w.sum_T + 4, Hq, D), 7.5, device="cuda"), torch.full((w.sum_T + 4, Hq), 7.5, device="cuda")
+            binding.tree_verify_attn(dw.q, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, None, dw.cu_T, dw.L, max_T=w.max_T, max_L=w.max_L,
+                                     scale=w.scale, cu_L=dw.cu_L, parent=dw.parent, plan_shape=shape, num_splits=splits,
+                                     out=big[2:-2], lse=big_lse[2:-2])
+            torch.cuda.synchronize()
+            assert np.abs(big[2:-2].cpu().numpy().astype(np.float64) - ro).max() <= TOL_O
+            assert np.abs(big_lse[2:-2].cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
+            for rows in (big[:2], big[-2:], big_lse[:2], big_lse[-2:]):
+                assert bool((rows == 7.5).all())
+
+
 @pytest.mark.parametrize("tiles", [16, 17, 19])
 @pytest.mark.parametrize("page_size", [0, 16])
 def test_spikes_in_every_part_of_the_pipelined_loop_match_oracle(gpu, tiles, page_size):
