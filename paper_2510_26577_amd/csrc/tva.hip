@@ -236,8 +236,9 @@ struct AttnCfg {
   static constexpr int WG_PER_CU = KV8 ? (KV8_REG ? 2 : 1) : (NSTAGE == 2 && TK == 64) ? 2 : 1;
   // wavefronts per SIMD that the registers have to leave room for.  (The rings of the eight-wave shapes with D = 64 let two
   // workgroups share a CU, and so do up to 128 registers per lane: with 131, 50 sequences of 200 keys took 21 us instead
-  // of 14.5, paged, 256-row shape.  The dense 256-row shape needs four more than that and has one workgroup per CU.)
-  static constexpr int WAVES_PER_SIMD = D == 64 && NW == 8 && (PAGED || WK == 2) ? 4 : WG_PER_CU;
+  // of 14.5, paged, 256-row shape.  The dense 256-row shape needs four more than that and has one workgroup per CU.  Of the 64-row shape's short ring four
+  // fit: with 131 registers 60 paged sequences of 300 keys, 30 nodes, took 23.7 us, with 128 22.2.)
+  static constexpr int WAVES_PER_SIMD = D == 64 && ((NW == 8 && (PAGED || WK == 2)) || (NW == 4 && NST == 2)) ? 4 : WG_PER_CU;
   // after the key loop the ring is reused: exchange area of the key-group merge, then (behind it,
   // when the groups are paired; else on top of it, after a barrier) the output transpose patches
   static constexpr bool PAIR = (WK == 2);
@@ -250,13 +251,16 @@ struct AttnCfg {
   static constexpr int LAND_OFF = NSTAGE * STAGE_BYTES;
   static constexpr int RING_BYTES = NSTAGE * STAGE_BYTES + NL * LAND_SLOT;
   // paged cache: table entries of the next LOOK tiles, fetched by the same LDS-writing loads as the
-  // tiles themselves: [slot][wave][load instruction of a tile][lane], behind the ring.  Entries are needed when their
+  // tiles themselves: [slot][wave][key of the tile], behind the ring.  Entries are needed when their
   // tile is queued, PD tiles ahead; requested LOOK >= PD tiles ahead they are older than every tile still in flight, so
   // that waiting for them drains none.
   static constexpr int LOOK = PD >= 3 ? 3 : 2, PG_SLOTS = LOOK >= 3 ? 4 : 2;
-  static constexpr int NPG = PAGED ? NLDK : 0;   // table-entry loads per wave and tile
+  static constexpr int NPG = PAGED ? 1 : 0;      // table-entry loads per wave and tile: one entry per lane and key
   static constexpr int TILE_OPS = NLD + NPG;     // this wave's memory operations per tile
-  static constexpr int PG_SLOT = NW * NLDK * 256;
+  static constexpr int PG_SLOT = NW * 256;
+  // (the paged 256-row shape with D = 64 has no register for the short form of the addresses outside its steady loop)
+  static constexpr bool SMALL_PAGES = PAGED && !(D == 64 && STEADY);
+  static constexpr bool PG_BY_KEY = NLDK > 1;
   static constexpr int PG_BYTES = PAGED ? PG_SLOTS * PG_SLOT : 0;
   // parent indices of the sequence's tree (used when no ancestor masks are passed), behind those
   static constexpr int PARENT_OFF = RING_BYTES + PG_BYTES;
@@ -267,6 +271,7 @@ struct AttnCfg {
   static constexpr int load_row0(int n) { return KV8 ? n * RPI8 : n / IPB + NBLK * ((n % IPB) * RPI); }
   static_assert(SMEM * WG_PER_CU <= 160 * 1024, "LDS of the workgroups that share a CU");
   static_assert(PD <= 3 && TILE_OPS * (PD > 1 ? PD - 1 : 1) < 64 && NPG * LOOK + TILE_OPS < 64, "the wait counter holds 6 bits");
+  static_assert(!PAGED || TK == 64, "a tile's table entries are one load of a wave");
   static_assert(TK % ((KV8 ? RPI8 : RPI) * NW) == 0, "tile must divide evenly over the waves");
   static_assert(!KV8 || (D == 128 && NLDK >= 1), "8-bit K/V: head dimension 128");
   static_assert(BLKB % 1024 == 0, "a block is a whole number of wave-wide loads");
@@ -536,6 +541,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   // D = 64 1 % slower, paged within 0.5 %; the 128-row shape within 1 % either way, shapes of fewer rows up to 2 % slower.)
   constexpr int LPI = KV8 ? C::RPI8 : RPI;
   auto full_key = [&](int j) __attribute__((always_inline)) { return (wave * NLDK + j) * LPI + lsub; };
+  auto row_of = [&](int t, int j) __attribute__((always_inline)) { return C::STEADY && t < n_full ? full_key(j) : row0_of(j) + lrow; };  // what the lane loads of tile t
 #define kdst_of(j) (KV8 ? (wave * 2 * NLDK + (j)) * 1024 : ((wave * NLDK + (j)) / IPB) * PK + ((wave * NLDK + (j)) % IPB) * 1024)
 #define vdst_of(j) (KV8 ? (wave * 2 * NLDK + NLDK + (j)) * 1024 : KTILE + ((wave * NLDK + (j)) / IPB) * PV + ((wave * NLDK + (j)) % IPB) * 1024)
   const char *const kc_bytes = reinterpret_cast<const char *>(p.k_cache);
@@ -543,35 +549,65 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   const char *const kt_bytes = reinterpret_cast<const char *>(p.k_tree);
   const char *const vt_bytes = reinterpret_cast<const char *>(p.v_tree);
   const int64_t cache_base = PAGED ? 0 : (int64_t)cuL * p.stride_tok + (int64_t)kvh * p.stride_head;
-  // paged cache: each lane needs the page of the row it loads, one table entry per load
-  // instruction of a cache tile.  The entries of tile t + LOOK are requested right after the loads of
-  // tile t have been queued, by LDS-writing loads like the tiles' own, into a ring of slots; the
-  // wave's memory operations then come in a fixed order and number per tile (every tile, also a
-  // tree tile or the last ones, is followed by a request: past the end it re-reads the entry of the
-  // last key), which is what the counted waits below rely on.
-  lds_byte *const pg_lds = lds + C::RING_BYTES + wave * (NLDK * 256);
-  auto request_pages = [&](int t) __attribute__((always_inline)) {
-    if (!PAGED) return;
-    // a tree tile whose keys live in the cache (no separate tree tensors): positions L_b + node
-    const bool tree_in_cache = t >= n_ct && p.k_tree == nullptr;
-    const int base = tree_in_cache ? Lb0 + (t - n_ct) * TK : k0 + t * TK;
-    const int last = tree_in_cache ? Lb0 + Tb - 1 : k1 - 1;
-#pragma unroll
-    for (int j = 0; j < NLDK; ++j) {
-      int key = base + (C::STEADY && t < n_full ? full_key(j) : row0_of(j) + lrow);
-      key = key < last ? key : last;
-      key = key < 0 ? 0 : key;
-      int pidx = p.page_shift >= 0 ? (key >> p.page_shift) : (key / p.page_size);
-      pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;  // never past the sequence's row of the table
-      const int32_t *src = p.page_table + (int64_t)b * p.max_pages + pidx;
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256, 4, 0, 0);
-    }
-  };
-  // full tiles of a dense cache: a wave-uniform row pointer plus one tile-independent lane offset
   // (8-bit K/V read in place: inside each 1 KiB piece -- 8 rows of 8 chunks -- the lane that lands in
   // slot (row, c) fetches chunk c ^ row ^ (j & 1) of that row, j the piece's index: the 8-byte operand
   // reads and the byte transpose reads then spread over the LDS banks)
   auto chunk_of = [&](int j) __attribute__((always_inline)) { return C::KV8_REG ? (lpos ^ lsub ^ (j & 1)) : lpos; };
+  // paged cache: each lane needs the page of the row it loads.  The entries of tile t + LOOK, lane i's that of the tile's
+  // key i, are requested right after the loads of tile t have been queued, by an LDS-writing load like the tiles' own, into a
+  // ring of slots; the wave's memory operations then come in a fixed order and number per tile (every tile, also a
+  // tree tile or the last ones, is followed by a request: past the end it re-reads the entry of the
+  // last key), which is what the counted waits below rely on.
+  // (Where a wave loads a tile with one instruction the entry is that of the row the lane loads: no register for another index.)
+  // STEADY_PART: there are cache keys, and the page size is a power of two.
+  lds_byte *const pg_lds = lds + C::RING_BYTES + wave * 256;
+  auto request_pages = [&](int t, auto steady_tag) __attribute__((always_inline)) {
+    if (!PAGED) return;
+    constexpr bool STEADY_PART = decltype(steady_tag)::value;
+    const int row = C::PG_BY_KEY ? lane : row_of(t, 0);
+    // a tree tile whose keys live in the cache (no separate tree tensors): positions L_b + node
+    const bool tree_in_cache = t >= n_ct && p.k_tree == nullptr;
+    int key;
+    if constexpr (STEADY_PART) {  // (written so, the 256-row shape with D = 64 has the registers for it)
+      key = k0 + t * TK + row;
+      key = key < k1 ? key : k1 - 1;
+      if (tree_in_cache) key = Lb0 + (t - n_ct) * TK + row, key = key < Lb0 + Tb ? key : Lb0 + Tb - 1;
+    } else {
+      const int last = tree_in_cache ? Lb0 + Tb - 1 : k1 - 1;
+      key = (tree_in_cache ? Lb0 + (t - n_ct) * TK : k0 + t * TK) + row;
+      key = key < last ? key : last;
+      key = key < 0 ? 0 : key;
+    }
+    int pidx = STEADY_PART || p.page_shift >= 0 ? (key >> p.page_shift) : (key / p.page_size);
+    pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;  // never past the sequence's row of the table
+    const int32_t *src = p.page_table + (int64_t)b * p.max_pages + pidx;
+    __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT, 4, 0, 0);
+  };
+  // the entry of row `row` of tile t
+  auto page_of = [&](int t, int row) __attribute__((always_inline)) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + (C::PG_BY_KEY ? row : lane) * 4);
+  };
+  // (pages whose slots and strides fit 32 bits: the row's address is one multiply-add on its page's
+  // number; others take 64-bit products and, where the page size is no power of two, a division.  With these addresses in every
+  // tile and one load of table entries per tile instead of one per load of rows, from which each row finds its own --
+  // bound by the instructions between two tiles' loads, 16 products and eight requests a tile in the two-wave shape:
+  // 48 sequences of 500 .. 1300 keys, 6 nodes, 42.1 -> 37.8 us, 8-bit 48 x 1000 35.4 -> 31.7, D = 64 40 x 500 .. 700
+  // 20.1 -> 17.1; 64-row shape, 16 x 1024 .. 4096, 8-bit, 40.0 -> 38.4; 128-row shape, 16 x 700 .. 1500, 30 nodes,
+  // 36.5 -> 34.1; 256-row shape, 4 x 16 .. 32 K, 48 nodes, 122.5 -> 114 at its power limit.  The strides are held in bytes
+  // once, 64 bits wide, and the 32-bit form takes their low words: with a second set the kernels had more scalars than
+  // registers.)
+  const bool small_pages = PAGED && p.page_shift >= 0 && p.stride_page * EB < (1ll << 31) &&
+                           ((int64_t)p.page_size * p.stride_tok + (int64_t)p.Hkv * p.stride_head) * EB < (1ll << 31);
+  const int64_t page_bytes = p.stride_page * EB, tok_bytes = p.stride_tok * EB, head_bytes = kvh * p.stride_head * EB;
+  auto small_off = [&](uint32_t page, int pos, int j) __attribute__((always_inline)) {
+    const uint32_t slot = (uint32_t)pos & ((uint32_t)p.page_size - 1u);
+    return (uint64_t)page * (uint32_t)page_bytes + (slot * (uint32_t)tok_bytes + (uint32_t)head_bytes + (uint32_t)chunk_of(j) * 16u);
+  };
+  auto large_off = [&](uint32_t page, int pos, int j) __attribute__((always_inline)) {
+    const int pidx = p.page_shift >= 0 ? (pos >> p.page_shift) : (pos / p.page_size);
+    return (uint64_t)((int64_t)(int)page * page_bytes + (int64_t)(pos - pidx * p.page_size) * tok_bytes + head_bytes + chunk_of(j) * 16);
+  };
+  // full tiles of a dense cache: a wave-uniform row pointer plus one tile-independent lane offset
   const int full_row = C::STEADY ? lsub : lrow;
   const uint32_t lane_off2[2] = {(uint32_t)full_row * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(0) * 16u,
                                  (uint32_t)full_row * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(1) * 16u};
@@ -590,40 +626,42 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         __builtin_amdgcn_global_load_lds(GLOBAL_PTR(ksrc), stage + kdst_of(j), 16, 0, kLoadOnce);
         __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vsrc), stage + vdst_of(j), 16, 0, kLoadOnce);
       }
+    } else if (PAGED && !(tree && p.k_tree != nullptr)) {
+      // (tree keys stored in the cache follow the sequence's L_b committed tokens)
+      if (C::SMALL_PAGES && small_pages) {
+#pragma unroll
+        for (int j = 0; j < NLDK; ++j) {
+          const int row = tree ? row0_of(j) + lrow : row_of(t, j);
+          int key = base + row;
+          key = key < limit ? key : limit - 1;
+          const uint64_t off = small_off(page_of(t, row), tree ? Lb0 + key : key, j);
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + off), stage + kdst_of(j), 16, 0, kLoadOnce);
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vc_bytes + off), stage + vdst_of(j), 16, 0, kLoadOnce);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < NLDK; ++j) {
+          const int row = tree ? row0_of(j) + lrow : row_of(t, j);
+          int key = base + row;
+          key = key < limit ? key : limit - 1;
+          const uint64_t off = large_off(page_of(t, row), tree ? Lb0 + key : key, j);
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + off), stage + kdst_of(j), 16, 0, kLoadOnce);
+          __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vc_bytes + off), stage + vdst_of(j), 16, 0, kLoadOnce);
+        }
+      }
     } else {
 #pragma unroll
     for (int j = 0; j < NLDK; ++j) {
       const char *ksrc, *vsrc;
-      int key = base + (C::STEADY && !tree && t < n_full ? full_key(j) : row0_of(j) + lrow);
+      int key = base + (tree ? row0_of(j) + lrow : row_of(t, j));
       key = key < limit ? key : limit - 1;
       const int eoff = chunk_of(j) * (16 / EB);  // first element of the lane's 16-byte chunk
       if (tree && p.k_tree != nullptr) {
         const int64_t off = ((int64_t)(t0 + key) * p.Hkv + kvh) * D + eoff;
         ksrc = kt_bytes + off * EB;
         vsrc = vt_bytes + off * EB;
-      } else if (tree) {
-        // tree keys stored in the cache behind the sequence's L_b committed tokens
-        const int pos = Lb0 + key;
-        int64_t off;
-        if (PAGED) {
-          const int pidx = p.page_shift >= 0 ? (pos >> p.page_shift) : (pos / p.page_size);
-          const int page = *reinterpret_cast<const __attribute__((address_space(3))) int *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
-          off = (int64_t)page * p.stride_page + (int64_t)(pos - pidx * p.page_size) * p.stride_tok +
-                (int64_t)kvh * p.stride_head + eoff;
-        } else {
-          off = cache_base + (int64_t)pos * p.stride_tok + eoff;
-        }
-        ksrc = kc_bytes + off * EB;
-        vsrc = vc_bytes + off * EB;
-      } else if (PAGED) {
-        const int pidx = p.page_shift >= 0 ? (key >> p.page_shift) : (key / p.page_size);
-        const int page = *reinterpret_cast<const __attribute__((address_space(3))) int *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
-        const int64_t off = (int64_t)page * p.stride_page + (int64_t)(key - pidx * p.page_size) * p.stride_tok +
-                            (int64_t)kvh * p.stride_head + eoff;
-        ksrc = kc_bytes + off * EB;
-        vsrc = vc_bytes + off * EB;
       } else {
-        const int64_t off = cache_base + (int64_t)key * p.stride_tok + eoff;
+        const int64_t off = cache_base + (int64_t)(tree ? Lb0 + key : key) * p.stride_tok + eoff;
         ksrc = kc_bytes + off * EB;
         vsrc = vc_bytes + off * EB;
       }
@@ -636,7 +674,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   auto issue_tile = [&](int t) __attribute__((always_inline)) {
     if (t >= n_ct) issue_impl(t, std::true_type{});
     else issue_impl(t, std::false_type{});
-    request_pages(t + C::LOOK);
+    request_pages(t + C::LOOK, std::false_type{});
   };
 
   // per-lane LDS read bases (row r of a tile: block r % NBLK, sub-row r / NBLK)
@@ -986,7 +1024,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     __builtin_amdgcn_global_load_lds(GLOBAL_PTR(p.parent + t0 + idx), lds + C::PARENT_OFF + wave * 256, 4, 0, 0);
   }
 #pragma unroll
-  for (int t = 0; t < C::LOOK; ++t) request_pages(t);
+  for (int t = 0; t < C::LOOK; ++t) request_pages(t, std::false_type{});
   // The first PD tiles (fewer if the chunk has fewer).  Q and the mask rows were requested before
   // them and have arrived once no more than the tiles' own operations are outstanding; that wait
   // sits in the same branch as the loads it counts, so that the number is plainly a constant.
@@ -1053,11 +1091,6 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     const char *k_next = kc_bytes + (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
     const char *v_next = vc_bytes + (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
     const int64_t tile_bytes = (int64_t)TK * p.stride_tok * EB;
-    // (paged: pages whose slots and strides fit 32 bits; others take the general path)
-    const bool small_pages = PAGED && p.page_shift >= 0 && p.stride_page * EB < (1ll << 31) &&
-                             ((int64_t)p.page_size * p.stride_tok + (int64_t)p.Hkv * p.stride_head) * EB < (1ll << 31);
-    const uint32_t page_bytes = (uint32_t)(p.stride_page * EB), tok_bytes = (uint32_t)(p.stride_tok * EB);
-    const uint32_t head_bytes = (uint32_t)(kvh * p.stride_head * EB), slot_mask = (uint32_t)p.page_size - 1u;
     if constexpr (D == 128) {
       // ---- as a software pipeline over 32-key blocks.  A step computes the scores of the next block, the probabilities of
       // this one and the output of the one before, a matrix instruction of each product and two probabilities per lane at a time,
@@ -1075,22 +1108,10 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           if constexpr (PAGED) {
 #pragma unroll
             for (int j = 0; j < NLDK; ++j) {
-              const uint32_t page = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
-              const uint32_t slot = (uint32_t)(k0 + t * TK + full_key(j)) & slot_mask;
-              row_at[j] = (uint64_t)page * page_bytes + (slot * tok_bytes + head_bytes + (uint32_t)chunk_of(j) * 16u);
+              row_at[j] = small_off(page_of(t, full_key(j)), k0 + t * TK + full_key(j), j);
               __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + row_at[j]), stage + kdst_of(j), 16, 0, kLoadOnce);
             }
-            // (the entries of tile t + LOOK; past the last key they re-read its entry)
-#pragma unroll
-            for (int j = 0; j < NLDK; ++j) {
-              const int ahead = t + C::LOOK, row = ahead < n_full ? full_key(j) : row0_of(j) + lrow;
-              int key = k0 + ahead * TK + row;
-              key = key < k1 ? key : k1 - 1;
-              if (ahead >= n_ct && p.k_tree == nullptr) key = Lb0 + (ahead - n_ct) * TK + row, key = key < Lb0 + Tb ? key : Lb0 + Tb - 1;
-              int pidx = key >> p.page_shift;
-              pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;
-              __builtin_amdgcn_global_load_lds(GLOBAL_PTR(p.page_table + (int64_t)b * p.max_pages + pidx), pg_lds + ((t + C::LOOK) & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256, 4, 0, 0);
-            }
+            request_pages(t + C::LOOK, std::true_type{});
           } else {
 #pragma unroll
             for (int j = 0; j < NLDK; ++j)
@@ -1276,23 +1297,11 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         if constexpr (PAGED) {
 #pragma unroll
           for (int j = 0; j < NLDK; ++j) {
-            const uint32_t page = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256 + lane * 4);
-            const uint32_t slot = (uint32_t)(k0 + t * TK + full_key(j)) & slot_mask;
-            const uint64_t off = (uint64_t)page * page_bytes + (slot * tok_bytes + head_bytes + (uint32_t)chunk_of(j) * 16u);
+            const uint64_t off = small_off(page_of(t, full_key(j)), k0 + t * TK + full_key(j), j);
             __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + off), stage + kdst_of(j), 16, 0, kLoadOnce);
             __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vc_bytes + off), stage + vdst_of(j), 16, 0, kLoadOnce);
           }
-          // (the entries of tile t + LOOK; past the last key they re-read its entry)
-#pragma unroll
-          for (int j = 0; j < NLDK; ++j) {
-            const int ahead = t + C::LOOK, row = ahead < n_full ? full_key(j) : row0_of(j) + lrow;
-            int key = k0 + ahead * TK + row;
-            key = key < k1 ? key : k1 - 1;
-            if (ahead >= n_ct && p.k_tree == nullptr) key = Lb0 + (ahead - n_ct) * TK + row, key = key < Lb0 + Tb ? key : Lb0 + Tb - 1;
-            int pidx = key >> p.page_shift;
-            pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;
-            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(p.page_table + (int64_t)b * p.max_pages + pidx), pg_lds + ((t + C::LOOK) & (C::PG_SLOTS - 1)) * C::PG_SLOT + j * 256, 4, 0, 0);
-          }
+          request_pages(t + C::LOOK, std::true_type{});
         } else {
 #pragma unroll
           for (int j = 0; j < NLDK; ++j) {

@@ -305,6 +305,39 @@ def test_head_major_pool_strides(gpu):
     assert np.abs(out.cpu().numpy() - ro).max() <= TOL_O and np.abs(lse.cpu().numpy() - rl).max() <= TOL_LSE
 
 
+@pytest.mark.parametrize("page_size", [1, 8, 48, 64, 256])
+@pytest.mark.parametrize("D", [128, 64])
+def test_pages_of_every_size_in_every_shape(gpu, page_size, D):
+    """Pages below, at and above the rows of one load and of a tile, and of a size that is no power of two; sequences that
+    end inside a page and inside a tile, on their edges, and an empty one."""
+    w = wl.random_workload(1400 + page_size + D, 5, 8, 2, D, [700, 64, 0, 131, 256], [40, 9, 3, 64, 17], page_size=page_size)
+    for shape in (1, 2, 3, 4, 5):
+        for splits in (1, 3):
+            check_full(gpu, w, label=f"page_size={page_size} shape={shape} splits={splits}", plan_shape=shape, num_splits=splits)
+
+
+@pytest.mark.parametrize("far", [(1 << 30) - 64, 1 << 30])
+def test_pages_far_apart(gpu, far):
+    """Pages (of 16-bit elements) just less than 2 GiB apart, the last that the 32-bit form of a row's address takes, and
+    2 GiB apart: the rows are the same, so the results are, bit for bit."""
+    import torch
+    w = wl.random_workload(1450, 2, 8, 2, 128, [37, 21], [20, 7], page_size=16)
+    dw = gpu.to_device(w)
+    mask = gpu.build_mask(dw)
+    want = {shape: gpu.attention(dw, mask, plan_shape=shape) for shape in (1, 2, 3, 4, 5)}
+    pages, row = dw.k_cache.shape[0], w.Hkv * w.D
+    pool = torch.empty(far * (pages - 1) + 2 * 16 * row, dtype=dw.k_cache.dtype, device="cuda:0")
+    at = lambda o: torch.as_strided(pool, (pages, 16 * row), (far, 1), o)
+    at(0).copy_(dw.k_cache.reshape(pages, -1))
+    at(16 * row).copy_(dw.v_cache.reshape(pages, -1))
+    dw.k_cache, dw.v_cache = pool, pool[16 * row:]
+    for shape, (o0, l0) in want.items():
+        say(f"[case] pages {far} elements apart, shape={shape}")
+        o, l = gpu.attention(dw, mask, plan_shape=shape, strides=(far, row, w.D))
+        torch.cuda.synchronize()
+        assert torch.equal(o, o0) and torch.equal(l, l0)
+
+
 def test_all_true_mask_is_full_attention(gpu):
     """Masking with all-true ancestor bits reproduces unmasked attention over L+T keys:
     compared with the oracle on a chain whose last node sees everything."""
