@@ -849,20 +849,24 @@ struct CommitParams {
   int n_layers, layers_per_wg;
 };
 
-// layers whose pieces a thread has in flight at once
-constexpr int kCommitLayers = 4;
+constexpr int kCommitLayers = 4;  // layers of one workgroup at most: a thread has its pieces of all of them in flight at once
+// Bound by a workgroup's chain of reads before it moves a byte.  Everything that only needs the sequence's number and the
+// place in its path is requested together, before it is known whether the place holds a node (every address is inside its array
+// whatever the path says); a paged cache's entry is the one read behind that.
 __global__ void __launch_bounds__(256) commit_kernel(const CommitParams p) {
   const int j = blockIdx.x, b = blockIdx.y, layer0 = blockIdx.z * p.layers_per_wg;
-  const int n = p.path_len[b];
-  const int Lb = p.L[b];
+  const int n = p.path_len[b], Lb = p.L[b], node = p.path[(size_t)b * p.max_path + j];
+  const int t0 = p.cu_T[b], t1 = p.cu_T[b + 1];
+  const int32_t *const rows = p.page_table ? p.cu_T : p.cu_L;  // (a paged cache has no rows of its own: the value is not used)
+  const int row0 = rows[b], row1 = rows[b + 1];
+  asm volatile("" ::"s"(n), "s"(Lb), "s"(node), "s"(t0), "s"(t1), "s"(row0), "s"(row1));  // all seven before the first branch
   if (j == 0 && layer0 == 0 && threadIdx.x == 0 && p.L_out) p.L_out[b] = Lb + (n < p.max_path ? n : p.max_path);
   if (j >= n || Lb < 0) return;
-  const int node = p.path[(size_t)b * p.max_path + j];
-  if (node < 0 || node >= p.cu_T[b + 1] - p.cu_T[b]) {  // not a node of this tree: nothing is copied
+  if (node < 0 || node >= t1 - t0) {  // not a node of this tree: nothing is copied
     if (threadIdx.x == 0 && p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
     return;
   }
-  const int64_t src_row = (int64_t)p.cu_T[b] + node;
+  const int64_t src_row = (int64_t)t0 + node;
   const int pos = Lb + j;
   int64_t dst;  // element offset of (position, head 0, d 0)
   bool room;
@@ -872,8 +876,8 @@ __global__ void __launch_bounds__(256) commit_kernel(const CommitParams p) {
     const int page = room ? p.page_table[(int64_t)b * p.max_pages + pi] : 0;
     dst = (int64_t)page * p.stride_page + (int64_t)(pos - pi * p.page_size) * p.stride_tok;
   } else {
-    room = (int64_t)p.cu_L[b] + pos < p.cu_L[b + 1];
-    dst = ((int64_t)p.cu_L[b] + pos) * p.stride_tok;
+    room = (int64_t)row0 + pos < row1;
+    dst = ((int64_t)row0 + pos) * p.stride_tok;
   }
   if (!room) {
     if (threadIdx.x == 0 && p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
@@ -882,21 +886,28 @@ __global__ void __launch_bounds__(256) commit_kernel(const CommitParams p) {
   // 16-byte pieces: piece q of head g; the tree tensors are packed [node, Hkv, D]
   const int per_head = p.D / 8;
   const int pieces = p.Hkv * per_head;
+  const int here = p.n_layers - layer0 < p.layers_per_wg ? p.n_layers - layer0 : p.layers_per_wg;
+  static_assert(kCommitLayers == 4, "the layers below are moved by fours, twos and ones");
   for (int q = threadIdx.x; q < 2 * pieces; q += blockDim.x) {
     const bool is_v = q >= pieces;
     const int r = is_v ? q - pieces : q;
     const int g = r / per_head, e = (r - g * per_head) * 8;
     const char *src = (is_v ? p.v_tree : p.k_tree) + ((src_row * p.Hkv + g) * p.D + e) * 2;
     char *out = (is_v ? p.v_cache : p.k_cache) + (dst + (int64_t)g * p.stride_head + e) * 2;
-    const int end = layer0 + p.layers_per_wg < p.n_layers ? layer0 + p.layers_per_wg : p.n_layers;
-    for (int l = layer0; l < end; l += kCommitLayers) {
-      u32x4 x[kCommitLayers];
+    // (counts known when compiled: behind a branch of its own every load would wait for the one before)
+    auto move = [&](auto count, int l) __attribute__((always_inline)) {
+      constexpr int N = decltype(count)::value;
+      u32x4 x[N];
 #pragma unroll
-      for (int i = 0; i < kCommitLayers; ++i)
-        if (l + i < end) x[i] = *reinterpret_cast<const u32x4 *>(src + (l + i) * p.layer_tree);
+      for (int i = 0; i < N; ++i) x[i] = *reinterpret_cast<const u32x4 *>(src + (l + i) * p.layer_tree);
 #pragma unroll
-      for (int i = 0; i < kCommitLayers; ++i)
-        if (l + i < end) *reinterpret_cast<u32x4 *>(out + (l + i) * p.layer_cache) = x[i];
+      for (int i = 0; i < N; ++i) *reinterpret_cast<u32x4 *>(out + (l + i) * p.layer_cache) = x[i];
+    };
+    if (here == kCommitLayers) {
+      move(std::integral_constant<int, kCommitLayers>{}, layer0);
+    } else {
+      if (here & 2) move(std::integral_constant<int, 2>{}, layer0);
+      if (here & 1) move(std::integral_constant<int, 1>{}, layer0 + (here & 2));
     }
   }
 }
@@ -1068,11 +1079,12 @@ int tva_commit_path(const tva_commit_args *a, void *stream) {
   (void)hipGetLastError();
   if (in_cache) hipLaunchKernelGGL(compact_kernel, dim3(a->B, layers), dim3(256), 0, (hipStream_t)stream, p);
   else {
-    // A workgroup finds its row through a chain of three reads (length, node, position) before it moves a byte: where
-    // there are workgroups enough without one per layer, each moves the row in several layers (64 sequences, 32
-    // layers: 17.8 us one layer each -> 14.9, 3.6 TB/s read and written).
+    // A workgroup finds its row through a chain of reads before it moves a byte: where there are workgroups enough without
+    // one per layer, each moves the row in several layers, as many as it has in flight at once (64 sequences, 32 layers,
+    // paths of 2.8 nodes: 8 layers in two turns 13.5 us, 4 layers 11.9; 16 sequences: acceptance and commit with 2 layers each
+    // 21.3 us, with 1 each, the launch twice as large, 22.3).
     p.layers_per_wg = 1;
-    while (p.layers_per_wg < 8 && (int64_t)a->max_path * a->B * layers / (2 * p.layers_per_wg) >= 2048) p.layers_per_wg *= 2;
+    while (p.layers_per_wg < kCommitLayers && (int64_t)a->max_path * a->B * layers / (2 * p.layers_per_wg) >= 2048) p.layers_per_wg *= 2;
     hipLaunchKernelGGL(commit_kernel, dim3(a->max_path, a->B, (layers + p.layers_per_wg - 1) / p.layers_per_wg), dim3(256), 0,
                        (hipStream_t)stream, p);
   }

@@ -255,6 +255,52 @@ def test_commit_of_all_layers_in_one_call(torch_dev, form):
     assert np.array_equal(k_d.cpu().numpy().view(np.uint16), k_ref) and np.array_equal(v_d.cpu().numpy().view(np.uint16), v_ref)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("B, max_path, layers, Hkv", [(40, 9, 11, 2), (64, 9, 9, 2), (64, 9, 17, 2), (64, 32, 6, 20)])
+def test_commit_by_layers_per_workgroup(torch_dev, B, max_path, layers, Hkv, paged):
+    """One, two, four and four layers per workgroup, with a remainder of layers behind two and four, and a row of more pieces
+    than a workgroup has threads.  What stands behind a path's end is never used as a node, whatever it is, and a sequence
+    of negative length is left alone."""
+    torch = torch_dev
+    from paper_2510_26577_amd import verify
+    rng = np.random.Generator(np.random.PCG64(977 + layers))
+    D, page_size = 64, 4
+    T = rng.integers(1, 12, B)
+    cu_T = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
+    L = rng.integers(0, 9, B).astype(np.int32)
+    L[3] = -1
+    path = rng.choice(np.array([-2 ** 31, -1, 0, 11, 2 ** 31 - 1]), (B, max_path)).astype(np.int32)
+    plen = np.minimum(rng.integers(0, max_path + 1, B), T).astype(np.int32)
+    plen[0] = 0
+    for b in range(B):
+        path[b, :plen[b]] = np.sort(rng.permutation(int(T[b]))[:plen[b]])
+    cap = 24
+    max_pages = cap // page_size
+    table = rng.permutation(B * max_pages).reshape(B, max_pages).astype(np.int32)
+    cu = (np.arange(B + 1) * cap).astype(np.int32)
+    k0, v0 = (rng.integers(-2 ** 15, 2 ** 15, (layers, B * cap, Hkv, D)).astype(np.int16) for _ in range(2))
+    kt, vt = (rng.integers(-2 ** 15, 2 ** 15, (layers, int(cu_T[-1]), Hkv, D)).astype(np.int16) for _ in range(2))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    k_d, v_d, kt_d, vt_d = dev(k0), dev(v0), dev(kt), dev(vt)
+    first = lambda t: t[0].view(-1, page_size, Hkv, D) if paged else t[0]
+    L_out = torch.zeros(B, dtype=torch.int32, device="cuda")
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    say(f"[case] commit, {layers} layers of {B} sequences, paged {paged}")
+    verify.commit_path(cu_T=dev(cu_T), L=dev(L), path=dev(path), path_len=dev(plen), k_tree=kt_d[0], v_tree=vt_d[0], k_cache=first(k_d),
+                       v_cache=first(v_d), cu_L=None if paged else dev(cu), page_table=dev(table) if paged else None,
+                       page_size=page_size if paged else 0, L_out=L_out, err_flag=err, n_layers=layers,
+                       layer_stride_cache=k0[0].size, layer_stride_tree=kt[0].size)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for j in range(int(plen[b]) if L[b] >= 0 else 0):
+            t = int(L[b]) + j
+            r = table[b, t // page_size] * page_size + t % page_size if paged else cu[b] + t
+            k0[:, r], v0[:, r] = kt[:, cu_T[b] + path[b, j]], vt[:, cu_T[b] + path[b, j]]
+    assert int(err.item()) == 0
+    assert np.array_equal(L_out.cpu().numpy(), L + plen)
+    assert np.array_equal(k_d.cpu().numpy(), k0) and np.array_equal(v_d.cpu().numpy(), v0)
+
+
 def test_accept_then_commit_then_attend(torch_dev):
     """The committed rows are what the next step's attention reads: after commit, attention over the longer cache
     (with a one-node tree) equals the oracle on the host-side committed cache."""
