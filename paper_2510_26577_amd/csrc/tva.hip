@@ -1135,7 +1135,6 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         // together, half a tile less.
         const int first = it;
         auto enter = [&](int t) __attribute__((always_inline)) {
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           if (t < first + 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * (PD - 1) - NLDK));
           else __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * (PD - 1)));
           __builtin_amdgcn_s_barrier();
@@ -1155,6 +1154,14 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           bf16x8 pA[2], pB[2];    // their probabilities
 #pragma unroll
           for (int i = 0; i < 4; ++i) vl[i] = vh[i] = s16x4{0, 0, 0, 0};
+          // Waits for all of them (as operands: none is elsewhere by then).  Until its wait the compiler takes such a register as
+          // written although the value is still to come, so nothing but the groups below may stand between a read and its
+          // wait: every other way on starts with this one.
+          auto settle_reads = [&]() __attribute__((always_inline)) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::"v"(kr[0]), "v"(kr[1]), "v"(kr[2]), "v"(kr[3]), "v"(vl[0]), "v"(vl[1]), "v"(vl[2]), "v"(vl[3]),
+                         "v"(vh[0]), "v"(vh[1]), "v"(vh[2]), "v"(vh[3])
+                         : "memory");
+          };
           const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
           auto stage_at = [&](int t) __attribute__((always_inline)) { return lds0 + (uint32_t)(t % NSTAGE) * STAGE_BYTES; };
           const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1219,6 +1226,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
             for (int s = 0; s < 2; ++s) pc[s] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * s], pw[4 * s + 1], pw[4 * s + 2], pw[4 * s + 3]});
             // (the bound of compute_block's settled form)
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(ls <= fminf(kLoThreshold * (l_run[0] + ls), cap[0]))) != 0, 0)) {
+              settle_reads();
               float mx = -INFINITY;
 #pragma unroll
               for (int i = 0; i < 16; ++i) mx = fmaxf(mx, cur[i]);
@@ -1271,7 +1279,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           auto tile = [&](auto pv_tag) __attribute__((always_inline)) {
             const uint32_t s0 = stage_at(it - 1 + NSTAGE), s1 = stage_at(it), s2 = stage_at(it + 1);
             block(sA, sB, pA, pB, s1 + kbase_off, s2 + kbase_off, s0 + vbase_off, s1 + vbase_off, std::integral_constant<int, 0>{}, pv_tag,
-                  [&]() __attribute__((always_inline)) { enter(it); });
+                  [&]() __attribute__((always_inline)) { settle_reads(), enter(it); });
             block(sB, sA, pB, pA, s2 + kbase_off, s2 + kbase_off, s1 + vbase_off, s1 + vbase_off, std::integral_constant<int, 1>{}, std::true_type{},
                   [&]() __attribute__((always_inline)) {});
           };
