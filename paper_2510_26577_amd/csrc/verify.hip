@@ -849,19 +849,28 @@ struct CommitParams {
   int n_layers, layers_per_wg;
 };
 
-constexpr int kCommitLayers = 4;  // layers of one workgroup at most: a thread has its pieces of all of them in flight at once
+constexpr int kCommitLayers = 4;  // layers whose pieces a thread has in flight at once
 // Bound by a workgroup's chain of reads before it moves a byte.  Everything that only needs the sequence's number and the
 // place in its path is requested together, before it is known whether the place holds a node (every address is inside its array
 // whatever the path says); a paged cache's entry is the one read behind that.
+// MANY: where most places hold none, or a workgroup has more layers than it has in flight at once, the path's length comes first
+// and the rest behind it: of 0.4 us that a place without a node holds its compute unit's slot, 0.15 less.
+template <bool MANY>
 __global__ void __launch_bounds__(256) commit_kernel(const CommitParams p) {
   const int j = blockIdx.x, b = blockIdx.y, layer0 = blockIdx.z * p.layers_per_wg;
-  const int n = p.path_len[b], Lb = p.L[b], node = p.path[(size_t)b * p.max_path + j];
-  const int t0 = p.cu_T[b], t1 = p.cu_T[b + 1];
+  const int n = p.path_len[b], Lb = p.L[b];
   const int32_t *const rows = p.page_table ? p.cu_T : p.cu_L;  // (a paged cache has no rows of its own: the value is not used)
-  const int row0 = rows[b], row1 = rows[b + 1];
-  asm volatile("" ::"s"(n), "s"(Lb), "s"(node), "s"(t0), "s"(t1), "s"(row0), "s"(row1));  // all seven before the first branch
+  int node, t0, t1, row0, row1;
+  auto look = [&]() __attribute__((always_inline)) {
+    node = p.path[(size_t)b * p.max_path + j];
+    t0 = p.cu_T[b], t1 = p.cu_T[b + 1];
+    row0 = rows[b], row1 = rows[b + 1];
+    asm volatile("" ::"s"(n), "s"(Lb), "s"(node), "s"(t0), "s"(t1), "s"(row0), "s"(row1));  // all before the next branch
+  };
+  if constexpr (!MANY) look();
   if (j == 0 && layer0 == 0 && threadIdx.x == 0 && p.L_out) p.L_out[b] = Lb + (n < p.max_path ? n : p.max_path);
   if (j >= n || Lb < 0) return;
+  if constexpr (MANY) look();
   if (node < 0 || node >= t1 - t0) {  // not a node of this tree: nothing is copied
     if (threadIdx.x == 0 && p.err_flag) atomicCAS(p.err_flag, 0, 1 + b);
     return;
@@ -903,11 +912,14 @@ __global__ void __launch_bounds__(256) commit_kernel(const CommitParams p) {
 #pragma unroll
       for (int i = 0; i < N; ++i) *reinterpret_cast<u32x4 *>(out + (l + i) * p.layer_cache) = x[i];
     };
-    if (here == kCommitLayers) {
-      move(std::integral_constant<int, kCommitLayers>{}, layer0);
+    int l = layer0, left = here;
+    if constexpr (MANY)
+      for (; left > kCommitLayers; left -= kCommitLayers, l += kCommitLayers) move(std::integral_constant<int, kCommitLayers>{}, l);
+    if (left == kCommitLayers) {
+      move(std::integral_constant<int, kCommitLayers>{}, l);
     } else {
-      if (here & 2) move(std::integral_constant<int, 2>{}, layer0);
-      if (here & 1) move(std::integral_constant<int, 1>{}, layer0 + (here & 2));
+      if (left & 2) move(std::integral_constant<int, 2>{}, l);
+      if (left & 1) move(std::integral_constant<int, 1>{}, l + (left & 2));
     }
   }
 }
@@ -1079,14 +1091,31 @@ int tva_commit_path(const tva_commit_args *a, void *stream) {
   (void)hipGetLastError();
   if (in_cache) hipLaunchKernelGGL(compact_kernel, dim3(a->B, layers), dim3(256), 0, (hipStream_t)stream, p);
   else {
-    // A workgroup finds its row through a chain of reads before it moves a byte: where there are workgroups enough without
-    // one per layer, each moves the row in several layers, as many as it has in flight at once (64 sequences, 32 layers,
-    // paths of 2.8 nodes: 8 layers in two turns 13.5 us, 4 layers 11.9; 16 sequences: acceptance and commit with 2 layers each
-    // 21.3 us, with 1 each, the launch twice as large, 22.3).
-    p.layers_per_wg = 1;
-    while (p.layers_per_wg < kCommitLayers && (int64_t)a->max_path * a->B * layers / (2 * p.layers_per_wg) >= 2048) p.layers_per_wg *= 2;
-    hipLaunchKernelGGL(commit_kernel, dim3(a->max_path, a->B, (layers + p.layers_per_wg - 1) / p.layers_per_wg), dim3(256), 0,
-                       (hipStream_t)stream, p);
+    // A workgroup finds its row through a chain of reads before it moves a byte, and most places in most paths hold no node: a
+    // launch of many workgroups lasts as long as their dispatch, 0.2 .. 0.4 ns each.  So a workgroup moves the row in
+    // several layers: up to as many as it has in flight at once while there are workgroups enough, up to 16 where they are few
+    // bytes (fewer where paths are short and more of the places hold a node), eight where the launch is one of tens of
+    // thousands even so.  MANY from 32 places on and 1024 workgroups: below them it costs 1 .. 2 % in the mean (up to 10 where most
+    // places hold a node), from there on it gains 3 .. 8 (up to 60).  (400 calls of 1 .. 256 sequences, 1 .. 80 layers, 1 .. 40
+    // heads of 128.  us with 1 / 2 / 4 / 8 / 16 layers each: 64 sequences, 9 places, paths of 3.3 nodes, 32 layers, 8 heads 15.3 /
+    // 12.7 / 13.3 / 14.9 / 15.7; 16, 14, 3.2, 32, 8 7.2 / 5.5 / 5.0 / 5.0 / 5.8; MANY: 32, 72, 3.2, 61, 1 32.7 / 18.2 / 10.9 /
+    // 7.6 / 6.5; 201, 72, 2.4, 8, 4 28.1 / 16.0 / 10.3 / 8.8 / 8.7.)
+    const int64_t groups = (int64_t)a->max_path * a->B * layers, row_bytes = (int64_t)a->Hkv * a->D * 2;
+    const int64_t few_bytes = a->max_path >= 32 ? 8192 : a->max_path >= 10 ? 4096 : 2048;
+    int k = 1;
+    for (bool more = true; more;) {
+      int64_t most;
+      if (k < kCommitLayers) most = 2 * k * row_bytes <= 8192 ? 1024 : 4096;
+      else if (k < 16 && 2 * k * row_bytes <= few_bytes) most = 4096;
+      else most = k < 8 ? 49152 : INT64_MAX;
+      more = groups / k > most;
+      if (more) k *= 2;
+    }
+    const bool many = k > kCommitLayers || (a->max_path >= 32 && groups / k > 1024 && row_bytes <= 8192);
+    p.layers_per_wg = k;
+    const dim3 grid(a->max_path, a->B, (layers + k - 1) / k);
+    if (many) hipLaunchKernelGGL(commit_kernel<true>, grid, dim3(256), 0, (hipStream_t)stream, p);
+    else hipLaunchKernelGGL(commit_kernel<false>, grid, dim3(256), 0, (hipStream_t)stream, p);
   }
   return hipPeekAtLastError() == hipSuccess ? TVA_OK : TVA_HIP_ERROR;
 }

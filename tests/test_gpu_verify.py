@@ -256,10 +256,11 @@ def test_commit_of_all_layers_in_one_call(torch_dev, form):
 
 
 @pytest.mark.parametrize("paged", [False, True])
-@pytest.mark.parametrize("B, max_path, layers, Hkv", [(40, 9, 11, 2), (64, 9, 9, 2), (64, 9, 17, 2), (64, 32, 6, 20)])
+@pytest.mark.parametrize("B, max_path, layers, Hkv", [(4, 9, 5, 2), (40, 9, 5, 2), (5, 32, 13, 2), (40, 9, 11, 2), (64, 9, 9, 2), (64, 9, 17, 2), (64, 32, 6, 20),
+                                                     (64, 31, 11, 1), (64, 32, 23, 2), (64, 9, 19, 20), (64, 40, 30, 1)])
 def test_commit_by_layers_per_workgroup(torch_dev, B, max_path, layers, Hkv, paged):
-    """One, two, four and four layers per workgroup, with a remainder of layers behind two and four, and a row of more pieces
-    than a workgroup has threads.  What stands behind a path's end is never used as a node, whatever it is, and a sequence
+    """One, two, four, eight and sixteen layers per workgroup, with a remainder of one, two and three layers behind each, and a row
+    of more pieces than a workgroup has threads.  What stands behind a path's end is never used as a node, whatever it is, and a sequence
     of negative length is left alone."""
     torch = torch_dev
     from paper_2510_26577_amd import verify
