@@ -77,6 +77,61 @@ def test_every_code_is_widened_exactly(gpu):
     check(gpu, w8, 1.0 / 4096, 1.0 / 128, label="all codes")
 
 
+@pytest.mark.parametrize("variant", [1, 2, 4, 5])
+def test_a_code_that_is_no_number_stays_one(gpu, variant):
+    """Both NaN codes, in a full tile, in the last one and among the tree's own keys: in V they make their column of every row
+    that attends to them no number and leave the others as they are, in K they make the rows no numbers.  (One split: a
+    merge drops a split whose sum is no number like an empty one.)"""
+    import torch
+    w8, ks, vs = wl.to_fp8_kv(wl.random_workload(1312, 1, 4, 1, 128, [333], [5], max_depth=3))
+    v, vt, k = w8.v_cache.copy(), w8.v_tree.copy(), w8.k_cache.copy()
+    v[70, 0, 5], v[330, 0, 77], vt[0, 0, 127] = 0x7F, 0xFF, 0x7F  # (node 0 is every node's ancestor)
+    bad = np.isin(np.arange(128), (5, 77, 127))
+    say(f"[case] fp8 codes that are no numbers, shape {variant}")
+    out, _ = gpu.attention(gpu.to_device(dataclasses.replace(w8, v_cache=v, v_tree=vt)), None, k_scale=ks, v_scale=vs, plan_shape=variant, num_splits=1)
+    torch.cuda.synchronize()
+    o = out.cpu().numpy().astype(np.float64)
+    assert np.isnan(o[..., bad]).all()
+    clean = dataclasses.replace(w8, v_cache=np.where(v & 0x7F == 0x7F, 0, v).astype(np.uint8), v_tree=np.where(vt & 0x7F == 0x7F, 0, vt).astype(np.uint8))
+    assert np.abs(o - f8.tree_verify_attn_fp8(clean, ks, vs)[0])[..., ~bad].max() <= TOL_O
+    for code in (0x7F, 0xFF):
+        k[200, 0, 64] = code
+        out, _ = gpu.attention(gpu.to_device(dataclasses.replace(w8, k_cache=k)), None, k_scale=ks, v_scale=vs, plan_shape=variant, num_splits=1)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(out).all())
+
+
+@pytest.mark.parametrize("page_size", [1, 4, 48, 64, 256])
+def test_fp8_pages_of_every_size_in_every_shape(gpu, page_size):
+    """Pages below, at and above the eight rows of one load and a tile, and of a size that is no power of two; sequences that end
+    inside a page and inside a tile, on their edges, and an empty one."""
+    w8, ks, vs = wl.to_fp8_kv(wl.random_workload(1410 + page_size, 5, 8, 2, 128, [700, 64, 0, 131, 256], [40, 9, 3, 64, 17], page_size=page_size))
+    for shape in (1, 2, 4, 5):
+        for splits in (1, 3):
+            check(gpu, w8, ks, vs, num_splits=splits, label=f"page_size={page_size} shape={shape}", plan_shape=shape)
+
+
+@pytest.mark.parametrize("over", [False, True])
+def test_fp8_pages_far_apart(gpu, over):
+    """Pages just less than 2 GiB apart, the last that the 32-bit form of a row's address takes, and 2 GiB apart: the rows are
+    the same, so the results are, bit for bit."""
+    import torch
+    w8, ks, vs = wl.to_fp8_kv(wl.random_workload(1420, 2, 8, 2, 128, [300, 521], [20, 7], page_size=256))
+    dw = gpu.to_device(w8)
+    want = {shape: gpu.attention(dw, None, k_scale=ks, v_scale=vs, plan_shape=shape, num_splits=1) for shape in (1, 2, 4, 5)}
+    pages, row, far = dw.k_cache.shape[0], w8.Hkv * w8.D, (1 << 31) - (0 if over else 64)
+    pool = torch.empty(far * (pages - 1) + 2 * 256 * row, dtype=torch.uint8, device="cuda:0")
+    at = lambda o: torch.as_strided(pool, (pages, 256 * row), (far, 1), o)
+    at(0).copy_(dw.k_cache.reshape(pages, -1))
+    at(256 * row).copy_(dw.v_cache.reshape(pages, -1))
+    dw.k_cache, dw.v_cache = pool, pool[256 * row:]
+    for shape, (o0, l0) in want.items():
+        say(f"[case] fp8 pages {far} bytes apart, shape={shape}")
+        o, l = gpu.attention(dw, None, k_scale=ks, v_scale=vs, plan_shape=shape, num_splits=1, strides=(far, row, w8.D))
+        torch.cuda.synchronize()
+        assert torch.equal(o, o0) and torch.equal(l, l0)
+
+
 @pytest.mark.parametrize("hints", [False, True])
 @pytest.mark.parametrize("B,L,T", [(1, 2048, 60), (16, 2048, 16), (8, 2048, 60), (40, 700, 8), (64, 900, 8)])
 def test_fp8_benchmark_like_shapes(gpu, B, L, T, hints):

@@ -338,6 +338,39 @@ def test_pages_far_apart(gpu, far):
         assert torch.equal(o, o0) and torch.equal(l, l0)
 
 
+@pytest.mark.parametrize("over", [False, True])
+@pytest.mark.parametrize("far", ["pages", "tokens"])
+@pytest.mark.parametrize("D", [128, 64])
+def test_long_caches_of_far_pages_and_tokens(gpu, D, far, over):
+    """The same for caches long enough for the steady loop of the 256-row shape, whose rows are addressed by a form of its own, and
+    for tokens of a page that lie so far apart that its last one is just below 2 GiB, or above: where a call takes the
+    32-bit form, and in every shape without a steady loop, the results are those of a packed pool, bit for bit."""
+    import torch
+    w = wl.random_workload(1460 + D, 1, 8, 2, D, [1100], [20], page_size=256)
+    ro, rl = orc.tree_verify_attn(w)
+    dw = gpu.to_device(w)
+    mask = gpu.build_mask(dw)
+    want = {shape: gpu.attention(dw, mask, plan_shape=shape, num_splits=1) for shape in (1, 2, 3, 4, 5)}
+    pages, row = dw.k_cache.shape[0], w.Hkv * w.D
+    if far == "pages":
+        page, tok, second = (1 << 30) - (0 if over else 64), row, 256 * row
+    else:
+        page, tok, second = 2 * row, (1 << 22) - (0 if over else 16), row
+    pool = torch.empty(page * (pages - 1) + tok * 255 + second + row, dtype=dw.k_cache.dtype, device="cuda:0")
+    at = lambda o: torch.as_strided(pool, (pages, 256, row), (page, tok, 1), o)
+    at(0).copy_(dw.k_cache.reshape(pages, 256, row))
+    at(second).copy_(dw.v_cache.reshape(pages, 256, row))
+    dw.k_cache, dw.v_cache = pool, pool[second:]
+    for shape, (o0, l0) in want.items():
+        say(f"[case] far {far}, over={over} D={D} shape={shape}")
+        o, l = gpu.attention(dw, mask, plan_shape=shape, num_splits=1, strides=(page, tok, w.D))
+        torch.cuda.synchronize()
+        assert np.abs(o.cpu().numpy().astype(np.float64) - ro).max() <= TOL_O
+        assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
+        if shape != 5 or not over:
+            assert torch.equal(o, o0) and torch.equal(l, l0)
+
+
 def test_all_true_mask_is_full_attention(gpu):
     """Masking with all-true ancestor bits reproduces unmasked attention over L+T keys:
     compared with the oracle on a chain whose last node sees everything."""

@@ -69,6 +69,12 @@ def test_attention_kernels_of_which_two_share_a_compute_unit_leave_the_registers
     assert seen == 7
 
 
+def test_the_64_row_shape_of_head_dimension_64_leaves_the_registers_for_four_wavefronts(table):
+    """Four workgroups' short rings fit a compute unit."""
+    seen = [k[".vgpr_count"] for name, k in table.items() if "attn_kernelILi64ELi2ELi2ELi1ELb0ELi2E" in name or "attn_kernelILi64ELi2ELi2ELi1ELb1ELi2E" in name]
+    assert len(seen) == 2 and max(seen) <= 128, seen
+
+
 def test_sampling_kernels_spill_vector_registers_in_one_form_only(table):
     """walk_kernel<16, false> (16 groups of a vocabulary that is no multiple of 4) keeps both rows and spills a dozen."""
     for name, k in table.items():
