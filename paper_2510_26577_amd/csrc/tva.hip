@@ -320,7 +320,6 @@ __device__ __forceinline__ void lds_wait_n(bf16x8 &a, s16x4 &b, s16x4 &c) {
 
 // 16-byte LDS read from a landing zone of the 8-bit K/V path (inline assembly for the same reason),
 // and its wait.
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u32x4 lds_read_b128(uint32_t addr) {
   u32x4 v;
   asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
@@ -707,6 +706,17 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 
   auto use_reference = [&](int r) __attribute__((always_inline)) { m_use[r] = (m_run[r] == -INFINITY) ? 0.f : m_run[r]; };
   auto set_cap = [&](int r) __attribute__((always_inline)) { cap[r] = (m_run[r] == -INFINITY) ? -1.f : kLazyCap; };
+  // moves row r's reference up to a block's maximum and rescales what was summed against the old one
+  auto move_reference = [&](int r, float mx) __attribute__((always_inline)) {
+    const float m_new = fmaxf(m_run[r], mx);
+    const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[r] - m_new);
+    m_run[r] = m_new;
+    l_run[r] *= alpha;
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oacc[r][d][i] *= alpha;
+  };
   // ---- one 32-key block of one tile: S^T = K Q^T, online softmax, O^T += V^T P^T ----
   auto compute_block = [&](const lds_byte *stage, auto kb_tag, int base, int limit, bool tree, auto masked_tag, auto settled_tag) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_tag)::value, SETTLED = decltype(settled_tag)::value;
@@ -790,17 +800,6 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     }
     bf16x8 pb[2][RB];
     uint64_t lo_votes = 0;
-    // moves row r's reference up to a block's maximum and rescales what was summed against the old one
-    auto move_reference = [&](int r, float mx) __attribute__((always_inline)) {
-      const float m_new = fmaxf(m_run[r], mx);
-      const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[r] - m_new);
-      m_run[r] = m_new;
-      l_run[r] *= alpha;
-#pragma unroll
-      for (int d = 0; d < ND; ++d)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[r][d][i] *= alpha;
-    };
     if constexpr (!SETTLED) {
       bool need_lo = false;
 #pragma unroll
@@ -1232,14 +1231,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
               for (int i = 0; i < 16; ++i) mx = fmaxf(mx, cur[i]);
               mx = half_max(mx) * p.scale_log2;
               if (__builtin_amdgcn_ballot_w64(mx > m_run[0] + kLazy) != 0) {
-                const float m_new = fmaxf(m_run[0], mx);
-                const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[0] - m_new);
-                m_run[0] = m_new;
-                l_run[0] *= alpha;
-#pragma unroll
-                for (int d = 0; d < ND; ++d)
-#pragma unroll
-                  for (int i = 0; i < 16; ++i) oacc[0][d][i] *= alpha;
+                move_reference(0, mx);
                 use_reference(0);
                 set_cap(0);
                 ls = 0.f;
