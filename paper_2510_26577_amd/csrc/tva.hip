@@ -76,10 +76,10 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
 // Full tiles from which a split runs the steady loop.  A shorter one would run little of it, from a cold instruction
-// cache, and its blocks still move the reference.  Timed with and without it: D = 64 (six head shapes, unsplit and in four
-// splits, geometric mean with / without at 8, 12, 16, 20 and 32 full tiles) dense 1.02, 0.98, 0.98, 0.92, 0.88, paged 1.00, 0.98,
-// 0.95, 0.92, 0.87; D = 128 (32 sequences of 60 nodes, us without / with at 8, 12, 16 and 24) dense 33.2 / 35.0, 42.6 / 43.6,
-// 52.6 / 52.0, 71.0 / 67.6, paged 37.3 / 38.2, 46.0 / 46.2, 56.3 / 55.0, 76.6 / 74.2.
+// cache, and its blocks still move the reference.  Timed with and without it, six head shapes, unsplit and in four splits,
+// geometric mean with / without at 8, 12, 16, 20 and 32 full tiles: D = 128 dense 1.05, 1.00, 0.96, 0.95, 0.91, paged 1.07,
+// 1.02, 0.98, 0.95, 0.90 (even at 13; single calls lose up to 4 % up to 14); D = 64 dense 1.02, 0.98, 0.98, 0.92, 0.88,
+// paged 1.00, 0.98, 0.95, 0.92, 0.87.
 template <int D>
 constexpr int kSteadyTiles = D == 64 ? 11 : 16;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -1095,9 +1095,10 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       // this one and the output of the one before, a matrix instruction of each product and two probabilities per lane at a time,
       // with their operands read from LDS four such groups ahead: the matrix unit has work while the vector ALUs exponentiate,
       // whatever the SIMD's other wave is at.  K is fetched a tile further ahead than V, whose place it would else wait for.
-      // (32 sequences of 2048 keys, 60 nodes: 150 -> 128 thousand cycles a workgroup, but the chip, at its power limit, lowers
-      // its clock from 2.1 to 1.75 GHz: 84.5 -> 80.5 us.  Paged, 4 x 16 .. 32 K keys: 126 -> 118 us.  Without the loads from
-      // memory the former takes 70 us, without the LDS reads as well 64, with neither nor the exponentials 57.) ----
+      // (32 sequences of 2048 keys, 60 nodes: 133 -> 113 thousand cycles in a workgroup's tiles, but the chip, at its power
+      // limit, lowers its clock from 1.87 to 1.65 GHz: 87.7 -> 84.3 us.  Paged, 4 x 16 .. 32 K keys: 130.1 -> 120.7 us.
+      // Without the loads from memory the former's attention takes 70 us, without the LDS reads as well 64, with neither nor the
+      // exponentials 57.) ----
       static_assert(!C::STEADY || (D == 64 || (RB == 1 && NS == 8 && ND == 4 && KBW == 2 && NSTAGE == 4)), "");
       const int end = n_full - PD;
       if ((!PAGED || small_pages) && it < end) {
@@ -1701,7 +1702,9 @@ void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
 
 // A launch's duration as a model of it says, in us: fitted to 9650 timed launches (2000 calls in every shape: B = 1 .. 64,
 // 64 .. 32768 keys, 4 .. 576 rows per KV head, D = 64 and 128, dense and paged, both storage types, equal and unequal lengths);
-// over 4837 others its error has a standard deviation of 9 %.  A round of workgroups
+// over 4837 others its error had a standard deviation of 9 %.  The kernels have become faster since, paged ones most: 500
+// calls now last 0.86 (32-row shape) .. 0.93 of what it says, paged 0.81 .. 0.92, with a standard deviation of 11 .. 16 %; what
+// is compared are shapes, and the one taken is 2.6 % slower than the best in the mean (2.3 then).  A round of workgroups
 // takes (tiles of the longest split) x (time per tile), more where two share a CU; workgroups beyond whole rounds take a part
 // of one more, more than half of it however few they are; every round starts and drains; the launch takes no less than
 // its bytes at the rate the shape streams; with splits there is a merge pass.

@@ -854,7 +854,8 @@ constexpr int kCommitLayers = 4;  // layers whose pieces a thread has in flight 
 // place in its path is requested together, before it is known whether the place holds a node (every address is inside its array
 // whatever the path says); a paged cache's entry is the one read behind that.
 // MANY: where most places hold none, or a workgroup has more layers than it has in flight at once, the path's length comes first
-// and the rest behind it: of 0.4 us that a place without a node holds its compute unit's slot, 0.15 less.
+// and the rest behind it: places without a node are left sooner (256 sequences, paths of 3 of 33 places, 32 layers of 4 heads,
+// two layers a workgroup: 35 us instead of 53; four: 24.5 instead of 29.4).
 template <bool MANY>
 __global__ void __launch_bounds__(256) commit_kernel(const CommitParams p) {
   const int j = blockIdx.x, b = blockIdx.y, layer0 = blockIdx.z * p.layers_per_wg;
@@ -1096,7 +1097,7 @@ int tva_commit_path(const tva_commit_args *a, void *stream) {
     // several layers: up to as many as it has in flight at once while there are workgroups enough, up to 16 where they are few
     // bytes (fewer where paths are short and more of the places hold a node), eight where the launch is one of tens of
     // thousands even so.  MANY from 32 places on and 1024 workgroups: below them it costs 1 .. 2 % in the mean (up to 10 where most
-    // places hold a node), from there on it gains 3 .. 8 (up to 60).  (400 calls of 1 .. 256 sequences, 1 .. 80 layers, 1 .. 40
+    // places hold a node), from there on it gains 3 .. 8 (up to 30).  (400 calls of 1 .. 256 sequences, 1 .. 80 layers, 1 .. 40
     // heads of 128.  us with 1 / 2 / 4 / 8 / 16 layers each: 64 sequences, 9 places, paths of 3.3 nodes, 32 layers, 8 heads 15.3 /
     // 12.7 / 13.3 / 14.9 / 15.7; 16, 14, 3.2, 32, 8 7.2 / 5.5 / 5.0 / 5.0 / 5.8; MANY: 32, 72, 3.2, 61, 1 32.7 / 18.2 / 10.9 /
     // 7.6 / 6.5; 201, 72, 2.4, 8, 4 28.1 / 16.0 / 10.3 / 8.8 / 8.7.)
