@@ -75,13 +75,10 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
-// Full tiles from which a split runs the steady loop.  A shorter one would run little of it, from a cold instruction
-// cache, and its blocks still move the reference.  Timed with and without it, six head shapes, unsplit and in four splits,
-// geometric mean with / without at 8, 12, 16, 20 and 32 full tiles: D = 128 dense 1.05, 1.00, 0.96, 0.95, 0.91, paged 1.07,
-// 1.02, 0.98, 0.95, 0.90 (even at 13; single calls lose up to 4 % up to 14); D = 64 dense 1.02, 0.98, 0.98, 0.92, 0.88,
-// paged 1.00, 0.98, 0.95, 0.92, 0.87.
-template <int D>
-constexpr int kSteadyTiles = D == 64 ? 11 : 16;
+// Full tiles from which a split of the 256-row shape with D = 64 runs its steady loop.  A shorter one would run little of it, and
+// its blocks still move the reference.  Timed with and without it, three head shapes, unsplit and in four splits, geometric
+// mean with / without at 8, 12, 16, 20 and 32 full tiles: dense 1.02, 0.98, 0.98, 0.92, 0.88, paged 1.00, 0.98, 0.95, 0.92, 0.87.
+constexpr int kSteadyTiles = 11;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 // A tile takes the low-order P pass when, for some row, (largest probability of the tile) >
@@ -228,6 +225,14 @@ struct AttnCfg {
   static constexpr int NSTAGE = KV8_REG ? 4 : KV8 ? 2 : NST;
   // the 256-row shape's loop has a steady part of its own (the others ran no faster with one: they wait for data)
   static constexpr bool STEADY = WK == 1 && !KV8;
+  // Splits of PIPE_TILES full tiles and more run a loop that is a software pipeline over 32-key blocks.  LEAD: tiles that K is
+  // fetched further ahead than V; the blocks of the first LO_TILES tiles come with the low-order pass ready.  With / without it,
+  // 1 .. 32 sequences unsplit: 256-row shape 0.98 at 6 full tiles, 0.92 at 12 and 16, 0.96 at 32, dense and paged alike; 128-row
+  // shape dense 1.04 at 6, 1.01 at 12, 0.98 at 16, 0.92 at 32; deep 64-row shape dense 1.02 at 12, 0.98 at 15, 0.89 at 32.  Paged, the
+  // two last lost up to 6 % below 27 tiles (K's and V's rows are each looked up, at one block per tile) and gain 2 % at 32: without.
+  static constexpr bool PIPED = D == 128 && !KV8 && NST == 4 && (WK == 1 || !PAGED);
+  static constexpr int LEAD = KBW == 1 ? 2 : 1, LO_TILES = KBW == 1 ? 6 : 3;
+  static constexpr int PIPE_TILES = KBW == 2 ? 5 : WM == 4 ? 15 : 14;
   // m_use (in the kernel) is kept from block to block, or derived in each from the reference: kept, launches are 0.5 %
   // faster, but 1 % slower where 8-bit tiles are widened through LDS, and the paged 256-row shape with D = 64 has no
   // register for it
@@ -238,7 +243,7 @@ struct AttnCfg {
   // workgroups share a CU, and so do up to 128 registers per lane: with 131, 50 sequences of 200 keys took 21 us instead
   // of 14.5, paged, 256-row shape.  The dense 256-row shape needs four more than that and has one workgroup per CU.  Of the 64-row shape's short ring four
   // fit: with 131 registers 60 paged sequences of 300 keys, 30 nodes, took 23.7 us, with 128 22.2.)
-  static constexpr int WAVES_PER_SIMD = D == 64 && ((NW == 8 && (PAGED || WK == 2)) || (NW == 4 && NST == 2)) ? 4 : WG_PER_CU;
+  static constexpr int WAVES_PER_SIMD = NST == 4 && D == 128 && !KV8 ? 2 : D == 64 && ((NW == 8 && (PAGED || WK == 2)) || (NW == 4 && NST == 2)) ? 4 : WG_PER_CU;
   // after the key loop the ring is reused: exchange area of the key-group merge, then (behind it,
   // when the groups are paired; else on top of it, after a barrier) the output transpose patches
   static constexpr bool PAIR = (WK == 2);
@@ -316,6 +321,11 @@ __device__ __forceinline__ void lds_read_k(bf16x8 &v, uint32_t addr) {
 template <int N>
 __device__ __forceinline__ void lds_wait_n(bf16x8 &a, s16x4 &b, s16x4 &c) {
   asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(a), "+v"(b), "+v"(c) : "n"(N));
+}
+
+template <int N>
+__device__ __forceinline__ void lds_wait_v(s16x4 &a, s16x4 &b) {
+  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
 }
 
 // 16-byte LDS read from a landing zone of the 8-bit K/V path (inline assembly for the same reason),
@@ -560,9 +570,10 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   // (Where a wave loads a tile with one instruction the entry is that of the row the lane loads: no register for another index.)
   // STEADY_PART: there are cache keys, and the page size is a power of two.
   lds_byte *const pg_lds = lds + C::RING_BYTES + wave * 256;
+  const int32_t *const pages_of_b = PAGED ? p.page_table + (int64_t)b * p.max_pages : nullptr;
   auto request_pages = [&](int t, auto steady_tag) __attribute__((always_inline)) {
     if (!PAGED) return;
-    constexpr bool STEADY_PART = decltype(steady_tag)::value;
+    constexpr bool STEADY_PART = decltype(steady_tag)::value == 1, SHIFT = decltype(steady_tag)::value != 0;
     const int row = C::PG_BY_KEY ? lane : row_of(t, 0);
     // a tree tile whose keys live in the cache (no separate tree tensors): positions L_b + node
     const bool tree_in_cache = t >= n_ct && p.k_tree == nullptr;
@@ -577,9 +588,9 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       key = key < last ? key : last;
       key = key < 0 ? 0 : key;
     }
-    int pidx = STEADY_PART || p.page_shift >= 0 ? (key >> p.page_shift) : (key / p.page_size);
+    int pidx = SHIFT || p.page_shift >= 0 ? (key >> p.page_shift) : (key / p.page_size);
     pidx = pidx < p.max_pages ? pidx : p.max_pages - 1;  // never past the sequence's row of the table
-    const int32_t *src = p.page_table + (int64_t)b * p.max_pages + pidx;
+    const int32_t *src = pages_of_b + pidx;
     __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), pg_lds + (t & (C::PG_SLOTS - 1)) * C::PG_SLOT, 4, 0, 0);
   };
   // the entry of row `row` of tile t
@@ -980,6 +991,19 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     }
   };
 
+  auto compute_tile = [&](int it, bool tree, auto masked_tag) __attribute__((always_inline)) {
+    const int base = tree ? (it - n_ct) * TK : k0 + it * TK;
+    const int limit = tree ? Tb : k1;
+    const lds_byte *stage = lds + (it % NSTAGE) * STAGE_BYTES;
+    static_assert(KBW <= 2, "");
+    // wave-uniform: a block is skipped when none of its keys exists, and all of them by a wave
+    // none of whose query rows exists (it still loads its share of every tile)
+    if (!wave_has_rows) return;
+    if (base + wk * KBW * 32 < limit) compute_block(stage, std::integral_constant<int, 0>{}, base, limit, tree, masked_tag, std::false_type{});
+    if constexpr (KBW > 1)
+      if (base + (wk * KBW + 1) * 32 < limit) compute_block(stage, std::integral_constant<int, 1>{}, base, limit, tree, masked_tag, std::false_type{});
+  };
+
   // ---- one pipeline step: wait for tile `it`, refill the stage tile it-1 used, compute ----
   auto step = [&](int it, auto masked_tag, auto tree_tag) __attribute__((always_inline)) {
     if constexpr (KV8 && !C::KV8_REG) {
@@ -996,23 +1020,77 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     if (!(C::KV8_REG && WM == 1)) __builtin_amdgcn_s_barrier();
     if (it + PD < n_tiles) issue_tile(it + PD);
     }
-    constexpr bool tree = decltype(tree_tag)::value;
-    const int base = tree ? (it - n_ct) * TK : k0 + it * TK;
-    const int limit = tree ? Tb : k1;
-    const lds_byte *stage = lds + (it % NSTAGE) * STAGE_BYTES;
-    {
-    // wave-uniform: a block is skipped when none of its keys exists, and all of them by a wave
-    // none of whose query rows exists (it still loads its share of every tile)
-    if (!wave_has_rows) return;
-    if (base + wk * KBW * 32 < limit) compute_block(stage, std::integral_constant<int, 0>{}, base, limit, tree, masked_tag, std::false_type{});
-    if constexpr (KBW > 1)
-      if (base + (wk * KBW + 1) * 32 < limit) compute_block(stage, std::integral_constant<int, 1>{}, base, limit, tree, masked_tag, std::false_type{});
-    if constexpr (KBW > 2)
-      if (base + (wk * KBW + 2) * 32 < limit) compute_block(stage, std::integral_constant<int, 2>{}, base, limit, tree, masked_tag, std::false_type{});
-    if constexpr (KBW > 3)
-      if (base + (wk * KBW + 3) * 32 < limit) compute_block(stage, std::integral_constant<int, 3>{}, base, limit, tree, masked_tag, std::false_type{});
-    }
+    compute_tile(it, decltype(tree_tag)::value, masked_tag);
   };
+
+  // ---- the pipelined loop's loads: K and V of a tile apart ----
+  constexpr int LEAD = C::LEAD, KOPS = NLDK + C::NPG;
+  const bool piped = C::PIPED && n_full >= C::PIPE_TILES && (PAGED ? small_pages : (uint64_t)tok_bytes < (1u << 24)) &&
+                     (int64_t)p.Hkv * D * EB < (1 << 24);
+  const bool tree_apart = p.k_tree != nullptr;
+  // full cache tiles.  Dense: an address per operand, carried along from tile to tile in scalar registers, and the lane's offset
+  const int64_t tile_bytes = (int64_t)TK * p.stride_tok * EB;
+  const char *k_next = kc_bytes + (cache_base + (int64_t)k0 * p.stride_tok) * EB;
+  const char *v_next = vc_bytes + (cache_base + (int64_t)k0 * p.stride_tok) * EB;
+  auto tile_row = [&](int j) __attribute__((always_inline)) { return C::STEADY ? full_key(j) : row0_of(j) + lrow; };
+  uint32_t lane_off[NLDK];
+#pragma unroll
+  for (int j = 0; j < NLDK; ++j) lane_off[j] = (uint32_t)tile_row(j) * (uint32_t)tok_bytes + (uint32_t)chunk_of(j) * 16u;
+  // Paged: a multiply-add on the number of each row's page, for K; V of that tile, queued next, takes the same offsets.
+  uint64_t row_at[NLDK];
+  auto issue_full = [&](int t, auto v_tag) __attribute__((always_inline)) {
+    constexpr bool V = decltype(v_tag)::value;
+    lds_byte *stage = lds + (t & (NSTAGE - 1)) * STAGE_BYTES;
+    const char *&next = V ? v_next : k_next;
+#pragma unroll
+    for (int j = 0; j < NLDK; ++j) {
+      const char *src = next + lane_off[j];
+      if constexpr (PAGED) {
+        if constexpr (!V) row_at[j] = small_off(page_of(t, tile_row(j)), k0 + t * TK + tile_row(j), j);
+        src = (V ? vc_bytes : kc_bytes) + row_at[j];
+      }
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), stage + (V ? vdst_of(j) : kdst_of(j)), 16, 0, kLoadOnce);
+    }
+    if constexpr (!PAGED) next += tile_bytes;
+    if constexpr (!V) request_pages(t + C::LOOK, std::integral_constant<int, 1>{});
+  };
+  // Arguments that only the last tiles and the end of the workgroup need are read again there: held over the loop, paged, they
+  // were the scalars too many (up to 25 parked in lanes of vector registers).
+  typedef const __attribute__((address_space(4))) AttnParams *const_args;
+  auto late_args = [&]() __attribute__((always_inline)) {
+    const_args a = (const_args)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return a;
+  };
+  // the partial cache tile and the tree's
+  auto issue_rest = [&](int t, auto v_tag) __attribute__((always_inline)) {
+    constexpr bool V = decltype(v_tag)::value;
+    const bool tree = t >= n_ct, apart = tree && tree_apart;
+    const int first_key = tree ? (t - n_ct) * TK : k0 + t * TK, last = (tree ? Tb : k1) - 1 - first_key;
+    const int pos0 = tree ? Lb0 + first_key : first_key;
+    lds_byte *stage = lds + (t & (NSTAGE - 1)) * STAGE_BYTES;
+    const char *base = V ? vc_bytes : kc_bytes;
+    uint32_t stride = (uint32_t)tok_bytes;
+    if (apart) {
+      const const_args late = late_args();
+      base = reinterpret_cast<const char *>(V ? late->v_tree : late->k_tree) + ((int64_t)(t0 + first_key) * late->Hkv + kvh) * (D * EB);
+      stride = (uint32_t)(late->Hkv * D * EB);
+    }
+    if (!PAGED && !apart) base += (cache_base + (int64_t)pos0 * p.stride_tok) * EB;
+#pragma unroll
+    for (int j = 0; j < NLDK; ++j) {
+      if constexpr (!V || !PAGED) {
+        const int row_in = row0_of(j) + lrow, row = row_in < last ? row_in : last;
+        row_at[j] = __umul24((uint32_t)row, stride) + (uint32_t)chunk_of(j) * 16u;
+        if constexpr (PAGED)
+          if (!apart) row_at[j] = small_off(page_of(t, row_in), pos0 + row, j);
+      }
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(base + row_at[j]), stage + (V ? vdst_of(j) : kdst_of(j)), 16, 0, kLoadOnce);
+    }
+    if constexpr (!V) request_pages(t + C::LOOK, std::integral_constant<int, 2>{});
+  };
+  auto issue_k = [&](int t) __attribute__((always_inline)) { issue_full(t, std::false_type{}); };
+  auto issue_v = [&](int t) __attribute__((always_inline)) { issue_full(t, std::true_type{}); };
 
   // No ancestor masks passed: the tree's parent array goes to LDS (by the first two waves, with the
   // same LDS-writing loads as everything else here, so it is covered by the counted wait below).
@@ -1042,7 +1120,31 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(vm_cap(C::LOOK * C::NPG + C::TILE_OPS * n)));
   };
-  if (PD >= 3 && n_tiles >= 3) issue_first(std::integral_constant<int, PD >= 3 ? 3 : 1>{});
+  if (C::PIPED && piped) {
+    // K of the first NSTAGE tiles and V of one less, in the order in which the loop queues them
+    auto entries = [&](auto n_tag) __attribute__((always_inline)) {
+      if constexpr (PAGED) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(decltype(n_tag)::value));
+        asm volatile("" ::: "memory");  // the entries are read from LDS below this line, not above
+      }
+    };
+    entries(std::integral_constant<int, 2 * C::NPG>{});
+    issue_k(0);
+    if constexpr (KBW == 2) issue_v(0);
+    entries(std::integral_constant<int, C::NPG + KOPS + (KBW == 2 ? NLDK : 0)>{});
+    issue_k(1);
+    // Q and the mask rows are waited for here, before the rest: queueing 112 KB takes longer than they do
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(vm_cap(C::LOOK * C::NPG + 2 * KOPS + (KBW == 2 ? NLDK : 0))));
+    if constexpr (KBW == 1) issue_v(0);
+    else issue_v(1);
+    entries(std::integral_constant<int, 2 * KOPS + (KBW == 2 ? 2 : 1) * NLDK>{});
+    issue_k(2);
+    if constexpr (KBW == 1) issue_v(1);
+    else issue_v(2);
+    entries(std::integral_constant<int, 2 * KOPS + 2 * NLDK>{});
+    issue_k(3);
+    if constexpr (KBW == 1) issue_v(2);
+  } else if (PD >= 3 && n_tiles >= 3) issue_first(std::integral_constant<int, PD >= 3 ? 3 : 1>{});
   else if (PD >= 2 && n_tiles >= 2) issue_first(std::integral_constant<int, PD >= 2 ? 2 : 1>{});
   else issue_first(std::integral_constant<int, 1>{});
   if (derive_masks) {
@@ -1075,224 +1177,398 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   int it = 0;
   TL_STAMP(2);  // Q and the mask rows have arrived, the first tiles are in flight
 #ifdef TVA_TIMELINE
-  if (n_full > 0) {
+  if (n_full > 0 && !piped) {
     step(0, std::false_type{}, std::false_type{});
     it = 1;
   }
   TL_STAMP(3);  // first full tile done (a split without one: the same moment as the stamp before)
 #endif
-  if constexpr (C::STEADY) if (n_full >= kSteadyTiles<D>) {
-    // ---- the steady part of the loop: full cache tiles that queue full cache tiles.  One address per tile and operand, carried
-    // along in scalar registers (dense), or one multiply-add per load on its page's number (paged); every wait is a constant ----
-    int64_t row_off[NLDK];  // bytes from a tile's first row to the row of (load instruction j, lane 0)
-#pragma unroll
-    for (int j = 0; j < NLDK; ++j) row_off[j] = (int64_t)((wave * NLDK + j) * LPI) * p.stride_tok * EB;
-    const char *k_next = kc_bytes + (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
-    const char *v_next = vc_bytes + (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
-    const int64_t tile_bytes = (int64_t)TK * p.stride_tok * EB;
-    if constexpr (D == 128) {
-      // ---- as a software pipeline over 32-key blocks.  A step computes the scores of the next block, the probabilities of
-      // this one and the output of the one before, a matrix instruction of each product and two probabilities per lane at a time,
-      // with their operands read from LDS four such groups ahead: the matrix unit has work while the vector ALUs exponentiate,
-      // whatever the SIMD's other wave is at.  K is fetched a tile further ahead than V, whose place it would else wait for.
-      // (32 sequences of 2048 keys, 60 nodes: 133 -> 113 thousand cycles in a workgroup's tiles, but the chip, at its power
-      // limit, lowers its clock from 1.87 to 1.65 GHz: 87.7 -> 84.3 us.  Paged, 4 x 16 .. 32 K keys: 130.1 -> 120.7 us.
-      // Without the loads from memory the former's attention takes 70 us, without the LDS reads as well 64, with neither nor the
-      // exponentials 57.) ----
-      static_assert(!C::STEADY || (D == 64 || (RB == 1 && NS == 8 && ND == 4 && KBW == 2 && NSTAGE == 4)), "");
-      const int end = n_full - PD;
-      if ((!PAGED || small_pages) && it < end) {
-        uint64_t row_at[NLDK];  // (paged) the offsets the last K loads used: V's follow one tile later
-        auto issue_k = [&](int t) __attribute__((always_inline)) {
-          lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
-          if constexpr (PAGED) {
-#pragma unroll
-            for (int j = 0; j < NLDK; ++j) {
-              row_at[j] = small_off(page_of(t, full_key(j)), k0 + t * TK + full_key(j), j);
-              __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + row_at[j]), stage + kdst_of(j), 16, 0, kLoadOnce);
-            }
-            request_pages(t + C::LOOK, std::true_type{});
-          } else {
-#pragma unroll
-            for (int j = 0; j < NLDK; ++j)
-              __builtin_amdgcn_global_load_lds(GLOBAL_PTR(k_next + row_off[j] + lane_off2[j & 1]), stage + kdst_of(j), 16, 0, kLoadOnce);
-            k_next += tile_bytes;
-          }
-        };
-        auto issue_v = [&](int t) __attribute__((always_inline)) {
-          lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
-#pragma unroll
-          for (int j = 0; j < NLDK; ++j) {
-            const char *src = PAGED ? vc_bytes + row_at[j] : v_next + row_off[j] + lane_off2[j & 1];
-            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), stage + vdst_of(j), 16, 0, kLoadOnce);
-          }
-          if constexpr (!PAGED) v_next += tile_bytes;
-        };
-        // K of tile t + 1 has landed everywhere, V of tile t long before; K of tile t and V of tile t - 1 have been read
-        // everywhere: their places take K of tile t + 4 (not past the last tile queued here: the loop behind this one
-        // expects both halves of PD tiles) and V of tile t + 3.  Queued behind K(t+1) and the entries that came with it are
-        // V(t+1), K(t+2), V(t+2), K(t+3), each K with entries; before the third call, where the tiles' halves were queued
-        // together, half a tile less.
-        const int first = it;
-        auto enter = [&](int t) __attribute__((always_inline)) {
-          if (t < first + 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * (PD - 1) - NLDK));
-          else __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * (PD - 1)));
+  if constexpr (C::PIPED) {
+    if (piped) {
+      // ---- the full tiles as a software pipeline over 32-key blocks.  A step computes the scores of the next block, the
+      // probabilities of this one and the output of the one before, a matrix instruction of each product and two probabilities per
+      // lane at a time, with their operands read from LDS four such groups ahead: the matrix unit has work while the vector ALUs
+      // exponentiate, whatever the SIMD's other wave is at.  K is fetched LEAD tiles further ahead than V, whose place it would
+      // else wait for.  The partial cache tile and the tree's are queued from here as well.
+      // (Per tile with 8 workgroups on the chip, before -> now: deep 64-row shape 0.97 -> 0.55 us -- 0.45 without the loads --
+      // 128-row shape 0.96 -> 0.67, 256-row shape, which had a pipeline for its steady part, 1.17 -> 1.15 and its first and last
+      // tiles 1.6 -> 1.2.  With 256 workgroups the chip's power bounds the two large shapes: 32 sequences of 2048 keys, 60 nodes,
+      // 83.8 -> 82 us, whose loop alone would take 51 at the clock of a lone launch; 8 of 4096 keys, 64 heads, 58.2 -> 56.8.
+      // 16 sequences of 512 .. 2048 keys, 16 nodes, deep 64-row shape: 29.4 -> 28.) ----
+      static_assert(!C::PIPED || (RB == 1 && NS == 8 && ND == 4 && KBW <= 2), "");
+      constexpr int V8 = 8 * PV, S2OFF = ROWB, BLK = KBW == 2 ? 2 * ROWB : 0;
+      // In tile t: K of tile t + LEAD - 1 and V of tile t - 1 have been read everywhere, so their places take K and V of NSTAGE tiles
+      // later, where those exist; and K of tile t + LEAD + 1 and V of tile t + 1 have landed everywhere for the tile that
+      // follows.  Queued behind them are V of tile t + 2 and K of tile t + LEAD + 2, where those exist.
+      static_assert(!C::PIPED || NSTAGE == 4, "");
+      auto enter = [&](int t) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(6)" ::: "memory");  // (two key groups: the reads since those of the K and V given up)
+        const int left = n_tiles - t;
+        if (__builtin_expect(n_full - t > 3 + LEAD, 1)) {
+          __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS));
           __builtin_amdgcn_s_barrier();
-          issue_v(t + PD);
-          if (t + 1 < end) issue_k(t + PD + 1);
-        };
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS * (PD - 1)));
-        __builtin_amdgcn_s_barrier();
-        issue_k(it + PD);
-        if (!wave_has_rows) {
-          for (; it < end; ++it) enter(it);
+          issue_v(t + 3);
+          issue_k(t + 3 + LEAD);
         } else {
-          constexpr int V8 = 8 * PV, S2OFF = ROWB, BLK = 2 * ROWB;
-          bf16x8 kr[4];           // K operands: four of the next block's eight
-          s16x4 vl[4], vh[4];     // V^T operands: four of the eight of the block before
-          f32x16 sA, sB;          // scores of the blocks, in turn
-          bf16x8 pA[2], pB[2];    // their probabilities
+          if (left > 2 + LEAD) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS));
+          else if (left > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NLDK));
+          else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+          __builtin_amdgcn_s_barrier();
+          if (t + 3 < n_full) issue_v(t + 3);
+          else if (left > 3) issue_rest(t + 3, std::true_type{});
+          if (left > 3 + LEAD) issue_rest(t + 3 + LEAD, std::false_type{});
+        }
+      };
+      // in the first tile, ahead of the first read of its V and of K of tile LEAD
+      auto first_landed = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * KOPS + 2 * NLDK));
+        __builtin_amdgcn_s_barrier();
+      };
+      // -- arithmetic --
+      bf16x8 kr[4];           // K operands: four of the next block's eight
+      s16x4 vl[4], vh[4];     // V^T operands: four of the eight of the block before
+      f32x16 sA, sB;          // scores of the blocks, in turn
+      bf16x8 pA[2], pB[2];    // their probabilities
 #pragma unroll
-          for (int i = 0; i < 4; ++i) vl[i] = vh[i] = s16x4{0, 0, 0, 0};
-          // Waits for all of them (as operands: none is elsewhere by then).  Until its wait the compiler takes such a register as
-          // written although the value is still to come, so nothing but the groups below may stand between a read and its
-          // wait: every other way on starts with this one.
-          auto settle_reads = [&]() __attribute__((always_inline)) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::"v"(kr[0]), "v"(kr[1]), "v"(kr[2]), "v"(kr[3]), "v"(vl[0]), "v"(vl[1]), "v"(vl[2]), "v"(vl[3]),
-                         "v"(vh[0]), "v"(vh[1]), "v"(vh[2]), "v"(vh[3])
-                         : "memory");
-          };
-          const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-          auto stage_at = [&](int t) __attribute__((always_inline)) { return lds0 + (uint32_t)(t % NSTAGE) * STAGE_BYTES; };
-          const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-          auto half = [&](auto &&f, auto second_tag) __attribute__((always_inline)) {
-            constexpr int g0 = decltype(second_tag)::value ? 4 : 0;
-            f(std::integral_constant<int, g0>{}), f(std::integral_constant<int, g0 + 1>{});
-            f(std::integral_constant<int, g0 + 2>{}), f(std::integral_constant<int, g0 + 3>{});
-          };
-          auto pv = [&](int d, const bf16x8 &pr) __attribute__((always_inline)) {
-            oacc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, __builtin_shufflevector(vl[d], vh[d], 0, 1, 2, 3, 4, 5, 6, 7)), pr, oacc[0][d], 0, 0, 0);
-          };
-          {  // the first block's scores
-            const uint32_t ka = stage_at(it) + kbase_off;
-            lds_read_k<0>(kr[0], ka), lds_read_k<32>(kr[1], ka), lds_read_k<64>(kr[2], ka), lds_read_k<96>(kr[3], ka);
-            auto group = [&](auto g_tag) __attribute__((always_inline)) {
-              constexpr int g = decltype(g_tag)::value;
-              lds_wait_n<3>(kr[g % 4], vl[0], vh[0]);
-              sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[g % 4], qreg[0][g], g == 0 ? zero16 : sA, 0, 0, 0);
-              lds_read_k<(g < 4 ? (g + 4) * 32 : BLK + (g - 4) * 32)>(kr[g % 4], ka);
-              __builtin_amdgcn_sched_barrier(0);
-            };
-            half(group, std::false_type{}), half(group, std::true_type{});
+      for (int i = 0; i < 4; ++i) vl[i] = vh[i] = s16x4{0, 0, 0, 0};
+      // Waits for all of them (as operands: none is elsewhere by then).  Until its wait the compiler takes such a register as
+      // written although the value is still to come, so nothing but the groups below may stand between a read and its
+      // wait: every other way on starts with this one.
+      auto settle_reads = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::"v"(kr[0]), "v"(kr[1]), "v"(kr[2]), "v"(kr[3]), "v"(vl[0]), "v"(vl[1]), "v"(vl[2]), "v"(vl[3]),
+                     "v"(vh[0]), "v"(vh[1]), "v"(vh[2]), "v"(vh[3])
+                     : "memory");
+      };
+      const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+      auto k_at = [&](int t) __attribute__((always_inline)) { return lds0 + (uint32_t)(t & (NSTAGE - 1)) * STAGE_BYTES + kbase_off; };
+      auto v_at = [&](int t) __attribute__((always_inline)) { return lds0 + (uint32_t)(t & (NSTAGE - 1)) * STAGE_BYTES + vbase_off; };
+      // (two key groups: the head dimension's halves in the accumulators' order, the kept one first)
+      auto v_of = [&](uint32_t va, int d) __attribute__((always_inline)) { return !C::PAIR ? va : d < ND / 2 ? va + wk * 128 : va - wk * 128; };
+      const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      auto half = [&](auto &&f, auto second_tag) __attribute__((always_inline)) {
+        constexpr int g0 = decltype(second_tag)::value ? 4 : 0;
+        f(std::integral_constant<int, g0>{}), f(std::integral_constant<int, g0 + 1>{});
+        f(std::integral_constant<int, g0 + 2>{}), f(std::integral_constant<int, g0 + 3>{});
+      };
+      auto pv = [&](int d, const bf16x8 &pr) __attribute__((always_inline)) {
+        oacc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8, __builtin_shufflevector(vl[d], vh[d], 0, 1, 2, 3, 4, 5, 6, 7)), pr, oacc[0][d], 0, 0, 0);
+      };
+      auto pack = [&](float a, float b) __attribute__((always_inline)) {
+        const bf16x2 pair = {(__bf16)a, (__bf16)b};
+        return __builtin_bit_cast(uint32_t, pair);
+      };
+      // what two probabilities lost when they were rounded to w
+      auto pack_rest = [&](float a, float b, uint32_t w) __attribute__((always_inline)) {
+        return pack(a - __uint_as_float(w << 16), b - __uint_as_float(w & 0xFFFF0000u));
+      };
+      auto operands = [&](const uint32_t (&w)[8], bf16x8 (&out)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) out[s] = __builtin_bit_cast(bf16x8, u32x4{w[4 * s], w[4 * s + 1], w[4 * s + 2], w[4 * s + 3]});
+      };
+      // a bound of a lane's largest probability of a block: of the rounded ones, which are not negative, the largest as 16-bit
+      // integers, and what rounding can have taken off it
+      auto largest = [&](const uint32_t (&w)[8]) __attribute__((always_inline)) {
+        typedef short s16x2 __attribute__((ext_vector_type(2)));
+        s16x2 top = __builtin_bit_cast(s16x2, w[0]);
+#pragma unroll
+        for (int i = 1; i < 8; ++i) top = __builtin_elementwise_max(top, __builtin_bit_cast(s16x2, w[i]));
+        return __uint_as_float((uint32_t)(uint16_t)(top[0] > top[1] ? top[0] : top[1]) << 16) * (1.f + 1.f / 256);
+      };
+      auto block_max = [&](const f32x16 &sc) __attribute__((always_inline)) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sc[i]);
+        return half_max(mx) * p.scale_log2;
+      };
+      // moves the reference if a block's maximum asks for it
+      auto settle_reference = [&](float mx) __attribute__((always_inline)) {
+        if (__builtin_amdgcn_ballot_w64(mx > m_run[0] + kLazy) == 0) return false;
+        move_reference(0, mx);
+        use_reference(0);
+        set_cap(0);
+        return true;
+      };
+      // group g of a step: K operand g of the next block, two of this block's probabilities, the read of K operands four groups on
+      // (of the next block, or the first ones of the block after it)
+      auto group_head = [&](auto g_tag, auto wait_tag, const f32x16 &cur, f32x16 &nxt, uint32_t ka1, uint32_t ka2, auto kb_tag, float &e0, float &e1) __attribute__((always_inline)) {
+        constexpr int g = decltype(g_tag)::value, d = g % 4, kb = decltype(kb_tag)::value;
+        lds_wait_n<decltype(wait_tag)::value>(kr[d], vl[d], vh[d]);
+        nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[d], qreg[0][g], g == 0 ? zero16 : nxt, 0, 0, 0);
+        e0 = fast_exp2(fmaf(cur[2 * g], p.scale_log2, -m_use[0]));
+        e1 = fast_exp2(fmaf(cur[2 * g + 1], p.scale_log2, -m_use[0]));
+        if constexpr (g < 4) lds_read_k<(1 - kb) * BLK + (g + 4) * 32>(kr[d], ka1);
+        else lds_read_k<kb * BLK + (g - 4) * 32>(kr[d], ka2);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      // what a block hands to the step after it: its probabilities, rounded, and (the first blocks, whose weights are large against
+      // what has been summed) what rounding took off them
+      uint32_t hA[8], hB[8], rA[8], rB[8];
+      bool rest = false;  // ... which is wanted
+      // the step of one of the first blocks.  ka1, ka2: where K of the next block and of the one after it are, va1, va2: V of the block
+      // before and of this one
+      auto block_lo = [&](f32x16 &cur, f32x16 &nxt, uint32_t (&hc)[8], uint32_t (&rc)[8], uint32_t (&hp)[8], uint32_t (&rp)[8],
+                          uint32_t ka1, uint32_t ka2, uint32_t va1, uint32_t va2, auto kb_tag, auto pv_tag, auto &&after) __attribute__((always_inline)) {
+        constexpr int kb = decltype(kb_tag)::value, HERE = kb * BLK, THERE = (1 - kb) * BLK;
+        constexpr bool HASPV = decltype(pv_tag)::value;
+        float ls = 0.f;
+        bf16x8 pp[2], pr[2];
+        if constexpr (HASPV) operands(hp, pp), operands(rp, pr);
+        auto group = [&](auto g_tag) __attribute__((always_inline)) {
+          constexpr int g = decltype(g_tag)::value, d = g % 4;
+          float e0, e1;
+          // (three reads a group; of K alone before the first)
+          group_head(g_tag, std::integral_constant<int, HASPV ? 9 : g < 4 ? 3 : 3 + 2 * d>{}, cur, nxt, ka1, ka2, kb_tag, e0, e1);
+          if constexpr (HASPV) pv(d, pp[g / 4]);
+          ls += e0;
+          ls += e1;
+          hc[g] = pack(e0, e1);
+          rc[g] = pack_rest(e0, e1, hc[g]);
+          asm volatile("" : "+v"(hc[g]), "+v"(rc[g]), "+v"(ls));  // (computed here, not where it is used)
+          if constexpr (HASPV)
+            if (rest) pv(d, pr[g / 4]);
+          if constexpr (g >= 4) {
+            lds_read_v<HERE + d * 64>(vl[d], v_of(va2, d));
+            lds_read_v<HERE + V8 + d * 64>(vh[d], v_of(va2, d));
+          } else if constexpr (HASPV) {
+            lds_read_v<THERE + S2OFF + d * 64>(vl[d], v_of(va1, d));
+            lds_read_v<THERE + S2OFF + V8 + d * 64>(vh[d], v_of(va1, d));
           }
-          // A step.  Block kb of a tile; ka1, ka2: where K of the next block and of the one after it are, va1, va2: V of the block
-          // before and of this one.
-          auto block = [&](f32x16 &cur, f32x16 &nxt, bf16x8 (&pc)[2], bf16x8 (&pp)[2], uint32_t ka1, uint32_t ka2, uint32_t va1, uint32_t va2,
-                           auto kb_tag, auto pv_tag, auto middle) __attribute__((always_inline)) {
-            constexpr int kb = decltype(kb_tag)::value, HERE = kb * BLK, THERE = (1 - kb) * BLK;
-            constexpr bool HASPV = decltype(pv_tag)::value;
-            float ls = 0.f;
-            uint32_t pw[8];
-            auto group = [&](auto g_tag) __attribute__((always_inline)) {
-              constexpr int g = decltype(g_tag)::value, d = g % 4;
-              lds_wait_n<HASPV || g >= 4 ? 9 : 3>(kr[d], vl[d], vh[d]);  // (three reads a group; of K alone before the first)
-              nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[d], qreg[0][g], g == 0 ? zero16 : nxt, 0, 0, 0);
-              const float e0 = fast_exp2(fmaf(cur[2 * g], p.scale_log2, -m_use[0]));
-              const float e1 = fast_exp2(fmaf(cur[2 * g + 1], p.scale_log2, -m_use[0]));
-              if constexpr (g < 4) lds_read_k<THERE + (g + 4) * 32>(kr[d], ka1);
-              else lds_read_k<HERE + (g - 4) * 32>(kr[d], ka2);
-              __builtin_amdgcn_sched_barrier(0);
-              if constexpr (HASPV) pv(d, pp[g / 4]);
+          __builtin_amdgcn_sched_barrier(0);
+          after(g_tag);
+        };
+        half(group, std::false_type{});
+        half(group, std::true_type{});
+        asm volatile("s_waitcnt lgkmcnt(9)" ::: "memory");  // (the next step's first operands)
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(ls <= cap[0])) != 0, 0)) {
+          settle_reads();
+          if (settle_reference(block_max(cur))) {
+            ls = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              const float e0 = fast_exp2(fmaf(cur[2 * i], p.scale_log2, -m_use[0])), e1 = fast_exp2(fmaf(cur[2 * i + 1], p.scale_log2, -m_use[0]));
               ls += e0;
               ls += e1;
-              const bf16x2 pair = {(__bf16)e0, (__bf16)e1};
-              uint32_t w = __builtin_bit_cast(uint32_t, pair);
-              asm volatile("" : "+v"(w), "+v"(ls));  // (computed here, not where it is used)
-              pw[g] = w;
-              if constexpr (g >= 4) {
-                lds_read_v<HERE + d * 64>(vl[d], va2);
-                lds_read_v<HERE + V8 + d * 64>(vh[d], va2);
-              } else if constexpr (HASPV) {
-                lds_read_v<THERE + S2OFF + d * 64>(vl[d], va1);
-                lds_read_v<THERE + S2OFF + V8 + d * 64>(vh[d], va1);
-              }
-              __builtin_amdgcn_sched_barrier(0);
-            };
-            half(group, std::false_type{});
-            middle();
-            half(group, std::true_type{});
+              hc[i] = pack(e0, e1);
+              rc[i] = pack_rest(e0, e1, hc[i]);
+            }
+          }
+        }
+        l_run[0] += ls;
+        rest = __builtin_amdgcn_ballot_w64(!(largest(hc) <= kLoThreshold * half_sum(l_run[0]))) != 0;
+      };
+      // any later block's step; va1, va2: where V of the block before and of this one are
+      auto block = [&](f32x16 &cur, f32x16 &nxt, bf16x8 (&pc)[2], bf16x8 (&pp)[2], uint32_t ka1, uint32_t ka2, uint32_t va1, uint32_t va2,
+                       auto kb_tag, auto pv_tag, auto &&after) __attribute__((always_inline)) {
+        constexpr int kb = decltype(kb_tag)::value, HERE = kb * BLK, THERE = (1 - kb) * BLK;
+        constexpr bool HASPV = decltype(pv_tag)::value;
+        float ls = 0.f;
+        uint32_t pw[8];
+        auto group = [&](auto g_tag) __attribute__((always_inline)) {
+          constexpr int g = decltype(g_tag)::value, d = g % 4;
+          float e0, e1;
+          // (three reads a group; of K alone before the first)
+          group_head(g_tag, std::integral_constant<int, HASPV ? 9 : g < 4 ? 3 : 3 + 2 * d>{}, cur, nxt, ka1, ka2, kb_tag, e0, e1);
+          if constexpr (HASPV) pv(d, pp[g / 4]);
+          ls += e0;
+          ls += e1;
+          pw[g] = pack(e0, e1);
+          asm volatile("" : "+v"(pw[g]), "+v"(ls));
+          if constexpr (g >= 4) {
+            lds_read_v<HERE + d * 64>(vl[d], v_of(va2, d));
+            lds_read_v<HERE + V8 + d * 64>(vh[d], v_of(va2, d));
+          } else if constexpr (HASPV) {
+            lds_read_v<THERE + S2OFF + d * 64>(vl[d], v_of(va1, d));
+            lds_read_v<THERE + S2OFF + V8 + d * 64>(vh[d], v_of(va1, d));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          after(g_tag);
+        };
+        half(group, std::false_type{});
+        half(group, std::true_type{});
+        operands(pw, pc);
+        // (the bound of compute_block's settled form)
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(ls <= fminf(kLoThreshold * (l_run[0] + ls), cap[0]))) != 0, 0)) {
+          settle_reads();
+          // (the scores are looked at where the rounded probabilities, against the row's sum of both lane halves, leave it open)
+          const bool open = __builtin_amdgcn_ballot_w64(!(ls <= cap[0]) | !(largest(pw) <= kLoThreshold * half_sum(l_run[0] + ls))) != 0;
+          const float mx = open ? block_max(cur) : -INFINITY;
+          if (open && settle_reference(mx)) {
+            ls = 0.f;
 #pragma unroll
-            for (int s = 0; s < 2; ++s) pc[s] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * s], pw[4 * s + 1], pw[4 * s + 2], pw[4 * s + 3]});
-            // (the bound of compute_block's settled form)
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(ls <= fminf(kLoThreshold * (l_run[0] + ls), cap[0]))) != 0, 0)) {
-              settle_reads();
-              float mx = -INFINITY;
+            for (int i = 0; i < 16; ++i) {
+              const float e = fast_exp2(fmaf(cur[i], p.scale_log2, -m_use[0]));
+              ls += e;
+              pc[i / 8][i % 8] = (__bf16)e;
+            }
+          }
+          if (open && __builtin_amdgcn_ballot_w64(fast_exp2(mx - m_use[0]) > kLoThreshold * half_sum(l_run[0] + ls)) != 0) {
+            // the low-order pass of this block, at once: its V^T operands are read for it alone
 #pragma unroll
-              for (int i = 0; i < 16; ++i) mx = fmaxf(mx, cur[i]);
-              mx = half_max(mx) * p.scale_log2;
-              if (__builtin_amdgcn_ballot_w64(mx > m_run[0] + kLazy) != 0) {
-                move_reference(0, mx);
-                use_reference(0);
-                set_cap(0);
-                ls = 0.f;
+            for (int s2 = 0; s2 < 2; ++s2) {
+              bf16x8 plo;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                  const float e = fast_exp2(fmaf(cur[i], p.scale_log2, -m_use[0]));
-                  ls += e;
-                  pc[i / 8][i % 8] = (__bf16)e;
-                }
-              }
-              if (__builtin_amdgcn_ballot_w64(fast_exp2(mx - m_use[0]) > kLoThreshold * half_sum(l_run[0] + ls)) != 0) {
-                // the low-order pass of this block, at once: its V^T operands are read for it alone
+              for (int i = 0; i < 8; ++i)
+                plo[i] = (__bf16)(fast_exp2(fmaf(cur[8 * s2 + i], p.scale_log2, -m_use[0])) - (float)pc[s2][i]);
 #pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2) {
-                  bf16x8 plo;
-#pragma unroll
-                  for (int i = 0; i < 8; ++i)
-                    plo[i] = (__bf16)(fast_exp2(fmaf(cur[8 * s2 + i], p.scale_log2, -m_use[0])) - (float)pc[s2][i]);
-#pragma unroll
-                  for (int d = 0; d < ND; ++d) {
-                    s16x4 a, c;
-                    const uint32_t va = va2 + s2 * S2OFF + d * 64;
-                    lds_read_v<HERE>(a, va);
-                    lds_read_v<HERE + V8>(c, va);
-                    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(c));
-                    oacc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7)), plo, oacc[0][d], 0, 0, 0);
-                  }
-                }
+              for (int d = 0; d < ND; ++d) {
+                s16x4 a, c;
+                const uint32_t va = v_of(va2, d) + s2 * S2OFF + d * 64;
+                lds_read_v<HERE>(a, va);
+                lds_read_v<HERE + V8>(c, va);
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(c));
+                oacc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7)), plo, oacc[0][d], 0, 0, 0);
               }
             }
-            l_run[0] += ls;
-          };
-          set_cap(0);
-          // (the barrier of a tile stands in the middle of its first block: K of the next tile is wanted from there on, V of the
-          // tile before up to there)
-          auto tile = [&](auto pv_tag) __attribute__((always_inline)) {
-            const uint32_t s0 = stage_at(it - 1 + NSTAGE), s1 = stage_at(it), s2 = stage_at(it + 1);
-            block(sA, sB, pA, pB, s1 + kbase_off, s2 + kbase_off, s0 + vbase_off, s1 + vbase_off, std::integral_constant<int, 0>{}, pv_tag,
-                  [&]() __attribute__((always_inline)) { settle_reads(), enter(it); });
-            block(sB, sA, pB, pA, s2 + kbase_off, s2 + kbase_off, s1 + vbase_off, s1 + vbase_off, std::integral_constant<int, 1>{}, std::true_type{},
-                  [&]() __attribute__((always_inline)) {});
-          };
-          tile(std::false_type{});
-          for (++it; it < end; ++it) tile(std::true_type{});
-          // the last block's output
-          const uint32_t va = stage_at(it - 1) + vbase_off;
-          auto last = [&](auto g_tag) __attribute__((always_inline)) {
-            constexpr int g = decltype(g_tag)::value, d = g % 4;
-            lds_wait_n<0>(kr[d], vl[d], vh[d]);
-            pv(d, pB[g / 4]);
-            if constexpr (g < 4) {
-              lds_read_v<BLK + S2OFF + d * 64>(vl[d], va);
-              lds_read_v<BLK + S2OFF + V8 + d * 64>(vh[d], va);
-            }
-          };
-          half(last, std::false_type{}), half(last, std::true_type{});
+          }
+        }
+        l_run[0] += ls;
+      };
+      // -- the loop --
+      std::integral_constant<int, 0> blk0;
+      std::integral_constant<int, 1> blk1;
+      // K of the first tile has landed
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * KOPS + 3 * NLDK));
+      __builtin_amdgcn_s_barrier();
+      if (wave_has_rows) {
+        const uint32_t ka = k_at(it);
+        lds_read_k<0>(kr[0], ka), lds_read_k<32>(kr[1], ka), lds_read_k<64>(kr[2], ka), lds_read_k<96>(kr[3], ka);
+        auto group = [&](auto g_tag) __attribute__((always_inline)) {
+          constexpr int g = decltype(g_tag)::value;
+          lds_wait_n<KBW == 2 || g < 5 ? 3 : 7 - g>(kr[g % 4], vl[0], vh[0]);
+          sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[g % 4], qreg[0][g], g == 0 ? zero16 : sA, 0, 0, 0);
+          if constexpr (g < 4) lds_read_k<(g + 4) * 32>(kr[g % 4], ka);
+          else if constexpr (KBW == 2) lds_read_k<BLK + (g - 4) * 32>(kr[g % 4], ka);
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        half(group, std::false_type{}), half(group, std::true_type{});
+      }
+      if constexpr (KBW == 1) {
+        // K of the second tile has landed, that of the first has been read everywhere
+        if (wave_has_rows) settle_reads();
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * KOPS + 3 * NLDK));
+        __builtin_amdgcn_s_barrier();
+        issue_k(4);
+        if (wave_has_rows) {
+          const uint32_t ka = k_at(1);
+          lds_read_k<0>(kr[0], ka), lds_read_k<32>(kr[1], ka), lds_read_k<64>(kr[2], ka), lds_read_k<96>(kr[3], ka);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-    } else {
+      if (!wave_has_rows) {
+        first_landed();
+        for (; it < n_full; ++it) enter(it);
+      } else {
+        m_run[0] = block_max(sA), use_reference(0), set_cap(0);
+        const int lo_end = C::LO_TILES < n_full ? C::LO_TILES : n_full;
+        const auto nothing = [&](auto) __attribute__((always_inline)) {};
+        // (two key groups: once the reads of the K and V given up are behind it; one: in the second block)
+        const auto entered = [&](auto g_tag) __attribute__((always_inline)) {
+          if constexpr (decltype(g_tag)::value == (KBW == 1 ? 5 : 1)) enter(it);
+        };
+        auto tile_lo = [&](f32x16 &cur, f32x16 &nxt, uint32_t (&hc)[8], uint32_t (&rc)[8], uint32_t (&hp)[8], uint32_t (&rp)[8], auto first_tag) __attribute__((always_inline)) {
+          constexpr bool FIRST = decltype(first_tag)::value;
+          const auto started = [&](auto g_tag) __attribute__((always_inline)) {
+            if constexpr (FIRST && decltype(g_tag)::value == 3) settle_reads(), first_landed();
+            if constexpr (KBW == 1) entered(g_tag);
+          };
+          if constexpr (KBW == 2) {
+            block_lo(cur, nxt, hc, rc, hp, rp, k_at(it), k_at(it + 1), v_at(it + 3), v_at(it), blk0, std::bool_constant<!FIRST>{}, started);
+            block_lo(nxt, cur, hp, rp, hc, rc, k_at(it + 1), k_at(it + 1), v_at(it), v_at(it), blk1, std::true_type{}, entered);
+          } else {
+            block_lo(cur, nxt, hc, rc, hp, rp, k_at(it + 1), k_at(it + 2), v_at(it + 3), v_at(it), blk0, std::bool_constant<!FIRST>{}, started);
+          }
+        };
+        // the output of the last block computed; va: its V, read anew (a copy of a register whose read is in flight would be made
+        // ahead of any wait)
+        auto drain = [&](uint32_t va, const bf16x8 (&ph)[2], const bf16x8 (&pr)[2]) __attribute__((always_inline)) {
+          settle_reads();
+          s16x4 a[4], c[4];
+          auto read = [&](auto g_tag) __attribute__((always_inline)) {
+            constexpr int g = decltype(g_tag)::value, d = g % 4;
+            lds_read_v<BLK + (g / 4) * S2OFF + d * 64>(a[d], v_of(va, d));
+            lds_read_v<BLK + (g / 4) * S2OFF + V8 + d * 64>(c[d], v_of(va, d));
+          };
+          auto product = [&](int d, const bf16x8 &x) __attribute__((always_inline)) {
+            oacc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(bf16x8, __builtin_shufflevector(a[d], c[d], 0, 1, 2, 3, 4, 5, 6, 7)), x, oacc[0][d], 0, 0, 0);
+          };
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2) {
+            if (s2 == 0) half(read, std::false_type{});
+            else half(read, std::true_type{});
+            lds_wait(a[0], a[1], a[2], a[3]), lds_wait(c[0], c[1], c[2], c[3]);
+#pragma unroll
+            for (int d = 0; d < ND; ++d) product(d, ph[s2]);
+            if (rest)
+#pragma unroll
+              for (int d = 0; d < ND; ++d) product(d, pr[s2]);
+          }
+        };
+        auto tile = [&](f32x16 &cur, f32x16 &nxt, bf16x8 (&pc)[2], bf16x8 (&pp)[2], auto pv_tag) __attribute__((always_inline)) {
+          if constexpr (KBW == 2) {
+            block(cur, nxt, pc, pp, k_at(it), k_at(it + 1), v_at(it + 3), v_at(it), blk0, pv_tag, nothing);
+            block(nxt, cur, pp, pc, k_at(it + 1), k_at(it + 1), v_at(it), v_at(it), blk1, std::true_type{}, entered);
+          } else {
+            block(cur, nxt, pc, pp, k_at(it + 1), k_at(it + 2), v_at(it + 3), v_at(it), blk0, pv_tag, entered);
+          }
+        };
+        bf16x8 ph[2], pr[2];
+        if constexpr (KBW == 2) {
+          tile_lo(sA, sB, hA, rA, hB, rB, std::true_type{});
+          for (++it; it < lo_end; ++it) tile_lo(sA, sB, hA, rA, hB, rB, std::false_type{});
+        } else {
+          static_assert(KBW == 2 || C::LO_TILES % 2 == 0, "");
+          tile_lo(sA, sB, hA, rA, hB, rB, std::true_type{});
+          for (;;) {
+            if (++it == lo_end) {
+#pragma unroll
+              for (int i = 0; i < 8; ++i) hB[i] = hA[i], rB[i] = rA[i];
+              break;
+            }
+            tile_lo(sB, sA, hB, rB, hA, rA, std::false_type{});
+            if (++it == lo_end) break;
+            tile_lo(sA, sB, hA, rA, hB, rB, std::false_type{});
+          }
+        }
+        operands(hB, ph), operands(rB, pr);
+        drain(v_at(it - 1), ph, pr);
+        if (it < n_full) {
+          if constexpr (KBW == 2) {
+            tile(sA, sB, pA, pB, std::false_type{});
+            for (++it; it < n_full; ++it) tile(sA, sB, pA, pB, std::true_type{});
+          } else {
+            tile(sA, sB, pA, pB, std::false_type{});
+            for (;;) {
+              if (++it == n_full) {
+                pB[0] = pA[0], pB[1] = pA[1];
+                break;
+              }
+              tile(sB, sA, pB, pA, std::true_type{});
+              if (++it == n_full) break;
+              tile(sA, sB, pA, pB, std::true_type{});
+            }
+          }
+          rest = false;
+          drain(v_at(it - 1), pB, pr);
+        }
+      }
+      // the partial cache tile and the tree's keys: queued long ago
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      __builtin_amdgcn_s_barrier();
+      for (; it < n_tiles; ++it) compute_tile(it, it >= n_ct, std::true_type{});
+    }
+  } else if constexpr (C::STEADY) {
+    if (n_full >= kSteadyTiles) {
+      // ---- the steady part of the loop: full cache tiles that queue full cache tiles.  One address per tile and operand, carried
+      // along in scalar registers (dense), or one multiply-add per load on its page's number (paged); every wait is a constant ----
+      int64_t row_off[NLDK];  // bytes from a tile's first row to the row of (load instruction j, lane 0)
+#pragma unroll
+      for (int j = 0; j < NLDK; ++j) row_off[j] = (int64_t)((wave * NLDK + j) * LPI) * p.stride_tok * EB;
+      const char *k_next = kc_bytes + (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
+      const char *v_next = vc_bytes + (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
+      const int64_t tile_bytes = (int64_t)TK * p.stride_tok * EB;
       auto issue_steady = [&](int t) __attribute__((always_inline)) {
         lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
         if constexpr (PAGED) {
@@ -1329,9 +1605,16 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         for (; it + PD < n_full; ++it) step_steady(it);
     }
   }
-  for (; it < n_full; ++it) step(it, std::false_type{}, std::false_type{});
-  for (; it < n_ct; ++it) step(it, std::true_type{}, std::false_type{});   // the partial cache tile
-  for (; it < n_tiles; ++it) step(it, std::true_type{}, std::true_type{});  // the tree's own keys
+  if (!C::PIPED || !piped) {
+    for (; it < n_full; ++it) step(it, std::false_type{}, std::false_type{});
+    for (; it < n_ct; ++it) step(it, std::true_type{}, std::false_type{});   // the partial cache tile
+    for (; it < n_tiles; ++it) step(it, std::true_type{}, std::true_type{});  // the tree's own keys
+  }
+  if constexpr (C::PIPED && PAGED) {
+    const const_args late = late_args();
+    p.G = late->G, p.g_magic = late->g_magic, p.g_bits = late->g_bits, p.Hq = late->Hq, p.sum_Q = late->sum_Q, p.n_chunks = late->n_chunks;
+    p.out = late->out, p.lse = late->lse, p.part_out = late->part_out, p.part_lse = late->part_lse, p.v_scale = late->v_scale;
+  }
   if constexpr (PAGED) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the last (unused) table entries have landed
   __builtin_amdgcn_s_barrier();  // all waves are done reading the ring before it is reused below
   TL_STAMP(4);  // all tiles done
@@ -1870,7 +2153,7 @@ hipError_t dispatch_variant(int variant, const AttnParams &p, dim3 grid, hipStre
   switch (variant) {
     case V_W8: return launch_attn<D, 8, 1, 1, PAGED, 4>(p, grid, st);
     case V_M4K2: return launch_attn<D, 4, 2, 1, PAGED, 4>(p, grid, st);
-    case V_M2K2_3: return launch_attn<D, 2, 2, 1, PAGED, 3>(p, grid, st);
+    case V_M2K2_3: return launch_attn<D, 2, 2, 1, PAGED, D == 128 ? 4 : 3>(p, grid, st);
     case V_K2: return launch_attn<D, 1, 2, 1, PAGED, 2>(p, grid, st);
     default: return launch_attn<D, 2, 2, 1, PAGED, 2>(p, grid, st);  // V_M2K2
   }

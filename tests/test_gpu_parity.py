@@ -614,6 +614,32 @@ def test_spikes_in_every_part_of_the_pipelined_loop_match_oracle(gpu, tiles, pag
             base.k_cache[at] = kept
 
 
+@pytest.mark.parametrize("shape,page_size,first", [(5, 0, 5), (5, 16, 5), (4, 0, 15), (3, 0, 14)])
+def test_ends_of_the_pipelined_loop_match_oracle(gpu, shape, page_size, first):
+    """D = 128: the last number of full tiles that runs without the pipelined loop, the first ones that run with it (tiles queued by
+    its prologue, from its loop and past its end; odd and even counts), with and without a tile begun, before trees of one and
+    two tiles; scaled keys in the first block, where the prepared low-order pass ends and
+    in the last one.  Tolerances are the task's."""
+    import torch
+    G = {5: 8, 4: 4, 3: 2}[shape]
+    for tiles in (first - 1, first, first + 1, first + 2):
+        for more, T in ((0, 1), (1, 40), (63, 65), (17, 128)):
+            L = 64 * tiles + more
+            w = wl.random_workload(1700 + shape + tiles + more + page_size, 2, 2 * G, 2, 128, [L, L - 30], [T, max(1, T // 2)], page_size=page_size)
+            for block, factor in ((0, 8.0), (6, 12.0), (7, 12.0), (2 * tiles - 1, 12.0)):
+                key = 32 * block + 11
+                at = (int(w.cu_L[0]) + key,) if page_size == 0 else (int(w.page_table[0, key // page_size]), key % page_size)
+                x = (w.k_cache[at].astype(np.uint32) << 16).view(np.float32) * np.float32(factor)
+                w.k_cache[at] = ((x.view(np.uint32) + 0x8000) >> 16).astype(np.uint16)
+            ro, rl = orc.tree_verify_attn(w)
+            dw = gpu.to_device(w)
+            say(f"[case] pipelined loop's ends shape={shape} page_size={page_size} tiles={tiles} more={more} T={T}")
+            o, l = gpu.attention(dw, gpu.build_mask(dw), num_splits=1, plan_shape=shape)
+            torch.cuda.synchronize()
+            assert np.abs(o.cpu().numpy().astype(np.float64) - ro).max() <= TOL_O
+            assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
+
+
 @pytest.mark.parametrize("shape", [3, 4, 5])
 def test_filled_splits_first_is_a_permutation(gpu, shape):
     """Split launches of more workgroups than the chip holds put the splits that the host's lengths fill first: true
