@@ -1983,6 +1983,8 @@ void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
 }
 
 
+inline bool dense_wide(const tva_args *a) { return a->D == 128 && !a->kv_fp8 && !a->page_table; }
+
 // A launch's duration as a model of it says, in us: fitted to 9650 timed launches (2000 calls in every shape: B = 1 .. 64,
 // 64 .. 32768 keys, 4 .. 576 rows per KV head, D = 64 and 128, dense and paged, both storage types, equal and unequal lengths);
 // over 4837 others its error had a standard deviation of 9 %.  The kernels have become faster since, paged ones most: 500
@@ -1991,6 +1993,8 @@ void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
 // takes (tiles of the longest split) x (time per tile), more where two share a CU; workgroups beyond whole rounds take a part
 // of one more, more than half of it however few they are; every round starts and drains; the launch takes no less than
 // its bytes at the rate the shape streams; with splits there is a merge pass.
+// Where the deep 64-row shape's loop is pipelined (dense_wide, PIPE_TILES) its tile is 0.85 of that, which is most of what it gained.
+// The eight-wave shapes' tiles stay as fitted: at 0.95 a few more calls moved between those two, for 0.1 % in the mean.
 double plan_cost(const tva_args *a, const Plan &pl) {
   struct Shape {
     double tile, fixed, round, d64, f8, paged, tb_s, tb_s8;
@@ -2011,6 +2015,7 @@ double plan_cost(const tva_args *a, const Plan &pl) {
   if (a->kv_fp8) tile *= s.f8;
   if (a->page_table) tile *= s.paged;
   const int longest = pl.n_chunks > 1 ? pl.chunk_keys / pl.TK : (a->max_L + pl.TK - 1) / pl.TK, own = (a->max_T + pl.TK - 1) / pl.TK;
+  if (pl.variant == V_M2K2_3 && dense_wide(a) && longest >= 14) tile *= 0.85;
   const double tiles = longest + own * (pl.n_chunks > 1 ? 0.89 : 1.0);
   double rounds = wgs > holds ? wgs / holds : 1.0;
   const double whole = std::floor(rounds), part = rounds - whole;
@@ -2073,10 +2078,14 @@ bool make_plan(const tva_args *a, Plan *pl) {
   // pairs or 4096 keys.  3000 calls timed in every shape: 509 take another one than the rules', 13 % faster in the geometric
   // mean, six of them more than 2 % slower (8 % at worst).  Against the best of the five shapes in each call the rules lose
   // 4.8 %, with the model 2.3 %.  Unsplit launches of 33 .. 64 sequences of few rows keep their shape: there the lengths
-  // only place the workgroups (fill_slots).
+  // only place the workgroups (fill_slots).  Dense calls with D = 128 and 16-bit K/V are asked about from 65 rows on without the
+  // lengths too (up to 80 rows: above 128 pairs or 4096 keys, where 14 calls take another shape and 23 % less time), and leave
+  // the 64-row shape for 5 %: of 907 drawn ones 62 change shape, 12 % faster in the mean, one of them more than 2 % slower (8 %);
+  // against the best shape in each they lost 3.2 %, now 2.4.
   const bool placed_only = a->Hkv == 8 && a->B > 32 && a->B <= 64 && rows <= 64;
   // (Nor does the draft stage's attention ask: few of a tree's nodes are queries there, which the fit has not seen.)
-  const bool ask = a->cu_Q ? false : a->L_host ? !placed_only : rows > 80 && (pairs > 64 || a->max_L > 4096);
+  const bool long_ones = a->max_L > 4096;
+  const bool ask = a->cu_Q ? false : a->L_host ? !placed_only : rows > 80 ? pairs > 64 || long_ones : dense_wide(a) && rows > 64 && (pairs > 128 || long_ones);
   if (!forced && ask && a->max_L > 0 && a->num_splits == 0) {
     tva_args shapes = *a;  // (the lengths shorten the splits of a shape, they do not choose it)
     shapes.sum_L = 0, shapes.L_host = nullptr;
@@ -2087,7 +2096,7 @@ bool make_plan(const tva_args *a, Plan *pl) {
     // where nearly every smaller promise was kept, more where one of 12 % was missed by 30.
     auto enough = [&](int v) {
       if (variant == V_K2) return 0.98;
-      if (variant == V_M4K2) return 0.95;
+      if (variant == V_M4K2 || (variant == V_M2K2 && dense_wide(a))) return 0.95;
       if (variant == V_W8 && a->kv_fp8) return 0.85;
       // (D = 64, dense: of the 256-row shape a CU holds one workgroup)
       if (variant == V_W8 && (a->D == 64 ? !a->page_table : v == V_M2K2)) return 0.98;
@@ -2096,6 +2105,14 @@ bool make_plan(const tva_args *a, Plan *pl) {
     // No shape whose partial rows need more than the library's own scratch array where the rules' plan does not: a call
     // without a workspace (tva_tree_verify_attn_static) is refused for its size only where it always was.
     const size_t own = TVA_STATIC_SCRATCH_BYTES, most = std::max(scratch_bytes(a, plan), own);
+    // Dense deep 64-row shape, lengths known: not where the splits they shorten are more than the chip holds at once, the empty ones
+    // among them (4 sequences of 13 .. 20 K keys as 320 workgroups took 70 us instead of 59).
+    auto crowded = [&](int v) {
+      if (v != V_M2K2_3 || !dense_wide(a) || !a->L_host) return false;
+      Plan own_lengths;
+      plan_splits_of(a, v, true, &own_lengths);
+      return own_lengths.n_chunks > 1 && (int64_t)pairs * own_lengths.n_row_blocks * own_lengths.n_chunks > 256;
+    };
     double best = 0.0;
     int chosen = -1;
     const int first = rows <= 64 ? V_K2 : V_M2K2, last = rows <= 32 ? V_M2K2 : V_LAST;
@@ -2104,7 +2121,7 @@ bool make_plan(const tva_args *a, Plan *pl) {
       if (v == variant || (a->kv_fp8 && (v == V_M2K2_3 || (v == V_M2K2 && rows > 64)))) continue;
       plan_splits_of(&shapes, v, true, &plan);
       const double us = plan_cost(&shapes, plan);
-      if (us < enough(v) * rules && (chosen < 0 || us < best) && scratch_bytes(a, plan) <= most) best = us, chosen = v;
+      if (us < enough(v) * rules && (chosen < 0 || us < best) && scratch_bytes(a, plan) <= most && !crowded(v)) best = us, chosen = v;
     }
     if (chosen >= 0) {
       // (splits that the lengths shorten are more splits: where those pass the limit they keep their length)

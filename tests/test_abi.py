@@ -289,6 +289,33 @@ def test_host_lengths_give_the_shortest_split_that_fits_one_round(lib):
         assert ck % 64 == 0 and ck >= 1024 and binding.plan_splits(d) == -(-int(L.max()) // ck)
 
 
+@pytest.mark.parametrize("kw,rows,splits", [
+    # 64 and 65 .. 80 rows per KV head without the lengths: at most 128 pairs and 4096 keys, more of either, paged, 8-bit, D = 64
+    (dict(B=64, max_L=1024, max_T=16), 64, 1), (dict(B=64, max_L=1024, max_T=18), 128, 1),
+    (dict(B=4, max_L=4096, max_T=18), 64, 8), (dict(B=3, max_L=32768, max_T=20), 128, 10),
+    (dict(B=64, max_L=1024, max_T=18, page_table=8, page_size=16), 64, 1), (dict(B=64, max_L=1024, max_T=18, kv_fp8=1), 64, 1),
+    (dict(B=64, max_L=1024, max_T=18, D=64), 64, 1),
+])
+def test_dense_wide_calls_ask_the_model_from_65_rows_on(lib, kw, rows, splits):
+    kw = {"Hkv": 8, **kw, "sum_T": kw["B"] * kw["max_T"]}
+    a = shape_args(**kw)
+    assert (binding.plan_workgroup_rows(a), binding.plan_splits(a)) == (rows, splits)
+    own = binding.plan_splits(shape_args(**kw, plan_shape=2))
+    rules = own * a.sum_T * 32 * (a.D + 1) * 4 if own > 1 else 0
+    assert binding.workspace_bytes(a) <= max(rules, binding.STATIC_SCRATCH_BYTES)
+
+
+@pytest.mark.parametrize("L,splits", [([13136, 15486, 17835, 20185], 19), ([2141 + 22 * i for i in range(30)], 1)])
+def test_deep_shape_is_not_taken_for_more_split_workgroups_than_fit(lib, L, splits):
+    import numpy as np
+    L = np.array(L, np.int32)
+    B = len(L)
+    T, Hq = (31, 16) if B == 4 else (6, 64)
+    a = shape_args(B=B, Hq=Hq, max_L=int(L.max()), max_T=T, sum_T=B * T, sum_L=int(L.sum()))
+    a.L_host = L.ctypes.data_as(ctypes.c_void_p)
+    assert (binding.plan_workgroup_rows(a), binding.plan_splits(a)) == (64, splits)
+
+
 def test_slot_table_is_a_permutation_that_pairs_long_with_short(lib):
     """tva_args.L_host in an unsplit launch of 33 .. 64 sequences, 8 KV heads, at most 64 rows per KV head: the slot
     table is a permutation of the sequences whatever the lengths are (ties, zeros, nonsense); slots j and j + 32
