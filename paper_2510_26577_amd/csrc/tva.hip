@@ -2079,9 +2079,10 @@ bool make_plan(const tva_args *a, Plan *pl) {
   // mean, six of them more than 2 % slower (8 % at worst).  Against the best of the five shapes in each call the rules lose
   // 4.8 %, with the model 2.3 %.  Unsplit launches of 33 .. 64 sequences of few rows keep their shape: there the lengths
   // only place the workgroups (fill_slots).  Dense calls with D = 128 and 16-bit K/V are asked about from 65 rows on without the
-  // lengths too (up to 80 rows: above 128 pairs or 4096 keys, where 14 calls take another shape and 23 % less time), and leave
-  // the 64-row shape for 5 %: of 907 drawn ones 62 change shape, 12 % faster in the mean, one of them more than 2 % slower (8 %);
-  // against the best shape in each they lost 3.2 %, now 2.4.
+  // lengths too (up to 80 rows: above 128 pairs or 4096 keys, where 12 calls take another shape and 26 % less time), and leave
+  // the 64-row shape for its deep ring for 5 %: of 907 drawn ones 38 change shape, 13 % faster in the mean, one of them more than 2 %
+  // slower (5 %); against the best shape in each they lost 3.2 %, now 2.6.  (5 % for the eight-wave shapes too: 62 change, 12 %
+  // faster, but of seven newly drawn ones three were 2.5 .. 5 % slower, three 15 .. 23 % faster.)
   const bool placed_only = a->Hkv == 8 && a->B > 32 && a->B <= 64 && rows <= 64;
   // (Nor does the draft stage's attention ask: few of a tree's nodes are queries there, which the fit has not seen.)
   const bool long_ones = a->max_L > 4096;
@@ -2096,7 +2097,7 @@ bool make_plan(const tva_args *a, Plan *pl) {
     // where nearly every smaller promise was kept, more where one of 12 % was missed by 30.
     auto enough = [&](int v) {
       if (variant == V_K2) return 0.98;
-      if (variant == V_M4K2 || (variant == V_M2K2 && dense_wide(a))) return 0.95;
+      if (variant == V_M4K2 || (variant == V_M2K2 && v == V_M2K2_3 && dense_wide(a))) return 0.95;
       if (variant == V_W8 && a->kv_fp8) return 0.85;
       // (D = 64, dense: of the 256-row shape a CU holds one workgroup)
       if (variant == V_W8 && (a->D == 64 ? !a->page_table : v == V_M2K2)) return 0.98;
