@@ -1210,6 +1210,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           issue_v(t + 3);
           issue_k(t + 3 + LEAD);
         } else {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           if (left > 2 + LEAD) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS));
           else if (left > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NLDK));
           else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -1231,12 +1232,16 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       bf16x8 pA[2], pB[2];    // their probabilities
 #pragma unroll
       for (int i = 0; i < 4; ++i) vl[i] = vh[i] = s16x4{0, 0, 0, 0};
-      // Waits for all of them (as operands: none is elsewhere by then).  Until its wait the compiler takes such a register as
-      // written although the value is still to come, so nothing but the groups below may stand between a read and its
-      // wait: every other way on starts with this one.
+      // Waits for all of them; what follows takes them as written here.  Until its wait the compiler takes such a register as written
+      // although the value is still to come, so nothing but the groups below and the barrier of a tile that queues full tiles may stand
+      // between a read and its wait: every other way on starts with this one, and every loop is entered and left at one place.
+      // (A loop over pairs of blocks that could be left between the two had its operands in other registers on either way out: a
+      // statement on one of them, and they were copied and spilled in flight.)
       auto settle_reads = [&]() __attribute__((always_inline)) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::"v"(kr[0]), "v"(kr[1]), "v"(kr[2]), "v"(kr[3]), "v"(vl[0]), "v"(vl[1]), "v"(vl[2]), "v"(vl[3]),
-                     "v"(vh[0]), "v"(vh[1]), "v"(vh[2]), "v"(vh[3])
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(kr[0]), "+v"(kr[1]), "+v"(kr[2]), "+v"(kr[3]), "+v"(vl[0]), "+v"(vl[1]), "+v"(vl[2]), "+v"(vl[3]), "+v"(vh[0]),
+                       "+v"(vh[1]), "+v"(vh[2]), "+v"(vh[3])
+                     :
                      : "memory");
       };
       const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
@@ -1461,7 +1466,6 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         for (; it < n_full; ++it) enter(it);
       } else {
         m_run[0] = block_max(sA), use_reference(0), set_cap(0);
-        const int lo_end = C::LO_TILES < n_full ? C::LO_TILES : n_full;
         const auto nothing = [&](auto) __attribute__((always_inline)) {};
         // (two key groups: once the reads of the K and V given up are behind it; one: in the second block)
         const auto entered = [&](auto g_tag) __attribute__((always_inline)) {
@@ -1515,44 +1519,44 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           }
         };
         bf16x8 ph[2], pr[2];
+        static_assert(!C::PIPED || C::PIPE_TILES >= C::LO_TILES + (KBW == 2 ? 2 : 3), "every loop runs");
         if constexpr (KBW == 2) {
           tile_lo(sA, sB, hA, rA, hB, rB, std::true_type{});
-          for (++it; it < lo_end; ++it) tile_lo(sA, sB, hA, rA, hB, rB, std::false_type{});
+          for (++it; it < C::LO_TILES; ++it) tile_lo(sA, sB, hA, rA, hB, rB, std::false_type{});
+          operands(hB, ph), operands(rB, pr);
+          drain(v_at(it - 1), ph, pr);
+          tile(sA, sB, pA, pB, std::false_type{});
+          ++it;
+          do {
+            tile(sA, sB, pA, pB, std::true_type{});
+          } while (++it < n_full);
         } else {
+          // (blocks take the two sets of registers in turn: one block more or less of the first ones leaves the others an odd number)
           static_assert(KBW == 2 || C::LO_TILES % 2 == 0, "");
           tile_lo(sA, sB, hA, rA, hB, rB, std::true_type{});
-          for (;;) {
-            if (++it == lo_end) {
+          do {
+            ++it, tile_lo(sB, sA, hB, rB, hA, rA, std::false_type{});
+            ++it, tile_lo(sA, sB, hA, rA, hB, rB, std::false_type{});
+          } while (it < C::LO_TILES - 2);
+          settle_reads();
+          if ((n_full & 1) != 0) {
+            ++it, tile_lo(sB, sA, hB, rB, hA, rA, std::false_type{});
+            settle_reads();
 #pragma unroll
-              for (int i = 0; i < 8; ++i) hB[i] = hA[i], rB[i] = rA[i];
-              break;
-            }
-            tile_lo(sB, sA, hB, rB, hA, rA, std::false_type{});
-            if (++it == lo_end) break;
-            tile_lo(sA, sB, hA, rA, hB, rB, std::false_type{});
+            for (int i = 0; i < 8; ++i) hA[i] = hB[i], rA[i] = rB[i];
+            sB = sA;
           }
+          operands(hA, ph), operands(rA, pr);
+          drain(v_at(it), ph, pr);
+          ++it, tile(sB, sA, pB, pA, std::false_type{});
+          do {
+            ++it, tile(sA, sB, pA, pB, std::true_type{});
+            ++it, tile(sB, sA, pB, pA, std::true_type{});
+          } while (it + 1 < n_full);
+          ++it;
         }
-        operands(hB, ph), operands(rB, pr);
-        drain(v_at(it - 1), ph, pr);
-        if (it < n_full) {
-          if constexpr (KBW == 2) {
-            tile(sA, sB, pA, pB, std::false_type{});
-            for (++it; it < n_full; ++it) tile(sA, sB, pA, pB, std::true_type{});
-          } else {
-            tile(sA, sB, pA, pB, std::false_type{});
-            for (;;) {
-              if (++it == n_full) {
-                pB[0] = pA[0], pB[1] = pA[1];
-                break;
-              }
-              tile(sB, sA, pB, pA, std::true_type{});
-              if (++it == n_full) break;
-              tile(sA, sB, pA, pB, std::true_type{});
-            }
-          }
-          rest = false;
-          drain(v_at(it - 1), pB, pr);
-        }
+        rest = false;
+        drain(v_at(it - 1), pB, pr);
       }
       // the partial cache tile and the tree's keys: queued long ago
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));

@@ -51,7 +51,7 @@ def lgkm_wait(code, i):
     return int(m[1]) if m else None
 
 
-def in_flight(code):
+def in_flight(code, reads=r"ds_(read|bpermute|permute|swizzle)"):
     """Per instruction: {register: LDS operations issued after its read}, the fewest over all ways there (LDS answers in order,
     so a wait that leaves n outstanding has seen every read with n or more behind it).  And the instructions that touch one."""
     state, touched, work = [None] * len(code), set(), [0]
@@ -69,7 +69,7 @@ def in_flight(code):
                 touched.add(i)
             if op.startswith("ds_"):
                 now = {r: n + 1 for r, n in now.items()}
-                if re.match(r"ds_(read|bpermute|permute|swizzle)", op):
+                if re.match(reads, op):
                     now.update((r, 0) for r in registers(args.split(",")[0]))
         for s in follow(code, i):
             old = state[s]
@@ -143,16 +143,15 @@ def test_no_kernel_touches_a_register_whose_read_is_in_flight(kernels):
         assert not touched, (name, [code[i][:2] for i in sorted(touched)][:4])
 
 
-def test_the_pipelined_loop_waits_for_its_reads_wherever_it_is_left(kernels):
-    """The 256-row shape with D = 128 and 16-bit K/V, dense and paged: 32 registers of operands are in flight there; its other
-    branches meet 16 at most."""
+@pytest.mark.parametrize("shape", ["8ELi1ELi1ELb0", "8ELi1ELi1ELb1", "4ELi2ELi1ELb0", "2ELi2ELi1ELb0"])
+def test_the_pipelined_loop_waits_for_its_reads_wherever_it_is_left(kernels, shape):
+    """The 256-row shape with D = 128 and 16-bit K/V, dense and paged, the 128-row and the deep 64-row shape dense: 24 to 32 registers of
+    operands of both products are in flight there; the branches of a tile's barrier meet 16, others reads of one kind."""
+    (name, code), = [(n, c) for n, c in kernels.items() if f"attn_kernelILi128ELi{shape}ELi4ELb0E" in n]
+    state, of_v = in_flight(code)[0], in_flight(code, r"ds_read_b64_tr_b16")[0]
     seen = 0
-    for name, code in kernels.items():
-        if not re.search(r"attn_kernelILi128ELi8ELi1ELi1ELb[01]ELi4ELb0E", name):
-            continue
-        state = in_flight(code)[0]
-        for i, (op, _, to) in enumerate(code):
-            if op.startswith("s_cbranch") and len(state[i]) >= 24:
-                assert waits_first(code, to), (name, code[i], to)
-                seen += 1
-    assert seen >= 2 * 4, seen  # out of the two blocks of the first tile and of the loop's
+    for i, (op, _, to) in enumerate(code):
+        if op.startswith("s_cbranch") and len(state[i]) >= 24 and of_v[i]:
+            assert waits_first(code, to), (name, code[i], to)
+            seen += 1
+    assert seen >= 4, seen  # out of the blocks of the first tile and of the loops'
