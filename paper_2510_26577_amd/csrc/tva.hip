@@ -227,12 +227,14 @@ struct AttnCfg {
   static constexpr bool STEADY = WK == 1 && !KV8;
   // Splits of PIPE_TILES full tiles and more run a loop that is a software pipeline over 32-key blocks.  LEAD: tiles that K is
   // fetched further ahead than V; the blocks of the first LO_TILES tiles come with the low-order pass ready.  With / without it,
-  // 1 .. 32 sequences unsplit: 256-row shape 0.98 at 6 full tiles, 0.92 at 12 and 16, 0.96 at 32, dense and paged alike; 128-row
-  // shape dense 1.04 at 6, 1.01 at 12, 0.98 at 16, 0.92 at 32; deep 64-row shape dense 1.02 at 12, 0.98 at 15, 0.89 at 32.  Paged, the
+  // 1 .. 32 sequences unsplit: 256-row shape 0.98 at 6 full tiles, 0.92 at 12 and 16, 0.96 at 32, dense and paged alike; deep
+  // 64-row shape dense 1.02 at 12, 0.98 at 15, 0.89 at 32.  128-row shape dense, 1950 drawn calls, split and unsplit: 1.000 at 18
+  // and 19 tiles, where one in nine is 2 .. 4 % slower, 0.987 at 20 (one in 22), 0.98 from 22 on, 0.964 beyond 33; of more rows than
+  // one workgroup has, where keys are read more than once (PIPE_TILES_ROWS), 1.00 at 16, 0.985 at 18, 0.97, 0.96 and 0.89.  Paged, the
   // two last lost up to 6 % below 27 tiles (K's and V's rows are each looked up, at one block per tile) and gain 2 % at 32: without.
   static constexpr bool PIPED = D == 128 && !KV8 && NST == 4 && (WK == 1 || !PAGED);
   static constexpr int LEAD = KBW == 1 ? 2 : 1, LO_TILES = KBW == 1 ? 6 : 3;
-  static constexpr int PIPE_TILES = KBW == 2 ? 5 : WM == 4 ? 15 : 14;
+  static constexpr int PIPE_TILES = KBW == 2 ? 5 : WM == 4 ? 22 : 14, PIPE_TILES_ROWS = KBW == 1 && WM == 4 ? 17 : PIPE_TILES;
   // m_use (in the kernel) is kept from block to block, or derived in each from the reference: kept, launches are 0.5 %
   // faster, but 1 % slower where 8-bit tiles are widened through LDS, and the paged 256-row shape with D = 64 has no
   // register for it
@@ -1025,7 +1027,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 
   // ---- the pipelined loop's loads: K and V of a tile apart ----
   constexpr int LEAD = C::LEAD, KOPS = NLDK + C::NPG;
-  const bool piped = C::PIPED && n_full >= C::PIPE_TILES && (PAGED ? small_pages : (uint64_t)tok_bytes < (1u << 24)) &&
+  const bool piped = C::PIPED && n_full >= (R > BM ? C::PIPE_TILES_ROWS : C::PIPE_TILES) && (PAGED ? small_pages : (uint64_t)tok_bytes < (1u << 24)) &&
                      (int64_t)p.Hkv * D * EB < (1 << 24);
   const bool tree_apart = p.k_tree != nullptr;
   // full cache tiles.  Dense: an address per operand, carried along from tile to tile in scalar registers, and the lane's offset
@@ -1198,29 +1200,40 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       static_assert(!C::PIPED || (RB == 1 && NS == 8 && ND == 4 && KBW <= 2), "");
       constexpr int V8 = 8 * PV, S2OFF = ROWB, BLK = KBW == 2 ? 2 * ROWB : 0;
       // In tile t: K of tile t + LEAD - 1 and V of tile t - 1 have been read everywhere, so their places take K and V of NSTAGE tiles
-      // later, where those exist; and K of tile t + LEAD + 1 and V of tile t + 1 have landed everywhere for the tile that
-      // follows.  Queued behind them are V of tile t + 2 and K of tile t + LEAD + 2, where those exist.
+      // later, where those exist.  And what is read from here on has landed everywhere: with two blocks per tile K of tile t + 2 and V of
+      // tile t + 1; with one K of tile t + 2 and V of tile t, whose first reads stand right behind.  So three tiles are in flight there, as
+      // in the plain loop.  (One group later, behind those reads, each had to land a tile earlier: two in flight, and calls of the
+      // 128-row shape bound by their reads took up to 10 % longer than in the plain loop.)
       static_assert(!C::PIPED || NSTAGE == 4, "");
       auto enter = [&](int t) __attribute__((always_inline)) {
-        asm volatile("s_waitcnt lgkmcnt(6)" ::: "memory");  // (two key groups: the reads since those of the K and V given up)
+        // (two blocks: but for the reads since those of the K and V given up)
+        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(KBW == 1 ? 0 : 6) : "memory");
         const int left = n_tiles - t;
         if (__builtin_expect(n_full - t > 3 + LEAD, 1)) {
-          __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS));
+          __builtin_amdgcn_s_waitcnt(vmcnt_imm((KBW == 1 ? 2 : 1) * C::TILE_OPS));
           __builtin_amdgcn_s_barrier();
           issue_v(t + 3);
           issue_k(t + 3 + LEAD);
         } else {
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-          if (left > 2 + LEAD) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS));
-          else if (left > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NLDK));
-          else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+          if constexpr (KBW == 1) {  // queued behind them: V(t+1) K(t+3) V(t+2) K(t+4), where those exist
+            if (left > 4) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * NLDK));
+            else if (left == 4) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * NLDK));
+            else if (left == 3) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NLDK));
+            else if (left == 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NLDK));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+          } else {  // V(t+2) K(t+3)
+            if (left > 2 + LEAD) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::TILE_OPS));
+            else if (left > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NLDK));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+          }
           __builtin_amdgcn_s_barrier();
           if (t + 3 < n_full) issue_v(t + 3);
           else if (left > 3) issue_rest(t + 3, std::true_type{});
           if (left > 3 + LEAD) issue_rest(t + 3 + LEAD, std::false_type{});
         }
       };
-      // in the first tile, ahead of the first read of its V and of K of tile LEAD
+      // (two blocks) in the first tile, ahead of the first read of its V and of K of the next one
       auto first_landed = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * KOPS + 2 * NLDK));
         __builtin_amdgcn_s_barrier();
@@ -1296,12 +1309,13 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       };
       // group g of a step: K operand g of the next block, two of this block's probabilities, the read of K operands four groups on
       // (of the next block, or the first ones of the block after it)
-      auto group_head = [&](auto g_tag, auto wait_tag, const f32x16 &cur, f32x16 &nxt, uint32_t ka1, uint32_t ka2, auto kb_tag, float &e0, float &e1) __attribute__((always_inline)) {
+      auto group_head = [&](auto g_tag, auto wait_tag, const f32x16 &cur, f32x16 &nxt, uint32_t ka1, uint32_t ka2, auto kb_tag, float &e0, float &e1, auto &&middle) __attribute__((always_inline)) {
         constexpr int g = decltype(g_tag)::value, d = g % 4, kb = decltype(kb_tag)::value;
         lds_wait_n<decltype(wait_tag)::value>(kr[d], vl[d], vh[d]);
         nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[d], qreg[0][g], g == 0 ? zero16 : nxt, 0, 0, 0);
         e0 = fast_exp2(fmaf(cur[2 * g], p.scale_log2, -m_use[0]));
         e1 = fast_exp2(fmaf(cur[2 * g + 1], p.scale_log2, -m_use[0]));
+        if constexpr (g == 4) middle();
         if constexpr (g < 4) lds_read_k<(1 - kb) * BLK + (g + 4) * 32>(kr[d], ka1);
         else lds_read_k<kb * BLK + (g - 4) * 32>(kr[d], ka2);
         __builtin_amdgcn_sched_barrier(0);
@@ -1313,7 +1327,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       // the step of one of the first blocks.  ka1, ka2: where K of the next block and of the one after it are, va1, va2: V of the block
       // before and of this one
       auto block_lo = [&](f32x16 &cur, f32x16 &nxt, uint32_t (&hc)[8], uint32_t (&rc)[8], uint32_t (&hp)[8], uint32_t (&rp)[8],
-                          uint32_t ka1, uint32_t ka2, uint32_t va1, uint32_t va2, auto kb_tag, auto pv_tag, auto &&after) __attribute__((always_inline)) {
+                          uint32_t ka1, uint32_t ka2, uint32_t va1, uint32_t va2, auto kb_tag, auto pv_tag, auto &&middle, auto &&after) __attribute__((always_inline)) {
         constexpr int kb = decltype(kb_tag)::value, HERE = kb * BLK, THERE = (1 - kb) * BLK;
         constexpr bool HASPV = decltype(pv_tag)::value;
         float ls = 0.f;
@@ -1323,7 +1337,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           constexpr int g = decltype(g_tag)::value, d = g % 4;
           float e0, e1;
           // (three reads a group; of K alone before the first)
-          group_head(g_tag, std::integral_constant<int, HASPV ? 9 : g < 4 ? 3 : 3 + 2 * d>{}, cur, nxt, ka1, ka2, kb_tag, e0, e1);
+          group_head(g_tag, std::integral_constant<int, HASPV ? 9 : g < 4 ? 3 : 3 + 2 * d>{}, cur, nxt, ka1, ka2, kb_tag, e0, e1, middle);
           if constexpr (HASPV) pv(d, pp[g / 4]);
           ls += e0;
           ls += e1;
@@ -1364,7 +1378,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       };
       // any later block's step; va1, va2: where V of the block before and of this one are
       auto block = [&](f32x16 &cur, f32x16 &nxt, bf16x8 (&pc)[2], bf16x8 (&pp)[2], uint32_t ka1, uint32_t ka2, uint32_t va1, uint32_t va2,
-                       auto kb_tag, auto pv_tag, auto &&after) __attribute__((always_inline)) {
+                       auto kb_tag, auto pv_tag, auto &&middle, auto &&after) __attribute__((always_inline)) {
         constexpr int kb = decltype(kb_tag)::value, HERE = kb * BLK, THERE = (1 - kb) * BLK;
         constexpr bool HASPV = decltype(pv_tag)::value;
         float ls = 0.f;
@@ -1373,7 +1387,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           constexpr int g = decltype(g_tag)::value, d = g % 4;
           float e0, e1;
           // (three reads a group; of K alone before the first)
-          group_head(g_tag, std::integral_constant<int, HASPV ? 9 : g < 4 ? 3 : 3 + 2 * d>{}, cur, nxt, ka1, ka2, kb_tag, e0, e1);
+          group_head(g_tag, std::integral_constant<int, HASPV ? 9 : g < 4 ? 3 : 3 + 2 * d>{}, cur, nxt, ka1, ka2, kb_tag, e0, e1, middle);
           if constexpr (HASPV) pv(d, pp[g / 4]);
           ls += e0;
           ls += e1;
@@ -1462,26 +1476,27 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         }
       }
       if (!wave_has_rows) {
-        first_landed();
+        if constexpr (KBW == 2) first_landed();
         for (; it < n_full; ++it) enter(it);
       } else {
         m_run[0] = block_max(sA), use_reference(0), set_cap(0);
-        const auto nothing = [&](auto) __attribute__((always_inline)) {};
-        // (two key groups: once the reads of the K and V given up are behind it; one: in the second block)
+        const auto nothing = [&]() __attribute__((always_inline)) {};
+        const auto none = [&](auto) __attribute__((always_inline)) {};
+        // one block per tile: ahead of the first reads from the next tile of K and from this one of V; two: in the second one
+        const auto enter_here = [&]() __attribute__((always_inline)) { enter(it); };
         const auto entered = [&](auto g_tag) __attribute__((always_inline)) {
-          if constexpr (decltype(g_tag)::value == (KBW == 1 ? 5 : 1)) enter(it);
+          if constexpr (decltype(g_tag)::value == 1) enter(it);
         };
         auto tile_lo = [&](f32x16 &cur, f32x16 &nxt, uint32_t (&hc)[8], uint32_t (&rc)[8], uint32_t (&hp)[8], uint32_t (&rp)[8], auto first_tag) __attribute__((always_inline)) {
           constexpr bool FIRST = decltype(first_tag)::value;
-          const auto started = [&](auto g_tag) __attribute__((always_inline)) {
-            if constexpr (FIRST && decltype(g_tag)::value == 3) settle_reads(), first_landed();
-            if constexpr (KBW == 1) entered(g_tag);
-          };
           if constexpr (KBW == 2) {
-            block_lo(cur, nxt, hc, rc, hp, rp, k_at(it), k_at(it + 1), v_at(it + 3), v_at(it), blk0, std::bool_constant<!FIRST>{}, started);
-            block_lo(nxt, cur, hp, rp, hc, rc, k_at(it + 1), k_at(it + 1), v_at(it), v_at(it), blk1, std::true_type{}, entered);
+            const auto started = [&](auto g_tag) __attribute__((always_inline)) {
+              if constexpr (FIRST && decltype(g_tag)::value == 3) settle_reads(), first_landed();
+            };
+            block_lo(cur, nxt, hc, rc, hp, rp, k_at(it), k_at(it + 1), v_at(it + 3), v_at(it), blk0, std::bool_constant<!FIRST>{}, nothing, started);
+            block_lo(nxt, cur, hp, rp, hc, rc, k_at(it + 1), k_at(it + 1), v_at(it), v_at(it), blk1, std::true_type{}, nothing, entered);
           } else {
-            block_lo(cur, nxt, hc, rc, hp, rp, k_at(it + 1), k_at(it + 2), v_at(it + 3), v_at(it), blk0, std::bool_constant<!FIRST>{}, started);
+            block_lo(cur, nxt, hc, rc, hp, rp, k_at(it + 1), k_at(it + 2), v_at(it + 3), v_at(it), blk0, std::bool_constant<!FIRST>{}, enter_here, none);
           }
         };
         // the output of the last block computed; va: its V, read anew (a copy of a register whose read is in flight would be made
@@ -1512,14 +1527,14 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         };
         auto tile = [&](f32x16 &cur, f32x16 &nxt, bf16x8 (&pc)[2], bf16x8 (&pp)[2], auto pv_tag) __attribute__((always_inline)) {
           if constexpr (KBW == 2) {
-            block(cur, nxt, pc, pp, k_at(it), k_at(it + 1), v_at(it + 3), v_at(it), blk0, pv_tag, nothing);
-            block(nxt, cur, pp, pc, k_at(it + 1), k_at(it + 1), v_at(it), v_at(it), blk1, std::true_type{}, entered);
+            block(cur, nxt, pc, pp, k_at(it), k_at(it + 1), v_at(it + 3), v_at(it), blk0, pv_tag, nothing, none);
+            block(nxt, cur, pp, pc, k_at(it + 1), k_at(it + 1), v_at(it), v_at(it), blk1, std::true_type{}, nothing, entered);
           } else {
-            block(cur, nxt, pc, pp, k_at(it + 1), k_at(it + 2), v_at(it + 3), v_at(it), blk0, pv_tag, entered);
+            block(cur, nxt, pc, pp, k_at(it + 1), k_at(it + 2), v_at(it + 3), v_at(it), blk0, pv_tag, enter_here, none);
           }
         };
         bf16x8 ph[2], pr[2];
-        static_assert(!C::PIPED || C::PIPE_TILES >= C::LO_TILES + (KBW == 2 ? 2 : 3), "every loop runs");
+        static_assert(!C::PIPED || C::PIPE_TILES_ROWS >= C::LO_TILES + (KBW == 2 ? 2 : 3), "every loop runs");
         if constexpr (KBW == 2) {
           tile_lo(sA, sB, hA, rA, hB, rB, std::true_type{});
           for (++it; it < C::LO_TILES; ++it) tile_lo(sA, sB, hA, rA, hB, rB, std::false_type{});

@@ -614,7 +614,7 @@ def test_spikes_in_every_part_of_the_pipelined_loop_match_oracle(gpu, tiles, pag
             base.k_cache[at] = kept
 
 
-@pytest.mark.parametrize("shape,page_size,first", [(5, 0, 5), (5, 16, 5), (4, 0, 15), (3, 0, 14)])
+@pytest.mark.parametrize("shape,page_size,first", [(5, 0, 5), (5, 16, 5), (4, 0, 17), (4, 0, 22), (3, 0, 14)])
 def test_ends_of_the_pipelined_loop_match_oracle(gpu, shape, page_size, first):
     """D = 128: the last number of full tiles that runs without the pipelined loop, the first ones that run with it (tiles queued by
     its prologue, from its loop and past its end; odd and even counts), with and without a tile begun, before trees of one and

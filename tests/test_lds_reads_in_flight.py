@@ -155,3 +155,21 @@ def test_the_pipelined_loop_waits_for_its_reads_wherever_it_is_left(kernels, sha
             assert waits_first(code, to), (name, code[i], to)
             seen += 1
     assert seen >= 4, seen  # out of the blocks of the first tile and of the loops'
+
+
+@pytest.mark.parametrize("shape, loads", [("4ELi2ELi1ELb0", 4), ("2ELi2ELi1ELb0", 8)])
+def test_the_pipelined_loops_of_two_key_groups_keep_three_tiles_in_flight(kernels, shape, loads):
+    """As the plain loop does (`loads` of a wave to a tile of K and V): at a barrier behind which a full tile is queued, those of the two
+    tiles before it may be outstanding."""
+    (name, code), = [(n, c) for n, c in kernels.items() if f"attn_kernelILi128ELi{shape}ELi4ELb0E" in n]
+    allowed = []
+    for i, (op, _, _) in enumerate(code):
+        if op != "s_barrier":
+            continue
+        queued, j = 0, i + 1
+        while not code[j][0].startswith(("s_cbranch", "s_branch", "s_barrier", "s_endpgm")):
+            queued += code[j][0] == "global_load_lds_dwordx4"
+            j += 1
+        if queued == loads:
+            allowed += [int(m[1]) for o, a, _ in code[i - 3:i] if o == "s_waitcnt" and (m := re.search(r"vmcnt\((\d+)\)", a))][-1:]
+    assert len(allowed) >= 5 and set(allowed) == {2 * loads}, (name, allowed)
