@@ -1027,8 +1027,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 
   // ---- the pipelined loop's loads: K and V of a tile apart ----
   constexpr int LEAD = C::LEAD, KOPS = NLDK + C::NPG;
-  const bool piped = C::PIPED && n_full >= (R > BM ? C::PIPE_TILES_ROWS : C::PIPE_TILES) && (PAGED ? small_pages : (uint64_t)tok_bytes < (1u << 24)) &&
-                     (int64_t)p.Hkv * D * EB < (1 << 24);
+  const bool piped = C::PIPED && n_full >= (R > BM ? C::PIPE_TILES_ROWS : C::PIPE_TILES) && (PAGED ? small_pages : tok_bytes < (1 << 26)) &&
+                     (int64_t)p.Hkv * D * EB < (1 << 26);  // (a tile's rows are within 32 bits; the entry points take tokens up to 32 MiB apart)
   const bool tree_apart = p.k_tree != nullptr;
   // full cache tiles.  Dense: an address per operand, carried along from tile to tile in scalar registers, and the lane's offset
   const int64_t tile_bytes = (int64_t)TK * p.stride_tok * EB;
@@ -1083,7 +1083,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     for (int j = 0; j < NLDK; ++j) {
       if constexpr (!V || !PAGED) {
         const int row_in = row0_of(j) + lrow, row = row_in < last ? row_in : last;
-        row_at[j] = __umul24((uint32_t)row, stride) + (uint32_t)chunk_of(j) * 16u;
+        row_at[j] = (__umul24((uint32_t)row, stride >> 4) + (uint32_t)chunk_of(j)) << 4;  // (strides are multiples of 16 bytes)
         if constexpr (PAGED)
           if (!apart) row_at[j] = small_off(page_of(t, row_in), pos0 + row, j);
       }

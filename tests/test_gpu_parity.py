@@ -338,6 +338,32 @@ def test_pages_far_apart(gpu, far):
         assert torch.equal(o, o0) and torch.equal(l, l0)
 
 
+@pytest.mark.parametrize("tok", [(1 << 23) - 8, 1 << 23, (1 << 24) - 8])
+@pytest.mark.parametrize("shape,L", [(5, 329), (3, 905), (4, 1417)])
+def test_dense_tokens_far_apart(gpu, shape, L, tok):
+    """Tokens of a dense cache (of 16-bit elements) just less than 16 MiB apart, 16 MiB, and as far as the entry points take: long enough for
+    the pipelined loop, with a tile begun and the tree's rows in tensors of their own and in the cache.  The rows are the same, and so
+    is the loop: the results are those of a packed cache, bit for bit."""
+    import torch
+    w = wl.random_workload(1480 + shape, 1, 16, 1, 128, [L], [7])
+    dw = gpu.to_device(w)
+    mask = gpu.build_mask(dw)
+    want = gpu.attention(dw, mask, plan_shape=shape, num_splits=1)
+    n, row = L + w.sum_T, w.Hkv * w.D
+    pool = torch.empty(tok * (n - 1) + 2 * row, dtype=dw.k_cache.dtype, device="cuda:0")
+    at = lambda o: torch.as_strided(pool, (n, w.Hkv, w.D), (tok, w.D, 1), o)
+    at(0).copy_(torch.cat([dw.k_cache, dw.k_tree]))
+    at(row).copy_(torch.cat([dw.v_cache, dw.v_tree]))
+    dw.k_cache, dw.v_cache = at(0), at(row)
+    for in_cache in (False, True):
+        if in_cache:
+            dw.k_tree = dw.v_tree = None
+        say(f"[case] dense tokens {tok} elements apart, shape={shape} in_cache={in_cache}")
+        o, l = gpu.attention(dw, mask, plan_shape=shape, num_splits=1, strides=(0, tok, w.D))
+        torch.cuda.synchronize()
+        assert torch.equal(o, want[0]) and torch.equal(l, want[1])
+
+
 @pytest.mark.parametrize("over", [False, True])
 @pytest.mark.parametrize("far", ["pages", "tokens"])
 @pytest.mark.parametrize("D", [128, 64])
