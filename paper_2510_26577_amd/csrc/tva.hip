@@ -2012,7 +2012,9 @@ inline bool dense_wide(const tva_args *a) { return a->D == 128 && !a->kv_fp8 && 
 // takes (tiles of the longest split) x (time per tile), more where two share a CU; workgroups beyond whole rounds take a part
 // of one more, more than half of it however few they are; every round starts and drains; the launch takes no less than
 // its bytes at the rate the shape streams; with splits there is a merge pass.
-// Where the deep 64-row shape's loop is pipelined (dense_wide, PIPE_TILES) its tile is 0.85 of that, which is most of what it gained.
+// The dense deep 64-row shape's tile is 0.85 of that from 14 on, one begun counted, which is most of what its four-stage ring and its
+// pipelined loop gained.  (The limit is the plan's own: the ring alone is worth it at 13 full tiles and a part of one, where the loop
+// does not run yet.  60 calls of 833 .. 895 keys that this moves to the shape take 0.947 of their time in the others.)
 // The eight-wave shapes' tiles stay as fitted: at 0.95 a few more calls moved between those two, for 0.1 % in the mean.
 double plan_cost(const tva_args *a, const Plan &pl) {
   struct Shape {
