@@ -325,11 +325,6 @@ __device__ __forceinline__ void lds_wait_n(bf16x8 &a, s16x4 &b, s16x4 &c) {
   asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(a), "+v"(b), "+v"(c) : "n"(N));
 }
 
-template <int N>
-__device__ __forceinline__ void lds_wait_v(s16x4 &a, s16x4 &b) {
-  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
-}
-
 // 16-byte LDS read from a landing zone of the 8-bit K/V path (inline assembly for the same reason),
 // and its wait.
 __device__ __forceinline__ u32x4 lds_read_b128(uint32_t addr) {
@@ -1547,7 +1542,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           } while (++it < n_full);
         } else {
           // (blocks take the two sets of registers in turn: one block more or less of the first ones leaves the others an odd number)
-          static_assert(KBW == 2 || C::LO_TILES % 2 == 0, "");
+          static_assert(KBW == 2 || (C::LO_TILES % 2 == 0 && C::LO_TILES >= 4), "");
           tile_lo(sA, sB, hA, rA, hB, rB, std::true_type{});
           do {
             ++it, tile_lo(sB, sA, hB, rB, hA, rA, std::false_type{});
@@ -2014,7 +2009,7 @@ inline bool dense_wide(const tva_args *a) { return a->D == 128 && !a->kv_fp8 && 
 // its bytes at the rate the shape streams; with splits there is a merge pass.
 // The dense deep 64-row shape's tile is 0.85 of that from 14 on, one begun counted, which is most of what its four-stage ring and its
 // pipelined loop gained.  (The limit is the plan's own: the ring alone is worth it at 13 full tiles and a part of one, where the loop
-// does not run yet.  60 calls of 833 .. 895 keys that this moves to the shape take 0.947 of their time in the others.)
+// does not run yet.  60 calls of 833 .. 895 keys that this moves to the shape take 0.953 of their time in the others.)
 // The eight-wave shapes' tiles stay as fitted: at 0.95 a few more calls moved between those two, for 0.1 % in the mean.
 double plan_cost(const tva_args *a, const Plan &pl) {
   struct Shape {
