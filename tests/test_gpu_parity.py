@@ -262,6 +262,29 @@ def test_queries_are_the_last_nodes_of_each_tree(gpu, page_size, variant):
             assert eo <= TOL_O and el <= TOL_LSE
 
 
+@pytest.mark.parametrize("shape,page_size", [(5, 0), (5, 16), (4, 0), (3, 0)])
+def test_queries_are_the_last_nodes_of_trees_behind_the_pipelined_loop(gpu, shape, page_size):
+    """The same on caches long enough for the pipelined loop, masks passed or derived from the parents."""
+    import torch
+    from paper_2510_26577_amd import binding
+    w = wl.random_workload(1250 + shape + page_size, 2, 8, 2, 128, [1500, 1420], [40, 72], max_depth=13, page_size=page_size)
+    Tq = np.array([12, 60])
+    cu_Q = torch.from_numpy(np.concatenate([[0], np.cumsum(Tq)]).astype(np.int32)).cuda()
+    sel = np.concatenate([np.arange(w.cu_T[b + 1] - Tq[b], w.cu_T[b + 1]) for b in range(w.B)]).astype(np.int64)
+    say(f"[case] query subset behind the pipelined loop shape={shape} page_size={page_size}")
+    dw = gpu.to_device(w)
+    q_sub = dw.q[torch.from_numpy(sel).cuda()].contiguous()
+    ro, rl = orc.tree_verify_attn(w)
+    for mask in (gpu.build_mask(dw), None):
+        out, lse = binding.tree_verify_attn(
+            q_sub, dw.k_tree, dw.v_tree, dw.k_cache, dw.v_cache, mask, dw.cu_T, dw.L, max_T=w.max_T, max_L=w.max_L, scale=w.scale,
+            cu_L=dw.cu_L, page_table=dw.page_table, page_size=w.page_size, num_splits=1, parent=None if mask is not None else dw.parent,
+            cu_Q=cu_Q, max_Q=int(Tq.max()), plan_shape=shape)
+        torch.cuda.synchronize()
+        assert np.abs(out.cpu().numpy().astype(np.float64) - ro[sel]).max() <= TOL_O
+        assert np.abs(lse.cpu().numpy().astype(np.float64) - rl[sel]).max() <= TOL_LSE
+
+
 def test_empty_trees_in_batch_and_chain_and_star(gpu):
     rng = np.random.Generator(np.random.PCG64(500))
     trees = [wl.tree_chain(13), np.zeros(0, np.int32), wl.tree_star(30), wl.tree_chain(1)]
@@ -537,14 +560,16 @@ def test_host_lengths_hint_in_split_launches_matches_oracle(gpu, L, T):
     assert binding.plan_chunk_keys(a) <= plain
 
 
-@pytest.mark.parametrize("shape,page_size,D", [(5, 0, 128), (5, 16, 128), (5, 5, 128), (5, 256, 128), (5, 0, 64), (5, 32, 64), (4, 16, 128),
-                                               (4, 0, 128), (3, 16, 128)])
-def test_long_splits_whose_scores_grow_match_oracle(gpu, shape, page_size, D):
+@pytest.mark.parametrize("shape,page_size,D,L", [(*case, [1500, 1089]) for case in ((5, 0, 128), (5, 16, 128), (5, 5, 128), (5, 256, 128), (5, 0, 64),
+                                                                                    (5, 32, 64), (4, 16, 128), (4, 0, 128), (3, 16, 128))]
+                         + [(3, 0, 128, [1990, 1801]), (4, 0, 128, [3000, 2850])])
+def test_long_splits_whose_scores_grow_match_oracle(gpu, shape, page_size, D, L):
     """Splits long enough for the steady part of the loop, with ends inside a tile: the keys grow along the cache, so that
     the softmax reference has to move and single weights dominate far into the split; page sizes below, at and above a
-    load's rows and a tile, and one that is no power of two."""
+    load's rows and a tile, and one that is no power of two.  (The last two: halves long enough for the pipelined loop of the
+    deep 64-row and the 128-row shape.)"""
     import torch
-    w = wl.random_workload(800 + shape + page_size + D, 2, 8, 2, D, [1500, 1089], [37, 11], page_size=page_size)
+    w = wl.random_workload(800 + shape + page_size + D, 2, 8, 2, D, L, [37, 11], page_size=page_size)
     grow = lambda n: np.where(np.arange(n) % 400 > 380, 5.0, 1.0 + np.arange(n) / 700.0).astype(np.float32)
     def scaled(bits, factor):
         x = (bits.astype(np.uint32) << 16).view(np.float32) * factor
@@ -571,11 +596,12 @@ def test_long_splits_whose_scores_grow_match_oracle(gpu, shape, page_size, D):
         assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
 
 
-@pytest.mark.parametrize("D,tiles", [(128, 15), (128, 16), (64, 10), (64, 11)])
+@pytest.mark.parametrize("D,tiles", [(128, 4), (128, 5), (128, 15), (128, 16), (64, 10), (64, 11)])
 @pytest.mark.parametrize("page_size", [0, 16])
 def test_splits_at_the_start_of_the_steady_loop_match_oracle(gpu, D, tiles, page_size):
-    """Second splits (their keys do not start at 0) of the last number of full tiles that runs without the steady loop and
-    the first that runs with it, whole and with a tile begun; a sequence whose last split is short."""
+    """256-row shape: second splits (their keys do not start at 0) of the last number of full tiles that runs without the steady loop
+    (D = 64: 10; the pipelined one, D = 128: 4) and the first that runs with it, and of 15 and 16, whole and with a tile begun; a
+    sequence whose last split is short."""
     import torch
     for more in (0, 1, 63):
         w = wl.random_workload(970 + tiles + more + page_size, 2, 8, 2, D, [2 * 64 * tiles + more, 64 * tiles + 5], [33, 9], page_size=page_size)
@@ -612,28 +638,40 @@ def test_rows_are_stored_in_place_and_nowhere_else(gpu, Hq, Hkv, D):
                 assert bool((rows == 7.5).all())
 
 
-@pytest.mark.parametrize("tiles", [16, 17, 19])
-@pytest.mark.parametrize("page_size", [0, 16])
-def test_spikes_in_every_part_of_the_pipelined_loop_match_oracle(gpu, tiles, page_size):
-    """256-row shape, D = 128, the smallest numbers of tiles that the pipelined loop takes (13, 14 and 16 of them in the loop):
-    one key at a time is scaled so that its block moves the reference or needs the low-order pass, in the first and second block
-    of the first tile, of one in the middle and of the last ones, and right behind the loop; waves with and without rows."""
+def _scaled_key(w, key, factor):
+    """Multiplies one cached key of the first sequence; returns its place and what it held."""
+    at = (int(w.cu_L[0]) + key,) if not w.paged else (int(w.page_table[0, key // w.page_size]), key % w.page_size)
+    kept = w.k_cache[at].copy()
+    x = (kept.astype(np.uint32) << 16).view(np.float32) * np.float32(factor)  # (a power of two, or rounded to bf16 below)
+    w.k_cache[at] = ((x.view(np.uint32) + 0x8000) >> 16).astype(np.uint16)
+    return at, kept
+
+
+def _blocks_of_the_pipelined_loop(shape, tiles):
+    """32-key blocks of a split (two to a tile) at which the pipelined loop's parts meet: the first tile's, the last with the
+    prepared low-order pass and the first without (of three tiles in the 256-row shape; of six, or five of an even number, in those
+    with two key groups, each of which has one block of a tile), one in the middle, the last ones."""
+    lo = 3 if shape == 5 else 5 + tiles % 2
+    return sorted({0, 1, 2, 3, 2 * lo - 2, 2 * lo - 1, 2 * lo, 2 * lo + 1, tiles, 2 * (tiles - 3) - 2, 2 * (tiles - 3) - 1, 2 * (tiles - 3),
+                   2 * tiles - 2, 2 * tiles - 1} & set(range(2 * tiles)))
+
+
+@pytest.mark.parametrize("shape,page_size,tiles", [(5, page_size, tiles) for page_size in (0, 16) for tiles in (5, 6, 16, 17, 19)]
+                         + [(4, 0, 22), (4, 0, 23), (3, 0, 14), (3, 0, 15)])
+def test_spikes_in_every_part_of_the_pipelined_loop_match_oracle(gpu, shape, page_size, tiles):
+    """D = 128, the smallest numbers of full tiles that the pipelined loop takes and larger ones, odd and even: one key at a time is
+    scaled so that its block moves the reference or needs the low-order pass; waves with and without rows."""
     import torch
-    L = 64 * tiles + 7
-    base = wl.random_workload(990 + tiles + page_size, 1, 8, 1, 128, [L], [25], page_size=page_size)
-    mask = None
-    for block in (0, 1, 2, 3, tiles, 2 * (tiles - 3) - 2, 2 * (tiles - 3) - 1, 2 * (tiles - 3), 2 * tiles - 1):
+    base = wl.random_workload(990 + tiles + page_size, 1, {5: 8, 4: 4, 3: 2}[shape], 1, 128, [64 * tiles + 7], [{5: 25, 4: 22, 3: 14}[shape]],
+                              page_size=page_size)
+    for block in _blocks_of_the_pipelined_loop(shape, tiles):
         for factor in (4.0, 12.0):
-            key = 32 * block + (5 * block + 3) % 32
-            at = (int(base.cu_L[0]) + key,) if page_size == 0 else (int(base.page_table[0, key // page_size]), key % page_size)
-            kept = base.k_cache[at].copy()
-            x = (kept.astype(np.uint32) << 16).view(np.float32) * np.float32(factor)  # (a power of two, or rounded to bf16 below)
-            base.k_cache[at] = ((x.view(np.uint32) + 0x8000) >> 16).astype(np.uint16)
+            at, kept = _scaled_key(base, 32 * block + (5 * block + 3) % 32, factor)
             ro, rl = orc.tree_verify_attn(base)
             dw = gpu.to_device(base)
             mask = gpu.build_mask(dw)
-            say(f"[case] spike tiles={tiles} page_size={page_size} block={block} factor={factor}")
-            o, l = gpu.attention(dw, mask, num_splits=1, plan_shape=5)
+            say(f"[case] spike shape={shape} tiles={tiles} page_size={page_size} block={block} factor={factor}")
+            o, l = gpu.attention(dw, mask, num_splits=1, plan_shape=shape)
             torch.cuda.synchronize()
             assert np.abs(o.cpu().numpy().astype(np.float64) - ro).max() <= TOL_O
             assert np.abs(l.cpu().numpy().astype(np.float64) - rl).max() <= TOL_LSE
@@ -644,19 +682,17 @@ def test_spikes_in_every_part_of_the_pipelined_loop_match_oracle(gpu, tiles, pag
 def test_ends_of_the_pipelined_loop_match_oracle(gpu, shape, page_size, first):
     """D = 128: the last number of full tiles that runs without the pipelined loop, the first ones that run with it (tiles queued by
     its prologue, from its loop and past its end; odd and even counts), with and without a tile begun, before trees of one and
-    two tiles; scaled keys in the first block, where the prepared low-order pass ends and
-    in the last one.  Tolerances are the task's."""
+    two tiles; scaled keys in the first block, on both sides of the prepared low-order pass's end in each key group, and in the last ones.
+    Tolerances are the task's."""
     import torch
     G = {5: 8, 4: 4, 3: 2}[shape]
     for tiles in (first - 1, first, first + 1, first + 2):
         for more, T in ((0, 1), (1, 40), (63, 65), (17, 128)):
             L = 64 * tiles + more
             w = wl.random_workload(1700 + shape + tiles + more + page_size, 2, 2 * G, 2, 128, [L, L - 30], [T, max(1, T // 2)], page_size=page_size)
-            for block, factor in ((0, 8.0), (6, 12.0), (7, 12.0), (2 * tiles - 1, 12.0)):
-                key = 32 * block + 11
-                at = (int(w.cu_L[0]) + key,) if page_size == 0 else (int(w.page_table[0, key // page_size]), key % page_size)
-                x = (w.k_cache[at].astype(np.uint32) << 16).view(np.float32) * np.float32(factor)
-                w.k_cache[at] = ((x.view(np.uint32) + 0x8000) >> 16).astype(np.uint16)
+            for block in _blocks_of_the_pipelined_loop(shape, tiles):
+                if block not in (1, 2, 3, tiles):
+                    _scaled_key(w, 32 * block + 11, 8.0 if block == 0 else 12.0)
             ro, rl = orc.tree_verify_attn(w)
             dw = gpu.to_device(w)
             say(f"[case] pipelined loop's ends shape={shape} page_size={page_size} tiles={tiles} more={more} T={T}")

@@ -406,23 +406,24 @@ def test_attention_with_tree_rows_in_the_cache(torch_dev, page_size, variant):
 
 
 @pytest.mark.parametrize("page_size", [16, 0, 48])
-@pytest.mark.parametrize("D, L, splits", [(128, [1024, 1100], 1), (128, [1088, 2111], 1), (128, [2304, 2240], 2), (64, [704, 768], 1), (64, [760, 1033], 1),
-                                          (64, [1408, 1500], 2)])
-def test_tree_rows_in_the_cache_behind_the_steady_loop(torch_dev, D, L, splits, page_size):
-    """The same in the 256-row shape on caches long enough for its steady loop, which asks for the tree tiles' pages while it still
-    runs over the cache's: lengths on a tile's edge and off it, trees of one tile and of two."""
+@pytest.mark.parametrize("shape, D, L, splits", [(5, 128, [1024, 1100], 1), (5, 128, [1088, 2111], 1), (5, 128, [2304, 2240], 2), (5, 64, [704, 768], 1),
+                                                 (5, 64, [760, 1033], 1), (5, 64, [1408, 1500], 2), (4, 128, [1088, 1430], 1), (4, 128, [2816, 2903], 2),
+                                                 (3, 128, [896, 1001], 1), (3, 128, [1792, 1925], 2)])
+def test_tree_rows_in_the_cache_behind_the_steady_loop(torch_dev, shape, D, L, splits, page_size):
+    """The same on caches long enough for the 256-row shape's steady loop and the others' pipelined one, which ask for the tree tiles (and
+    their pages) while they still run over the cache's: lengths on a tile's edge and off it, trees of one tile and of two."""
     torch = torch_dev
     from oracle import tva_oracle as orc
     from paper_2510_26577_amd import binding
     rng = np.random.Generator(np.random.PCG64(75 + page_size + D))
     w = wl.random_workload(1020 + page_size + L[1], 2, 8, 2, D, L, [40, 72], max_depth=12)
     k, v, cu, table = _in_cache_layout(w, rng, page_size)
-    say(f"[case] in-cache tree rows behind the steady loop, D={D} L={L} splits={splits} page_size={page_size}")
+    say(f"[case] in-cache tree rows behind the steady loop, shape={shape} D={D} L={L} splits={splits} page_size={page_size}")
     dev = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
     i16 = lambda a: a.view(np.int16)
     out, lse = binding.tree_verify_attn(dev(i16(w.q)), None, None, dev(i16(k)), dev(i16(v)), None, dev(w.cu_T), dev(w.L.astype(np.int32)),
                                         max_T=w.max_T, max_L=w.max_L, scale=w.scale, cu_L=dev(cu), page_table=dev(table),
-                                        page_size=page_size, num_splits=splits, parent=dev(w.parent), plan_shape=5)
+                                        page_size=page_size, num_splits=splits, parent=dev(w.parent), plan_shape=shape)
     torch.cuda.synchronize()
     ro, rl = orc.tree_verify_attn(w)
     assert np.abs(out.cpu().numpy().astype(np.float64) - ro).max() <= 2e-3
