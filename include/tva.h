@@ -59,7 +59,7 @@ typedef enum {
   TVA_SHAPE_AUTO = 0,
   TVA_SHAPE_R32_W2 = 1,       /*  32 rows, 1 x 2 waves (the two waves split each tile's keys) */
   TVA_SHAPE_R64_W4 = 2,       /*  64 rows, 2 x 2 waves, two workgroups per CU */
-  TVA_SHAPE_R64_W4_DEEP = 3,  /*  the same with one more tile in flight, one workgroup per CU */
+  TVA_SHAPE_R64_W4_DEEP = 3,  /*  the same with more tiles in flight, one workgroup per CU */
   TVA_SHAPE_R128_W8 = 4,      /* 128 rows, 4 x 2 waves */
   TVA_SHAPE_R256_W8 = 5       /* 256 rows, 8 x 1 waves */
 } tva_shape;

@@ -223,7 +223,8 @@ struct AttnCfg {
   static constexpr int NL = KV8_REG ? 0 : KV8 ? NST : 0;
   static constexpr int LAND_SLOT = KV8 ? 2 * TK * D : 0;
   static constexpr int NSTAGE = KV8_REG ? 4 : KV8 ? 2 : NST;
-  // the 256-row shape's loop has a steady part of its own (the others ran no faster with one: they wait for data)
+  // the 256-row shape: its full tiles take consecutive keys per load and, with D = 64, its loop has a steady part of its own (the
+  // others' plain loops ran no faster with one: they wait for data)
   static constexpr bool STEADY = WK == 1 && !KV8;
   // Splits of PIPE_TILES full tiles and more run a loop that is a software pipeline over 32-key blocks.  LEAD: tiles that K is
   // fetched further ahead than V; the blocks of the first LO_TILES tiles come with the low-order pass ready.  With / without it,
@@ -1178,7 +1179,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     step(0, std::false_type{}, std::false_type{});
     it = 1;
   }
-  TL_STAMP(3);  // first full tile done (a split without one: the same moment as the stamp before)
+  TL_STAMP(3);  // first full tile done (a split without one: the same moment as the stamp before; the pipelined loop stamps it anew)
 #endif
   if constexpr (C::PIPED) {
     if (piped) {
@@ -1535,6 +1536,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           for (++it; it < C::LO_TILES; ++it) tile_lo(sA, sB, hA, rA, hB, rB, std::false_type{});
           operands(hB, ph), operands(rB, pr);
           drain(v_at(it - 1), ph, pr);
+          TL_STAMP(3);  // the first tiles, with the prepared low-order pass, done
           tile(sA, sB, pA, pB, std::false_type{});
           ++it;
           do {
@@ -1558,6 +1560,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           }
           operands(hA, ph), operands(rA, pr);
           drain(v_at(it), ph, pr);
+          TL_STAMP(3);
           ++it, tile(sB, sA, pB, pA, std::false_type{});
           do {
             ++it, tile(sA, sB, pA, pB, std::true_type{});
@@ -1990,7 +1993,7 @@ void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
   }
   pl->chunk_keys = ck;
   pl->n_chunks = a->max_L > 0 ? (a->max_L + ck - 1) / ck : 1;
-  // one 2 x 2 workgroup per CU at most and long splits: a third ring stage (two tiles in flight)
+  // one 2 x 2 workgroup per CU at most and long splits: a deeper ring (two tiles in flight, with D = 128 three)
   // pays; with more workgroups the second one on the CU hides more than the deeper ring would
   if (pl->variant == V_M2K2 && !named && !a->kv_fp8 && (int64_t)pairs * pl->n_row_blocks * pl->n_chunks <= 256 && ck >= 12 * pl->TK)
     pl->variant = V_M2K2_3;

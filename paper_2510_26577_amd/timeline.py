@@ -23,7 +23,7 @@ import numpy as np
 
 from . import binding, device, workloads
 
-STAGES = ("entry (dispatch skew)", "scalars arrived", "key loop entered (Q, mask rows arrived)", "first tile done",
+STAGES = ("entry (dispatch skew)", "scalars arrived", "key loop entered (Q, mask rows arrived)", "first tile done *",
           "all tiles done", "key groups merged, stores issued")
 
 
@@ -128,6 +128,7 @@ def summarise(name, w, us_plain, us_instr, plan, attn, merge, cmd, mode) -> str:
     for i in range(1, 6):
         lines.append(f"  + {STAGES[i]:<42s} {st(a[:, i] - a[:, i - 1])}")
     lines.append(f"  = {'result stores issued, absolute':<42s} {st(a[:, 5])}")
+    lines.append("  * of splits that run the pipelined loop: the tiles with the prepared low-order pass (5 or 6; 256-row shape 3)")
     if merge is not None and len(merge):
         m = merge - t0
         lines += [
