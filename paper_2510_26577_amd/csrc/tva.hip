@@ -1188,11 +1188,10 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       // lane at a time, with their operands read from LDS four such groups ahead: the matrix unit has work while the vector ALUs
       // exponentiate, whatever the SIMD's other wave is at.  K is fetched LEAD tiles further ahead than V, whose place it would
       // else wait for.  The partial cache tile and the tree's are queued from here as well.
-      // (Per tile with 8 workgroups on the chip, before -> now: deep 64-row shape 0.97 -> 0.55 us -- 0.45 without the loads --
-      // 128-row shape 0.96 -> 0.67, 256-row shape, which had a pipeline for its steady part, 1.17 -> 1.15 and its first and last
-      // tiles 1.6 -> 1.2.  With 256 workgroups the chip's power bounds the two large shapes: 32 sequences of 2048 keys, 60 nodes,
-      // 83.8 -> 82 us, whose loop alone would take 51 at the clock of a lone launch; 8 of 4096 keys, 64 heads, 58.2 -> 56.8.
-      // 16 sequences of 512 .. 2048 keys, 16 nodes, deep 64-row shape: 29.4 -> 28.) ----
+      // (Per tile with 8 workgroups on the chip, without -> with: deep 64-row shape 0.97 -> 0.69 us, 128-row shape 0.95 -> 0.71,
+      // 256-row shape, which had a pipeline for its middle tiles, 1.17 -> 1.16.  With 256 workgroups the chip's power bounds the two
+      // large shapes: 8 sequences of 4096 keys, 64 heads, spend 17 % fewer cycles in the loop at 9 % less clock, 57.8 -> 56.4 us; 32 of
+      // 2048 keys, 60 nodes, 7 % fewer, 82.4 -> 80.3.  16 of 512 .. 2048 keys, 16 nodes, deep 64-row shape: 29.8 -> 28.0.) ----
       static_assert(!C::PIPED || (RB == 1 && NS == 8 && ND == 4 && KBW <= 2), "");
       constexpr int V8 = 8 * PV, S2OFF = ROWB, BLK = KBW == 2 ? 2 * ROWB : 0;
       // In tile t: K of tile t + LEAD - 1 and V of tile t - 1 have been read everywhere, so their places take K and V of NSTAGE tiles
