@@ -1241,8 +1241,9 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 #pragma unroll
       for (int i = 0; i < 4; ++i) vl[i] = vh[i] = s16x4{0, 0, 0, 0};
       // Waits for all of them; what follows takes them as written here.  Until its wait the compiler takes such a register as written
-      // although the value is still to come, so nothing but the groups below and the barrier of a tile that queues full tiles may stand
-      // between a read and its wait: every other way on starts with this one, and every loop is entered and left at one place.
+      // although the value is still to come, so nothing but a straight line, the groups below and (with two blocks per tile) the barrier of a
+      // tile that queues full tiles may stand between a read and its wait: every other way on starts with this one, and every loop is
+      // entered and left at one place.
       // (A loop over pairs of blocks that could be left between the two had its operands in other registers on either way out: a
       // statement on one of them, and they were copied and spilled in flight.)
       auto settle_reads = [&]() __attribute__((always_inline)) {
@@ -1450,30 +1451,26 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         lds_read_k<0>(kr[0], ka), lds_read_k<32>(kr[1], ka), lds_read_k<64>(kr[2], ka), lds_read_k<96>(kr[3], ka);
         auto group = [&](auto g_tag) __attribute__((always_inline)) {
           constexpr int g = decltype(g_tag)::value;
-          lds_wait_n<KBW == 2 || g < 5 ? 3 : 7 - g>(kr[g % 4], vl[0], vh[0]);
+          lds_wait_n<g < 5 ? 3 : 7 - g>(kr[g % 4], vl[0], vh[0]);
           sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[g % 4], qreg[0][g], g == 0 ? zero16 : sA, 0, 0, 0);
           if constexpr (g < 4) lds_read_k<(g + 4) * 32>(kr[g % 4], ka);
-          else if constexpr (KBW == 2) lds_read_k<BLK + (g - 4) * 32>(kr[g % 4], ka);
           __builtin_amdgcn_sched_barrier(0);
         };
         half(group, std::false_type{}), half(group, std::true_type{});
       }
       if constexpr (KBW == 1) {
-        // K of the second tile has landed, that of the first has been read everywhere
-        if (wave_has_rows) settle_reads();
+        // K of the second tile has landed, that of the first has been read everywhere (each wave has waited for its reads)
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * KOPS + 3 * NLDK));
         __builtin_amdgcn_s_barrier();
         issue_k(4);
-        if (wave_has_rows) {
-          const uint32_t ka = k_at(1);
-          lds_read_k<0>(kr[0], ka), lds_read_k<32>(kr[1], ka), lds_read_k<64>(kr[2], ka), lds_read_k<96>(kr[3], ka);
-          __builtin_amdgcn_sched_barrier(0);
-        }
       }
       if (!wave_has_rows) {
         if constexpr (KBW == 2) first_landed();
         for (; it < n_full; ++it) enter(it);
       } else {
+        const uint32_t ka = k_at(KBW == 1 ? 1 : 0);  // the second block
+        lds_read_k<BLK>(kr[0], ka), lds_read_k<BLK + 32>(kr[1], ka), lds_read_k<BLK + 64>(kr[2], ka), lds_read_k<BLK + 96>(kr[3], ka);
+        __builtin_amdgcn_sched_barrier(0);
         m_run[0] = block_max(sA), use_reference(0), set_cap(0);
         const auto nothing = [&]() __attribute__((always_inline)) {};
         const auto none = [&](auto) __attribute__((always_inline)) {};
