@@ -2107,7 +2107,10 @@ bool make_plan(const tva_args *a, Plan *pl) {
     shapes.sum_L = 0, shapes.L_host = nullptr;
     Plan plan;
     plan_splits_of(&shapes, variant, false, &plan);
-    const double rules = plan_cost(&shapes, plan);
+    // (Dense, D = 128: where the lengths shorten the rules' splits to more workgroups than the deep 64-row shape may have, the two-stage
+    // shape is what the rules come to, and what it takes is asked: 40 calls that were held to the deep shape's discount instead, 4
+    // sequences of 2.5 .. 4 K keys, 30 nodes, 25 -> 35 us, take 0.99 of what they did before there was one, 28 others 0.83.)
+    const double rules = plan_cost(&shapes, dense_wide(a) && pl->variant != plan.variant ? *pl : plan);
     // How much: 8 %, which is about the model's error (6 % for all pairs: twice as many calls more than 2 % slower); less
     // where nearly every smaller promise was kept, more where one of 12 % was missed by 30.
     auto enough = [&](int v) {

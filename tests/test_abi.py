@@ -316,6 +316,18 @@ def test_deep_shape_is_not_taken_for_more_split_workgroups_than_fit(lib, L, spli
     assert (binding.plan_workgroup_rows(a), binding.plan_splits(a)) == (64, splits)
 
 
+@pytest.mark.parametrize("Hq,L,T,splits", [(32, [4194, 3787, 3380, 2972], 32, 8), (32, [8599, 4875], 23, 15), (16, [5179, 3586, 1992], 63, 9)])
+def test_rules_that_come_to_the_two_stage_shape_are_not_priced_as_the_deep_one(lib, Hq, L, T, splits):
+    """The lengths shorten the 64-row splits to more workgroups than the chip holds of its deep ring: the 128-row shape, a third
+    faster there, is the one taken."""
+    import numpy as np
+    L = np.array(L, np.int32)
+    B = len(L)
+    a = shape_args(B=B, Hq=Hq, max_L=int(L.max()), max_T=T, sum_T=B * T, sum_L=int(L.sum()))
+    a.L_host = L.ctypes.data_as(ctypes.c_void_p)
+    assert (binding.plan_workgroup_rows(a), binding.plan_splits(a)) == (128, splits)
+
+
 def test_slot_table_is_a_permutation_that_pairs_long_with_short(lib):
     """tva_args.L_host in an unsplit launch of 33 .. 64 sequences, 8 KV heads, at most 64 rows per KV head: the slot
     table is a permutation of the sequences whatever the lengths are (ties, zeros, nonsense); slots j and j + 32
