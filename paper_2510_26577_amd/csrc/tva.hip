@@ -2010,6 +2010,8 @@ inline bool dense_wide(const tva_args *a) { return a->D == 128 && !a->kv_fp8 && 
 // pipelined loop gained.  (The limit is the plan's own: the ring alone is worth it at 13 full tiles and a part of one, where the loop
 // does not run yet.  60 calls of 833 .. 895 keys that this moves to the shape take 0.953 of their time in the others.)
 // The eight-wave shapes' tiles stay as fitted: at 0.95 a few more calls moved between those two, for 0.1 % in the mean.
+inline int longest_split(const tva_args *a, const Plan &pl) { return pl.n_chunks > 1 ? pl.chunk_keys / pl.TK : (a->max_L + pl.TK - 1) / pl.TK; }
+inline bool deep_wide(const tva_args *a, const Plan &pl) { return pl.variant == V_M2K2_3 && dense_wide(a) && longest_split(a, pl) >= 14; }
 double plan_cost(const tva_args *a, const Plan &pl) {
   struct Shape {
     double tile, fixed, round, d64, f8, paged, tb_s, tb_s8;
@@ -2029,8 +2031,8 @@ double plan_cost(const tva_args *a, const Plan &pl) {
   if (a->D == 64) tile *= s.d64;
   if (a->kv_fp8) tile *= s.f8;
   if (a->page_table) tile *= s.paged;
-  const int longest = pl.n_chunks > 1 ? pl.chunk_keys / pl.TK : (a->max_L + pl.TK - 1) / pl.TK, own = (a->max_T + pl.TK - 1) / pl.TK;
-  if (pl.variant == V_M2K2_3 && dense_wide(a) && longest >= 14) tile *= 0.85;
+  const int longest = longest_split(a, pl), own = (a->max_T + pl.TK - 1) / pl.TK;
+  if (deep_wide(a, pl)) tile *= 0.85;
   const double tiles = longest + own * (pl.n_chunks > 1 ? 0.89 : 1.0);
   double rounds = wgs > holds ? wgs / holds : 1.0;
   const double whole = std::floor(rounds), part = rounds - whole;
@@ -2113,9 +2115,12 @@ bool make_plan(const tva_args *a, Plan *pl) {
     const double rules = plan_cost(&shapes, dense_wide(a) && pl->variant != plan.variant ? *pl : plan);
     // How much: 8 %, which is about the model's error (6 % for all pairs: twice as many calls more than 2 % slower); less
     // where nearly every smaller promise was kept, more where one of 12 % was missed by 30.
-    auto enough = [&](int v) {
+    // (5 % for the deep shape where its tile counts less.  On shorter splits such promises were not kept: of 540000 drawn calls
+    // 30 took the shape for one, 8 % slower in the mean; one sequence of 1.6 K keys, 66 nodes, splits of five tiles 15.7 -> 17.9 us)
+    auto enough = [&](const Plan &other) {
+      const int v = other.variant;
       if (variant == V_K2) return 0.98;
-      if (variant == V_M4K2 || (variant == V_M2K2 && v == V_M2K2_3 && dense_wide(a))) return 0.95;
+      if (variant == V_M4K2 || (variant == V_M2K2 && deep_wide(a, other))) return 0.95;
       if (variant == V_W8 && a->kv_fp8) return 0.85;
       // (D = 64, dense: of the 256-row shape a CU holds one workgroup)
       if (variant == V_W8 && (a->D == 64 ? !a->page_table : v == V_M2K2)) return 0.98;
@@ -2140,7 +2145,7 @@ bool make_plan(const tva_args *a, Plan *pl) {
       if (v == variant || (a->kv_fp8 && (v == V_M2K2_3 || (v == V_M2K2 && rows > 64)))) continue;
       plan_splits_of(&shapes, v, true, &plan);
       const double us = plan_cost(&shapes, plan);
-      if (us < enough(v) * rules && (chosen < 0 || us < best) && scratch_bytes(a, plan) <= most && !crowded(v)) best = us, chosen = v;
+      if (us < enough(plan) * rules && (chosen < 0 || us < best) && scratch_bytes(a, plan) <= most && !crowded(v)) best = us, chosen = v;
     }
     if (chosen >= 0) {
       // (splits that the lengths shorten are more splits: where those pass the limit they keep their length)
