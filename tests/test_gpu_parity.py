@@ -368,6 +368,7 @@ def test_dense_tokens_far_apart(gpu, shape, L, tok):
     the pipelined loop, with a tile begun and the tree's rows in tensors of their own and in the cache.  The rows are the same, and so
     is the loop: the results are those of a packed cache, bit for bit."""
     import torch
+    torch.cuda.empty_cache()  # (up to 48 GB a case)
     w = wl.random_workload(1480 + shape, 1, 16, 1, 128, [L], [7])
     dw = gpu.to_device(w)
     mask = gpu.build_mask(dw)
