@@ -42,6 +42,7 @@
 
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "tva.h"
 
@@ -240,6 +241,11 @@ struct AttnCfg {
   // faster, but 1 % slower where 8-bit tiles are widened through LDS, and the paged 256-row shape with D = 64 has no
   // register for it
   static constexpr bool KEEP_USE = (!KV8 || KV8_REG) && !(D == 64 && PAGED && WK == 1);
+  // A block's K operands and V^T operands are read ahead, in one go, and (dense) the loads of the tile to come are queued under
+  // its products.  (One sequence of 2048 keys, 60 nodes, 7 splits of five tiles, one wave per SIMD; cycles a tile: queueing 434 -> 102,
+  // since a CU takes 64 bytes a cycle and all waves queue at once, the arithmetic with the queueing in it 1541 -> 1621; 13.1 -> 12.6 us.
+  // 128 keys, 4 heads, D = 64: 5.47 -> 5.38.  The shapes with a pipelined loop keep their plain one for their short splits.)
+  static constexpr bool AHEAD = WK > 1 && !KV8 && RB == 1 && !PIPED;
   static constexpr int PD = KV8_REG ? NSTAGE - 1 : KV8 ? NL : NSTAGE - 1;  // tiles in flight ahead of the one being computed (widened)
   static constexpr int WG_PER_CU = KV8 ? (KV8_REG ? 2 : 1) : (NSTAGE == 2 && TK == 64) ? 2 : 1;
   // wavefronts per SIMD that the registers have to leave room for.  (The rings of the eight-wave shapes with D = 64 let two
@@ -285,6 +291,11 @@ struct AttnCfg {
   static_assert(BLKB % 1024 == 0, "a block is a whole number of wave-wide loads");
 };
 
+template <int N, typename F, int... I>
+__device__ __forceinline__ void static_for_each(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) { static_for_each<N>(f, std::make_integer_sequence<int, N>{}); }
+
 // s_waitcnt immediate that waits for vmcnt <= n only (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
 constexpr int vm_cap(int n) { return n > 63 ? 63 : n; }  // the counter holds 6 bits; waiting for less is safe
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | (((n >> 4) & 3) << 14); }
@@ -320,6 +331,10 @@ __device__ __forceinline__ void lds_read_v(s16x4 &v, uint32_t addr) {
 template <int OFF>
 __device__ __forceinline__ void lds_read_k(bf16x8 &v, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+}
+template <int N>
+__device__ __forceinline__ void lds_wait_n(bf16x8 &a) {
+  asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "n"(N));
 }
 template <int N>
 __device__ __forceinline__ void lds_wait_n(bf16x8 &a, s16x4 &b, s16x4 &c) {
@@ -619,6 +634,10 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   const int full_row = C::STEADY ? lsub : lrow;
   const uint32_t lane_off2[2] = {(uint32_t)full_row * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(0) * 16u,
                                  (uint32_t)full_row * (uint32_t)p.stride_tok * (uint32_t)EB + (uint32_t)chunk_of(1) * 16u};
+  auto tile_row = [&](int j) __attribute__((always_inline)) { return C::STEADY ? full_key(j) : row0_of(j) + lrow; };
+  uint32_t lane_off[NLDK];
+#pragma unroll
+  for (int j = 0; j < NLDK; ++j) lane_off[j] = (uint32_t)tile_row(j) * (uint32_t)tok_bytes + (uint32_t)chunk_of(j) * 16u;
   auto issue_impl = [&](int t, auto tree_tag) __attribute__((always_inline)) {
     constexpr bool tree = decltype(tree_tag)::value;
     const int base = tree ? (t - n_ct) * TK : k0 + t * TK;
@@ -628,11 +647,11 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     if (!PAGED && t < n_full) {
 #pragma unroll
       for (int j = 0; j < NLDK; ++j) {
-        const int64_t urow = cache_base + (int64_t)(base + (C::STEADY ? (wave * NLDK + j) * LPI : row0_of(j))) * p.stride_tok;
-        const char *ksrc = kc_bytes + urow * EB + lane_off2[j & 1];
-        const char *vsrc = vc_bytes + urow * EB + lane_off2[j & 1];
-        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(ksrc), stage + kdst_of(j), 16, 0, kLoadOnce);
-        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vsrc), stage + vdst_of(j), 16, 0, kLoadOnce);
+        // (8-bit K/V: an address per load, 1 % faster there than a register per load of a tile)
+        const int64_t at = (cache_base + (int64_t)(base + (KV8 ? row0_of(j) : 0)) * p.stride_tok) * EB;
+        const uint32_t off = KV8 ? lane_off2[j & 1] : lane_off[j];
+        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + at + off), stage + kdst_of(j), 16, 0, kLoadOnce);
+        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vc_bytes + at + off), stage + vdst_of(j), 16, 0, kLoadOnce);
       }
     } else if (PAGED && !(tree && p.k_tree != nullptr)) {
       // (tree keys stored in the cache follow the sequence's L_b committed tokens)
@@ -727,7 +746,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       for (int i = 0; i < 16; ++i) oacc[r][d][i] *= alpha;
   };
   // ---- one 32-key block of one tile: S^T = K Q^T, online softmax, O^T += V^T P^T ----
-  auto compute_block = [&](const lds_byte *stage, auto kb_tag, int base, int limit, bool tree, auto masked_tag, auto settled_tag) __attribute__((always_inline)) {
+  auto compute_block = [&](const lds_byte *stage, auto kb_tag, int base, int limit, bool tree, auto masked_tag, auto settled_tag, auto &&refill) __attribute__((always_inline)) {
+    constexpr bool AHEAD = C::AHEAD;
     constexpr bool MASKED = decltype(masked_tag)::value, SETTLED = decltype(settled_tag)::value;
     constexpr int kb = decltype(kb_tag)::value;
     constexpr int KBOFF = kb * (32 / NBLK) * ROWB;     // this 32-key block inside the wave's part of the tile
@@ -755,7 +775,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         for (int r = 0; r < RB; ++r)
           sacc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[r][s], sacc[r], 0, 0, 0);
       }
-    } else {
+    } else if constexpr (!AHEAD) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const bf16x8 ka = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>(kp + s * 32);
@@ -768,9 +788,31 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     auto v_at = [&](int d) __attribute__((always_inline)) { return !C::PAIR ? va + d * 64 : d < ND / 2 ? va_kept + d * 64 : va_other + (d - ND / 2) * 64; };
     s16x4 vlo[2][ND], vhi[2][ND];
     u32x2 vraw[2][ND];  // (8-bit K/V read in place: one byte transpose read per operand)
+    constexpr int S2OFF = (16 / NBLK) * ROWB;
+    if constexpr (AHEAD) {
+      // (behind the K operand waited for: those after it and as many reads of V as K operands have been used, NS - 1 in all)
+      const uint32_t kp0 = (uint32_t)(uintptr_t)kp;
+      bf16x8 ka[NS];
+      static_for<NS>([&](auto s_tag) __attribute__((always_inline)) { lds_read_k<decltype(s_tag)::value * 32>(ka[decltype(s_tag)::value], kp0); });
+      static_for<NS>([&](auto s_tag) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_tag)::value, d = s / 2;
+        lds_wait_n<NS - 1>(ka[s]);
+        sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[s], qreg[0][s], s == 0 ? f32x16{} : sacc[0], 0, 0, 0);
+        if constexpr (s % 2 == 0) lds_read_v<KBOFF>(vlo[0][d], v_at(d));
+        else lds_read_v<KBOFF + V8>(vhi[0][d], v_at(d));
+        refill(s_tag);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      static_for<ND>([&](auto d_tag) __attribute__((always_inline)) {
+        constexpr int d = decltype(d_tag)::value;
+        lds_read_v<KBOFF + S2OFF>(vlo[1][d], v_at(d));
+        lds_read_v<KBOFF + S2OFF + V8>(vhi[1][d], v_at(d));
+      });
+    }
 #pragma unroll
     for (int d = 0; d < ND; ++d) {
-      if constexpr (C::KV8_REG) {
+      if constexpr (AHEAD) {
+      } else if constexpr (C::KV8_REG) {
         vraw[0][d] = lds_read_tr8(sb8 + voff8[d]);
       } else {
         vlo[0][d] = lds_read_tr<KBOFF + 0>(v_at(d));
@@ -885,14 +927,14 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       for (int r = 0; r < RB; ++r) l_run[r] += ls[r];
     }
     // O^T += V^T P^T: first 16 keys while the operands of the second 16 arrive
-    constexpr int S2OFF = (16 / NBLK) * ROWB;
     static_assert(ND == 4 || ND == 2, "head dimension 128 or 64");
     if constexpr (C::KV8_REG) lds_wait(vraw[0][0], vraw[0][1], vraw[0][ND - 2], vraw[0][ND - 1]);
     else if constexpr (ND == 4) lds_wait(vlo[0][0], vlo[0][1], vlo[0][2], vlo[0][3]), lds_wait(vhi[0][0], vhi[0][1], vhi[0][2], vhi[0][3]);
     else lds_wait(vlo[0][0], vlo[0][1], vhi[0][0], vhi[0][1]);
 #pragma unroll
     for (int d = 0; d < ND; ++d) {
-      if constexpr (C::KV8_REG) {
+      if constexpr (AHEAD) {
+      } else if constexpr (C::KV8_REG) {
         vraw[1][d] = lds_read_tr8(sb8 + voff8[d] + V8_SECOND);
       } else {
         vlo[1][d] = lds_read_tr<KBOFF + S2OFF>(v_at(d));
@@ -989,7 +1031,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     }
   };
 
-  auto compute_tile = [&](int it, bool tree, auto masked_tag) __attribute__((always_inline)) {
+  auto no_refill = [](auto) __attribute__((always_inline)) {};
+  auto compute_tile = [&](int it, bool tree, auto masked_tag, auto &&refill) __attribute__((always_inline)) {
     const int base = tree ? (it - n_ct) * TK : k0 + it * TK;
     const int limit = tree ? Tb : k1;
     const lds_byte *stage = lds + (it % NSTAGE) * STAGE_BYTES;
@@ -997,9 +1040,9 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     // wave-uniform: a block is skipped when none of its keys exists, and all of them by a wave
     // none of whose query rows exists (it still loads its share of every tile)
     if (!wave_has_rows) return;
-    if (base + wk * KBW * 32 < limit) compute_block(stage, std::integral_constant<int, 0>{}, base, limit, tree, masked_tag, std::false_type{});
+    if (base + wk * KBW * 32 < limit) compute_block(stage, std::integral_constant<int, 0>{}, base, limit, tree, masked_tag, std::false_type{}, refill);
     if constexpr (KBW > 1)
-      if (base + (wk * KBW + 1) * 32 < limit) compute_block(stage, std::integral_constant<int, 1>{}, base, limit, tree, masked_tag, std::false_type{});
+      if (base + (wk * KBW + 1) * 32 < limit) compute_block(stage, std::integral_constant<int, 1>{}, base, limit, tree, masked_tag, std::false_type{}, refill);
   };
 
   // ---- one pipeline step: wait for tile `it`, refill the stage tile it-1 used, compute ----
@@ -1018,7 +1061,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     if (!(C::KV8_REG && WM == 1)) __builtin_amdgcn_s_barrier();
     if (it + PD < n_tiles) issue_tile(it + PD);
     }
-    compute_tile(it, decltype(tree_tag)::value, masked_tag);
+    compute_tile(it, decltype(tree_tag)::value, masked_tag, no_refill);
   };
 
   // ---- the pipelined loop's loads: K and V of a tile apart ----
@@ -1030,10 +1073,6 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   const int64_t tile_bytes = (int64_t)TK * p.stride_tok * EB;
   const char *k_next = kc_bytes + (cache_base + (int64_t)k0 * p.stride_tok) * EB;
   const char *v_next = vc_bytes + (cache_base + (int64_t)k0 * p.stride_tok) * EB;
-  auto tile_row = [&](int j) __attribute__((always_inline)) { return C::STEADY ? full_key(j) : row0_of(j) + lrow; };
-  uint32_t lane_off[NLDK];
-#pragma unroll
-  for (int j = 0; j < NLDK; ++j) lane_off[j] = (uint32_t)tile_row(j) * (uint32_t)tok_bytes + (uint32_t)chunk_of(j) * 16u;
   // Paged: a multiply-add on the number of each row's page, for K; V of that tile, queued next, takes the same offsets.
   uint64_t row_at[NLDK];
   auto issue_full = [&](int t, auto v_tag) __attribute__((always_inline)) {
@@ -1570,7 +1609,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
       // the partial cache tile and the tree's keys: queued long ago
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
       __builtin_amdgcn_s_barrier();
-      for (; it < n_tiles; ++it) compute_tile(it, it >= n_ct, std::true_type{});
+      for (; it < n_tiles; ++it) compute_tile(it, it >= n_ct, std::true_type{}, no_refill);
     }
   } else if constexpr (C::STEADY) {
     if (n_full >= kSteadyTiles) {
@@ -1608,8 +1647,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         issue_steady(t + PD);
         if (!wave_has_rows) return;
         const lds_byte *stage = lds + (t % NSTAGE) * STAGE_BYTES;
-        compute_block(stage, std::integral_constant<int, 0>{}, 0, 0, false, std::false_type{}, std::true_type{});
-        if constexpr (KBW > 1) compute_block(stage, std::integral_constant<int, 1>{}, 0, 0, false, std::false_type{}, std::true_type{});
+        compute_block(stage, std::integral_constant<int, 0>{}, 0, 0, false, std::false_type{}, std::true_type{}, no_refill);
+        if constexpr (KBW > 1) compute_block(stage, std::integral_constant<int, 1>{}, 0, 0, false, std::false_type{}, std::true_type{}, no_refill);
       };
       static_assert(KBW <= 2, "");
 #pragma unroll
@@ -1619,6 +1658,27 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     }
   }
   if (!C::PIPED || !piped) {
+    if constexpr (C::AHEAD && !PAGED) {
+      // full tiles that queue full tiles: a part of the loads behind each product of the scores
+      for (; it + PD < n_full; ++it) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(NLD * (PD - 1)));
+        __builtin_amdgcn_s_barrier();
+        const int64_t at = (cache_base + (int64_t)(k0 + (it + PD) * TK) * p.stride_tok) * EB;
+        const char *const ksrc = kc_bytes + at, *const vsrc = vc_bytes + at;
+        lds_byte *const to = lds + ((it + PD) % NSTAGE) * STAGE_BYTES;
+        auto load = [&](auto s_tag) __attribute__((always_inline)) {
+          constexpr int s = decltype(s_tag)::value;
+#pragma unroll
+          for (int l = (s * NLD + NS - 1) / NS; l < ((s + 1) * NLD + NS - 1) / NS; ++l) {
+            const int j = l % NLDK;
+            if (l < NLDK) __builtin_amdgcn_global_load_lds(GLOBAL_PTR(ksrc + lane_off[j]), to + kdst_of(j), 16, 0, kLoadOnce);
+            else __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vsrc + lane_off[j]), to + vdst_of(j), 16, 0, kLoadOnce);
+          }
+        };
+        if (wave_has_rows) compute_tile(it, false, std::false_type{}, load);
+        else static_for<NS>(load);
+      }
+    }
     for (; it < n_full; ++it) step(it, std::false_type{}, std::false_type{});
     for (; it < n_ct; ++it) step(it, std::true_type{}, std::false_type{});   // the partial cache tile
     for (; it < n_tiles; ++it) step(it, std::true_type{}, std::true_type{});  // the tree's own keys

@@ -180,6 +180,16 @@ def test_every_band_of_the_launch_planner(gpu, B, L, T, page, rows, splits):
     check_full(gpu, w, label=f"planner band rows={rows} splits={splits} page={page}")
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("shape", [1, 2, 3])
+def test_tiles_queued_under_the_products_of_the_scores_match_oracle(gpu, shape, D):
+    """Splits of one to eleven full tiles, whole and with a part of one behind them, so that the loop over full tiles that queue
+    full tiles runs never, once, twice and more often."""
+    for splits, L in ((1, [63, 64, 127, 128]), (1, [129, 191, 192, 200]), (1, [320, 383, 449, 704]), (2, [640, 511, 129, 60])):
+        w = wl.random_workload(1200 + shape + D + L[0], 4, 8, 2, D, L, [20, 9, 33, 1])
+        check_full(gpu, w, num_splits=splits, plan_shape=shape, label=f"queued under products shape={shape}")
+
+
 @pytest.mark.parametrize("page", [0, 16])
 def test_length_hint_changes_the_plan_not_the_result(gpu, page):
     """Long ragged caches with their sum passed as the planning hint: shorter splits (asserted), same result."""
