@@ -248,6 +248,13 @@ int32_t tva_plan_workgroup_rows(const tva_args *a);
 int tva_tree_verify_attn(const tva_args *a, void *stream);
 
 /*
+ * For tests of the bounded wait: the same call, where the splits are merged in the attention launch itself each workgroup looks
+ * `polls` (>= 0) times for the others of its row block before it leaves its share of the rows to the last of them.  The result is
+ * the same.
+ */
+int tva_tree_verify_attn_wait_bound_test(const tva_args *a, int32_t polls, void *stream);
+
+/*
  * tva_tree_verify_attn for callers that cannot allocate device memory or have none to hand over
  * for the KV splits: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, same kernels, same result as tva_tree_verify_attn, except that
@@ -259,7 +266,7 @@ int tva_tree_verify_attn(const tva_args *a, void *stream);
  *     refused with TVA_WORKSPACE_TOO_SMALL and nothing is queued; a smaller num_splits, or
  *     tva_tree_verify_attn with a caller-owned workspace, serves them.
  *   - All calls on one GPU share that GPU's array.  The array keeps whatever the last call
- *     left; nothing in it needs to start at zero (each call writes every slot it later reads).
+ *     left; nothing in it needs to start at zero (a call takes from it only what it has written there itself).
  *     Calls that overlap on one GPU (different streams, or threads) race on it: serialise them,
  *     or use tva_tree_verify_attn with one workspace per stream.
  */

@@ -104,7 +104,7 @@ class TvaArgs(ctypes.Structure):
 
 
 EXPORTS = ("tva_build_ancestor_mask", "tva_build_ancestor_mask_host", "tva_workspace_bytes", "tva_plan_splits", "tva_plan_chunk_keys", "tva_plan_workgroup_rows", "tva_plan_slot_sequences",
-           "tva_tree_verify_attn", "tva_tree_verify_attn_static", "tva_static_scratch_bytes", "tva_tree_verify_attn_splits", "tva_merge_splits", "tva_strerror", "tva_version", "tva_sizeof_args", "tva_timeline_read")
+           "tva_tree_verify_attn", "tva_tree_verify_attn_wait_bound_test", "tva_tree_verify_attn_static", "tva_static_scratch_bytes", "tva_tree_verify_attn_splits", "tva_merge_splits", "tva_strerror", "tva_version", "tva_sizeof_args", "tva_timeline_read")
 # entry points of include/tva_verify.h (bound in verify.py)
 DRAFT_EXPORTS = ("tva_expand_workspace_bytes", "tva_expand_layer", "tva_sizeof_expand_args", "tva_tree_select_subtree",
                  "tva_tree_rerank_count", "tva_rerank_workspace_bytes",
@@ -160,6 +160,8 @@ def load_library():
     lib.tva_plan_workgroup_rows.argtypes = [ctypes.POINTER(TvaArgs)]
     lib.tva_tree_verify_attn.restype = ctypes.c_int
     lib.tva_tree_verify_attn.argtypes = [ctypes.POINTER(TvaArgs), ctypes.c_void_p]
+    lib.tva_tree_verify_attn_wait_bound_test.restype = ctypes.c_int
+    lib.tva_tree_verify_attn_wait_bound_test.argtypes = [ctypes.POINTER(TvaArgs), ctypes.c_int32, ctypes.c_void_p]
     lib.tva_tree_verify_attn_static.restype = ctypes.c_int
     lib.tva_tree_verify_attn_static.argtypes = [ctypes.POINTER(TvaArgs), ctypes.c_void_p]
     lib.tva_static_scratch_bytes.restype = ctypes.c_size_t

@@ -41,6 +41,7 @@
 #include <cmath>
 
 #include <atomic>
+#include <random>
 #include <type_traits>
 #include <utility>
 
@@ -55,7 +56,7 @@ namespace {
 #ifdef TVA_TIMELINE
 constexpr int TL_MAX_WG = 8192, TL_SLOTS = 8;
 __device__ unsigned long long timeline[TL_MAX_WG * TL_SLOTS];
-#define TL_DECL unsigned long long tl_t[6] = {0, 0, 0, 0, 0, 0}
+#define TL_DECL unsigned long long tl_t[8] = {0, 0, 0, 0, 0, 0, 0, 0}
 #define TL_STAMP(i) tl_t[i] = __builtin_amdgcn_s_memrealtime()
 #define TL_STORE(wg, first, n)                                                              \
   if (threadIdx.x == 0 && (wg) < TL_MAX_WG)                                                 \
@@ -80,6 +81,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // its blocks still move the reference.  Timed with and without it, three head shapes, unsplit and in four splits, geometric
 // mean with / without at 8, 12, 16, 20 and 32 full tiles: dense 1.02, 0.98, 0.98, 0.92, 0.88, paged 1.00, 0.98, 0.95, 0.92, 0.87.
 constexpr int kSteadyTiles = 11;
+constexpr int kShareSplits = 12;  // the most splits that are merged in the attention launch (merged_in_launch)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 // A tile takes the low-order P pass when, for some row, (largest probability of the tile) >
@@ -164,6 +166,8 @@ struct AttnParams {
   int64_t stride_page, stride_tok, stride_head;
   float scale_log2;  // scale * log2(e) (times the K scale of an fp8 cache)
   float v_scale;     // 1, or the V scale of an fp8 cache
+  uint64_t share_tag;  // not 0: a row block's splits are merged in this launch, and this is what tells it from every other
+  int share_polls;     // ... looks for the others after which a workgroup stops waiting for them
 };
 
 // The node of a query row (row = node * G + head in the group): row / G, exact for rows below 2^30 (g_magic is
@@ -279,7 +283,12 @@ struct AttnCfg {
   // parent indices of the sequence's tree (used when no ancestor masks are passed), behind those
   static constexpr int PARENT_OFF = RING_BYTES + PG_BYTES;
   static constexpr int PARENT_BYTES = TVA_MAX_TREE * 4;
-  static constexpr int TAIL_BYTES = PAIR ? MERGE_BYTES + PATCH_BYTES : (MERGE_BYTES > PATCH_BYTES ? MERGE_BYTES : PATCH_BYTES);
+  // Splits merged in the launch itself (the end of the kernel): per row its log-sum-exp, its number and where each wave stores it, and
+  // a word.  Where the references of the key groups were, or behind the patches.
+  static constexpr bool SHARES = D == 128 && WM > 1;
+  static constexpr int OWN_OFF = PAIR ? 0 : PATCH_BYTES, OWN_BYTES = SHARES ? (2 * WM + NW) * 32 * 4 + 16 : 0;
+  static_assert(RB == 1 && (!PAIR || !SHARES || OWN_BYTES <= MERGE_BYTES), "");
+  static constexpr int TAIL_BYTES = PAIR ? MERGE_BYTES + PATCH_BYTES : PATCH_BYTES + OWN_BYTES;
   static constexpr int SMEM = PARENT_OFF + PARENT_BYTES > TAIL_BYTES ? PARENT_OFF + PARENT_BYTES : TAIL_BYTES;
   // load instruction n of a tile (n = wave * NLDK + j): the first tile row it covers
   static constexpr int load_row0(int n) { return KV8 ? n * RPI8 : n / IPB + NBLK * ((n % IPB) * RPI); }
@@ -471,7 +480,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   int nc = (Lb + p.chunk_keys - 1) / p.chunk_keys;
   nc = nc < 1 ? 1 : nc;
   if (chunk >= nc) {
-    // this sequence has fewer chunks than the launch provides: mark the slot empty for the merge
+    // this sequence has fewer chunks than the launch provides: mark the slot empty for the merge's launch
+    if (C::SHARES && p.share_tag != 0) return;
     for (int row = rblk * BM + (int)threadIdx.x; row < R && row < (rblk + 1) * BM; row += blockDim.x) {
       const int t = node_of(p, row), g = row - t * p.G;
       p.part_lse[(size_t)chunk * p.sum_Q * p.Hq + (size_t)(tq0 + t) * p.Hq + kvh * p.G + g] = -INFINITY;
@@ -1683,7 +1693,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     for (; it < n_ct; ++it) step(it, std::true_type{}, std::false_type{});   // the partial cache tile
     for (; it < n_tiles; ++it) step(it, std::true_type{}, std::true_type{});  // the tree's own keys
   }
-  if constexpr (C::PIPED && PAGED) {
+  if constexpr (PAGED && C::SHARES) {
     const const_args late = late_args();
     p.G = late->G, p.g_magic = late->g_magic, p.g_bits = late->g_bits, p.Hq = late->Hq, p.sum_Q = late->sum_Q, p.n_chunks = late->n_chunks;
     p.out = late->out, p.lse = late->lse, p.part_out = late->part_out, p.part_lse = late->part_lse, p.v_scale = late->v_scale;
@@ -1692,6 +1702,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   __builtin_amdgcn_s_barrier();  // all waves are done reading the ring before it is reused below
   TL_STAMP(4);  // all tiles done
 
+  const uint64_t share_tag = C::SHARES ? late_args()->share_tag : 0;
   // ---- combine the two lane halves' partial sums, and the two key groups' references and sums ----
   // (factor: what a row's O is multiplied by -- to the groups' common reference, and 1 / sum)
   constexpr bool PAIR = C::PAIR;
@@ -1718,6 +1729,14 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
 #pragma unroll
   for (int r = 0; r < RB; ++r) factor[r] *= l_tot[r] > 0.f ? p.v_scale / l_tot[r] : 0.f;
+
+  // (A row whose sum is none -- NaN scores -- has no weight in the merge of the splits: in this launch its outputs are zeros then.)
+  if (C::SHARES && share_tag != 0 && nc > 1 && __builtin_expect(__builtin_amdgcn_ballot_w64(!(l_tot[0] > 0.f)) != 0, 0)) {
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oacc[0][d][i] = l_tot[0] > 0.f ? oacc[0][d][i] : 0.f;
+  }
 
   // ---- merge the WK key groups through LDS ----
   // Two key groups: each wave keeps one half of the head dimension and hands the other half to
@@ -1756,14 +1775,28 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   // The accumulators hold O^T (lane = row, registers = 16 scattered d per 32-wide block); each
   // wave transposes one 32-row block at a time through its own LDS patch so that global stores
   // are whole contiguous rows (of the half of the head dimension the wave holds, when paired).
-  const bool final_out = (p.n_chunks == 1);
+  const bool final_out = p.n_chunks == 1 || (share_tag != 0 && nc == 1);
   float *obase = final_out ? p.out : p.part_out + (size_t)chunk * p.sum_Q * p.Hq * D;
   float *lbase = final_out ? p.lse : p.part_lse + (size_t)chunk * p.sum_Q * p.Hq;
   constexpr int NDW = C::NDW;       // 32-wide d blocks this wave writes
   constexpr int TP = C::TP;         // patch row pitch in floats: 16 rows x 16 B apart in bank position
   constexpr int LPR = NDW * 8;      // lanes that cover one row piece with 16 bytes each
   constexpr int RPP = 64 / LPR;     // rows per wave-wide store
-  float *tbuf = reinterpret_cast<float *>(smem + C::PATCH_OFF) + (PAIR ? wave : wm) * (32 * TP);
+  float *const patches = reinterpret_cast<float *>(smem + C::PATCH_OFF);
+  float *tbuf = patches + (PAIR ? wave : wm) * (32 * TP);
+  const float own_lse2 = l_tot[0] > 0.f ? m_run[0] + __builtin_amdgcn_logf(l_tot[0]) : -INFINITY;
+  // (lane = row, registers = 16 scattered d) -> the wave's patch
+  auto to_patch = [&](int r) __attribute__((always_inline)) {
+#pragma unroll
+    for (int d = 0; d < NDW; ++d)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = PAIR ? oacc[r][d][i4 * 4 + e] : oacc[r][d][i4 * 4 + e] * factor[r];
+        *reinterpret_cast<f32x4 *>(tbuf + l32 * TP + 32 * d + 8 * i4 + 4 * hh) = v;
+      }
+  };
   // One basic block per 32 rows: rows past the last are stored as copies of the last one (to its own address, the same values),
   // so that no store sits behind a branch of its own and the reads of all pieces are in flight together.  What remains is the
   // LDS traffic of the two exchanges.  (One sequence of 2048 keys in 7 splits, from the last tile to the last store: 1.76 us
@@ -1778,15 +1811,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     float *const first = obase + ((int64_t)tq0 * p.Hq + kvh * p.G) * D + kept0 + (lane % LPR) * 4;
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-#pragma unroll
-      for (int d = 0; d < NDW; ++d)
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = PAIR ? oacc[r][d][i4 * 4 + e] : oacc[r][d][i4 * 4 + e] * factor[r];
-          *reinterpret_cast<f32x4 *>(tbuf + l32 * TP + 32 * d + 8 * i4 + 4 * hh) = v;
-        }
+      to_patch(r);
       const int row0 = rblk * BM + (wm * RB + r) * 32;
       if (row0 >= R) break;  // (wave-uniform)
       const int last = R - 1 - row0;
@@ -1806,14 +1831,215 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         if constexpr (ONCE) __builtin_nontemporal_store(v[i], dst);
         else *dst = v[i];
       }
-      if (rvalid[r] && hh == 0 && wk == 0)
-        lbase[orow[r]] = l_tot[r] > 0.f ? (m_run[r] + __builtin_amdgcn_logf(l_tot[r])) * kLn2 : -INFINITY;
+      if (rvalid[r] && hh == 0 && wk == 0) lbase[orow[r]] = own_lse2 * kLn2;
     }
   };
   if (final_out) write_out(std::false_type{});
-  else write_out(std::true_type{});
-  TL_STAMP(5);  // key groups merged, result stores issued
-  TL_STORE(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), 0, 6);
+  else if (share_tag == 0) write_out(std::true_type{});
+  if (!C::SHARES || final_out || share_tag == 0) {
+    TL_STAMP(5);  // key groups merged, result stores issued
+    TL_STORE(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), 0, 6);
+    return;
+  }
+  if constexpr (C::SHARES) {
+  // ---- the row block's splits merged in this launch, each workgroup a share of the rows ----
+  // The nc workgroups of a (sequence, KV head, row block) take a share of its rows each.  A workgroup stores the rows of the others'
+  // shares, says that it has, waits until all have, and merges its own share, which never leaves its LDS.  All that travels between
+  // them is written and read at device scope (past the caches of one XCD).
+  // What they say stands in the scratch memory where split 0 would keep the first row of its own share, which nobody else reads: a word
+  // per split, the launch's tag and a state.  The memory may hold anything: a word of another call, or of the same launch replayed,
+  // has no such tag, since tags are drawn per call and the words of a launch are cleared behind it.
+  //  - ARRIVED: its rows are there for the others.
+  //  - LEFT, once it has seen all arrive, or GAVE, once it has looked share_polls times: it will not look for arrivals again.  One
+  //    that gives up leaves its share's rows where the results go.
+  // Whoever then finds every word in one of the last two clears them; where some gave up, the one that takes the first word away does,
+  // and merges their shares.  The last to store such a state finds them so.  So nobody relies on the others being resident, and none
+  // waits longer than its looks.
+  enum : uint64_t { ARRIVED = 1, LEFT = 2, GAVE = 3 };
+  constexpr int LPW = D / 4, GROUPS = 64 / LPW;
+  constexpr int kDevice = 16;                  // the cache policy's sc1: device scope
+  constexpr uint32_t kNowhere = 0x80000000u;   // past every bound, with what may be added: neither read nor stored
+  const bool keeps_words = wave == C::NW - 1;  // (this wave merges no rows of its workgroup's share)
+  const int Rb = R - rblk * BM < BM ? R - rblk * BM : BM;
+  // (Rb / nc rounded up: whole or at least 1/32 above it, and the reciprocal is good to a few units of 2^-23)
+  const int per = __builtin_amdgcn_readfirstlane((int)fmaf((float)Rb, __builtin_amdgcn_rcpf((float)nc), 0.99f));
+  const int share0 = chunk * per, end = share0 + per < Rb ? share0 + per : Rb;
+  const uint32_t n_rows = (uint32_t)p.sum_Q * (uint32_t)p.Hq;  // (all rows of all splits are less than 2 GiB)
+  float *const own_lses = reinterpret_cast<float *>(smem + C::OWN_OFF);
+  uint32_t *const rows = reinterpret_cast<uint32_t *>(own_lses + WM * 32), *const stored = rows + WM * 32 + wave * 32;
+  int *const seen = reinterpret_cast<int *>(rows + WM * 32 + C::NW * 32);
+  const auto parts = __builtin_amdgcn_make_buffer_rsrc(p.part_out, 0, (int)((uint32_t)p.n_chunks * n_rows * (D * 4)), 0x00020000);
+  const auto part_lses = __builtin_amdgcn_make_buffer_rsrc(p.part_lse, 0, (int)((uint32_t)p.n_chunks * n_rows * 4), 0x00020000);
+  const auto results = __builtin_amdgcn_make_buffer_rsrc(p.out, 0, (int)(n_rows * (D * 4)), 0x00020000);
+  const auto result_lses = __builtin_amdgcn_make_buffer_rsrc(p.lse, 0, (int)(n_rows * 4), 0x00020000);
+  {
+    const int rl = wm * 32 + l32;
+    const uint32_t at = (uint32_t)chunk * n_rows + (uint32_t)orow[0];
+    if (hh == 0) stored[l32] = rl < Rb && (rl < share0 || rl >= end) ? at * (D * 4) : kNowhere;
+    if (hh == 0 && wk == 0) {
+      own_lses[rl] = own_lse2, rows[rl] = (uint32_t)orow[0];
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(own_lse2), part_lses, rl < Rb ? at * 4 : kNowhere, 0, kDevice);
+    }
+    to_patch(0);
+    f32x4 v[32 / RPP];
+    uint32_t to[32 / RPP];
+#pragma unroll
+    for (int i = 0; i < 32 / RPP; ++i) {
+      to[i] = stored[i * RPP + lane / LPR];
+      v[i] = *reinterpret_cast<const f32x4 *>(tbuf + (i * RPP + lane / LPR) * TP + (lane % LPR) * 4);
+    }
+#pragma unroll
+    for (int i = 0; i < 32 / RPP; ++i)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[i]), parts, to[i] + (uint32_t)(kept0 + (lane % LPR) * 4) * 4, 0, kDevice);
+  }
+  TL_STAMP(5);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  uint64_t *const words = reinterpret_cast<uint64_t *>(p.part_out + (size_t)__builtin_amdgcn_readfirstlane(rows[0]) * D);
+  auto look = [&]() __attribute__((always_inline)) -> uint64_t {  // a split's state, 0: none; lanes past the splits: LEFT
+    if (lane >= nc) return LEFT;
+    const uint64_t w = __hip_atomic_load(words + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return (w & ~3ull) == share_tag ? w & 3 : 0;
+  };
+  auto say = [&](uint64_t state) __attribute__((always_inline)) {
+    if (lane == 0) __hip_atomic_store(words + chunk, share_tag | state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  const int grp = lane / LPW, col = (lane % LPW) * 4;
+  auto own_row = [&](int rl) __attribute__((always_inline)) {
+    const int wave_of = (PAIR ? col / (D / 2) * WM : 0) + rl / 32;
+    return *reinterpret_cast<const f32x4 *>(patches + (wave_of * 32 + rl % 32) * TP + (PAIR ? col % (D / 2) : col));
+  };
+  bool mine = true;        // the share that is merged is this workgroup's own
+  // A group of lanes takes a row, a lane 16 bytes of it: from all other splits, NI of them in flight for each of ROWS rows, and
+  // without a branch between the loads and what is computed from them.  Code that runs once costs about 0.1 us for every 64 bytes of
+  // it (one sequence of 2048 keys, 60 nodes: 0.9 us more with a comparison and four selections per split and row), so the
+  // log-sum-exps are to the base 2 here, and past the splits nothing is read (the last one again instead, for shorter addresses:
+  // 2 .. 20 % of calls of 3, 4, 8 and 11 splits).
+  auto merge_share = [&](int share, auto ni_tag, auto rows_tag) __attribute__((always_inline)) {
+    constexpr int NI = decltype(ni_tag)::value, ROWS = decltype(rows_tag)::value;
+    const int last = (share + 1) * per < Rb ? (share + 1) * per : Rb;
+    for (int rl0 = share * per + (mine ? wave * GROUPS * ROWS : 0); rl0 < last; rl0 += (mine ? C::NW - 1 : 1) * GROUPS * ROWS) {
+      uint32_t row[ROWS];
+      float m[ROWS], z[ROWS];
+      f32x4 acc[ROWS];
+#pragma unroll
+      for (int j = 0; j < ROWS; ++j) {
+        const int rl = rl0 + j * GROUPS + grp;
+        row[j] = rows[rl < last ? rl : last - 1];
+      }
+      for (int k0 = 0; k0 < nc - 1; k0 += NI) {
+        float l[ROWS][NI];
+        f32x4 v[ROWS][NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const int k = k0 + i, s = k < share ? k : k + 1;
+          const uint32_t from = (uint32_t)s * n_rows, past = s < nc ? 0u : kNowhere;  // (past the splits: nothing is read)
+#pragma unroll
+          for (int j = 0; j < ROWS; ++j) {
+            l[j][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part_lses, (from + row[j]) * 4 | past, 0, kDevice));
+            v[j][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(parts, ((from + row[j]) * (D * 4) + col * 4) | past, 0, kDevice));
+          }
+        }
+        if (k0 == 0) {
+          if (mine) {
+#pragma unroll
+            for (int j = 0; j < ROWS; ++j) {
+              const int rl = rl0 + j * GROUPS + grp, rc = rl < last ? rl : last - 1;
+              m[j] = own_lses[rc], acc[j] = own_row(rc);
+            }
+          } else {
+#pragma unroll
+            for (int j = 0; j < ROWS; ++j) {
+              m[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(result_lses, row[j] * 4, 0, kDevice));
+              acc[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(results, row[j] * (D * 4) + col * 4, 0, kDevice));
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < ROWS; ++j) z[j] = m[j] > -INFINITY ? 1.f : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+          float top = m[j];
+#pragma unroll
+          for (int i = 0; i < NI; ++i) {
+            if (NI > 1) l[j][i] += k0 + i < nc - 1 ? 0.f : -INFINITY;
+            top = fmaxf(top, l[j][i]);
+          }
+          const float ref = top > -INFINITY ? top : 0.f, keep = fast_exp2(m[j] - ref);
+          m[j] = top;
+          z[j] *= keep;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[j][e] *= keep;
+#pragma unroll
+          for (int i = 0; i < NI; ++i) {
+            const float w = fast_exp2(l[j][i] - ref);
+            z[j] += w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(v[j][i][e], w, acc[j][e]);
+          }
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < ROWS; ++j) {
+        const bool any = z[j] > 0.f;
+        const uint32_t past = rl0 + j * GROUPS + grp < last ? 0u : kNowhere;
+        const float f0 = __builtin_amdgcn_rcpf(z[j]), f = fmaf(f0, fmaf(-z[j], f0, 1.f), f0);  // (a sum is 1 or more)
+        f32x4 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = any ? acc[j][e] * f : 0.f;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), results, (row[j] * (D * 4) + col * 4) | past, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(any ? (m[j] + __builtin_amdgcn_logf(z[j])) * kLn2 : -INFINITY), result_lses, row[j] * 4 | (col == 0 ? past : kNowhere), 0, 0);
+      }
+    }
+  };
+  if (keeps_words) {
+    say(ARRIVED);
+    bool all = false;
+    for (int polls = late_args()->share_polls; polls > 0; --polls) {
+      all = __builtin_amdgcn_ballot_w64(look() == 0) == 0;
+      if (all) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    if (all) say(LEFT);
+    if (lane == 0) *seen = all;
+  }
+  __syncthreads();
+  TL_STAMP(6);  // all have arrived
+  uint64_t shares = 1ull << chunk;  // those to merge
+  if (*seen == 0) {
+    for (int rl = share0 + wave * GROUPS + grp; rl < end; rl += C::NW * GROUPS) {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, own_row(rl)), results, rows[rl] * (D * 4) + col * 4, 0, kDevice);
+      if (col == 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(own_lses[rl]), result_lses, rows[rl] * 4, 0, kDevice);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (!keeps_words) return;
+    say(GAVE);
+  }
+  if (keeps_words) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (its last word is there for the others)
+    const uint64_t state = look();
+    if (__builtin_amdgcn_ballot_w64(state < LEFT) != 0) return;
+    shares = __builtin_amdgcn_ballot_w64(lane < nc && state == GAVE);
+    if (shares != 0) {
+      bool taken = false;
+      if (lane == 0) {
+        uint64_t word = share_tag | state;
+        taken = __hip_atomic_compare_exchange_strong(words, &word, (uint64_t)0, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (__builtin_amdgcn_ballot_w64(taken) == 0) return;
+    }
+    if (lane < nc) __hip_atomic_store(words + lane, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    mine = false;
+  }
+  for (; shares != 0; shares &= shares - 1) {
+    if (nc == 2) merge_share(__builtin_ctzll(shares), std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+    else if (nc <= 5) merge_share(__builtin_ctzll(shares), std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+    else merge_share(__builtin_ctzll(shares), std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
+  }
+  TL_STAMP(7);  // the share's results issued
+  TL_STORE(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), 0, 8);
+  }
 }
 #undef lrow
 #undef kdst_of
@@ -2217,6 +2443,33 @@ bool make_plan(const tva_args *a, Plan *pl) {
   return true;
 }
 
+// Whether a row block's splits are merged in the attention launch itself: D = 128, more rows than the 32-row shape's (of its two waves
+// one would merge: single sequences of 12 query nodes 0.9 .. 1.2 us slower than with a second launch; D = 64 up to 20 %), 2 .. 12
+// splits, and all workgroups (with the lengths given, those the plan puts first) on the chip at once, where none waits for one that
+// has not started.  Against a second launch, 28 drawn calls of these: 0.948 of the time called one by one, 0.950 in a graph (0.79 ..
+// 1.05 each); four of 15 .. 31 splits 1.00.  One sequence of 2048 keys, 60 nodes: 12.5 -> 11.7 us; 16 of 512 .. 2048 keys, 16 nodes
+// 27.8 -> 26.0; 8 of 4096 keys, 64 heads, 55.9 -> 52.4.  (A named number of splits: by the whole grid, so that hints change no bit of
+// the result there.)
+bool merged_in_launch(const tva_args *a, const Plan &pl, const AttnParams &p, const void *workspace) {
+  if (a->D != 128 || pl.variant == V_K2 || pl.n_chunks < 2 || pl.n_chunks > kShareSplits || ((uintptr_t)workspace & 15)) return false;
+  if ((int64_t)pl.n_chunks * query_rows(a) * a->Hq * a->D * 4 >= (1ll << 31)) return false;  // (offsets into the partial rows)
+  const int64_t splits = p.real_splits > 0 && a->num_splits == 0 ? p.real_splits : (int64_t)a->B * pl.n_chunks;
+  return splits * a->Hkv * pl.n_row_blocks <= (pl.variant == V_M2K2 ? 512 : 256);
+}
+// Looks at the others' words, about 0.6 us each, before a workgroup gives up: some 30 us and twice the time of its tiles
+int share_polls(const Plan &pl) { return 48 + 4 * (pl.chunk_keys / pl.TK); }
+
+// A number that no other call of the process is given and that scratch memory does not hold by chance; its last two bits are free
+uint64_t next_share_tag() {
+  static const uint64_t seed = ((uint64_t)std::random_device{}() << 32) | std::random_device{}();
+  static std::atomic<uint64_t> calls{0};
+  uint64_t x = seed + (calls.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9E3779B97F4A7C15ull;
+  x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+  x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+  x = (x ^ (x >> 31)) & ~3ull;
+  return x ? x : 4;
+}
+
 typedef void (*attn_fn)(const AttnParams);
 
 // Launch status.  An error some earlier HIP call of the process left behind is cleared before a
@@ -2422,7 +2675,7 @@ size_t tva_workspace_bytes(const tva_args *a) {
   return scratch_bytes(a, pl);
 }
 
-static int run_attention(const tva_args *a, void *workspace, size_t workspace_bytes, void *stream, bool merge);
+static int run_attention(const tva_args *a, void *workspace, size_t workspace_bytes, void *stream, bool merge, int polls = -1);
 
 int tva_tree_verify_attn(const tva_args *a, void *stream) {
   return a ? run_attention(a, a->workspace, a->workspace_bytes, stream, true) : TVA_INVALID_ARG;
@@ -2430,6 +2683,10 @@ int tva_tree_verify_attn(const tva_args *a, void *stream) {
 
 int tva_tree_verify_attn_splits(const tva_args *a, void *stream) {
   return a ? run_attention(a, a->workspace, a->workspace_bytes, stream, false) : TVA_INVALID_ARG;
+}
+
+int tva_tree_verify_attn_wait_bound_test(const tva_args *a, int32_t polls, void *stream) {
+  return a && polls >= 0 ? run_attention(a, a->workspace, a->workspace_bytes, stream, true, polls) : TVA_INVALID_ARG;
 }
 
 size_t tva_static_scratch_bytes(void) { return TVA_STATIC_SCRATCH_BYTES; }
@@ -2452,7 +2709,7 @@ int tva_tree_verify_attn_static(const tva_args *a, void *stream) {
   return run_attention(a, ptr, need > 0 ? TVA_STATIC_SCRATCH_BYTES : 0, stream, true);
 }
 
-static int run_attention(const tva_args *a, void *workspace, size_t workspace_bytes, void *stream, bool merge) {
+static int run_attention(const tva_args *a, void *workspace, size_t workspace_bytes, void *stream, bool merge, int polls) {
   int rc = check_args(a, false);
   if (rc != TVA_OK) return rc;
   if (a->sum_T == 0 || a->max_T == 0 || query_rows(a) == 0) return TVA_OK;
@@ -2503,6 +2760,10 @@ static int run_attention(const tva_args *a, void *workspace, size_t workspace_by
   p.scale_log2 = a->scale * kLog2e * ((a->kv_fp8 && a->k_scale > 0.f) ? a->k_scale : 1.f);
   p.v_scale = (a->kv_fp8 && a->v_scale > 0.f) ? a->v_scale : 1.f;
 
+  const bool in_launch = merge && merged_in_launch(a, pl, p, workspace);
+  p.share_tag = in_launch ? next_share_tag() : 0;
+  p.share_polls = polls < 0 ? share_polls(pl) : polls;
+
   if ((int64_t)a->B * pl.n_chunks > 65535 || pl.n_row_blocks > 65535) return TVA_UNSUPPORTED;
   const dim3 grid(a->Hkv, pl.n_row_blocks, a->B * pl.n_chunks);
   const bool paged = a->page_table != nullptr;
@@ -2516,7 +2777,7 @@ static int run_attention(const tva_args *a, void *workspace, size_t workspace_by
     e = paged ? dispatch_variant<64, true>(pl.variant, p, grid, st) : dispatch_variant<64, false>(pl.variant, p, grid, st);
   if (e != hipSuccess) return TVA_HIP_ERROR;
 
-  if (merge && pl.n_chunks > 1) {
+  if (merge && pl.n_chunks > 1 && !in_launch) {
     const int64_t n_rows = (int64_t)query_rows(a) * a->Hq;
     clear_stale_hip_error();
     if (a->D == 128) launch_merge<128>(p.part_out, p.part_lse, pl.n_chunks, n_rows, a->out, a->lse, st);

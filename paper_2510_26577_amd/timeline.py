@@ -103,6 +103,8 @@ def per_call_us(lib_is_timeline: bool, w, copies: int, replays: int, num_splits:
     attn = t[:min(n_wg, n), :6]
     attn = attn[attn[:, 5] > 0]              # (workgroups without rows or keys return early and leave none)
     merge = t[:min(n_merge, n), 6:8]
+    # (splits merged in the attention launch: a workgroup's two last stamps are its own)
+    merge = merge[merge[:, 0] > 0]
     return us, (rows, S, ck), attn, merge
 
 
@@ -118,7 +120,7 @@ def summarise(name, w, us_plain, us_instr, plan, attn, merge, cmd, mode) -> str:
         " microseconds; distribution over the workgroups of the last call of a HIP-graph replay: " + mode + ")",
         "",
         f"plan: {plan[0]} rows per workgroup, {plan[1]} KV splits of {plan[2]} keys; {len(attn)} attention workgroups"
-        + (f", {len(merge)} merge blocks" if merge is not None and len(merge) else ""),
+        + (f", {len(merge)} merges" if merge is not None and len(merge) else ""),
         f"per call, median of the replays: {us_instr:.2f} us (instrumented build)"
         + (f", {us_plain:.2f} us (libtva.so, same protocol)" if us_plain > 0 else ""),
         "",
@@ -131,12 +133,13 @@ def summarise(name, w, us_plain, us_instr, plan, attn, merge, cmd, mode) -> str:
     lines.append("  * of splits that run the pipelined loop: the tiles with the prepared low-order pass (5 or 6; 256-row shape 3)")
     if merge is not None and len(merge):
         m = merge - t0
+        apart = m[:, 0].min() > a[:, 5].max() + 1.0  # (a launch of its own starts no sooner)
         lines += [
-            "merge kernel, same clock:",
-            f"  {'entry, absolute':<44s} {st(m[:, 0])}",
+            "merge kernel, same clock:" if apart else "merge in the attention launch, same clock:",
+            f"  {'entry, absolute' if apart else 'all splits have arrived, absolute':<44s} {st(m[:, 0])}",
             f"  + {'partials read, merged, stores issued':<42s} {st(m[:, 1] - m[:, 0])}",
             f"  = {'stores issued, absolute':<42s} {st(m[:, 1])}",
-            f"gap between the last attention workgroup's stores and the first merge block: {m[:, 0].min() - a[:, 5].max():.2f} us",
+            *([f"gap between the last attention workgroup's stores and the first merge block: {m[:, 0].min() - a[:, 5].max():.2f} us"] if apart else []),
             f"from the first attention entry to the last merge store: {m[:, 1].max():.2f} us; the rest of the "
             f"{us_instr:.2f} us per call is the gap to the next call's first workgroup",
         ]

@@ -737,6 +737,137 @@ def test_filled_splits_first_is_a_permutation(gpu, shape):
         assert torch.equal(o, base) and torch.equal(l, lbase)
 
 
+def prepared(device, w, scales=(1.0, 1.0), **kw):
+    """(argument block, out, lse, scratch memory as 8-byte words) of a call on w with the parent arrays."""
+    import torch
+    from paper_2510_26577_amd import binding
+    dw = device.to_device(w)
+    out = torch.full((w.sum_T, w.Hq, w.D), float("nan"), dtype=torch.float32, device="cuda:0")
+    lse = torch.full((w.sum_T, w.Hq), float("nan"), dtype=torch.float32, device="cuda:0")
+    args = binding.make_args(q=dw.q, k_tree=dw.k_tree, v_tree=dw.v_tree, k_cache=dw.k_cache, v_cache=dw.v_cache, anc_mask=None,
+                             parent=dw.parent, cu_T=dw.cu_T, L=dw.L, max_T=w.max_T, max_L=w.max_L, scale=w.scale, cu_L=dw.cu_L,
+                             page_table=dw.page_table, page_size=w.page_size, out=out, lse=lse, kv_fp8=dw.k_cache.dtype == torch.uint8,
+                             k_scale=scales[0], v_scale=scales[1], **kw)
+    ws = torch.zeros(binding.workspace_bytes(args) // 8 + 2, dtype=torch.int64, device="cuda:0")
+    args.workspace, args.workspace_bytes = ws.data_ptr(), ws.numel() * 8
+    args._test = dw
+    return args, out, lse, ws
+
+
+@pytest.mark.parametrize("shape, page, fp8", [(2, 0, False), (3, 0, False), (4, 0, False), (5, 0, False), (2, 16, False), (3, 5, False),
+                                              (4, 16, False), (5, 16, False), (2, 0, True), (4, 16, True), (5, 0, True)])
+def test_splits_merged_in_the_launch(gpu, shape, page, fp8):
+    """2 .. 12 splits of row blocks of 4 .. 256 rows (fewer than splits, shares that no row is left for, sequences of fewer splits and
+    of none), whatever the scratch memory holds, and with workgroups that stop waiting for the others at once or soon: the oracle's
+    results, and the same bits each time.  Scratch memory on which it does not apply (not 16-byte aligned) takes the second launch."""
+    import torch
+    from oracle import fp8_oracle as f8
+    from paper_2510_26577_amd import binding
+    lib = binding.load_library()
+    for splits, L in ((2, [1500, 90, 0]), (3, [700, 1500, 129]), (5, [1500, 64, 900]), (6, [1500, 1100, 65]), (9, [1500, 700, 300]), (12, [1500, 1, 1400])):
+        Hkv = 2 if splits < 9 else 1  # (256 workgroups at most)
+        w = wl.random_workload(2400 + splits + shape, 3, 4 * Hkv, Hkv, 128, L, [65, 33, 1], max_depth=9, page_size=page)
+        scales = (1.0, 1.0)
+        if fp8:
+            w, *scales = wl.to_fp8_kv(w)
+        say(f"[case] merged in the launch shape={shape} page={page} fp8={fp8} splits={splits}")
+        ro, rl = f8.tree_verify_attn_fp8(w, *scales) if fp8 else orc.tree_verify_attn(w)
+        args, out, lse, ws = prepared(gpu, w, scales, num_splits=splits, plan_shape=shape)
+        S = binding.plan_splits(args)
+        assert S >= splits - 1
+        first = None
+        for fill in (0, -1, 0x7FF8000000000000, None):
+            for polls in (None, 0, 1, 3):
+                out.fill_(float("nan")), lse.fill_(float("nan"))
+                if fill is not None:
+                    ws.fill_(fill)
+                rc = lib.tva_tree_verify_attn(args, None) if polls is None else lib.tva_tree_verify_attn_wait_bound_test(args, polls, None)
+                assert rc == 0
+                torch.cuda.synchronize()
+                # (sequence 0 always has splits: its first words stand at the start of the memory and are cleared again)
+                nc = max(1, -(-L[0] // binding.plan_chunk_keys(args)))
+                assert nc < 2 or not ws[:nc].any().item()
+                got = (out.cpu().numpy(), lse.cpu().numpy())
+                if first is None:
+                    first = got
+                    assert np.abs(got[0] - ro).max() <= TOL_O and np.abs(got[1] - rl).max() <= TOL_LSE
+                assert np.array_equal(first[0], got[0]) and np.array_equal(first[1], got[1]), (splits, fill, polls)
+        args.workspace += 8
+        assert lib.tva_tree_verify_attn(args, None) == 0
+        torch.cuda.synchronize()
+        # (the same partial rows in another order: a few units of the last place of sums of at most 12 terms of size 4)
+        assert np.abs(out.cpu().numpy() - first[0]).max() <= 1e-5 and np.abs(lse.cpu().numpy() - first[1]).max() <= 1e-5
+
+
+def test_splits_merged_in_the_launch_on_shared_scratch_in_a_graph_and_on_three_streams(gpu):
+    """Layers that take turns on one scratch memory, captured and replayed between eager calls on it; and calls on three streams at
+    once, more workgroups together than the chip holds, each with scratch memory of its own."""
+    import torch
+    from paper_2510_26577_amd import binding
+    layers = [prepared(gpu, wl.random_workload(2500 + i, 1, 32, 8, 128, [L], [T], max_depth=9)) for i, (L, T) in
+              enumerate(((2048, 60), (1300, 60), (2048, 33), (900, 64)))]
+    ws = max((x[3] for x in layers), key=lambda t: t.numel())
+    want = []
+    for args, out, lse, own in layers:
+        binding.tree_verify_attn_raw(args)
+        torch.cuda.synchronize()
+        assert binding.plan_splits(args) > 1 and not own[:2].any().item()
+        want.append((out.clone(), lse.clone()))
+        args.workspace, args.workspace_bytes = ws.data_ptr(), ws.numel() * 8
+    same = lambda: all(torch.equal(x[1], o) and torch.equal(x[2], l) for x, (o, l) in zip(layers, want))
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(3):
+            for x in layers:
+                binding.tree_verify_attn_raw(x[0], stream=stream)
+    for replay in range(5):
+        for x in layers:
+            x[1].fill_(float("nan")), x[2].fill_(float("nan"))
+        ws.random_() if replay % 2 else ws.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same(), replay
+        for x in layers[::-1]:
+            binding.tree_verify_attn_raw(x[0])
+        torch.cuda.synchronize()
+        assert same(), replay
+    for args, _, _, own in layers:
+        args.workspace, args.workspace_bytes = own.data_ptr(), own.numel() * 8
+    streams = [torch.cuda.Stream() for _ in layers[:3]]
+    for x in layers:
+        x[1].fill_(float("nan")), x[2].fill_(float("nan"))
+    layers[3][1].copy_(want[3][0]), layers[3][2].copy_(want[3][1])
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for s, x in zip(streams, layers):
+            binding.tree_verify_attn_raw(x[0], stream=s)
+    torch.cuda.synchronize()
+    assert same()
+
+
+def test_a_row_without_weight_in_one_split_is_merged_like_in_a_second_launch(gpu):
+    """Values that are not numbers in one split's keys, and infinite scores in another's: as the second launch has them."""
+    import torch
+    from paper_2510_26577_amd import binding
+    lib = binding.load_library()
+    for shape in (2, 5):
+        args, out, lse, ws = prepared(gpu, wl.random_workload(2600, 2, 8, 2, 128, [1024, 1024], [40, 20], max_depth=9), num_splits=4, plan_shape=shape)
+        dw = args._test
+        dw.k_cache.view(torch.bfloat16)[300, 0] = float("nan")
+        dw.k_cache.view(torch.bfloat16)[1024 + 900, 1] = float("inf")
+        dw.v_cache.view(torch.bfloat16)[1024 + 20, 1, 5] = float("inf")
+        res = []
+        for shift in (0, 8):
+            args.workspace = ws.data_ptr() + shift
+            assert lib.tva_tree_verify_attn(args, None) == 0
+            torch.cuda.synchronize()
+            res.append((out.cpu().numpy(), lse.cpu().numpy()))
+        for a, b in zip(*res):
+            assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
+            ok = np.isfinite(a)
+            assert np.abs(a[ok] - b[ok]).max() <= 1e-5
+
+
 @pytest.mark.parametrize("splits", [2, 3, 7])
 def test_splits_entry_point_partials_match_oracle_key_ranges(gpu, splits):
     """tva_tree_verify_attn_splits leaves per-split partials that equal the oracle restricted to
