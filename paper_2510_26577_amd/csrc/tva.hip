@@ -2215,7 +2215,13 @@ void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
     const int tiles = max_by_len, tree_tiles = (a->max_T + pl->TK - 1) / pl->TK;
     const double tile_us = 1.30 * a->D / 128.0;
     const double part_mb = 2.0 * query_rows(a) * a->Hq * (a->D + 1) * sizeof(float) * 1e-6;
-    double best = 0.0;
+    // Where that comes to more splits than are merged in the attention launch (merged_in_launch), and a number that is, of splits
+    // of 12 tiles and more, one per CU (what the deep ring takes), promises less at what the merge costs there, that number is
+    // taken.  (16-bit K/V: 73 of 24019 drawn calls, 34 of them timed: 0.89 of the time in the mean, 0.75 .. 0.99; 3 sequences of 9311
+    // keys, 12 nodes, 21 splits of 7 tiles -> 10 of 15: 35 -> 26 us.  8-bit K/V, without the deep ring, 0.88 .. 1.09; splits of fewer
+    // tiles 0.89 .. 1.21.)
+    double best = 0.0, shared_best = 0.0;
+    int shared = 0;
     S = 1;
     for (int s = 1; s <= (tiles > 1 ? tiles : 1); ++s) {
       const int ckt = (tiles + s - 1) / s, nch = (tiles + ckt - 1) / ckt;
@@ -2231,9 +2237,14 @@ void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
       const int longest = nch > 1 && ckt > last ? ckt : last;
       const double share = wgs <= 256 ? 1.0 : 1.5 * (double)((wgs + 511) / 512);
       double cost = tile_us * longest * share;
+      if (nch > 1 && nch <= kShareSplits && a->D == 128 && variant == V_M2K2 && !a->kv_fp8 && wgs <= 256 && ckt >= 12) {
+        const double c = cost + 2.0 + 0.20 * part_mb * nch;
+        if (shared == 0 || c < shared_best - 1e-9) shared_best = c, shared = nch;
+      }
       if (nch > 1) cost += 3.0 + 0.30 * part_mb * nch;
       if (s == 1 || cost < best - 1e-9) best = cost, S = nch;
     }
+    if (S > kShareSplits && shared > 0 && shared_best < best) S = shared;
   } else if (S == 0) {
     // one workgroup per CU (256) if the batch allows, but no split shorter than two tiles:
     // every split costs a partial O of the size of the output, written and read back

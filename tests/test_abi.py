@@ -155,6 +155,16 @@ def test_launch_plan_bands(lib, B, L, T, rows, splits):
     assert ck % 32 == 0 and ck * splits >= L > ck * (splits - 1)
 
 
+@pytest.mark.parametrize("B, L, T, extra, rows, splits", [
+    (3, 9311, 12, {}, 64, 10),                   # 146 tiles: 10 splits of 15 that share the merge, one per CU, for 21 of 7
+    (3, 9311, 12, dict(kv_fp8=1), 64, 21),       # (8-bit K/V: no deep ring)
+    (2, 3700, 13, {}, 64, 15),                   # 58 tiles: 12 splits would be of 5
+])
+def test_long_splits_that_share_the_merge_are_taken_for_many_short_ones(lib, B, L, T, extra, rows, splits):
+    a = shape_args(B=B, max_L=L, max_T=T, sum_T=B * T, **extra)
+    assert (binding.plan_workgroup_rows(a), binding.plan_splits(a)) == (rows, splits)
+
+
 def test_launch_plan_properties_over_the_cost_table_grid(lib):
     """The grid the attention cost tables are measured on (paper, Method: f(B, c, n) for c = k L, n = 1..N;
     here B = 1, 2, 4 and 8, c = 256..2048, n = 1..72, benchmark head shape).  Whatever the split count the
