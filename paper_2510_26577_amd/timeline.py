@@ -135,11 +135,11 @@ def summarise(name, w, us_plain, us_instr, plan, attn, merge, cmd, mode) -> str:
         m = merge - t0
         apart = m[:, 0].min() > a[:, 5].max() + 1.0  # (a launch of its own starts no sooner)
         lines += [
-            "merge kernel, same clock:" if apart else "merge in the attention launch, same clock:",
+            "merge kernel, same clock:" if apart else "no merge kernel: merged in the attention launch, same clock:",
             f"  {'entry, absolute' if apart else 'all splits have arrived, absolute':<44s} {st(m[:, 0])}",
             f"  + {'partials read, merged, stores issued':<42s} {st(m[:, 1] - m[:, 0])}",
             f"  = {'stores issued, absolute':<42s} {st(m[:, 1])}",
-            *([f"gap between the last attention workgroup's stores and the first merge block: {m[:, 0].min() - a[:, 5].max():.2f} us"] if apart else []),
+            f"gap between the last attention workgroup's stores and the first merge: {m[:, 0].min() - a[:, 5].max():.2f} us",
             f"from the first attention entry to the last merge store: {m[:, 1].max():.2f} us; the rest of the "
             f"{us_instr:.2f} us per call is the gap to the next call's first workgroup",
         ]
