@@ -116,7 +116,8 @@ typedef struct tva_args {
   float *out; /* device fp32 [sum_T, Hq, D]  (sum_Q rows with cu_Q, below) */
   float *lse; /* device fp32 [sum_T, Hq]: natural-log sum-exp of the scaled scores */
 
-  void *workspace;        /* device scratch for the KV splits, may be NULL if 0 bytes */
+  void *workspace;        /* device scratch for the KV splits, may be NULL if 0 bytes; what it holds before
+                             does not matter (16-byte aligned: tva_tree_verify_attn may merge the splits in the attention launch) */
   size_t workspace_bytes; /* >= tva_workspace_bytes(args) */
   int32_t num_splits;     /* KV splits per sequence; 0 = library chooses */
 
