@@ -268,8 +268,13 @@ def measure(a):
         n_rows = w.sum_T * w.Hq
         po = [ws[: n_splits * n_rows * w.D].view(n_splits, n_rows, w.D) for ws in wss]
         pl = [ws[n_splits * n_rows * w.D: n_splits * n_rows * (w.D + 1)].view(n_splits, n_rows) for ws in wss]
+        for args in argv:  # (the step itself may merge in the attention launch and leave no partial results)
+            binding.tree_verify_attn_splits_raw(args, stream=stream)
         ms_merge = med(timed(a.steps, lambda i: binding.merge_splits(po[i % R], pl[i % R], out=outs[i % R].view(n_rows, w.D),
                                                                      lse=lses[i % R].view(n_rows), stream=stream)))
+        for i in range(R):  # (what is checked below are the step's own results)
+            step(i)
+        stream.synchronize()
 
     # ---- the CPU oracle leg (--no-cpu-baseline skips all of it; nothing else here touches the oracle):
     # first a spot check of what was just timed (first input set, sampled rows), then the oracle timed on
