@@ -285,7 +285,8 @@ struct AttnCfg {
   static constexpr int PARENT_BYTES = TVA_MAX_TREE * 4;
   // Splits merged in the launch itself (the end of the kernel): per row its log-sum-exp, its number and where each wave stores it, and
   // a word.  Where the references of the key groups were, or behind the patches.
-  static constexpr bool SHARES = D == 128 && WM > 1;
+  // (Not the paged 256-row shape with 8-bit K/V, whose loop pays for it: 49 sequences of 557 keys, unsplit, 62.6 -> 64.0 us.)
+  static constexpr bool SHARES = D == 128 && WM > 1 && !(KV8 && PAGED && WM == 8);
   static constexpr int OWN_OFF = PAIR ? 0 : PATCH_BYTES, OWN_BYTES = SHARES ? (2 * WM + NW) * 32 * 4 + 16 : 0;
   static_assert(RB == 1 && (!PAIR || !SHARES || OWN_BYTES <= MERGE_BYTES), "");
   static constexpr int TAIL_BYTES = PAIR ? MERGE_BYTES + PATCH_BYTES : PATCH_BYTES + OWN_BYTES;
@@ -2463,6 +2464,7 @@ bool make_plan(const tva_args *a, Plan *pl) {
 // 27.8 -> 26.0; 8 of 4096 keys, 64 heads, 55.9 -> 52.4.  (A named number of splits: by the whole grid, so that hints change no bit of
 // the result there.)
 bool merged_in_launch(const tva_args *a, const Plan &pl, const AttnParams &p, const void *workspace) {
+  if (a->kv_fp8 && a->page_table && pl.variant == V_W8) return false;
   if (a->D != 128 || pl.variant == V_K2 || pl.n_chunks < 2 || pl.n_chunks > kShareSplits || ((uintptr_t)workspace & 15)) return false;
   if ((int64_t)pl.n_chunks * query_rows(a) * a->Hq * a->D * 4 >= (1ll << 31)) return false;  // (offsets into the partial rows)
   const int64_t splits = p.real_splits > 0 && a->num_splits == 0 ? p.real_splits : (int64_t)a->B * pl.n_chunks;
