@@ -1981,6 +1981,46 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
           }
         }
       }
+      // A part without weight adds nothing, whatever it holds, as in merge_kernel.  Here that is told by what comes of it, 0 times
+      // infinity not being a number: rows with such an element are added up again, in the same order, without those parts.
+      bool lost = false;
+#pragma unroll
+      for (int j = 0; j < ROWS; ++j) {
+        const float sum = (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
+        lost |= sum != sum;
+      }
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(lost) != 0, 0)) {
+#pragma unroll 1
+        for (int again = 0; again < ROWS; ++again) {
+          const int rl = rl0 + again * GROUPS + grp, rc = rl < last ? rl : last - 1;
+          const uint32_t r = rows[rc];
+          float m1 = mine ? own_lses[rc] : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(result_lses, r * 4, 0, kDevice));
+          f32x4 a = mine ? own_row(rc) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(results, r * (D * 4) + col * 4, 0, kDevice));
+#pragma unroll 1
+          for (int k0 = 0; k0 < nc - 1; k0 += NI) {
+            const int k1 = k0 + NI < nc - 1 ? k0 + NI : nc - 1;
+            auto lse_of = [&](int k) __attribute__((always_inline)) {
+              return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part_lses, ((uint32_t)(k < share ? k : k + 1) * n_rows + r) * 4, 0, kDevice));
+            };
+            float top = m1;
+#pragma unroll 1
+            for (int k = k0; k < k1; ++k) top = fmaxf(top, lse_of(k));
+            const float ref = top > -INFINITY ? top : 0.f, keep = fast_exp2(m1 - ref);
+            m1 = top;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = keep != 0.f ? a[e] * keep : 0.f;
+#pragma unroll 1
+            for (int k = k0; k < k1; ++k) {
+              const float w = fast_exp2(lse_of(k) - ref);
+              const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(parts, ((uint32_t)(k < share ? k : k + 1) * n_rows + r) * (D * 4) + col * 4, 0, kDevice));
+#pragma unroll
+              for (int e = 0; e < 4; ++e) a[e] = w != 0.f ? fmaf(v[e], w, a[e]) : a[e];
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < ROWS; ++j) acc[j] = j == again ? a : acc[j];
+        }
+      }
 #pragma unroll
       for (int j = 0; j < ROWS; ++j) {
         const bool any = z[j] > 0.f;

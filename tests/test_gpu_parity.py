@@ -868,6 +868,38 @@ def test_a_row_without_weight_in_one_split_is_merged_like_in_a_second_launch(gpu
             assert np.abs(a[ok] - b[ok]).max() <= 1e-5
 
 
+@pytest.mark.parametrize("shape, S", [(2, 2), (2, 4), (3, 5), (2, 12), (4, 4), (5, 6)])
+def test_what_a_split_without_weight_holds_is_dropped(gpu, shape, S):
+    """Scores so low in one split that its weight is zero, and values there that are infinite or not numbers: the oracle's results for
+    finite values in their place, merged in the launch (also by workgroups that give up) and, S = 4 and more, in a second one."""
+    import torch
+    from paper_2510_26577_amd import binding
+    lib = binding.load_library()
+    L = S * 128
+    w = wl.random_workload(2700 + S + shape, 1, 8, 2, 128, [L], [40], max_depth=9)
+    w.q &= 0x7FFF  # (all positive)
+    k = w.k_cache.copy()
+    for dead in sorted({0, 1, S // 2, S - 2} - {S - 1}):
+        w.k_cache = k.copy()
+        w.k_cache[dead * 128:(dead + 1) * 128] = wl.f32_to_bf16_bits(np.float32(-32.0))  # (scores near -290)
+        ro, rl = orc.tree_verify_attn(w)
+        args, out, lse, ws = prepared(gpu, w, num_splits=S, plan_shape=shape)
+        assert (binding.plan_splits(args), binding.plan_chunk_keys(args)) == (S, 128)
+        v = args._test.v_cache.view(torch.bfloat16)[dead * 128:(dead + 1) * 128]
+        v[3, 0, 5], v[70, 0, 77], v[127, 1, 100] = float("inf"), float("nan"), float("-inf")
+        say(f"[case] a split without weight shape={shape} {dead} of {S}")
+        for how in ("in the launch", 0, 1) + (("second launch",) if S >= 4 else ()):
+            out.fill_(float("nan")), lse.fill_(float("nan"))
+            if how == "second launch":
+                args.workspace += 8  # (not 16-byte aligned)
+            rc = lib.tva_tree_verify_attn_wait_bound_test(args, how, None) if isinstance(how, int) else lib.tva_tree_verify_attn(args, None)
+            assert rc == 0
+            torch.cuda.synchronize()
+            o, l = out.cpu().numpy(), lse.cpu().numpy()
+            assert np.isfinite(o).all(), (dead, how)
+            assert np.abs(o - ro).max() <= TOL_O and np.abs(l - rl).max() <= TOL_LSE, (dead, how)
+
+
 @pytest.mark.parametrize("splits", [2, 3, 7])
 def test_splits_entry_point_partials_match_oracle_key_ranges(gpu, splits):
     """tva_tree_verify_attn_splits leaves per-split partials that equal the oracle restricted to
