@@ -2179,6 +2179,7 @@ struct Plan {
   int variant;  // index into the kernel table
   int BM, TK;
   int n_row_blocks, n_chunks, chunk_keys;
+  bool fewer;  // the splits are the fewer, longer ones that share the merge (plan_splits_of)
 };
 
 // workgroup shapes (values of tva_shape in tva.h, minus one)
@@ -2232,13 +2233,15 @@ void fill_slots(const tva_args *a, const Plan &pl, AttnParams *p) {
 }
 
 // The splits of one workgroup shape.  named: the shape is to be this one (else the 2 x 2 shape may take its deeper ring).
-void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
+// share: fewer, longer splits that share the merge may take the place of many short ones.
+void plan_splits_of(const tva_args *a, int variant, bool named, bool share, Plan *pl) {
   const int G = a->Hq / a->Hkv;
   const int rows = (a->cu_Q ? a->max_Q : a->max_T) * G;
   const int pairs = a->B * a->Hkv;
   pl->variant = variant;
   pl->BM = variant == V_W8 ? 256 : variant == V_M4K2 ? 128 : variant == V_K2 ? 32 : 64;
   pl->TK = 64;
+  pl->fewer = false;
   pl->n_row_blocks = rows > 0 ? (rows + pl->BM - 1) / pl->BM : 1;
   int S = a->num_splits;
   const int max_by_len = a->max_L > 0 ? (a->max_L + pl->TK - 1) / pl->TK : 1;
@@ -2259,8 +2262,7 @@ void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
     const double part_mb = 2.0 * query_rows(a) * a->Hq * (a->D + 1) * sizeof(float) * 1e-6;
     // Where that comes to more splits than are merged in the attention launch (merged_in_launch), and a number that is, of splits
     // of 12 tiles and more, one per CU (what the deep ring takes), promises less at what the merge costs there, that number is
-    // taken.  (16-bit K/V: 73 of 24019 drawn calls, 34 of them timed: 0.89 of the time in the mean, 0.75 .. 0.99; 3 sequences of 9311
-    // keys, 12 nodes, 21 splits of 7 tiles -> 10 of 15: 35 -> 26 us.  8-bit K/V, without the deep ring, 0.88 .. 1.09; splits of fewer
+    // taken, if that is what becomes of it (make_plan).  (8-bit K/V, without the deep ring, 0.88 .. 1.09 of the time; splits of fewer
     // tiles 0.89 .. 1.21.)
     double best = 0.0, shared_best = 0.0;
     int shared = 0;
@@ -2286,7 +2288,7 @@ void plan_splits_of(const tva_args *a, int variant, bool named, Plan *pl) {
       if (nch > 1) cost += 3.0 + 0.30 * part_mb * nch;
       if (s == 1 || cost < best - 1e-9) best = cost, S = nch;
     }
-    if (S > kShareSplits && shared > 0 && shared_best < best) S = shared;
+    if (share && S > kShareSplits && shared > 0 && shared_best < best) S = shared, pl->fewer = true;
   } else if (S == 0) {
     // one workgroup per CU (256) if the batch allows, but no split shorter than two tiles:
     // every split costs a partial O of the size of the output, written and read back
@@ -2390,7 +2392,8 @@ inline size_t scratch_bytes(const tva_args *a, const Plan &pl) {
   return pl.n_chunks > 1 ? (size_t)pl.n_chunks * query_rows(a) * a->Hq * (a->D + 1) * sizeof(float) : 0;
 }
 
-bool make_plan(const tva_args *a, Plan *pl) {
+// The plan, and whether fewer splits that share the merge had a part in it (or in what other shapes were held against).
+bool plan_of(const tva_args *a, bool share, Plan *pl, bool *fewer) {
   if (!a || a->B <= 0 || a->Hq <= 0 || a->Hkv <= 0 || a->Hq % a->Hkv) return false;
   if (a->sum_T < 0 || a->max_T < 0 || a->max_L < 0 || a->num_splits < 0) return false;
   if (a->plan_shape < TVA_SHAPE_AUTO || a->plan_shape > V_LAST + 1) return false;
@@ -2428,7 +2431,8 @@ bool make_plan(const tva_args *a, Plan *pl) {
   const bool forced = a->plan_shape != TVA_SHAPE_AUTO;
   if (forced) variant = a->plan_shape - 1;
   if (a->kv_fp8 && variant == V_M2K2_3) variant = V_M2K2;  // (8-bit K/V: no deep variant of the 2 x 2 shape)
-  plan_splits_of(a, variant, forced, pl);
+  plan_splits_of(a, variant, forced, share, pl);
+  *fewer = pl->fewer;
   // The rules above against the model: another shape is taken where it promises enough.  Asked where the rules have most
   // to lose: with the lengths of the caches known, and without them where more than 80 rows per KV head meet more than 64
   // pairs or 4096 keys.  3000 calls timed in every shape: 509 take another one than the rules', 13 % faster in the geometric
@@ -2447,7 +2451,8 @@ bool make_plan(const tva_args *a, Plan *pl) {
     tva_args shapes = *a;  // (the lengths shorten the splits of a shape, they do not choose it)
     shapes.sum_L = 0, shapes.L_host = nullptr;
     Plan plan;
-    plan_splits_of(&shapes, variant, false, &plan);
+    plan_splits_of(&shapes, variant, false, share, &plan);
+    *fewer |= plan.fewer;
     // (Dense, D = 128: where the lengths shorten the rules' splits to more workgroups than the deep 64-row shape may have, the two-stage
     // shape is what the rules come to, and what it takes is asked: 40 calls that were held to the deep shape's discount instead, 4
     // sequences of 2.5 .. 4 K keys, 30 nodes, 25 -> 35 us, take 0.99 of what they did before there was one, 28 others 0.83.)
@@ -2473,7 +2478,7 @@ bool make_plan(const tva_args *a, Plan *pl) {
     auto crowded = [&](int v) {
       if (v != V_M2K2_3 || !dense_wide(a) || !a->L_host) return false;
       Plan own_lengths;
-      plan_splits_of(a, v, true, &own_lengths);
+      plan_splits_of(a, v, true, share, &own_lengths);
       return own_lengths.n_chunks > 1 && (int64_t)pairs * own_lengths.n_row_blocks * own_lengths.n_chunks > 256;
     };
     double best = 0.0;
@@ -2482,16 +2487,36 @@ bool make_plan(const tva_args *a, Plan *pl) {
     for (int v = first; v <= last; ++v) {
       // (8-bit K/V: no deep variant; its four-wave shape widens every key once per row group, which short caches show)
       if (v == variant || (a->kv_fp8 && (v == V_M2K2_3 || (v == V_M2K2 && rows > 64)))) continue;
-      plan_splits_of(&shapes, v, true, &plan);
+      plan_splits_of(&shapes, v, true, share, &plan);
       const double us = plan_cost(&shapes, plan);
       if (us < enough(plan) * rules && (chosen < 0 || us < best) && scratch_bytes(a, plan) <= most && !crowded(v)) best = us, chosen = v;
     }
     if (chosen >= 0) {
       // (splits that the lengths shorten are more splits: where those pass the limit they keep their length)
       const size_t limit = std::max(scratch_bytes(a, *pl), own);
-      plan_splits_of(a, chosen, true, pl);
-      if (scratch_bytes(a, *pl) > limit) plan_splits_of(&shapes, chosen, true, pl);
+      plan_splits_of(a, chosen, true, share, pl);
+      *fewer |= pl->fewer;
+      if (scratch_bytes(a, *pl) > limit) plan_splits_of(&shapes, chosen, true, share, pl);
     }
+  }
+  return true;
+}
+
+// Fewer, longer splits are taken for the merge that they share, in place of many short ones of the 64-row shape.  The plan is made
+// without them where what becomes of them is of that shape but does not share it -- known lengths have made them more splits than
+// that, or more workgroups than the deep ring takes -- and where another shape's promise beats the short ones.
+// Timed, with / without them, all 184 of 96014 drawn calls whose plan they change: 88 as promised 0.92 of the time (0.84 .. 1.00, one
+// 1.07; 3 sequences of 9311 keys, 12 nodes, 21 splits of 7 tiles -> 10 of 15: 30.5 -> 27.0 us), 74 that the 128-row shape and five that
+// the 32-row shape take, which promise enough against longer splits and not against short ones, 0.94 (0.86 .. 1.03) and 0.98; 11 of more
+// splits or workgroups 1.11 (1.04 .. 1.23) and six for another shape 1.02 (0.95 .. 1.06): those are sent back.
+bool make_plan(const tva_args *a, Plan *pl) {
+  bool fewer = false;
+  if (!plan_of(a, true, pl, &fewer)) return false;
+  if (fewer) {
+    Plan without;
+    plan_of(a, false, &without, &fewer);
+    const bool shares = pl->variant == V_M2K2_3 && pl->n_chunks <= kShareSplits;
+    if (pl->BM == 64 && (!shares || without.BM != 64)) *pl = without;
   }
   return true;
 }

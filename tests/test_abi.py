@@ -165,6 +165,23 @@ def test_long_splits_that_share_the_merge_are_taken_for_many_short_ones(lib, B, 
     assert (binding.plan_workgroup_rows(a), binding.plan_splits(a)) == (rows, splits)
 
 
+@pytest.mark.parametrize("lengths, T, extra, rows, splits", [
+    ([11735, 9694, 7654], 16, dict(page_table=1, page_size=32, max_pages=367), 64, 21),  # known lengths make 8 long splits 12 on 288 workgroups
+    ([11640, 9961, 8283, 6604], 14, dict(cu_L=1), 64, 16),                               # (... 10 on 320)
+    ([10326, 10326], 32, dict(cu_L=1), 128, 15),                                         # the 128-row shape promises less than short splits
+    ([9311, 9311, 9311], 12, dict(cu_L=1), 64, 10),
+    ([9311, 9311, 9311], 12, dict(cu_L=1, plan_shape=2), 64, 21),                        # (a named shape is that shape: no deep ring)
+])
+def test_long_splits_give_way_where_they_would_not_share_the_merge(lib, lengths, T, extra, rows, splits):
+    L = np.array(lengths, np.int32)
+    B = len(lengths)
+    a = shape_args(B=B, max_L=int(L.max()), max_T=T, sum_T=B * T, sum_L=int(L.sum()), L_host=L.ctypes.data, **extra)
+    assert (binding.plan_workgroup_rows(a), binding.plan_splits(a)) == (rows, splits)
+    ck = binding.plan_chunk_keys(a)
+    if rows == 64 and 2 <= splits <= 12:
+        assert ck >= 12 * 64 and B * 8 * -(-T * 4 // 64) * splits <= 256
+
+
 def test_launch_plan_properties_over_the_cost_table_grid(lib):
     """The grid the attention cost tables are measured on (paper, Method: f(B, c, n) for c = k L, n = 1..N;
     here B = 1, 2, 4 and 8, c = 256..2048, n = 1..72, benchmark head shape).  Whatever the split count the
