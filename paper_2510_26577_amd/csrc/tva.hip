@@ -186,6 +186,11 @@ __device__ __forceinline__ float half_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The shapes that can merge a row block's splits in the attention launch (row_groups: their 32-row groups, AttnCfg::WM), for their
+// kernels and for the launch alike.  Not the 32-row shape nor D = 64 (merged_in_launch), nor the paged 256-row shape with 8-bit K/V,
+// whose loop pays for it: 49 sequences of 557 keys, unsplit, 62.6 -> 64.0 us.
+constexpr bool shape_shares(int D, int row_groups, bool paged, bool kv8) { return D == 128 && row_groups > 1 && !(kv8 && paged && row_groups == 8); }
+
 template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8 = false>
 struct AttnCfg {
   static constexpr int NW = WM * WK;
@@ -285,8 +290,7 @@ struct AttnCfg {
   static constexpr int PARENT_BYTES = TVA_MAX_TREE * 4;
   // Splits merged in the launch itself (the end of the kernel): per row its log-sum-exp, its number and where each wave stores it, and
   // a word.  Where the references of the key groups were, or behind the patches.
-  // (Not the paged 256-row shape with 8-bit K/V, whose loop pays for it: 49 sequences of 557 keys, unsplit, 62.6 -> 64.0 us.)
-  static constexpr bool SHARES = D == 128 && WM > 1 && !(KV8 && PAGED && WM == 8);
+  static constexpr bool SHARES = shape_shares(D, WM, PAGED, KV8);
   static constexpr int OWN_OFF = PAIR ? 0 : PATCH_BYTES, OWN_BYTES = SHARES ? (2 * WM + NW) * 32 * 4 + 16 : 0;
   static_assert(RB == 1 && (!PAIR || !SHARES || OWN_BYTES <= MERGE_BYTES), "");
   static constexpr int TAIL_BYTES = PAIR ? MERGE_BYTES + PATCH_BYTES : PATCH_BYTES + OWN_BYTES;
@@ -2529,8 +2533,7 @@ bool make_plan(const tva_args *a, Plan *pl) {
 // 27.8 -> 26.0; 8 of 4096 keys, 64 heads, 55.9 -> 52.4.  (A named number of splits: by the whole grid, so that hints change no bit of
 // the result there.)
 bool merged_in_launch(const tva_args *a, const Plan &pl, const AttnParams &p, const void *workspace) {
-  if (a->kv_fp8 && a->page_table && pl.variant == V_W8) return false;
-  if (a->D != 128 || pl.variant == V_K2 || pl.n_chunks < 2 || pl.n_chunks > kShareSplits || ((uintptr_t)workspace & 15)) return false;
+  if (!shape_shares(a->D, pl.BM / 32, a->page_table != nullptr, a->kv_fp8 != 0) || pl.n_chunks < 2 || pl.n_chunks > kShareSplits || ((uintptr_t)workspace & 15)) return false;
   if ((int64_t)pl.n_chunks * query_rows(a) * a->Hq * a->D * 4 >= (1ll << 31)) return false;  // (offsets into the partial rows)
   const int64_t splits = p.real_splits > 0 && a->num_splits == 0 ? p.real_splits : (int64_t)a->B * pl.n_chunks;
   return splits * a->Hkv * pl.n_row_blocks <= (pl.variant == V_M2K2 ? 512 : 256);
@@ -2564,6 +2567,7 @@ inline hipError_t launch_status(const char *what) {
 template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8 = false>
 hipError_t launch_attn(const AttnParams &p, dim3 grid, hipStream_t st) {
   using C = AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>;
+  if (p.share_tag != 0 && !C::SHARES) return hipErrorInvalidValue;  // (it would leave the results to a launch that nobody queues)
   // raising the dynamic-LDS limit is idempotent and needed once per device (and per instantiation)
   static std::atomic<uint64_t> attr_done{0};
   auto kfn = attn_kernel<D, WM, WK, RB, PAGED, NST, KV8>;
