@@ -36,12 +36,14 @@
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
+#include <sys/random.h>
+#include <time.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <cmath>
 
 #include <atomic>
-#include <random>
 #include <type_traits>
 #include <utility>
 
@@ -2541,15 +2543,21 @@ bool merged_in_launch(const tva_args *a, const Plan &pl, const AttnParams &p, co
 // Looks at the others' words, about 0.6 us each, before a workgroup gives up: some 30 us and twice the time of its tiles
 int share_polls(const Plan &pl) { return 48 + 4 * (pl.chunk_keys / pl.TK); }
 
-// A number that no other call of the process is given and that scratch memory does not hold by chance; its last two bits are free
+// A number that no other call of the process is given (an odd step visits all 2^62 before it comes back to one) and that scratch
+// memory does not hold by chance; its last two bits are free.  0 stands for none and is passed over.  Nothing here throws.
+uint64_t share_tag_seed() {
+  uint64_t seed = 0;
+  if (getrandom(&seed, sizeof seed, GRND_NONBLOCK) == (ssize_t)sizeof seed) return seed;
+  timespec now{};
+  clock_gettime(CLOCK_REALTIME, &now);
+  return ((uint64_t)now.tv_sec * 1000000007u + (uint64_t)now.tv_nsec) * 0xBF58476D1CE4E5B9ull ^ (uint64_t)getpid() << 40 ^ (uint64_t)(uintptr_t)&seed;
+}
 uint64_t next_share_tag() {
-  static const uint64_t seed = ((uint64_t)std::random_device{}() << 32) | std::random_device{}();
-  static std::atomic<uint64_t> calls{0};
-  uint64_t x = seed + (calls.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9E3779B97F4A7C15ull;
-  x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
-  x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-  x = (x ^ (x >> 31)) & ~3ull;
-  return x ? x : 4;
+  static std::atomic<uint64_t> next{share_tag_seed()};
+  uint64_t tag;
+  do tag = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed) << 2;
+  while (tag == 0);
+  return tag;
 }
 
 typedef void (*attn_fn)(const AttnParams);

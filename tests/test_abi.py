@@ -106,6 +106,11 @@ def shape_args(**kw):
     return a
 
 
+def test_the_library_draws_no_numbers_from_what_can_throw(lib):
+    """std::random_device throws where it has no source, and the entry points are C functions."""
+    assert b"random_device" not in open(binding.LIB_PATH, "rb").read()
+
+
 def test_plan_and_workspace(lib):
     a = shape_args(num_splits=1)
     assert binding.plan_splits(a) == 1 and binding.workspace_bytes(a) == 0
