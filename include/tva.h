@@ -250,8 +250,9 @@ int tva_tree_verify_attn(const tva_args *a, void *stream);
 
 /*
  * For tests of the bounded wait: the same call, where the splits are merged in the attention launch itself each workgroup looks
- * `polls` (>= 0) times for the others of its row block before it leaves its share of the rows to the last of them.  The result is
- * the same.
+ * `polls` (>= 0) times for the others of its row block before it leaves its share of the rows to the last of them.  The looks are the
+ * low 16 bits of it; bit 16 + s makes those of split s look for none, so that some of a row block give up and others do not.  The
+ * result is the same.
  */
 int tva_tree_verify_attn_wait_bound_test(const tva_args *a, int32_t polls, void *stream);
 

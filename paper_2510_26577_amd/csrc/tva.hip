@@ -169,7 +169,7 @@ struct AttnParams {
   float scale_log2;  // scale * log2(e) (times the K scale of an fp8 cache)
   float v_scale;     // 1, or the V scale of an fp8 cache
   uint64_t share_tag;  // not 0: a row block's splits are merged in this launch, and this is what tells it from every other
-  int share_polls;     // ... looks for the others after which a workgroup stops waiting for them
+  int share_polls;     // ... looks for the others after which a workgroup stops waiting for them (16 bits; bit 16 + s: split s looks for none)
 };
 
 // The node of a query row (row = node * G + head in the group): row / G, exact for rows below 2^30 (g_magic is
@@ -2043,7 +2043,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   if (keeps_words) {
     say(ARRIVED);
     bool all = false;
-    for (int polls = late_args()->share_polls; polls > 0; --polls) {
+    const int looks = late_args()->share_polls;
+    for (int polls = looks >> (16 + chunk) & 1 ? 0 : looks & 0xFFFF; polls > 0; --polls) {
       all = __builtin_amdgcn_ballot_w64(look() == 0) == 0;
       if (all) break;
       __builtin_amdgcn_s_sleep(1);
@@ -2541,7 +2542,7 @@ bool merged_in_launch(const tva_args *a, const Plan &pl, const AttnParams &p, co
   return splits * a->Hkv * pl.n_row_blocks <= (pl.variant == V_M2K2 ? 512 : 256);
 }
 // Looks at the others' words, about 0.6 us each, before a workgroup gives up: some 30 us and twice the time of its tiles
-int share_polls(const Plan &pl) { return 48 + 4 * (pl.chunk_keys / pl.TK); }
+int share_polls(const Plan &pl) { return std::min(48 + 4 * (pl.chunk_keys / pl.TK), 0xFFFF); }
 
 // A number that no other call of the process is given (an odd step visits all 2^62 before it comes back to one) and that scratch
 // memory does not hold by chance; its last two bits are free.  0 stands for none and is passed over.  Nothing here throws.

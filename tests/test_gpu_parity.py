@@ -758,8 +758,9 @@ def prepared(device, w, scales=(1.0, 1.0), **kw):
                                               (4, 16, False), (5, 16, False), (2, 0, True), (4, 16, True), (5, 0, True)])
 def test_splits_merged_in_the_launch(gpu, shape, page, fp8):
     """2 .. 12 splits of row blocks of 4 .. 256 rows (fewer than splits, shares that no row is left for, sequences of fewer splits and
-    of none), whatever the scratch memory holds, and with workgroups that stop waiting for the others at once or soon: the oracle's
-    results, and the same bits each time.  Scratch memory on which it does not apply (not 16-byte aligned) takes the second launch."""
+    of none), whatever the scratch memory holds, and with workgroups that stop waiting for the others at once or soon -- all of a row
+    block, or the first, the last, every other one or all but one of its splits, while the rest wait: the oracle's results, and the
+    same bits each time.  Scratch memory on which it does not apply (not 16-byte aligned) takes the second launch."""
     import torch
     from oracle import fp8_oracle as f8
     from paper_2510_26577_amd import binding
@@ -776,8 +777,9 @@ def test_splits_merged_in_the_launch(gpu, shape, page, fp8):
         S = binding.plan_splits(args)
         assert S >= splits - 1
         first = None
+        some = [4000 | at_once << 16 for at_once in (1, 1 << (S - 1), 0x555 & ((1 << S) - 1), (1 << S) - 1 - (1 << S // 2))]
         for fill in (0, -1, 0x7FF8000000000000, None):
-            for polls in (None, 0, 1, 3):
+            for polls in (None, 0, 1, 3, *some):
                 out.fill_(float("nan")), lse.fill_(float("nan"))
                 if fill is not None:
                     ws.fill_(fill)
