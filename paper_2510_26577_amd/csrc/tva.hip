@@ -1860,8 +1860,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   //  - LEFT, once it has seen all arrive, or GAVE, once it has looked share_polls times: it will not look for arrivals again.  One
   //    that gives up leaves its share's rows where the results go.
   // Whoever then finds every word in one of the last two clears them; where some gave up, the one that takes the first word away does,
-  // and merges their shares.  The last to store such a state finds them so.  So nobody relies on the others being resident, and none
-  // waits longer than its looks.
+  // and merges their shares, with all its waves.  The last to store such a state finds them so.  So nobody relies on the others being
+  // resident, and none waits longer than its looks.
   enum : uint64_t { ARRIVED = 1, LEFT = 2, GAVE = 3 };
   constexpr int LPW = D / 4, GROUPS = 64 / LPW;
   constexpr int kDevice = 16;                  // the cache policy's sc1: device scope
@@ -1916,40 +1916,52 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     const int wave_of = (PAIR ? col / (D / 2) * WM : 0) + rl / 32;
     return *reinterpret_cast<const f32x4 *>(patches + (wave_of * 32 + rl % 32) * TP + (PAIR ? col % (D / 2) : col));
   };
-  bool mine = true;        // the share that is merged is this workgroup's own
   // A group of lanes takes a row, a lane 16 bytes of it: from all other splits, NI of them in flight for each of ROWS rows, and
   // without a branch between the loads and what is computed from them.  Code that runs once costs about 0.1 us for every 64 bytes of
   // it (one sequence of 2048 keys, 60 nodes: 0.9 us more with a comparison and four selections per split and row), so the
   // log-sum-exps are to the base 2 here (made natural by one multiply-add: 2.57e-7 off, root mean square, 2.73e-7 by the second
   // launch), and past the splits nothing is read (the last one again instead, for shorter addresses:
   // 2 .. 20 % of calls of 3, 4, 8 and 11 splits).
-  auto merge_share = [&](int share, auto ni_tag, auto rows_tag) __attribute__((always_inline)) {
+  // Merged are the rows of the workgroup's own share, by the waves that do not keep the words, or, GIVEN, those of the shares that were
+  // given up, by all waves: the row block's rows one after the other, so that as many are in flight as the waves hold, whoever gave them up.
+  auto merge_rows = [&](uint32_t given, auto given_tag, auto ni_tag, auto rows_tag) __attribute__((always_inline)) {
+    constexpr bool GIVEN = decltype(given_tag)::value;
     constexpr int NI = decltype(ni_tag)::value, ROWS = decltype(rows_tag)::value;
-    const int last = (share + 1) * per < Rb ? (share + 1) * per : Rb;
-    for (int rl0 = share * per + (mine ? wave * GROUPS * ROWS : 0); rl0 < last; rl0 += (mine ? C::NW - 1 : 1) * GROUPS * ROWS) {
+    const float one_by_per = __builtin_amdgcn_rcpf((float)per);  // (GIVEN: quotients of numbers below 256, a half above whole ones)
+    auto share_of = [&](int rl) __attribute__((always_inline)) { return GIVEN ? (int)(((float)rl + 0.5f) * one_by_per) : chunk; };
+    const int last = GIVEN ? Rb : end;
+    for (int rl0 = (GIVEN ? 0 : share0) + wave * GROUPS * ROWS; rl0 < last; rl0 += (GIVEN ? C::NW : C::NW - 1) * GROUPS * ROWS) {
       uint32_t row[ROWS];
+      int share[ROWS];
+      bool mine[ROWS];  // the row is one that is to be merged
       float m[ROWS], z[ROWS];
       f32x4 acc[ROWS];
 #pragma unroll
       for (int j = 0; j < ROWS; ++j) {
-        const int rl = rl0 + j * GROUPS + grp;
-        row[j] = rows[rl < last ? rl : last - 1];
+        const int rl = rl0 + j * GROUPS + grp, rc = rl < last ? rl : last - 1;
+        row[j] = rows[rc], share[j] = share_of(rc), mine[j] = rl < last && (!GIVEN || (given >> share[j] & 1));
+      }
+      if constexpr (GIVEN) {
+        bool some = false;
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) some |= mine[j];
+        if (__builtin_amdgcn_ballot_w64(some) == 0) continue;
       }
       for (int k0 = 0; k0 < nc - 1; k0 += NI) {
         float l[ROWS][NI];
         f32x4 v[ROWS][NI];
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-          const int k = k0 + i, s = k < share ? k : k + 1;
-          const uint32_t from = (uint32_t)s * n_rows, past = s < nc ? 0u : kNowhere;  // (past the splits: nothing is read)
 #pragma unroll
           for (int j = 0; j < ROWS; ++j) {
+            const int k = k0 + i, s = k < share[j] ? k : k + 1;
+            const uint32_t from = (uint32_t)s * n_rows, past = s < nc ? 0u : kNowhere;  // (past the splits: nothing is read)
             l[j][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part_lses, (from + row[j]) * 4 | past, 0, kDevice));
             v[j][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(parts, ((from + row[j]) * (D * 4) + col * 4) | past, 0, kDevice));
           }
         }
         if (k0 == 0) {
-          if (mine) {
+          if constexpr (!GIVEN) {
 #pragma unroll
             for (int j = 0; j < ROWS; ++j) {
               const int rl = rl0 + j * GROUPS + grp, rc = rl < last ? rl : last - 1;
@@ -2000,13 +2012,14 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
         for (int again = 0; again < ROWS; ++again) {
           const int rl = rl0 + again * GROUPS + grp, rc = rl < last ? rl : last - 1;
           const uint32_t r = rows[rc];
-          float m1 = mine ? own_lses[rc] : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(result_lses, r * 4, 0, kDevice));
-          f32x4 a = mine ? own_row(rc) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(results, r * (D * 4) + col * 4, 0, kDevice));
+          const int own = share_of(rc);
+          float m1 = !GIVEN ? own_lses[rc] : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(result_lses, r * 4, 0, kDevice));
+          f32x4 a = !GIVEN ? own_row(rc) : __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(results, r * (D * 4) + col * 4, 0, kDevice));
 #pragma unroll 1
           for (int k0 = 0; k0 < nc - 1; k0 += NI) {
             const int k1 = k0 + NI < nc - 1 ? k0 + NI : nc - 1;
             auto lse_of = [&](int k) __attribute__((always_inline)) {
-              return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part_lses, ((uint32_t)(k < share ? k : k + 1) * n_rows + r) * 4, 0, kDevice));
+              return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part_lses, ((uint32_t)(k < own ? k : k + 1) * n_rows + r) * 4, 0, kDevice));
             };
             float top = m1;
 #pragma unroll 1
@@ -2018,7 +2031,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 #pragma unroll 1
             for (int k = k0; k < k1; ++k) {
               const float w = fast_exp2(lse_of(k) - ref);
-              const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(parts, ((uint32_t)(k < share ? k : k + 1) * n_rows + r) * (D * 4) + col * 4, 0, kDevice));
+              const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(parts, ((uint32_t)(k < own ? k : k + 1) * n_rows + r) * (D * 4) + col * 4, 0, kDevice));
 #pragma unroll
               for (int e = 0; e < 4; ++e) a[e] = w != 0.f ? fmaf(v[e], w, a[e]) : a[e];
             }
@@ -2030,7 +2043,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 #pragma unroll
       for (int j = 0; j < ROWS; ++j) {
         const bool any = z[j] > 0.f;
-        const uint32_t past = rl0 + j * GROUPS + grp < last ? 0u : kNowhere;
+        const uint32_t past = mine[j] ? 0u : kNowhere;
         const float f0 = __builtin_amdgcn_rcpf(z[j]), f = fmaf(f0, fmaf(-z[j], f0, 1.f), f0);  // (a sum is 1 or more)
         f32x4 x;
 #pragma unroll
@@ -2054,40 +2067,44 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
   __syncthreads();
   TL_STAMP(6);  // all have arrived
-  uint64_t shares = 1ull << chunk;  // those to merge
-  if (*seen == 0) {
+  // (the splits and rows in flight, by what registers hold)
+  auto merge = [&](uint32_t given, auto given_tag) __attribute__((always_inline)) {
+    if (nc == 2) merge_rows(given, given_tag, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+    else if (nc <= 5) merge_rows(given, given_tag, std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+    else merge_rows(given, given_tag, std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
+  };
+  if (*seen != 0) {
+    if (!keeps_words) merge(0, std::false_type{});
+  } else {
     for (int rl = share0 + wave * GROUPS + grp; rl < end; rl += C::NW * GROUPS) {
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, own_row(rl)), results, rows[rl] * (D * 4) + col * 4, 0, kDevice);
       if (col == 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(own_lses[rl]), result_lses, rows[rl] * 4, 0, kDevice);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (!keeps_words) return;
-    say(GAVE);
-  }
-  if (keeps_words) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (its last word is there for the others)
-    const uint64_t state = look();
-    if (__builtin_amdgcn_ballot_w64(state < LEFT) != 0) return;
-    shares = __builtin_amdgcn_ballot_w64(lane < nc && state == GAVE);
-    if (shares != 0) {
-      bool taken = false;
-      if (lane == 0) {
-        uint64_t word = share_tag | state;
-        taken = __hip_atomic_compare_exchange_strong(words, &word, (uint64_t)0, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      if (__builtin_amdgcn_ballot_w64(taken) == 0) return;
-    }
-    if (lane < nc) __hip_atomic_store(words + lane, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    mine = false;
-  }
-  for (; shares != 0; shares &= shares - 1) {
-    if (nc == 2) merge_share(__builtin_ctzll(shares), std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
-    else if (nc <= 5) merge_share(__builtin_ctzll(shares), std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
-    else merge_share(__builtin_ctzll(shares), std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
+    if (keeps_words) say(GAVE);
   }
   TL_STAMP(7);  // the share's results issued
   TL_STORE(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), 0, 8);
+  if (keeps_words) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (its last word is there for the others)
+    const uint64_t state = look();
+    uint32_t given = 0;
+    if (__builtin_amdgcn_ballot_w64(state < LEFT) == 0) {
+      given = (uint32_t)__builtin_amdgcn_ballot_w64(lane < nc && state == GAVE);
+      bool taken = given == 0;
+      if (lane == 0 && !taken) {
+        uint64_t word = share_tag | state;
+        taken = __hip_atomic_compare_exchange_strong(words, &word, (uint64_t)0, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (__builtin_amdgcn_ballot_w64(taken) == 0) given = 0;
+      else if (lane < nc) __hip_atomic_store(words + lane, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (lane == 0) seen[1] = (int)given;
+  }
+  __syncthreads();
+  const uint32_t given = (uint32_t)__builtin_amdgcn_readfirstlane(seen[1]);
+  if (__builtin_expect(given != 0, 0)) merge(given, std::true_type{});
   }
 }
 #undef lrow
@@ -2541,8 +2558,13 @@ bool merged_in_launch(const tva_args *a, const Plan &pl, const AttnParams &p, co
   const int64_t splits = p.real_splits > 0 && a->num_splits == 0 ? p.real_splits : (int64_t)a->B * pl.n_chunks;
   return splits * a->Hkv * pl.n_row_blocks <= (pl.variant == V_M2K2 ? 512 : 256);
 }
-// Looks at the others' words, about 0.6 us each, before a workgroup gives up: some 30 us and twice the time of its tiles
-int share_polls(const Plan &pl) { return std::min(48 + 4 * (pl.chunk_keys / pl.TK), 0xFFFF); }
+// Looks at the others' words, about 0.6 us each, before a workgroup gives up: some 10 us and twice the time of its tiles, which covers
+// splits of unequal length and two workgroups to a CU.  Alone on the chip nobody gives up (a call in which all do takes 17.6 us for 12.8,
+// one sequence of 2048 keys, 60 nodes); what it bounds is how long a CU is held for partners that wait for one, where other streams
+// have the chip: that sequence on four streams at once, us for the four calls: bound of 300 looks 42.8, 48 and four per tile 39, this
+// one 32.6, none 30.5, with a second launch 28.5; on three streams 23.3, two 16.7, by a second launch 23.3 and 17.4.  16 sequences of
+// 512 .. 2048 keys at 16 looks 26.5, from 48 on 25.4.
+int share_polls(const Plan &pl) { return std::min(16 + 3 * (pl.chunk_keys / pl.TK), 0xFFFF); }
 
 // A number that no other call of the process is given (an odd step visits all 2^62 before it comes back to one) and that scratch
 // memory does not hold by chance; its last two bits are free.  0 stands for none and is passed over.  Nothing here throws.
