@@ -2562,7 +2562,7 @@ bool merged_in_launch(const tva_args *a, const Plan &pl, const AttnParams &p, co
 // splits of unequal length and two workgroups to a CU.  Alone on the chip nobody gives up (a call in which all do takes 17.6 us for 12.8,
 // one sequence of 2048 keys, 60 nodes); what it bounds is how long a CU is held for partners that wait for one, where other streams
 // have the chip: that sequence on four streams at once, us for the four calls: bound of 300 looks 42.8, 48 and four per tile 39, this
-// one 32.6, none 30.5, with a second launch 28.5; on three streams 23.3, two 16.7, by a second launch 23.3 and 17.4.  16 sequences of
+// one 32.6, none 30.5, with a second launch 29.1; on three streams 23.6, two 16.6, by a second launch 23.6 and 17.6.  16 sequences of
 // 512 .. 2048 keys at 16 looks 26.5, from 48 on 25.4.
 int share_polls(const Plan &pl) { return std::min(16 + 3 * (pl.chunk_keys / pl.TK), 0xFFFF); }
 
