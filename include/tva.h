@@ -163,8 +163,10 @@ typedef struct tva_args {
      a CU decides when the launch ends; given the lengths, the library hands the workgroup slots out so that a long
      and a short sequence share one (a ragged batch of 64: 3 % faster, 17 % with an 8-bit cache).  In a launch with
      KV splits, the split length that sum_L only bounds is found by counting the non-empty splits (lengths of 16 K to
-     32 K tokens: 3 % shorter splits).  Results do not depend on the values beyond the split length (any values give
-     a valid plan); tva_workspace_bytes and the tva_plan_* queries read it the same way, so pass them the same. */
+     32 K tokens: 3 % shorter splits).  Results do not depend on the values beyond the split length and, with splits of
+     the library's choice, beyond whether the attention launch merges them or a second one does, which sums the same
+     partial results in another order: the last place may differ (any values give a valid plan).  tva_workspace_bytes and
+     the tva_plan_* queries read it the same way, so pass them the same. */
   const int32_t *L_host;
 } tva_args;
 

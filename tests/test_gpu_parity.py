@@ -801,6 +801,35 @@ def test_splits_merged_in_the_launch(gpu, shape, page, fp8):
         assert np.abs(out.cpu().numpy() - first[0]).max() <= 1e-5 and np.abs(lse.cpu().numpy() - first[1]).max() <= 1e-5
 
 
+@pytest.mark.parametrize("short", [1000, 3000])
+def test_lengths_that_place_the_splits_and_have_them_merged_in_the_launch(gpu, short):
+    """One long sequence among 24 short ones, splits by the library's choice, an eight-wave shape: the hints put the splits that they say
+    are filled first, and by their number have the launch merge them.  True, overstated and understated ones (of 3000 keys, in 80 splits
+    for 25: more workgroups wait for each other than the chip holds), waited for and given up at once: the oracle's results."""
+    import torch
+    from paper_2510_26577_amd import binding
+    lib = binding.load_library()
+    true = [8192] + [short + 3 * i for i in range(24)]
+    w = wl.random_workload(2450 + short, 25, 16, 4, 128, true, [32] + [4] * 24, max_depth=9)
+    ro, rl = orc.tree_verify_attn(w)
+    for name, lengths, S in (("true", true, 8 if short == 1000 else 3), ("overstated", [8192] * 25, 2), ("understated", [100] * 25, 8)):
+        hint = np.array(lengths, np.int32)
+        args, out, lse, ws = prepared(gpu, w, sum_L=int(hint.sum()), L_host=hint)
+        assert (binding.plan_workgroup_rows(args), binding.plan_splits(args)) == (128, S)
+        say(f"[case] lengths that place the splits, short={short}, {name}")
+        first = None
+        for polls in (None, 0, 4000 | 0x55 << 16):
+            out.fill_(float("nan")), lse.fill_(float("nan")), ws.fill_(-1)
+            rc = lib.tva_tree_verify_attn(args, None) if polls is None else lib.tva_tree_verify_attn_wait_bound_test(args, polls, None)
+            assert rc == 0
+            torch.cuda.synchronize()
+            assert not ws[:2].any().item()  # (merged in the launch: its words are cleared)
+            got = (out.cpu().numpy(), lse.cpu().numpy())
+            assert np.abs(got[0] - ro).max() <= TOL_O and np.abs(got[1] - rl).max() <= TOL_LSE, (name, polls)
+            first = first or got
+            assert np.array_equal(first[0], got[0]) and np.array_equal(first[1], got[1]), (name, polls)
+
+
 def test_splits_merged_in_the_launch_on_shared_scratch_in_a_graph_and_on_three_streams(gpu):
     """Layers that take turns on one scratch memory, captured and replayed between eager calls on it; and calls on three streams at
     once, more workgroups together than the chip holds, each with scratch memory of its own."""
