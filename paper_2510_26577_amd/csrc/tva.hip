@@ -60,12 +60,14 @@ constexpr int TL_MAX_WG = 8192, TL_SLOTS = 8;
 __device__ unsigned long long timeline[TL_MAX_WG * TL_SLOTS];
 #define TL_DECL unsigned long long tl_t[8] = {0, 0, 0, 0, 0, 0, 0, 0}
 #define TL_STAMP(i) tl_t[i] = __builtin_amdgcn_s_memrealtime()
+#define TL_MARK(i) tl_t[i] |= 1ull << 63  /* a stamp of merge_kernel */
 #define TL_STORE(wg, first, n)                                                              \
   if (threadIdx.x == 0 && (wg) < TL_MAX_WG)                                                 \
     for (int tl_i = 0; tl_i < (n); ++tl_i) timeline[(size_t)(wg) * TL_SLOTS + (first) + tl_i] = tl_t[tl_i]
 #else
 #define TL_DECL
 #define TL_STAMP(i)
+#define TL_MARK(i)
 #define TL_STORE(wg, first, n)
 #endif
 
@@ -2179,6 +2181,8 @@ __global__ void __launch_bounds__(256) merge_kernel(const float *__restrict__ pa
   if (grp == 0) *reinterpret_cast<f32x4 *>(out + row * D + col) = any ? acc * (1.f / z) : f32x4{0.f, 0.f, 0.f, 0.f};
   if (lane == 0) lse[row] = any ? m + __logf(z) : -INFINITY;
   TL_STAMP(1);  // stores issued
+  TL_MARK(0);
+  TL_MARK(1);
   TL_STORE(blockIdx.x, 6, 2);
 }
 

@@ -43,7 +43,7 @@ def get_workload(name: str):
 
 def per_call_us(lib_is_timeline: bool, w, copies: int, replays: int, num_splits: int, plan_shape: int, cold: bool = True):
     """Times the call (cold caches, HIP graph of `copies` calls) and, on the instrumented build, returns the
-    stamps of the last call: (microseconds per call, plan, attention stamps [wgs, 6], merge stamps [blocks, 2])."""
+    stamps of the last call: (microseconds per call, plan, *split_stamps)."""
     import torch
     lib = binding.load_library()
     base = device.to_device(w)
@@ -90,7 +90,7 @@ def per_call_us(lib_is_timeline: bool, w, copies: int, replays: int, num_splits:
             ts.append(e0.elapsed_time(e1) * 1e3 / calls)
     us = float(np.median(ts))
     if not lib_is_timeline:
-        return us, (rows, S, ck), None, None
+        return us, (rows, S, ck), None, None, False
     G = w.Hq // w.Hkv
     n_wg = w.Hkv * (-(-(w.max_T * G) // rows)) * w.B * S
     n_merge = -(-(w.sum_T * w.Hq) // 4) if S > 1 else 0
@@ -99,16 +99,25 @@ def per_call_us(lib_is_timeline: bool, w, copies: int, replays: int, num_splits:
     rc = lib.tva_timeline_read(buf.ctypes.data, n)
     if rc != 0:
         raise binding.TvaError(rc)
-    t = buf.astype(np.int64) * 0.01          # 100 MHz counts -> microseconds
-    attn = t[:min(n_wg, n), :6]
+    return us, (rows, S, ck), *split_stamps(buf, n_wg, n_merge)
+
+
+MERGE_LAUNCH = np.uint64(1 << 63)            # on the stamps of merge_kernel
+
+
+def split_stamps(buf, n_wg: int, n_merge: int):
+    """The stamps of a call: (attention [wgs, 6], merge [blocks or wgs, 2], whether the merge was a launch of its own), microseconds.
+    A workgroup that merged its share of the splits itself has its two last stamps in its own slot: its rows of `merge` are then the
+    attention's rows, those of workgroups without splits to merge NaN."""
+    apart = bool((buf[:, 6] & MERGE_LAUNCH).any())
+    t = (buf & ~MERGE_LAUNCH).astype(np.int64) * 0.01          # 100 MHz counts -> microseconds
+    attn = t[:n_wg]
     attn = attn[attn[:, 5] > 0]              # (workgroups without rows or keys return early and leave none)
-    merge = t[:min(n_merge, n), 6:8]
-    # (splits merged in the attention launch: a workgroup's two last stamps are its own)
-    merge = merge[merge[:, 0] > 0]
-    return us, (rows, S, ck), attn, merge
+    merge = t[:n_merge, 6:8] if apart else np.where(attn[:, 6:8] > 0, attn[:, 6:8], np.nan)
+    return attn[:, :6], merge, apart
 
 
-def summarise(name, w, us_plain, us_instr, plan, attn, merge, cmd, mode) -> str:
+def summarise(name, w, us_plain, us_instr, plan, attn, merge, apart, cmd, mode) -> str:
     def st(x):
         return f"min {x.min():6.2f}   median {np.median(x):6.2f}   max {x.max():6.2f}"
     t0 = attn[:, 0].min()
@@ -120,7 +129,7 @@ def summarise(name, w, us_plain, us_instr, plan, attn, merge, cmd, mode) -> str:
         " microseconds; distribution over the workgroups of the last call of a HIP-graph replay: " + mode + ")",
         "",
         f"plan: {plan[0]} rows per workgroup, {plan[1]} KV splits of {plan[2]} keys; {len(attn)} attention workgroups"
-        + (f", {len(merge)} merges" if merge is not None and len(merge) else ""),
+        + (f", {len(merge)} merge blocks" if apart else ""),
         f"per call, median of the replays: {us_instr:.2f} us (instrumented build)"
         + (f", {us_plain:.2f} us (libtva.so, same protocol)" if us_plain > 0 else ""),
         "",
@@ -131,16 +140,26 @@ def summarise(name, w, us_plain, us_instr, plan, attn, merge, cmd, mode) -> str:
         lines.append(f"  + {STAGES[i]:<42s} {st(a[:, i] - a[:, i - 1])}")
     lines.append(f"  = {'result stores issued, absolute':<42s} {st(a[:, 5])}")
     lines.append("  * of splits that run the pipelined loop: the tiles with the prepared low-order pass (5 or 6; 256-row shape 3)")
-    if merge is not None and len(merge):
-        m = merge - t0
-        apart = m[:, 0].min() > a[:, 5].max() + 1.0  # (a launch of its own starts no sooner)
+    m = merge - t0
+    shared = ~np.isnan(m[:, 0])
+    if apart:
         lines += [
-            "merge kernel, same clock:" if apart else "no merge kernel: merged in the attention launch, same clock:",
-            f"  {'entry, absolute' if apart else 'all splits have arrived, absolute':<44s} {st(m[:, 0])}",
+            "merge kernel, same clock:",
+            f"  {'entry, absolute':<44s} {st(m[:, 0])}",
             f"  + {'partials read, merged, stores issued':<42s} {st(m[:, 1] - m[:, 0])}",
             f"  = {'stores issued, absolute':<42s} {st(m[:, 1])}",
             f"gap between the last attention workgroup's stores and the first merge: {m[:, 0].min() - a[:, 5].max():.2f} us",
             f"from the first attention entry to the last merge store: {m[:, 1].max():.2f} us; the rest of the "
+            f"{us_instr:.2f} us per call is the gap to the next call's first workgroup",
+        ]
+    elif shared.any():
+        last = np.where(shared, m[:, 1], a[:, 5]).max()
+        lines += [
+            f"no merge kernel: merged in the attention launch, by {int(shared.sum())} workgroups, same clock:",
+            f"  + {'all splits of the row block have arrived':<42s} {st((m[:, 0] - a[:, 5])[shared])}",
+            f"  + {'partials read, merged, stores issued':<42s} {st((m[:, 1] - m[:, 0])[shared])}",
+            f"  = {'stores issued, absolute':<42s} {st(m[shared, 1])}",
+            f"from the first attention entry to the last store: {last:.2f} us; the rest of the "
             f"{us_instr:.2f} us per call is the gap to the next call's first workgroup",
         ]
     else:
@@ -165,15 +184,15 @@ def main(argv=None) -> int:
     a = ap.parse_args(argv)
     w = get_workload(a.workload)
     if a.plain:
-        us, plan, _, _ = per_call_us(False, w, a.copies, a.replays, a.splits, a.shape, cold=not a.warm)
+        us, plan, *_ = per_call_us(False, w, a.copies, a.replays, a.splits, a.shape, cold=not a.warm)
         print(f"{us:.3f}")
         return 0
     binding.use_timeline_library()
-    us, plan, attn, merge = per_call_us(True, w, a.copies, a.replays, a.splits, a.shape, cold=not a.warm)
+    us, plan, attn, merge, apart = per_call_us(True, w, a.copies, a.replays, a.splits, a.shape, cold=not a.warm)
     cmd = "python -m paper_2510_26577_amd.timeline " + " ".join(sys.argv[1:] if argv is None else argv)
     mode = (f"{a.copies} input cop{'y' if a.copies == 1 else 'ies'}, " +
             ("caches left as the calls before leave them" if a.warm else "caches flushed before the replay"))
-    text = summarise(a.workload, w, a.plain_us, us, plan, attn, merge, cmd, mode)
+    text = summarise(a.workload, w, a.plain_us, us, plan, attn, merge, apart, cmd, mode)
     print(text, end="")
     if a.out:
         with open(a.out, "w") as f:

@@ -11,7 +11,7 @@ import sys
 import numpy as np
 import pytest
 
-from paper_2510_26577_amd import binding, profile_kernels, small_rows, timeline
+from paper_2510_26577_amd import binding, profile_kernels, small_rows, timeline, workloads
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -80,7 +80,30 @@ def test_instrumented_build_stamps_are_ordered():
                         "--replays", "2"], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]
     stage_lines = [l for l in r.stdout.splitlines() if l.startswith("  + ")]
-    assert len(stage_lines) == 6                                 # five attention stages + the merge block
+    assert len(stage_lines) == 7                                 # five attention stages, the wait for the other splits, the merge
     for l in stage_lines:
         assert float(l.split("min")[1].split()[0]) >= 0.0, l
-    assert "merge kernel" in r.stdout and "gap between" in r.stdout
+    assert "no merge kernel: merged in the attention launch, by " in r.stdout and "gap between" not in r.stdout
+
+
+def test_timeline_tells_a_merge_in_the_launch_from_a_launch_of_its_own():
+    """Synthetic stamps: four workgroups, the last without splits to merge or without rows, one call of each form; what is said does
+    not follow from the times, which are the same in both."""
+    t = np.arange(8, dtype=np.uint64) * np.uint64(100) + np.uint64(5000)         # a microsecond a stage
+    buf = np.tile(t, (4, 1)) + np.arange(4, dtype=np.uint64)[:, None] * np.uint64(50)
+    shared = buf.copy()
+    shared[3, 6:] = 0
+    own = buf.copy()
+    own[3, :6] = 0
+    own[:, 6:] |= timeline.MERGE_LAUNCH
+    told = []
+    for stamps, n_merge in ((shared, 1), (own, 4)):
+        attn, merge, apart = timeline.split_stamps(stamps, 4, n_merge)
+        told.append(timeline.summarise("x", workloads.config1(), 0.0, 9.0, (64, 2, 64), attn, merge, apart, "cmd", "mode"))
+        assert len(attn) == (3 if apart else 4) and len(merge) == 4
+    assert "no merge kernel: merged in the attention launch, by 3 workgroups" in told[0] and "gap between" not in told[0]
+    assert "all splits of the row block have arrived   min   1.00   median   1.00   max   1.00" in told[0]
+    assert "to the last store: 8.00 us" in told[0]
+    assert "merge kernel, same clock:" in told[1] and "no merge kernel" not in told[1]
+    assert "gap between the last attention workgroup's stores and the first merge: 0.00 us" in told[1]
+    assert "3 attention workgroups, 4 merge blocks" in told[1]
