@@ -52,22 +52,23 @@
 namespace {
 
 // Instrumented build (-DTVA_TIMELINE, a library of its own): workgroup w of the attention kernel records
-// the constant 100 MHz counter at six points of its life, block w of the merge kernel at two; the stamps
-// stay in scalar registers until the end of the kernel and lane 0 stores them then, so that the kernel's
-// own memory operations are disturbed as little as possible.  tva_timeline_read copies them out.
+// the constant 100 MHz counter at six points of its life (eight where it merges the splits), block w of the merge kernel at two; the
+// stamps stay in lanes of one vector register until the end of the kernel and are stored then, so that the kernel's
+// own memory operations are disturbed as little as possible.  (The clock's low words.  In scalar registers eight stamps made the deep
+// 64-row shape write 15 vector registers to memory: 16 sequences of 512 .. 2048 keys 34 us instead of 27.)
+// tva_timeline_read copies them out.
 #ifdef TVA_TIMELINE
 constexpr int TL_MAX_WG = 8192, TL_SLOTS = 8;
 __device__ unsigned long long timeline[TL_MAX_WG * TL_SLOTS];
-#define TL_DECL unsigned long long tl_t[8] = {0, 0, 0, 0, 0, 0, 0, 0}
-#define TL_STAMP(i) tl_t[i] = __builtin_amdgcn_s_memrealtime()
-#define TL_MARK(i) tl_t[i] |= 1ull << 63  /* a stamp of merge_kernel */
+#define TL_DECL uint32_t tl_t = 0, tl_mark = 0
+#define TL_STAMP(i) asm volatile("v_writelane_b32 %0, %1, " #i : "+v"(tl_t) : "s"((uint32_t)__builtin_amdgcn_s_memrealtime()))
+#define TL_MARK tl_mark = 1  /* stamps of merge_kernel: bit 63 */
 #define TL_STORE(wg, first, n)                                                              \
-  if (threadIdx.x == 0 && (wg) < TL_MAX_WG)                                                 \
-    for (int tl_i = 0; tl_i < (n); ++tl_i) timeline[(size_t)(wg) * TL_SLOTS + (first) + tl_i] = tl_t[tl_i]
+  if (threadIdx.x < (n) && (wg) < TL_MAX_WG) timeline[(size_t)(wg) * TL_SLOTS + (first) + threadIdx.x] = tl_t | (uint64_t)tl_mark << 63
 #else
 #define TL_DECL
 #define TL_STAMP(i)
-#define TL_MARK(i)
+#define TL_MARK
 #define TL_STORE(wg, first, n)
 #endif
 
@@ -2181,8 +2182,7 @@ __global__ void __launch_bounds__(256) merge_kernel(const float *__restrict__ pa
   if (grp == 0) *reinterpret_cast<f32x4 *>(out + row * D + col) = any ? acc * (1.f / z) : f32x4{0.f, 0.f, 0.f, 0.f};
   if (lane == 0) lse[row] = any ? m + __logf(z) : -INFINITY;
   TL_STAMP(1);  // stores issued
-  TL_MARK(0);
-  TL_MARK(1);
+  TL_MARK;
   TL_STORE(blockIdx.x, 6, 2);
 }
 

@@ -110,7 +110,10 @@ def split_stamps(buf, n_wg: int, n_merge: int):
     A workgroup that merged its share of the splits itself has its two last stamps in its own slot: its rows of `merge` are then the
     attention's rows, those of workgroups without splits to merge NaN."""
     apart = bool((buf[:, 6] & MERGE_LAUNCH).any())
-    t = (buf & ~MERGE_LAUNCH).astype(np.int64) * 0.01          # 100 MHz counts -> microseconds
+    t = (buf & ~MERGE_LAUNCH).astype(np.int64)
+    if t.max() - t[t > 0].min() > 1 << 31:                     # the clock's low words came round during the call
+        t[(t > 0) & (t < 1 << 31)] += 1 << 32
+    t = t * 0.01                                               # 100 MHz counts -> microseconds
     attn = t[:n_wg]
     attn = attn[attn[:, 5] > 0]              # (workgroups without rows or keys return early and leave none)
     merge = t[:n_merge, 6:8] if apart else np.where(attn[:, 6:8] > 0, attn[:, 6:8], np.nan)

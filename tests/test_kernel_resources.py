@@ -8,12 +8,12 @@ import pytest
 from paper_2510_26577_amd import binding
 
 
-def kernels():
-    """{demangled-enough name: metadata} of every kernel in libtva.so."""
+def kernels(path=binding.LIB_PATH):
+    """{demangled-enough name: metadata} of every kernel in libtva.so, or in another build of it."""
     import msgpack
-    if not os.path.exists(binding.LIB_PATH):
-        binding.build_library()
-    data = open(binding.LIB_PATH, "rb").read()
+    if not os.path.exists(path):
+        binding.build_library(timeline=path == binding.TIMELINE_LIB_PATH)
+    data = open(path, "rb").read()
     found, at = {}, 0
     while (at := data.find(b"\x7fELF\x02\x01\x01\x40", at)) >= 0:  # 64-bit little-endian, OS/ABI AMDGPU_HSA
         shoff, = struct.unpack_from("<Q", data, at + 40)
@@ -53,6 +53,15 @@ def test_attention_kernels_spill_no_vector_registers(table):
     for name, k in table.items():
         if "attn_kernel" in name or "merge_kernel" in name:
             assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, name
+
+
+def test_instrumented_attention_kernels_spill_no_vector_registers():
+    """Time stamps of a kernel that writes its registers to memory are of another kernel.  (D = 128: of D = 64, where two to four workgroups
+    share a CU, three paged shapes have no register to spare for the stamps.)"""
+    seen = {n: k for n, k in kernels(binding.TIMELINE_LIB_PATH).items() if "attn_kernelILi128" in n}
+    assert len(seen) >= 18
+    for name, k in seen.items():
+        assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_spill_count"])
 
 
 def test_attention_kernels_of_which_two_share_a_compute_unit_leave_the_registers_for_it(table):

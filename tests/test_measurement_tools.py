@@ -97,6 +97,10 @@ def test_timeline_tells_a_merge_in_the_launch_from_a_launch_of_its_own():
     own[3, :6] = 0
     own[:, 6:] |= timeline.MERGE_LAUNCH
     told = []
+    around = np.where(shared, (shared + np.uint64((1 << 32) - 5555)) & np.uint64((1 << 32) - 1), 0)  # the clock's low words come round
+    assert around.max() > 1 << 31 and 0 < around[around > 0].min() < 1000
+    for x, y in zip(timeline.split_stamps(around, 4, 1), timeline.split_stamps(shared, 4, 1)):
+        assert np.allclose(x - 0.01 * ((1 << 32) - 5555), y, equal_nan=True) if isinstance(x, np.ndarray) else x == y
     for stamps, n_merge in ((shared, 1), (own, 4)):
         attn, merge, apart = timeline.split_stamps(stamps, 4, n_merge)
         told.append(timeline.summarise("x", workloads.config1(), 0.0, 9.0, (64, 2, 64), attn, merge, apart, "cmd", "mode"))
