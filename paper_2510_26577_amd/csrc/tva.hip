@@ -259,7 +259,10 @@ struct AttnCfg {
   // its products.  (One sequence of 2048 keys, 60 nodes, 7 splits of five tiles, one wave per SIMD; cycles a tile: queueing 434 -> 102,
   // since a CU takes 64 bytes a cycle and all waves queue at once, the arithmetic with the queueing in it 1541 -> 1621; 13.1 -> 12.6 us.
   // 128 keys, 4 heads, D = 64: 5.47 -> 5.38.  The shapes with a pipelined loop keep their plain one for their short splits.)
-  static constexpr bool AHEAD = WK > 1 && !KV8 && RB == 1 && !PIPED;
+  // The rings of three and four stages, 24 drawn calls each, with / without: paged deep 64-row shape 0.964; D = 64 dense, deep 64-row shape
+  // 0.985, 128-row shape 0.995, paged 0.996.  Not the paged 128-row shape, 1.008 (two at 1.02 and more; 16 sequences of 3000 keys, 60
+  // nodes, two row blocks, 1.05), nor D = 64, paged, in the deep 64-row shape, 1.003 (27 sequences of 1707 keys, 55 nodes, 1.04).
+  static constexpr bool AHEAD = WK > 1 && !KV8 && RB == 1 && !PIPED && !(PAGED && (D == 128 ? WM == 4 : NST == 3));
   static constexpr int PD = KV8_REG ? NSTAGE - 1 : KV8 ? NL : NSTAGE - 1;  // tiles in flight ahead of the one being computed (widened)
   static constexpr int WG_PER_CU = KV8 ? (KV8_REG ? 2 : 1) : (NSTAGE == 2 && TK == 64) ? 2 : 1;
   // wavefronts per SIMD that the registers have to leave room for.  (The rings of the eight-wave shapes with D = 64 let two
