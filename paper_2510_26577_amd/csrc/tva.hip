@@ -2073,7 +2073,9 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
   __syncthreads();
   TL_STAMP(6);  // all have arrived
-  // (the splits and rows in flight, by what registers hold)
+  // (splits x rows in flight, by what registers hold, as few past the splits as that allows.  One sequence of 256 keys a split, 12 and 60
+  // nodes, three shapes: two splits by 1 x 8 rows take 0.86 .. 0.93 of 8 x 2's time and 0.92 .. 1.00 of 4 x 4's, 3 .. 5 by 4 x 4
+  // 0.94 .. 1.01 of 8 x 2's, 6 .. 12 by 8 x 2 0.92 .. 0.99 of 4 x 4's.)
   auto merge = [&](uint32_t given, auto given_tag) __attribute__((always_inline)) {
     if (nc == 2) merge_rows(given, given_tag, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
     else if (nc <= 5) merge_rows(given, given_tag, std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
