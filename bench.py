@@ -80,7 +80,8 @@ def main():
                          "(the full default run, with the CPU baseline, does so anyway)")
     ap.add_argument("--no-traffic", action="store_true", help="leave roofline.traffic null")
     ap.add_argument("--traffic-probe", action="store_true",
-                    help="(used by profile_traffic) make one plain 64 MiB device-to-device copy first: the counters' calibration")
+                    help="(used by the profile writers, with --no-graph) make one plain 64 MiB device-to-device copy first, the counters' "
+                         "calibration, and say in the line which attention launches belong to what")
     ap.add_argument("--microbench", action="store_true",
                     help="run the microbenchmarks of the machine rates (libtva_ubench) instead of a workload")
     ap.add_argument("--kv-fp8", action="store_true",
@@ -247,6 +248,11 @@ def measure(a):
             step_two_calls(i)
     torch.cuda.synchronize()
 
+    # what the attention launches of an eager run belong to, in order, for the profile writers (a call is one such launch)
+    launches = [["warm-up", 2 * max(a.warmup, R)]] + [[r, a.steps] for r in ("step", "warm", "kernel", "call", "two calls")]
+    if n_splits > 1:
+        launches += [["partial results", R], ["results", R]]
+
     # ---- the timed region: exactly K steps of the whole path (one graph replay), REPS times, each
     #      starting from flushed caches; `ms_per_step` is the median, the minimum is reported beside it ----
     step_runs = timed(a.steps, step)
@@ -374,6 +380,8 @@ def measure(a):
                      "mfma_tflops": tflops_kernel, "mfma_frac": tflops_kernel / MFMA_BF16_PEAK_TFLOPS},
         "cpu_baseline": cpu,
     }
+    if a.traffic_probe:
+        line["attention_launches"] = launches
     return line
 
 

@@ -22,9 +22,11 @@ import subprocess
 import sys
 import tempfile
 
+from .profile_traffic import by_region
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # eager launches, few steps: counters are read per dispatch
-PMC_BENCH = ["--no-cpu-baseline", "--no-saturated", "--steps", "8", "--warmup", "2", "--rotate", "2", "--no-graph"]
+PMC_BENCH = ["--no-cpu-baseline", "--no-saturated", "--steps", "8", "--warmup", "2", "--rotate", "2", "--no-graph", "--traffic-probe"]
 COUNTER_SETS = (
     ["SQ_BUSY_CU_CYCLES", "SQ_VALU_MFMA_BUSY_CYCLES", "SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_INSTS_MFMA", "SQ_INSTS_VALU", "SQ_WAVES",
      "GRBM_GUI_ACTIVE"],
@@ -68,8 +70,9 @@ def trace(workload: str) -> str:
            "made by:  python3 -m paper_2510_26577_amd.profile_kernels trace " + workload,
            "which runs:  " + shown,
            "(bench.py times five regions -- the one-call step, the attention kernel alone, the attention call, the two-call step,",
-           " the merge alone -- each as HIP-graph replays after untimed ones: hence the call counts.  Microseconds; the step times",
-           " of a run under the tracer read high.)", "",
+           " the merge alone -- each as HIP-graph replays after untimed ones: hence the call counts.  Attention launches that merge their",
+           " splits, in whole calls, and those that leave them, alone, are one line.  Microseconds; the step times of a run under the",
+           " tracer read high.)", "",
            f"{'kernel':72s} {'calls':>6s} {'avg_us':>9s} {'min_us':>9s} {'max_us':>9s} {'pct':>6s}"]
     for x in rows:
         if float(x["Percentage"]) >= 0.05:
@@ -92,24 +95,22 @@ def counters(workload: str) -> str:
     vals, name, cmds = {}, "", []
     try:
         for i, cs in enumerate(COUNTER_SETS):
-            d, _, shown = _rocprof(["--pmc", *cs], bench_args(workload) + PMC_BENCH, work, f"set{i}")
+            d, line, shown = _rocprof(["--pmc", *cs], bench_args(workload) + PMC_BENCH, work, f"set{i}")
             cmds.append(shown)
             files = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
             if not files:
                 raise RuntimeError("no counter_collection.csv under " + d)
-            agg = collections.defaultdict(list)
-            for row in csv.DictReader(open(files[0])):
-                if "attn_kernel" in row["Kernel_Name"]:
-                    name = row["Kernel_Name"]
-                    agg[row["Counter_Name"]].append(float(row["Counter_Value"]))
-            vals.update({k: sum(v) / len(v) for k, v in agg.items()})
+            rows = sorted(csv.DictReader(open(files[0])), key=lambda r: int(r["Dispatch_Id"]))
+            for c in cs:  # (of the launches alone: those of whole calls may merge their splits, under the same name)
+                of = [(r["Kernel_Name"], float(r["Counter_Value"])) for r in rows if r["Counter_Name"] == c]
+                name, vals[c] = next(iter(by_region(of, line["attention_launches"])["kernel"].items()))
     finally:
         shutil.rmtree(work, ignore_errors=True)
     wc = vals["SQ_WAVE_CYCLES"]
     util = vals["SQ_VALU_MFMA_BUSY_CYCLES"] / (vals["GRBM_GUI_ACTIVE"] / 8 * 1024)
     out = [f"Wave-level counters of the attention kernel, workload {workload}, rocprofv3 --pmc, MI355X",
            "made by:  python3 -m paper_2510_26577_amd.profile_kernels counters " + workload,
-           "which runs (one run per counter set; values are sums over the chip, means over the kernel's dispatches):"]
+           "which runs (one run per counter set; values are sums over the chip, means over the launches alone, without a merge):"]
     out += ["  " + c for c in cmds]
     out += ["", "kernel " + name[:110]] + [f"    {k:32s} {v:16.1f}" for k, v in vals.items()]
     out += ["",

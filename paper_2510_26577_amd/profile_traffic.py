@@ -1,7 +1,8 @@
 """HBM traffic of the benchmark's kernels from hardware counters: runs `bench.py` twice under
 `rocprofv3 --pmc` (FETCH_SIZE, then WRITE_SIZE: the two do not fit one pass), scales both by what the same
 counters read for a plain device-to-device copy of known size made in the same run, and reports bytes per
-dispatch of every kernel next to the workload's algorithmic bytes.
+attention launch and per step next to the workload's algorithmic bytes.  A launch that merges its splits has the name of one that
+leaves them to the caller: which is which follows from the order of the launches, which bench.py says.
 
     python3 -m paper_2510_26577_amd.profile_traffic cfg2 cfg4 ...     writes profiles/hbm_traffic_<workload>.txt
     python3 bench.py --with-traffic ...                               fills roofline.traffic of that run
@@ -50,17 +51,32 @@ def _run(counter: str, bench_args: list, workdir: str):
     files = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
     if not files:
         raise RuntimeError(f"rocprofv3 --pmc {counter}: no counter_collection.csv under {d}")
-    agg = collections.defaultdict(list)
-    rows = sorted(csv.DictReader(open(files[0])), key=lambda r: int(r["Dispatch_Id"]))
-    cal = None               # the probe's copy is the first plain copy kernel of the run
-    for r in rows:
-        if cal is None and "copyBuffer" in r["Kernel_Name"]:
-            cal = float(r["Counter_Value"])
-        agg[(r["Kernel_Name"], r["Grid_Size"])].append(float(r["Counter_Value"]))
+    rows = [(r["Kernel_Name"], float(r["Counter_Value"]))
+            for r in sorted(csv.DictReader(open(files[0])), key=lambda r: int(r["Dispatch_Id"]))]
+    # the probe's copy is the first plain copy kernel of the run
+    cal = next((v for name, v in rows if "copyBuffer" in name), None)
     if cal is None:
         raise RuntimeError("no plain copy kernel found for calibration")
     line = next((json.loads(l) for l in res.stdout.splitlines() if l.startswith("{")), None)
-    return {k: sum(v) / len(v) for k, v in agg.items()}, cal, line, " ".join(cmd[:-len(PROBE) - len(bench_args) - 2] + ["python3", "bench.py", *bench_args, *PROBE])
+    return by_region(rows, line["attention_launches"]), cal, line, " ".join(cmd[:-len(PROBE) - len(bench_args) - 2] + ["python3", "bench.py", *bench_args, *PROBE])
+
+
+def by_region(rows, launches) -> dict:
+    """{region: {kernel: mean per attention launch of the region}} of a run's dispatches (kernel, value) in their order.  launches:
+    [region, number of attention launches] in order (bench.py's attention_launches); a merge launch belongs to the attention launch
+    before it."""
+    owner = [region for region, n in launches for _ in range(n)]
+    count, total = collections.Counter(owner), collections.defaultdict(lambda: collections.defaultdict(float))
+    at = -1
+    for name, value in rows:
+        at += "attn_kernel" in name
+        if at >= len(owner):
+            raise RuntimeError(f"more than the {len(owner)} attention launches that the run names")
+        if at >= 0 and ("attn_kernel" in name or "merge_kernel" in name):
+            total[owner[at]][name] += value
+    if at + 1 != len(owner):
+        raise RuntimeError(f"{at + 1} attention launches, {len(owner)} named")
+    return {region: {k: v / count[region] for k, v in kernels.items()} for region, kernels in total.items()}
 
 
 def measure(bench_args: list) -> dict:
@@ -72,12 +88,12 @@ def measure(bench_args: list) -> dict:
         shutil.rmtree(work, ignore_errors=True)
     sf, sw = CAL_KIB / cal_f, CAL_KIB / cal_w
     kernels = {}
-    for k, v in fetch.items():
-        if "attn_kernel" in k[0] or "merge_kernel" in k[0] or "anc_mask_kernel" in k[0]:
-            f_kib, w_kib = v * sf, write.get(k, 0.0) * sw
-            kernels[k[0][:96]] = {"fetch_KiB": f_kib, "write_KiB": w_kib, "bytes": (f_kib + w_kib) * 1024}
-    attn = max((v["bytes"] for k, v in kernels.items() if "attn_kernel" in k), default=None)
-    return {"kernels": kernels, "attn_kernel_bytes": attn, "fetch_scale": sf, "write_scale": sw,
+    for region in ("kernel", "step"):
+        for k, v in fetch[region].items():
+            f_kib, w_kib = v * sf, write[region].get(k, 0.0) * sw
+            kernels[region, k[:96]] = {"fetch_KiB": f_kib, "write_KiB": w_kib, "bytes": (f_kib + w_kib) * 1024}
+    of = lambda region: sum(v["bytes"] for (r, _), v in kernels.items() if r == region)
+    return {"kernels": kernels, "attn_kernel_bytes": of("kernel"), "step_bytes": of("step"), "fetch_scale": sf, "write_scale": sw,
             "calibration_reads": {"FETCH_SIZE": cal_f, "WRITE_SIZE": cal_w}, "bench_line": line,
             "commands": [cmd_f, cmd_w]}
 
@@ -91,13 +107,15 @@ def write_summary(workload: str, t: dict) -> str:
     out += [f"calibration: the probe's plain device-to-device copy of {CAL_KIB} KiB reads FETCH_SIZE = {t['calibration_reads']['FETCH_SIZE']:.1f}, "
             f"WRITE_SIZE = {t['calibration_reads']['WRITE_SIZE']:.1f}",
             f"             -> scale factors to KiB: {t['fetch_scale']:.4f} (fetch), {t['write_scale']:.4f} (write)", "",
-            f"{'kernel (mean per dispatch)':72s} {'fetch_KiB':>12s} {'write_KiB':>12s} {'total_MB':>10s}"]
-    for k, v in t["kernels"].items():
-        out.append(f"{k[:72]:72s} {v['fetch_KiB']:12.1f} {v['write_KiB']:12.1f} {v['bytes'] / 1e6:10.3f}")
+            f"{'launches (mean)':84s} {'fetch_KiB':>12s} {'write_KiB':>12s} {'total_MB':>10s}"]
+    for (region, k), v in t["kernels"].items():
+        what = "alone:   " if region == "kernel" else "in step: "
+        out.append(f"{(what + k)[:84]:84s} {v['fetch_KiB']:12.1f} {v['write_KiB']:12.1f} {v['bytes'] / 1e6:10.3f}")
+    out.append("(alone: attention launches that leave their splits to the caller; in step: those of whole calls, which merge them or are")
+    out.append(" followed by the merge's launch)")
     out += ["", f"algorithmic bytes of one launch (K/V + Q + O + LSE + masks + page table): {alg / 1e6:.3f} MB; kv_splits {line['config']['kv_splits']}",
             f"attention kernel traffic / algorithmic bytes = {t['attn_kernel_bytes'] / alg:.2f}"]
-    total = sum(v["bytes"] for k, v in t["kernels"].items() if "attn_kernel" in k or "merge_kernel" in k)
-    out.append(f"attention + merge traffic / algorithmic bytes = {total / alg:.2f}")
+    out.append(f"whole step's traffic / algorithmic bytes = {t['step_bytes'] / alg:.2f}")
     path = os.path.join(ROOT, "profiles", f"hbm_traffic_{workload}.txt")
     open(path, "w").write("\n".join(out) + "\n")
     return path

@@ -86,6 +86,20 @@ def test_instrumented_build_stamps_are_ordered():
     assert "no merge kernel: merged in the attention launch, by " in r.stdout and "gap between" not in r.stdout
 
 
+def test_counters_are_those_of_the_launches_they_are_said_to_be():
+    """Launches of one kernel's name that merge their splits, leave them, or are followed by a merge: told apart by their order."""
+    from paper_2510_26577_amd import profile_traffic
+    attn, merge = "attn_kernel<1>(args)", "merge_kernel<2>(args)"
+    launches = [["warm-up", 2], ["step", 2], ["kernel", 3], ["two calls", 1]]
+    rows = ([("fill", 7.0), (attn, 9.0), (attn, 9.0), ("fill", 7.0)] + [(attn, 4.0), (merge, 1.0), (attn, 6.0), (merge, 2.0)] +
+            [(attn, 1.0), (attn, 2.0), (attn, 3.0)] + [("anc_mask_kernel", 8.0), (attn, 5.0)])
+    got = profile_traffic.by_region(rows, launches)
+    assert got["step"] == {attn: 5.0, merge: 1.5} and got["kernel"] == {attn: 2.0} and got["two calls"] == {attn: 5.0}
+    for wrong in (rows + [(attn, 1.0)], rows[:-1]):
+        with pytest.raises(RuntimeError):
+            profile_traffic.by_region(wrong, launches)
+
+
 def test_timeline_tells_a_merge_in_the_launch_from_a_launch_of_its_own():
     """Synthetic stamps: four workgroups, the last without splits to merge or without rows, one call of each form; what is said does
     not follow from the times, which are the same in both."""
