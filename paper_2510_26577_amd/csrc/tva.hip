@@ -6,7 +6,8 @@
 //   attn_kernel       split-KV attention of all tree tokens of one (sequence, KV head)
 //                     against one chunk of that sequence's cache (+ the tree's own
 //                     keys under the ancestor mask, folded into the last chunk)
-//   merge_kernel      merges the KV splits where attn_kernel has not done so at its end
+//   attn_kernel_shared  the same, merging the KV splits at its end
+//   merge_kernel      merges the KV splits of attn_kernel
 //
 // attn_kernel in one paragraph.  The T_b*G query rows that share a KV head
 // (row = node*G + head-in-group) form the N side of 32x32x16 bf16 MFMAs; keys
@@ -410,10 +411,11 @@ __device__ __forceinline__ void widen_e4m3(const u32x4 raw, bf16x8 &lo, bf16x8 &
   hi = widen_e4m3(u32x2{raw[2], raw[3]});
 }
 
-template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8>
-__global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>::WAVES_PER_SIMD))
-    attn_kernel(const AttnParams p_in) {
+// SHARED: the row block's splits are merged at the end (attn_kernel_shared, below).
+template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8, bool SHARED>
+__device__ __forceinline__ void attn_body(const AttnParams &p_in) {
   using C = AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>;
+  static_assert(!SHARED || C::SHARES, "");
   // The arguments the prologue needs, tied together by an empty statement so that they are fetched
   // in one batch at the top rather than one by one, each with its own wait, at their first uses.
   AttnParams p = p_in;
@@ -464,6 +466,14 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   }
   const int chunk = split;
 
+  // Arguments that only the last tiles and the end of the workgroup need are read again there: held over the loop, paged, they
+  // were the scalars too many (up to 25 parked in lanes of vector registers).
+  typedef const __attribute__((address_space(4))) AttnParams *const_args;
+  auto late_args = [&]() __attribute__((always_inline)) {
+    const_args a = (const_args)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return a;
+  };
   // every per-sequence scalar is requested before the first one is needed
   // (read through the constant address space: none of these arrays changes while the kernel
   // runs, and saying so keeps the loads scalar wherever they sit)
@@ -493,8 +503,8 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   int nc = (Lb + p.chunk_keys - 1) / p.chunk_keys;
   nc = nc < 1 ? 1 : nc;
   if (chunk >= nc) {
-    // this sequence has fewer chunks than the launch provides: mark the slot empty for the merge's launch
-    if (C::SHARES && p.share_tag != 0) return;
+    // this sequence has fewer chunks than the launch provides: mark the slot empty, for the merge's launch
+    if constexpr (SHARED) return;
     for (int row = rblk * BM + (int)threadIdx.x; row < R && row < (rblk + 1) * BM; row += blockDim.x) {
       const int t = node_of(p, row), g = row - t * p.G;
       p.part_lse[(size_t)chunk * p.sum_Q * p.Hq + (size_t)(tq0 + t) * p.Hq + kvh * p.G + g] = -INFINITY;
@@ -670,11 +680,15 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     if (!PAGED && t < n_full) {
 #pragma unroll
       for (int j = 0; j < NLDK; ++j) {
-        // (8-bit K/V: an address per load, 1 % faster there than a register per load of a tile)
-        const int64_t at = (cache_base + (int64_t)(base + (KV8 ? row0_of(j) : 0)) * p.stride_tok) * EB;
-        const uint32_t off = KV8 ? lane_off2[j & 1] : lane_off[j];
-        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(kc_bytes + at + off), stage + kdst_of(j), 16, 0, kLoadOnce);
-        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vc_bytes + at + off), stage + vdst_of(j), 16, 0, kLoadOnce);
+        // (an address per load, or, where operands are read ahead, a register per load of a tile: 8-bit K/V 1 % slower with it, the
+        // short splits of the dense deep 64-row and 256-row shapes 0.5 %)
+        const int row0 = C::AHEAD ? 0 : C::STEADY ? (wave * NLDK + j) * LPI : row0_of(j);
+        const int64_t urow = cache_base + (int64_t)(base + row0) * p.stride_tok;
+        const uint32_t off = C::AHEAD ? lane_off[j] : lane_off2[j & 1];
+        const char *ksrc = kc_bytes + urow * EB + off;
+        const char *vsrc = vc_bytes + urow * EB + off;
+        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(ksrc), stage + kdst_of(j), 16, 0, kLoadOnce);
+        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(vsrc), stage + vdst_of(j), 16, 0, kLoadOnce);
       }
     } else if (PAGED && !(tree && p.k_tree != nullptr)) {
       // (tree keys stored in the cache follow the sequence's L_b committed tokens)
@@ -1113,14 +1127,6 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     }
     if constexpr (!PAGED) next += tile_bytes;
     if constexpr (!V) request_pages(t + C::LOOK, std::integral_constant<int, 1>{});
-  };
-  // Arguments that only the last tiles and the end of the workgroup need are read again there: held over the loop, paged, they
-  // were the scalars too many (up to 25 parked in lanes of vector registers).
-  typedef const __attribute__((address_space(4))) AttnParams *const_args;
-  auto late_args = [&]() __attribute__((always_inline)) {
-    const_args a = (const_args)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(a));
-    return a;
   };
   // the partial cache tile and the tree's
   auto issue_rest = [&](int t, auto v_tag) __attribute__((always_inline)) {
@@ -1706,7 +1712,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     for (; it < n_ct; ++it) step(it, std::true_type{}, std::false_type{});   // the partial cache tile
     for (; it < n_tiles; ++it) step(it, std::true_type{}, std::true_type{});  // the tree's own keys
   }
-  if constexpr (PAGED && C::SHARES) {
+  if constexpr (PAGED && (C::PIPED || C::SHARES)) {
     const const_args late = late_args();
     p.G = late->G, p.g_magic = late->g_magic, p.g_bits = late->g_bits, p.Hq = late->Hq, p.sum_Q = late->sum_Q, p.n_chunks = late->n_chunks;
     p.out = late->out, p.lse = late->lse, p.part_out = late->part_out, p.part_lse = late->part_lse, p.v_scale = late->v_scale;
@@ -1715,7 +1721,6 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   __builtin_amdgcn_s_barrier();  // all waves are done reading the ring before it is reused below
   TL_STAMP(4);  // all tiles done
 
-  const uint64_t share_tag = C::SHARES ? late_args()->share_tag : 0;
   // ---- combine the two lane halves' partial sums, and the two key groups' references and sums ----
   // (factor: what a row's O is multiplied by -- to the groups' common reference, and 1 / sum)
   constexpr bool PAIR = C::PAIR;
@@ -1744,7 +1749,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   for (int r = 0; r < RB; ++r) factor[r] *= l_tot[r] > 0.f ? p.v_scale / l_tot[r] : 0.f;
 
   // (A row whose sum is none -- NaN scores -- has no weight in the merge of the splits: in this launch its outputs are zeros then.)
-  if (C::SHARES && share_tag != 0 && nc > 1 && __builtin_expect(__builtin_amdgcn_ballot_w64(!(l_tot[0] > 0.f)) != 0, 0)) {
+  if (SHARED && nc > 1 && __builtin_expect(__builtin_amdgcn_ballot_w64(!(l_tot[0] > 0.f)) != 0, 0)) {
 #pragma unroll
     for (int d = 0; d < ND; ++d)
 #pragma unroll
@@ -1788,7 +1793,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   // The accumulators hold O^T (lane = row, registers = 16 scattered d per 32-wide block); each
   // wave transposes one 32-row block at a time through its own LDS patch so that global stores
   // are whole contiguous rows (of the half of the head dimension the wave holds, when paired).
-  const bool final_out = p.n_chunks == 1 || (share_tag != 0 && nc == 1);
+  const bool final_out = (SHARED ? nc : p.n_chunks) == 1;
   float *obase = final_out ? p.out : p.part_out + (size_t)chunk * p.sum_Q * p.Hq * D;
   float *lbase = final_out ? p.lse : p.part_lse + (size_t)chunk * p.sum_Q * p.Hq;
   constexpr int NDW = C::NDW;       // 32-wide d blocks this wave writes
@@ -1848,13 +1853,13 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
     }
   };
   if (final_out) write_out(std::false_type{});
-  else if (share_tag == 0) write_out(std::true_type{});
-  if (!C::SHARES || final_out || share_tag == 0) {
+  else if constexpr (!SHARED) write_out(std::true_type{});
+  if (!SHARED || final_out) {
     TL_STAMP(5);  // key groups merged, result stores issued
     TL_STORE(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), 0, 6);
     return;
   }
-  if constexpr (C::SHARES) {
+  if constexpr (SHARED) {
   // ---- the row block's splits merged in this launch, each workgroup a share of the rows ----
   // The nc workgroups of a (sequence, KV head, row block) take a share of its rows each.  A workgroup stores the rows of the others'
   // shares, says that it has, waits until all have, and merges its own share, which never leaves its LDS.  All that travels between
@@ -1872,6 +1877,7 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
   constexpr int LPW = D / 4, GROUPS = 64 / LPW;
   constexpr int kDevice = 16;                  // the cache policy's sc1: device scope
   constexpr uint32_t kNowhere = 0x80000000u;   // past every bound, with what may be added: neither read nor stored
+  const uint64_t share_tag = late_args()->share_tag;
   const bool keeps_words = wave == C::NW - 1;  // (this wave merges no rows of its workgroup's share)
   const int Rb = R - rblk * BM < BM ? R - rblk * BM : BM;
   // (Rb / nc rounded up: whole or at least 1/32 above it, and the reciprocal is good to a few units of 2^-23)
@@ -2118,6 +2124,21 @@ __global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NS
 #undef lrow
 #undef kdst_of
 #undef vdst_of
+
+template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8 = false>
+__global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>::WAVES_PER_SIMD))
+    attn_kernel(const AttnParams p) {
+  attn_body<D, WM, WK, RB, PAGED, NST, KV8, false>(p);
+}
+// The launches that merge their splits have a kernel of their own.  With the 10 to 20 KB that only they run behind its loops, calls without
+// splits and those whose splits a second launch merges took 1 .. 3 % longer in the dense deep 64-row and 128-row shapes below 14 and 22
+// tiles (8 sequences of 700 keys, 30 nodes: 16.9 -> 17.3 and 20.9 -> 21.4 us; 36 such calls of three shapes now 0.99 of the time before
+// there was a merge in the launch, the 128-row shape's 1.01).
+template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8 = false>
+__global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>::WAVES_PER_SIMD))
+    attn_kernel_shared(const AttnParams p) {
+  attn_body<D, WM, WK, RB, PAGED, NST, KV8, true>(p);
+}
 
 // ---------------------------------------------------------------------------------------
 // merge of the KV splits
@@ -2607,18 +2628,23 @@ inline hipError_t launch_status(const char *what) {
 template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8 = false>
 hipError_t launch_attn(const AttnParams &p, dim3 grid, hipStream_t st) {
   using C = AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>;
-  if (p.share_tag != 0 && !C::SHARES) return hipErrorInvalidValue;  // (it would leave the results to a launch that nobody queues)
   // raising the dynamic-LDS limit is idempotent and needed once per device (and per instantiation)
-  static std::atomic<uint64_t> attr_done{0};
-  auto kfn = attn_kernel<D, WM, WK, RB, PAGED, NST, KV8>;
+  static std::atomic<uint64_t> attr_done[2]{};
+  const bool shared = p.share_tag != 0;
+  attn_fn kfn = attn_kernel<D, WM, WK, RB, PAGED, NST, KV8>;
+  if constexpr (C::SHARES) {
+    if (shared) kfn = attn_kernel_shared<D, WM, WK, RB, PAGED, NST, KV8>;
+  } else if (shared) {
+    return hipErrorInvalidValue;  // (the results would be left to a launch that nobody queues)
+  }
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
   const uint64_t bit = (dev >= 0 && dev < 64) ? 1ull << dev : 0;
-  if (!(attr_done.load(std::memory_order_relaxed) & bit)) {
+  if (!(attr_done[shared].load(std::memory_order_relaxed) & bit)) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kfn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
     if (e != hipSuccess) return e;
-    attr_done.fetch_or(bit, std::memory_order_relaxed);
+    attr_done[shared].fetch_or(bit, std::memory_order_relaxed);
   }
   clear_stale_hip_error();
   hipLaunchKernelGGL(kfn, grid, dim3(C::NT), C::SMEM, st, p);

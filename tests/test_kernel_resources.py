@@ -90,3 +90,12 @@ def test_sampling_kernels_spill_vector_registers_in_one_form_only(table):
         if "walk_kernel" in name or "sample_kernel" in name or "topk_parts_kernel" in name:
             most = 12 if "walk_kernelILi16ELb0E" in name else 0
             assert k[".vgpr_spill_count"] <= most, (name, k[".vgpr_spill_count"])
+
+
+def test_launches_that_merge_their_splits_have_kernels_of_their_own(table):
+    """D = 128, the 64-row shapes (two of 16-bit K/V, one of 8-bit), the 128-row and the 256-row shape, dense and paged, but for the paged 256-row
+    shape with 8-bit K/V; each beside the kernel of the same shape that merges nothing."""
+    shared = {n.split("attn_kernel_shared")[1].split("EEEv")[0] for n in table if "attn_kernel_shared" in n}
+    alone = {n.split("attn_kernelI")[1].split("EEEv")[0] for n in table if "attn_kernelI" in n}
+    assert len(shared) == 13 and len(alone) == 28 and {n[1:] for n in shared} < alone
+    assert all(n.startswith("ILi128E") and not n.startswith("ILi128ELi1E") for n in shared) and "ILi128ELi8ELi1ELi1ELb1ELi3ELb1" not in shared
