@@ -2588,13 +2588,14 @@ bool merged_in_launch(const tva_args *a, const Plan &pl, const AttnParams &p, co
   const int64_t splits = p.real_splits > 0 && a->num_splits == 0 ? p.real_splits : (int64_t)a->B * pl.n_chunks;
   return splits * a->Hkv * pl.n_row_blocks <= (pl.variant == V_M2K2 ? 512 : 256);
 }
-// Looks at the others' words, about 0.6 us each, before a workgroup gives up: some 10 us and twice the time of its tiles, which covers
-// splits of unequal length and two workgroups to a CU.  Alone on the chip nobody gives up (a call in which all do takes 17.6 us for 12.8,
-// one sequence of 2048 keys, 60 nodes); what it bounds is how long a CU is held for partners that wait for one, where other streams
-// have the chip: that sequence on four streams at once, us for the four calls: bound of 300 looks 42.8, 48 and four per tile 39, this
-// one 32.6, none 30.5, with a second launch 29.1; on three streams 23.6, two 16.6, by a second launch 23.6 and 17.6.  16 sequences of
-// 512 .. 2048 keys at 16 looks 26.5, from 48 on 25.4.
-int share_polls(const Plan &pl) { return std::min(16 + 3 * (pl.chunk_keys / pl.TK), 0xFFFF); }
+// Looks at the others' words, up to 0.6 us each, before a workgroup gives up: up to 5 us and four times the time of its tiles.  Alone on
+// the chip nobody gives up: splits of unequal length, two workgroups to a CU, need six and, of 8 tiles, seven looks a tile (4 sequences
+// of 2057 .. 3883 keys, 61 nodes, 8 splits of 8 tiles: 23.2 us, 25.2 with 16 + 3 a tile; of 4, 7, 12 and 16 tiles 24 .. 32, 32 .. 48, 48
+// .. 96 and 64 .. 96 looks), and a call in which all give up takes 18.0 us for 12.6 (one sequence of 2048 keys, 60 nodes, 5 tiles).  What
+// it bounds is how long a CU is held for partners that wait for one, where other streams have the chip: that sequence on four streams
+// at once, us for the four calls: 300 looks 42.8, 64 38.1, 56 35.7, 48 34.1, 40 33.0, 16 .. 32 32.3, none 31.5, with a second launch
+// 29.1; on three streams 23.6, two 16.6, by a second launch 23.6 and 17.6.
+int share_polls(const Plan &pl) { return std::min(8 + 7 * (pl.chunk_keys / pl.TK), 0xFFFF); }
 
 // A number that no other call of the process is given (an odd step visits all 2^62 before it comes back to one) and that scratch
 // memory does not hold by chance; its last two bits are free.  0 stands for none and is passed over.  Nothing here throws.
