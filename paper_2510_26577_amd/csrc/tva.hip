@@ -6,8 +6,7 @@
 //   attn_kernel       split-KV attention of all tree tokens of one (sequence, KV head)
 //                     against one chunk of that sequence's cache (+ the tree's own
 //                     keys under the ancestor mask, folded into the last chunk)
-//   attn_kernel_shared  the same, merging the KV splits at its end
-//   merge_kernel      merges the KV splits of attn_kernel
+//   merge_kernel      merges the KV splits where attn_kernel has not done so at its end
 //
 // attn_kernel in one paragraph.  The T_b*G query rows that share a KV head
 // (row = node*G + head-in-group) form the N side of 32x32x16 bf16 MFMAs; keys
@@ -411,9 +410,17 @@ __device__ __forceinline__ void widen_e4m3(const u32x4 raw, bf16x8 &lo, bf16x8 &
   hi = widen_e4m3(u32x2{raw[2], raw[3]});
 }
 
-// SHARED: the row block's splits are merged at the end (attn_kernel_shared, below).
-template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8, bool SHARED>
-__device__ __forceinline__ void attn_body(const AttnParams &p_in) {
+// RBS: the 32-row blocks of a wave, below 0 (SHARED) in the kernels that merge the row block's splits at their end.
+// They are kernels of their own: with the 10 to 20 KB that only those launches run behind its loops, calls without splits and those whose
+// splits a second launch merges took 1 .. 3 % longer in the dense deep 64-row and 128-row shapes below 14 and 22 tiles (8 sequences of 700
+// keys, 30 nodes: 16.9 -> 17.3 and 20.9 -> 21.4 us; 36 such calls of three shapes now 0.99 of the time before there was a merge in
+// the launch, the 128-row shape's 1.01).  And both are this function, not two that call one: inlined into them, it came out with more
+// scalar instructions in the loops of the paged shapes with D = 64 (60 sequences of 1384 keys, 37 nodes, 62 -> 64 us).
+template <int D, int WM, int WK, int RBS, bool PAGED, int NST, bool KV8>
+__global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RBS < 0 ? -RBS : RBS, PAGED, NST, KV8>::WAVES_PER_SIMD))
+    attn_kernel(const AttnParams p_in) {
+  constexpr bool SHARED = RBS < 0;
+  constexpr int RB = SHARED ? -RBS : RBS;
   using C = AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>;
   static_assert(!SHARED || C::SHARES, "");
   // The arguments the prologue needs, tied together by an empty statement so that they are fetched
@@ -2125,21 +2132,6 @@ __device__ __forceinline__ void attn_body(const AttnParams &p_in) {
 #undef kdst_of
 #undef vdst_of
 
-template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8 = false>
-__global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>::WAVES_PER_SIMD))
-    attn_kernel(const AttnParams p) {
-  attn_body<D, WM, WK, RB, PAGED, NST, KV8, false>(p);
-}
-// The launches that merge their splits have a kernel of their own.  With the 10 to 20 KB that only they run behind its loops, calls without
-// splits and those whose splits a second launch merges took 1 .. 3 % longer in the dense deep 64-row and 128-row shapes below 14 and 22
-// tiles (8 sequences of 700 keys, 30 nodes: 16.9 -> 17.3 and 20.9 -> 21.4 us; 36 such calls of three shapes now 0.99 of the time before
-// there was a merge in the launch, the 128-row shape's 1.01).
-template <int D, int WM, int WK, int RB, bool PAGED, int NST, bool KV8 = false>
-__global__ void __launch_bounds__(WM *WK * 64, (AttnCfg<D, WM, WK, RB, PAGED, NST, KV8>::WAVES_PER_SIMD))
-    attn_kernel_shared(const AttnParams p) {
-  attn_body<D, WM, WK, RB, PAGED, NST, KV8, true>(p);
-}
-
 // ---------------------------------------------------------------------------------------
 // merge of the KV splits
 // ---------------------------------------------------------------------------------------
@@ -2634,7 +2626,7 @@ hipError_t launch_attn(const AttnParams &p, dim3 grid, hipStream_t st) {
   const bool shared = p.share_tag != 0;
   attn_fn kfn = attn_kernel<D, WM, WK, RB, PAGED, NST, KV8>;
   if constexpr (C::SHARES) {
-    if (shared) kfn = attn_kernel_shared<D, WM, WK, RB, PAGED, NST, KV8>;
+    if (shared) kfn = attn_kernel<D, WM, WK, -RB, PAGED, NST, KV8>;
   } else if (shared) {
     return hipErrorInvalidValue;  // (the results would be left to a launch that nobody queues)
   }
