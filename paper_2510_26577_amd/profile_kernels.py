@@ -71,8 +71,8 @@ def trace(workload: str) -> str:
            "which runs:  " + shown,
            "(bench.py times five regions -- the one-call step, the attention kernel alone, the attention call, the two-call step,",
            " the merge alone -- each as HIP-graph replays after untimed ones: hence the call counts.  Attention launches that merge their",
-           " splits, in whole calls, and those that leave them, alone, are one line.  Microseconds; the step times of a run under the",
-           " tracer read high.)", "",
+           " splits, in whole calls, have a kernel of their own, of fourth argument -1; the others, alone or in calls whose merge is a",
+           " launch, are one line.  Microseconds; the step times of a run under the tracer read high.)", "",
            f"{'kernel':72s} {'calls':>6s} {'avg_us':>9s} {'min_us':>9s} {'max_us':>9s} {'pct':>6s}"]
     for x in rows:
         if float(x["Percentage"]) >= 0.05:
@@ -101,7 +101,7 @@ def counters(workload: str) -> str:
             if not files:
                 raise RuntimeError("no counter_collection.csv under " + d)
             rows = sorted(csv.DictReader(open(files[0])), key=lambda r: int(r["Dispatch_Id"]))
-            for c in cs:  # (of the launches alone: those of whole calls may merge their splits, under the same name)
+            for c in cs:  # (of the launches alone: those of whole calls may merge their splits, in a kernel of their own)
                 of = [(r["Kernel_Name"], float(r["Counter_Value"])) for r in rows if r["Counter_Name"] == c]
                 name, vals[c] = next(iter(by_region(of, line["attention_launches"])["kernel"].items()))
     finally:

@@ -1,8 +1,8 @@
 """HBM traffic of the benchmark's kernels from hardware counters: runs `bench.py` twice under
 `rocprofv3 --pmc` (FETCH_SIZE, then WRITE_SIZE: the two do not fit one pass), scales both by what the same
 counters read for a plain device-to-device copy of known size made in the same run, and reports bytes per
-attention launch and per step next to the workload's algorithmic bytes.  A launch that merges its splits has the name of one that
-leaves them to the caller: which is which follows from the order of the launches, which bench.py says.
+attention launch and per step next to the workload's algorithmic bytes.  What a launch belongs to follows from the order of the
+launches, which bench.py says: by its name alone, one that leaves its splits to the caller is none of a call whose merge is a launch.
 
     python3 -m paper_2510_26577_amd.profile_traffic cfg2 cfg4 ...     writes profiles/hbm_traffic_<workload>.txt
     python3 bench.py --with-traffic ...                               fills roofline.traffic of that run
