@@ -2299,8 +2299,9 @@ void plan_splits_of(const tva_args *a, int variant, bool named, bool share, Plan
     // trees of 1 .. 72 nodes on the benchmark head shape:
     //   (tiles of the longest split, the tree's own tiles counted with the last one) x time per tile
     //      x 1 while every workgroup has a CU to itself (256), x 1.5 while two share one (512),
-    //   + with splits: a merge pass (second launch, 3.0 us) and the partial rows written and read back
-    //     (0.30 us per MB).
+    //   + with splits: a merge pass (3.0 us) and the partial rows written and read back (0.30 us per MB), as a second launch
+    //     costs.  (The merge in the attention launch costs 1 us and a third less; priced so in all splits, or in short ones,
+    //     the count it comes to is the slower one as often as the faster.)
     // Splits keep two tiles or more (one, in launches of at most 128 workgroups over six tiles or more) and
     // together stay within 512 workgroups.
     const int tiles = max_by_len, tree_tiles = (a->max_T + pl->TK - 1) / pl->TK;
@@ -2343,8 +2344,9 @@ void plan_splits_of(const tva_args *a, int variant, bool named, bool share, Plan
     const int cap = a->max_L > 0 ? (a->max_L + 2 * pl->TK - 1) / (2 * pl->TK) : 1;
     if (S > cap) S = cap;
     if (S > max_by_len) S = max_by_len;
-    // A split has to save more tile time than its merge pass costs (a second launch and the partial rows
-    // written and read back: about six tiles' worth): short caches are split less, or not at all.
+    // A split has to save more tile time than its merge pass costs (six tiles' worth as a second launch, with
+    // the partial rows written and read back; not asked again of the merge in the attention launch): short
+    // caches are split less, or not at all.
     while (S > 1 && max_by_len - (max_by_len + S - 1) / S < 6) --S;
   }
   if (S > max_by_len) S = max_by_len;
@@ -2392,7 +2394,7 @@ inline bool dense_wide(const tva_args *a) { return a->D == 128 && !a->kv_fp8 && 
 // is compared are shapes, and the one taken is 2.6 % slower than the best in the mean (2.3 then).  A round of workgroups
 // takes (tiles of the longest split) x (time per tile), more where two share a CU; workgroups beyond whole rounds take a part
 // of one more, more than half of it however few they are; every round starts and drains; the launch takes no less than
-// its bytes at the rate the shape streams; with splits there is a merge pass.
+// its bytes at the rate the shape streams; with splits there is a merge pass, priced as the second launch that it was in all of those.
 // The dense deep 64-row shape's tile is 0.85 of that from 14 on, one begun counted, which is most of what its four-stage ring and its
 // pipelined loop gained.  (The limit is the plan's own: the ring alone is worth it at 13 full tiles and a part of one, where the loop
 // does not run yet.  60 calls of 833 .. 895 keys that this moves to the shape take 0.953 of their time in the others.)
@@ -2465,9 +2467,11 @@ bool plan_of(const tva_args *a, bool share, Plan *pl, bool *fewer) {
   // (8-bit K/V from 128 K keys on, lengths known: four waves queue a tile's loads faster than two; 4 sequences of 16000
   // keys 36 -> 31.5 us; not where long and short sequences share a CU, see fill_slots: 41.4 -> 42.0)
   if (rows <= 32) variant = a->kv_fp8 && a->L_host && a->B <= 32 && keys >= (128 << 10) ? V_M2K2 : V_K2;
-  // (the draft stage's attention of one or two sequences -- queries are the newest nodes, at most 48 rows per KV head:
-  // two 32-row workgroups, the second three quarters empty, beat one of 64 rows by 0.4 .. 1.1 us of 12; from eight
-  // sequences on the 64-row shape wins)
+  // (the draft stage's attention of one or two sequences -- queries are the newest nodes, at most 48 rows per KV head: two
+  // 32-row workgroups, the second three quarters empty, and a second launch for their splits against one of 64 rows that may
+  // merge its own.  12 nodes, 256, 700, 1024, 2048 and 4096 keys, us: one sequence 9.2, 9.9, 10.0, 11.2, 13.6 against 9.8, 9.9,
+  // 11.4, 11.9, 13.4; two 9.6, 10.6, 10.5, 13.2, 16.8 against 10.3, 10.3, 10.5, 12.8, 15.5.  From eight sequences on the 64-row
+  // shape wins)
   else if (a->cu_Q && rows <= 48 && pairs <= 16) variant = V_K2;
   else if (rows >= 128) {
     if (n128 >= 96 && n128 <= 256 && (s128 == 1 || a->max_L / s128 >= 16 * 64)) variant = V_M4K2;
@@ -2675,8 +2679,10 @@ hipError_t dispatch_variant_fp8(int variant, const AttnParams &p, dim3 grid, hip
 // at its own address, from the moment the module is loaded there until the process ends.  In host
 // code the array's name is only a handle for hipGetSymbolAddress; the address it returns for the
 // current device is what kernels, copies and fills are given.  Nothing in it has to start at zero:
-// the attention kernel writes every partial row and every partial log-sum-exp (also the "empty"
-// marks of splits a short sequence does not reach) that the merge of the same call reads.
+// where a second launch merges the splits, the attention kernel writes every partial row and every
+// partial log-sum-exp (also the "empty" marks of splits a short sequence does not reach) that it
+// reads; where the attention launch merges them, each workgroup's rows outside its own share, and
+// the words that say so carry a tag that no other call has.
 static __device__ __align__(256) unsigned char scratch[TVA_STATIC_SCRATCH_BYTES];
 
 namespace {
