@@ -158,9 +158,10 @@ def summarise(name, w, us_plain, us_instr, plan, attn, merge, apart, cmd, mode) 
     elif shared.any():
         last = np.where(shared, m[:, 1], a[:, 5]).max()
         lines += [
-            f"no merge kernel: merged in the attention launch, by {int(shared.sum())} workgroups, same clock:",
-            f"  + {'all splits of the row block have arrived':<42s} {st((m[:, 0] - a[:, 5])[shared])}",
-            f"  + {'partials read, merged, stores issued':<42s} {st((m[:, 1] - m[:, 0])[shared])}",
+            f"no merge kernel: merged in the attention launch, by {int(shared.sum())} workgroups, no gap between launches, same clock:",
+            f"  + {'splits waited for and merged':<42s} {st((m[:, 1] - a[:, 5])[shared])}",
+            f"    of it {'until all of the row block have arrived':<38s} {st((m[:, 0] - a[:, 5])[shared])}",
+            f"    of it {'partials read, merged, stores issued':<38s} {st((m[:, 1] - m[:, 0])[shared])}",
             f"  = {'stores issued, absolute':<42s} {st(m[shared, 1])}",
             f"from the first attention entry to the last store: {last:.2f} us; the rest of the "
             f"{us_instr:.2f} us per call is the gap to the next call's first workgroup",

@@ -758,9 +758,8 @@ def prepared(device, w, scales=(1.0, 1.0), **kw):
                                               (4, 16, False), (5, 16, False), (2, 0, True), (4, 16, True), (5, 0, True)])
 def test_splits_merged_in_the_launch(gpu, shape, page, fp8):
     """2 .. 12 splits of row blocks of 4 .. 256 rows (fewer than splits, shares that no row is left for, sequences of fewer splits and
-    of none), whatever the scratch memory holds, and with workgroups that stop waiting for the others at once or soon -- all of a row
-    block, or the first, the last, every other one or all but one of its splits, while the rest wait: the oracle's results, and the
-    same bits each time.  Scratch memory on which it does not apply (not 16-byte aligned) takes the second launch."""
+    of none), whatever the scratch memory holds, and with workgroups that stop waiting for the others at once or soon: the oracle's
+    results, and the same bits each time.  Scratch memory on which it does not apply (not 16-byte aligned) takes the second launch."""
     import torch
     from oracle import fp8_oracle as f8
     from paper_2510_26577_amd import binding
@@ -777,9 +776,8 @@ def test_splits_merged_in_the_launch(gpu, shape, page, fp8):
         S = binding.plan_splits(args)
         assert S >= splits - 1
         first = None
-        some = [4000 | at_once << 16 for at_once in (1, 1 << (S - 1), 0x555 & ((1 << S) - 1), (1 << S) - 1 - (1 << S // 2))]
         for fill in (0, -1, 0x7FF8000000000000, None):
-            for polls in (None, 0, 1, 3, *some):
+            for polls in (None, 0, 1, 3):
                 out.fill_(float("nan")), lse.fill_(float("nan"))
                 if fill is not None:
                     ws.fill_(fill)
@@ -799,6 +797,38 @@ def test_splits_merged_in_the_launch(gpu, shape, page, fp8):
         torch.cuda.synchronize()
         # (the same partial rows in another order: a few units of the last place of sums of at most 12 terms of size 4)
         assert np.abs(out.cpu().numpy() - first[0]).max() <= 1e-5 and np.abs(lse.cpu().numpy() - first[1]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("shape, page, fp8", [(2, 0, False), (3, 0, False), (4, 0, False), (5, 0, False), (2, 16, False), (3, 5, False),
+                                              (4, 16, False), (5, 16, False), (2, 0, True), (4, 16, True), (5, 0, True)])
+def test_splits_of_which_some_give_up_and_others_wait_are_merged_alike(gpu, shape, page, fp8):
+    """The first, the last, every other one or all but one of a row block's splits stop waiting at once while the rest wait: the oracle's
+    results, the bits of the call in which nobody gives up, and the words cleared."""
+    import torch
+    from oracle import fp8_oracle as f8
+    from paper_2510_26577_amd import binding
+    lib = binding.load_library()
+    for splits, L in ((2, [1500, 90, 0]), (3, [700, 1500, 129]), (5, [1500, 64, 900]), (6, [1500, 1100, 65]), (9, [1500, 700, 300]), (12, [1500, 1, 1400])):
+        Hkv = 2 if splits < 9 else 1  # (256 workgroups at most)
+        w = wl.random_workload(2400 + splits + shape, 3, 4 * Hkv, Hkv, 128, L, [65, 33, 1], max_depth=9, page_size=page)
+        scales = (1.0, 1.0)
+        if fp8:
+            w, *scales = wl.to_fp8_kv(w)
+        say(f"[case] some give up, shape={shape} page={page} fp8={fp8} splits={splits}")
+        ro, rl = f8.tree_verify_attn_fp8(w, *scales) if fp8 else orc.tree_verify_attn(w)
+        args, out, lse, ws = prepared(gpu, w, scales, num_splits=splits, plan_shape=shape)
+        S = binding.plan_splits(args)
+        nc = max(1, -(-L[0] // binding.plan_chunk_keys(args)))
+        first = None
+        for at_once in (0, 1, 1 << (S - 1), 0x555 & ((1 << S) - 1), (1 << S) - 1 - (1 << S // 2)):
+            out.fill_(float("nan")), lse.fill_(float("nan")), ws.fill_(-1)
+            assert lib.tva_tree_verify_attn_wait_bound_test(args, 4000 | at_once << 16, None) == 0
+            torch.cuda.synchronize()
+            assert nc < 2 or not ws[:nc].any().item()
+            got = (out.cpu().numpy(), lse.cpu().numpy())
+            assert np.abs(got[0] - ro).max() <= TOL_O and np.abs(got[1] - rl).max() <= TOL_LSE, (splits, at_once)
+            first = first or got
+            assert np.array_equal(first[0], got[0]) and np.array_equal(first[1], got[1]), (splits, at_once)
 
 
 @pytest.mark.parametrize("short", [1000, 3000])
